@@ -266,7 +266,7 @@ int hm_tridiag_lowest(int32_t k, const double *alpha, const double *beta,
  * ones included (the block form of the method's Lanczos recurrence, with p x p
  * blocks in place of alpha_k and beta_k; FP64 throughout):
  *   V_0 R_0 = X0;  W = H V_k - V_{k-1} B_{k-1}^T;  A_k = V_k^T W;
- *   W -= V_k A_k;  twice W -= sum_{j<=k} V_j (V_j^T W);  V_{k+1} B_k = W
+ *   twice W -= sum_{j<=k} V_j (V_j^T W);  V_{k+1} B_k = W
  * (QR by Cholesky QR applied twice, B_k upper triangular).  The eigenvalues of
  * the block tridiagonal matrix with diagonal blocks A_0..A_{n-1} and
  * sub-diagonal blocks B_0..B_{n-2} (n = *steps_done) approximate the lowest

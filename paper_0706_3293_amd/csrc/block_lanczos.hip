@@ -5,9 +5,9 @@
 // The paper's recurrence is the single-vector Lanczos method (Secs. 1, 4); its
 // block form replaces the scalars alpha_k, beta_k by p x p blocks:
 //   V_0 R_0 = X0                      (QR of the start block)
-//   W = H V_k - V_{k-1} B_{k-1}^T
-//   A_k = V_k^T W;   W -= V_k A_k
-//   twice:  W -= sum_{j<=k} V_j (V_j^T W)      (full reorthogonalization)
+//   W = H V_k - V_{k-1} B_{k-1}^T;   A_k = V_k^T W
+//   twice:  W -= sum_{j<=k} V_j (V_j^T W)      (full reorthogonalization; the
+//                                               first pass subtracts V_k A_k)
 //   V_{k+1} B_k = W                   (QR; B_k upper triangular)
 // and the eigenvalues of the block tridiagonal matrix with diagonal blocks
 // A_k and sub-diagonal blocks B_k approximate the lowest eigenvalues of H.
@@ -15,21 +15,29 @@
 // Blocks are stored row-interleaved, [dim][p] FP64, so one decode of a basis
 // state serves all p columns and a gathered row is p contiguous doubles.  The
 // QR is Cholesky QR applied twice (the second pass restores orthogonality to
-// rounding level); the p x p Cholesky factorizations run on the host.  Block
-// dot products V^T W are per-workgroup partials summed in a fixed order, so a
-// run is reproducible.
+// rounding level).  Block dot products V^T W run on the matrix cores
+// (tall_dots.h) as per-workgroup partials summed in a fixed order, so a run is
+// reproducible.  The p x p factorizations, the breakdown test and the blocks
+// A_k, B_k stay on the device: a step is 13 launches that the host enqueues
+// ahead, where reading each set of dots back cost 5 round trips a step.
 #include <algorithm>
-#include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "device_common.h"
 #include "hm_internal.h"
 #include "hx_row.h"
+#include "tall_dots.h"
 
 namespace hm {
 
-constexpr int kDotBlock = 256;
-constexpr int kDotGrid = 256;
+// Device state of one run: nothing is read back before the end, so the host
+// only enqueues.
+struct BlockDev {
+    int stopped;      // steps done when the block Krylov space was exhausted,
+                      // -1 if the start block is rank deficient, 0 while running
+    double scale;     // running max |entry| of the A and B blocks
+};
 
 template <int P>
 __device__ __forceinline__ void load_drow(const double *__restrict__ p, double (&v)[P]) {
@@ -45,12 +53,33 @@ __device__ __forceinline__ void load_drow(const double *__restrict__ p, double (
     }
 }
 
-// Y = H X for a [dim][P] block (generic digits, any s).
+template <int P>
+__device__ __forceinline__ void store_drow(double *__restrict__ p, const double (&v)[P]) {
+    if constexpr (P % 2 == 0) {
+#pragma unroll
+        for (int q = 0; q < P / 2; ++q)
+            reinterpret_cast<double2 *>(p)[q] = make_double2(v[2 * q], v[2 * q + 1]);
+    } else {
+        p[0] = v[0];
+    }
+}
+
+// Moves whose gathers are in flight together in one row of H X: as many as
+// the registers hold rows of P doubles.
+template <int P> constexpr int block_moves() { return P <= 4 ? 8 : 16 / P * 2; }
+
+// W = H X - Xprev B^T for [dim][P] blocks (generic digits, any s; Xprev may be
+// null).  The moves of a row go in batches: the targets and gathers of a
+// batch are issued before its products are added, in bond order.  With s = 1/2
+// a bond has at most one move.  Folding the previous block's update in saves a
+// launch and two passes over W.
 template <typename I, int B, int P>
 __global__ __launch_bounds__(kBlock) void block_hx_kernel(
     const I *__restrict__ gprefix, const double *__restrict__ gladder,
     const BondDev *__restrict__ bonds, int nb, int N, int A, int two_s, I dim,
-    const double *__restrict__ X, double *__restrict__ Y) {
+    const double *__restrict__ X, const double *__restrict__ Xprev,
+    const double *__restrict__ Bm, double *__restrict__ Y, const BlockDev *__restrict__ dev) {
+    if (dev->stopped) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int plen = N * (A + 1) * (two_s + 1);
     I *Pt = reinterpret_cast<I *>(smem);
@@ -62,6 +91,8 @@ __global__ __launch_bounds__(kBlock) void block_hx_kernel(
     const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
     I first, last;
     block_rows<I>(lb, gridDim.x, dim, first, last);
+    constexpr int kPer = B == 1 ? 1 : 2;                  // moves of one bond
+    constexpr int kBatch = block_moves<P>() / kPer;       // bonds of a batch
     for (I row = first + threadIdx.x; row < last; row += blockDim.x) {
         const uint64_t st = unrank_state<I, B>(row, pv, N, A, two_s);
         double xi[P], acc[P];
@@ -69,131 +100,77 @@ __global__ __launch_bounds__(kBlock) void block_hx_kernel(
         double diag = 0.0;
 #pragma unroll
         for (int q = 0; q < P; ++q) acc[q] = 0.0;
-        for (int b = 0; b < nb; ++b) {
-            const int u = bonds[b].u, v = bonds[b].v;
-            const double mJ2 = bonds[b].mJ2;
-            const int au = digit_at<B>(st, u), av = digit_at<B>(st, v);
-            diag += bonds[b].mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
-            if (au >= 1 && av < two_s) {
-                const I j = row + move_delta<I, B>(st, u, v, -1, pv);
-                const double c = mJ2 * F[au] * F[av + 1];
-                double xj[P];
-                load_drow<P>(X + (size_t)j * P, xj);
+        for (int b0 = 0; b0 < nb; b0 += kBatch) {
+            double xj[kBatch * kPer][P], cf[kBatch * kPer];
+            bool on[kBatch * kPer];
 #pragma unroll
-                for (int q = 0; q < P; ++q) acc[q] += c * xj[q];
-            }
-            if (av >= 1 && au < two_s) {
-                const I j = row + move_delta<I, B>(st, u, v, +1, pv);
-                const double c = mJ2 * F[av] * F[au + 1];
-                double xj[P];
-                load_drow<P>(X + (size_t)j * P, xj);
+            for (int t = 0; t < kBatch; ++t) {
 #pragma unroll
-                for (int q = 0; q < P; ++q) acc[q] += c * xj[q];
+                for (int m = 0; m < kPer; ++m) on[kPer * t + m] = false;
+                const int b = b0 + t;
+                if (b >= nb) continue;
+                const int u = bonds[b].u, v = bonds[b].v;
+                const double mJ2 = bonds[b].mJ2;
+                const int au = digit_at<B>(st, u), av = digit_at<B>(st, v);
+                diag += bonds[b].mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
+                if constexpr (B == 1) {
+                    if (au != av) {                       // s = 1/2: F[1] = 1
+                        const I j = row + move_delta<I, B>(st, u, v, au ? -1 : +1, pv);
+                        cf[t] = mJ2;
+                        load_drow<P>(X + (size_t)j * P, xj[t]);
+                        on[t] = true;
+                    }
+                } else {
+                    if (au >= 1 && av < two_s) {
+                        const I j = row + move_delta<I, B>(st, u, v, -1, pv);
+                        cf[2 * t] = mJ2 * F[au] * F[av + 1];
+                        load_drow<P>(X + (size_t)j * P, xj[2 * t]);
+                        on[2 * t] = true;
+                    }
+                    if (av >= 1 && au < two_s) {
+                        const I j = row + move_delta<I, B>(st, u, v, +1, pv);
+                        cf[2 * t + 1] = mJ2 * F[av] * F[au + 1];
+                        load_drow<P>(X + (size_t)j * P, xj[2 * t + 1]);
+                        on[2 * t + 1] = true;
+                    }
+                }
             }
+#pragma unroll
+            for (int m = 0; m < kBatch * kPer; ++m)
+                if (on[m])
+#pragma unroll
+                    for (int q = 0; q < P; ++q) acc[q] += cf[m] * xj[m][q];
         }
 #pragma unroll
-        for (int q = 0; q < P; ++q) Y[(size_t)row * P + q] = diag * xi[q] + acc[q];
-    }
-}
-
-// Per-workgroup partials of X_j^T W for the blocks j = blockIdx.y (X_j at
-// X + j * dim * P): thread t of a group handles the pair (t / P, t % P); the
-// 256 / P^2 groups take interleaved rows and are added in group order.
-template <int P>
-__global__ __launch_bounds__(kDotBlock) void block_dots_kernel(const double *__restrict__ X,
-                                                               const double *__restrict__ W,
-                                                               int64_t dim,
-                                                               double *__restrict__ partial) {
-    constexpr int PP = P * P, G = kDotBlock / PP;
-    __shared__ double red[kDotBlock];
-    const double *__restrict__ Xj = X + (size_t)blockIdx.y * dim * P;
-    const int t = threadIdx.x % PP, g = threadIdx.x / PP;
-    const int r = t / P, c = t % P;
-    double s = 0.0;
-    if (g < G) {
-        const int64_t per = (dim + gridDim.x - 1) / gridDim.x;
-        const int64_t lo = per * blockIdx.x, hi = std::min<int64_t>(lo + per, dim);
-        for (int64_t row = lo + g; row < hi; row += G) s += Xj[row * P + r] * W[row * P + c];
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x < PP) {
-        double acc = 0.0;
-        for (int q = 0; q < G; ++q) acc += red[q * PP + threadIdx.x];
-        partial[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * PP + threadIdx.x] = acc;
-    }
-}
-
-// The same dots for P <= 4, JC blocks per workgroup: a thread keeps the P
-// entries of W of its row in registers and adds the outer products with the
-// rows of JC consecutive blocks, so each entry of W and X_j is loaded once per
-// chunk (the kernel above loads each P times and W once per block).  Sums
-// in a fixed order: per thread over its rows, a butterfly per wave, the waves
-// in order.
-constexpr int kDotChunk = 4;
-
-template <int P>
-__global__ __launch_bounds__(kDotBlock) void block_dots_chunk_kernel(
-    const double *__restrict__ X, const double *__restrict__ W, int64_t dim, int nblk,
-    double *__restrict__ partial) {
-    constexpr int PP = P * P, JC = kDotChunk;
-    __shared__ double stage[(kDotBlock / 64) * JC * PP];
-    const int j0 = blockIdx.y * JC;
-    double acc[JC][PP];
-#pragma unroll
-    for (int jj = 0; jj < JC; ++jj)
-#pragma unroll
-        for (int q = 0; q < PP; ++q) acc[jj][q] = 0.0;
-    const int64_t per = (dim + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = per * blockIdx.x, hi = std::min<int64_t>(lo + per, dim);
-    for (int64_t row = lo + threadIdx.x; row < hi; row += blockDim.x) {
-        double w[P];
-        load_drow<P>(W + row * P, w);
-#pragma unroll
-        for (int jj = 0; jj < JC; ++jj) {
-            if (j0 + jj >= nblk) break;
-            double xv[P];
-            load_drow<P>(X + ((size_t)(j0 + jj) * dim + row) * P, xv);
+        for (int q = 0; q < P; ++q) acc[q] += diag * xi[q];
+        if (Xprev) {
+            load_drow<P>(Xprev + (size_t)row * P, xi);
 #pragma unroll
             for (int r = 0; r < P; ++r)
 #pragma unroll
-                for (int c = 0; c < P; ++c) acc[jj][r * P + c] += xv[r] * w[c];
+                for (int c = 0; c < P; ++c) acc[c] -= xi[r] * Bm[c * P + r];
         }
-    }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int jj = 0; jj < JC; ++jj)
-#pragma unroll
-        for (int q = 0; q < PP; ++q) {
-            const double v = wave_sum(acc[jj][q]);
-            if (lane == 0) stage[(wid * JC + jj) * PP + q] = v;
-        }
-    __syncthreads();
-    for (int t = threadIdx.x; t < JC * PP; t += blockDim.x) {
-        const int jj = t / PP, q = t % PP;
-        if (j0 + jj >= nblk) continue;
-        double v = 0.0;
-        for (int w8 = 0; w8 < (int)(blockDim.x >> 6); ++w8) v += stage[(w8 * JC + jj) * PP + q];
-        partial[((size_t)(j0 + jj) * gridDim.x + blockIdx.x) * PP + q] = v;
+        store_drow<P>(Y + (size_t)row * P, acc);
     }
 }
 
-// out[j][pp] = sum over workgroups in order of partial[j][w][pp].
-__global__ void block_dots_finish(const double *__restrict__ partial, int nparts, int PP,
-                                  double *__restrict__ out) {
-    const int j = blockIdx.x, pp = threadIdx.x;
-    if (pp >= PP) return;
-    double s = 0.0;
-    for (int w = 0; w < nparts; ++w) s += partial[((size_t)j * nparts + w) * PP + pp];
-    out[(size_t)j * PP + pp] = s;
+// out[o] = sum over the row ranges of partial[.][o].
+__global__ __launch_bounds__(kTallBlock) void block_dots_finish(
+    const double *__restrict__ partial, int splits, int nout, double *__restrict__ out,
+    const BlockDev *__restrict__ dev) {
+    if (dev->stopped) return;
+    __shared__ double red[4][64];
+    tall_sum(partial, splits, nout, blockIdx.x * 64, out, red);
 }
 
-// W[row][c] -= sum_{j < nblk} sum_r X_j[row][r] M_j[r][c]
+// W[row][c] -= sum_{j < nblk} sum_r X_j[row][r] M_j[r][c].  In the first pass
+// of the reorthogonalization (Aout given) the last block of M is V_k^T W: its
+// symmetric part is A_k, which one workgroup writes.
 template <int P>
-__global__ __launch_bounds__(kBlock) void block_update_kernel(const double *__restrict__ X,
-                                                              const double *__restrict__ M,
-                                                              int nblk, int64_t dim,
-                                                              double *__restrict__ W) {
+__global__ __launch_bounds__(kBlock) void block_update_kernel(
+    const double *__restrict__ X, const double *__restrict__ M, int nblk, int64_t dim,
+    double *__restrict__ W, double *__restrict__ Aout, BlockDev *__restrict__ dev) {
+    if (dev->stopped) return;
     for (int64_t row = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; row < dim;
          row += (int64_t)gridDim.x * blockDim.x) {
         double w[P];
@@ -207,16 +184,88 @@ __global__ __launch_bounds__(kBlock) void block_update_kernel(const double *__re
 #pragma unroll
                 for (int c = 0; c < P; ++c) w[c] -= x[r] * Mj[r * P + c];
         }
-#pragma unroll
-        for (int c = 0; c < P; ++c) W[row * P + c] = w[c];
+        store_drow<P>(W + row * P, w);
+    }
+    if (Aout && blockIdx.x == 0) {
+        const double *__restrict__ A = M + (size_t)(nblk - 1) * P * P;
+        for (int t = threadIdx.x; t < P * P; t += blockDim.x)
+            Aout[t] = 0.5 * (A[t] + A[(t % P) * P + t / P]);
+        if (threadIdx.x == 0) {
+            double sc = dev->scale;
+            for (int t = 0; t < P * P; ++t)
+                sc = fmax(sc, fabs(0.5 * (A[t] + A[(t % P) * P + t / P])));
+            dev->scale = sc;
+        }
+    }
+}
+
+// One workgroup: G = W^T W from its partials, symmetrized, and its upper
+// Cholesky factor R (G = R^T R) in LDS, P rows of eliminations by P x P
+// threads.  pass 0 stops the run when W is at rounding level of the
+// recurrence's scale or numerically rank deficient (a pivot not above tol
+// times the largest diagonal entry); pass 1 also writes R2 R1 to Rout.  k < 0:
+// the start block, where stopping is the caller's error.
+template <int P>
+__global__ __launch_bounds__(kTallBlock) void block_cholesky_kernel(
+    const double *__restrict__ partial, int splits, double *__restrict__ G,
+    double *__restrict__ R, const double *__restrict__ R1, int pass, int k,
+    double *__restrict__ Rout, BlockDev *__restrict__ dev) {
+    if (dev->stopped) return;
+    constexpr int PP = P * P;
+    __shared__ double red[4][64];
+    __shared__ double a[PP], r[PP];
+    __shared__ int bad;
+    for (int f = 0; f < PP; f += 64) tall_sum(partial, splits, PP, f, G, red);
+    __syncthreads();
+    const int t = threadIdx.x, ti = t / P, tj = t % P;
+    if (t < PP) {
+        a[t] = ti == tj ? G[t] : 0.5 * (G[t] + G[tj * P + ti]);
+        r[t] = 0.0;
+    }
+    if (t == 0) bad = 0;
+    __syncthreads();
+    double dmax = 0.0;
+    for (int i = 0; i < P; ++i) dmax = fmax(dmax, a[i * P + i]);
+    const double floor1 = k < 0 ? 0.0 : 1e-12 * dev->scale;
+    const double tol = pass == 0 ? 1e-12 : 1e-14;
+    if (t == 0 && (!(dmax > 0.0) || (pass == 0 && !(dmax > floor1 * floor1)))) bad = 1;
+    for (int i = 0; i < P; ++i) {
+        __syncthreads();
+        const double d = a[i * P + i];
+        if (t == 0 && !(d > tol * dmax)) bad = 1;
+        const double rii = sqrt(d);
+        if (t < PP && ti == i && tj >= i) r[t] = tj == i ? rii : a[t] / rii;
+        __syncthreads();
+        if (t < PP && ti > i && tj >= ti) a[t] -= r[i * P + ti] * r[i * P + tj];
+    }
+    __syncthreads();
+    if (bad) {
+        if (t == 0) dev->stopped = k + 1 > 0 ? k + 1 : -1;
+        return;
+    }
+    if (t < PP) R[t] = r[t];
+    if (pass == 1 && Rout) {
+        double s = 0.0;
+        if (t < PP) {
+            for (int q = 0; q < P; ++q) s += r[ti * P + q] * R1[q * P + tj];
+            Rout[t] = s;
+            a[t] = fabs(s);
+        }
+        __syncthreads();
+        if (t == 0) {
+            double sc = dev->scale;
+            for (int q = 0; q < PP; ++q) sc = fmax(sc, a[q]);
+            dev->scale = sc;
+        }
     }
 }
 
 // W[row] <- W[row] R^{-1} for the upper triangular R (row-vector solve)
 template <int P>
 __global__ __launch_bounds__(kBlock) void block_trsm_kernel(const double *__restrict__ R,
-                                                            int64_t dim,
-                                                            double *__restrict__ W) {
+                                                            int64_t dim, double *__restrict__ W,
+                                                            const BlockDev *__restrict__ dev) {
+    if (dev->stopped) return;
     for (int64_t row = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; row < dim;
          row += (int64_t)gridDim.x * blockDim.x) {
         double w[P];
@@ -228,13 +277,17 @@ __global__ __launch_bounds__(kBlock) void block_trsm_kernel(const double *__rest
             for (int r = 0; r < c; ++r) v -= w[r] * R[r * P + c];
             w[c] = v / R[c * P + c];
         }
-#pragma unroll
-        for (int c = 0; c < P; ++c) W[row * P + c] = w[c];
+        store_drow<P>(W + row * P, w);
     }
 }
 
+__global__ void block_init(BlockDev *dev) {
+    dev->stopped = 0;
+    dev->scale = 0.0;
+}
+
 struct BlockLayout {
-    size_t V, Wtmp, partial, dots, mats, total;
+    size_t V, partial, dots, R1, R2, dev, A, B, total;
 };
 
 static size_t al256b(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -243,41 +296,24 @@ static int block_layout(const Basis *b, int p, int steps, BlockLayout *L) {
     if (p != 1 && p != 2 && p != 4 && p != 8 && p != 16)
         return fail(HM_EINVAL, "block size p must be 1, 2, 4, 8 or 16");
     if (steps < 1) return fail(HM_EINVAL, "steps must be >= 1");
-    const size_t blk = (size_t)b->dim * p * sizeof(double);
+    const size_t blk = (size_t)b->dim * p * sizeof(double), pp = (size_t)p * p;
     size_t off = 0;
     L->V = off; off = al256b(off + blk * (size_t)(steps + 1));
-    L->Wtmp = off; off = al256b(off + blk);
-    L->partial = off; off = al256b(off + sizeof(double) * (size_t)(steps + 1) * kDotGrid * p * p);
-    L->dots = off; off = al256b(off + sizeof(double) * (size_t)(steps + 1) * p * p);
-    L->mats = off; off = al256b(off + sizeof(double) * (size_t)(steps + 1) * p * p);
-    L->total = off;
+    L->partial = off; off = al256b(off + sizeof(double) * (size_t)(steps + 1) * kTallSplits * pp);
+    L->dots = off; off = al256b(off + sizeof(double) * (size_t)(steps + 1) * pp);
+    L->R1 = off; off = al256b(off + sizeof(double) * pp);
+    L->R2 = off; off = al256b(off + sizeof(double) * pp);
+    // the results, read back in one copy
+    L->dev = off; off = al256b(off + sizeof(BlockDev));
+    L->A = off; off += sizeof(double) * (size_t)steps * pp;
+    L->B = off; off += sizeof(double) * (size_t)steps * pp;
+    L->total = al256b(off);
     return HM_OK;
 }
 
-// Upper Cholesky factor R (G = R^T R) of a p x p symmetric matrix; false if
-// a pivot is not above tol * (largest diagonal entry).
-static bool cholesky_upper(const std::vector<double> &G, int p, double tol,
-                           std::vector<double> &R) {
-    R.assign((size_t)p * p, 0.0);
-    double dmax = 0.0;
-    for (int i = 0; i < p; ++i) dmax = std::max(dmax, G[(size_t)i * p + i]);
-    if (!(dmax > 0.0)) return false;
-    for (int i = 0; i < p; ++i) {
-        double d = G[(size_t)i * p + i];
-        for (int k = 0; k < i; ++k) d -= R[(size_t)k * p + i] * R[(size_t)k * p + i];
-        if (!(d > tol * dmax)) return false;
-        const double rii = std::sqrt(d);
-        R[(size_t)i * p + i] = rii;
-        for (int j = i + 1; j < p; ++j) {
-            double s = G[(size_t)i * p + j];
-            for (int k = 0; k < i; ++k) s -= R[(size_t)k * p + i] * R[(size_t)k * p + j];
-            R[(size_t)i * p + j] = s / rii;
-        }
-    }
-    return true;
-}
-
 namespace {
+
+constexpr int kStopCheck = 16;   // steps between two looks at the stop flag
 
 struct BlockRun {
     const Basis *b;
@@ -287,127 +323,86 @@ struct BlockRun {
     BlockLayout L;
     hipStream_t st;
     double *V(int k) const { return (double *)(w + L.V) + (size_t)k * b->dim * p; }
-    double *Wt() const { return (double *)(w + L.Wtmp); }
     double *partial() const { return (double *)(w + L.partial); }
     double *dots() const { return (double *)(w + L.dots); }
-    double *mats() const { return (double *)(w + L.mats); }
+    double *R(int pass) const { return (double *)(w + (pass == 0 ? L.R1 : L.R2)); }
+    BlockDev *dev() const { return (BlockDev *)(w + L.dev); }
+    double *A(int k) const { return (double *)(w + L.A) + (size_t)k * p * p; }
+    double *B(int k) const { return (double *)(w + L.B) + (size_t)k * p * p; }
 };
 
+// Partials of X^T W for nblk blocks of X; returns the number of row ranges.
 template <int P>
-int dots(const BlockRun &R, const double *X, int nblk, const double *W, std::vector<double> &out) {
-    if constexpr (P <= 4)
-        hipLaunchKernelGGL((block_dots_chunk_kernel<P>), dim3(kDotGrid, (nblk + kDotChunk - 1) / kDotChunk),
-                           dim3(kDotBlock), 0, R.st, X, W, (int64_t)R.b->dim, nblk, R.partial());
-    else
-        hipLaunchKernelGGL((block_dots_kernel<P>), dim3(kDotGrid, nblk), dim3(kDotBlock), 0, R.st,
-                           X, W, (int64_t)R.b->dim, R.partial());
-    hipLaunchKernelGGL(block_dots_finish, dim3(nblk), dim3(P * P), 0, R.st, R.partial(),
-                       kDotGrid, P * P, R.dots());
-    HM_HIP(hipGetLastError());
-    out.resize((size_t)nblk * P * P);
-    HM_HIP(hipMemcpyAsync(out.data(), R.dots(), sizeof(double) * out.size(),
-                          hipMemcpyDeviceToHost, R.st));
-    HM_HIP(hipStreamSynchronize(R.st));
-    return HM_OK;
+int dots(const BlockRun &R, const double *X, int nblk, const double *W) {
+    const int ncol = nblk * P, splits = tall_splits<P>(R.b->dim, ncol);
+    hipLaunchKernelGGL((tall_dots_kernel<double, P>),
+                       dim3(splits, (ncol + tall_cols<P>() - 1) / tall_cols<P>()),
+                       dim3(kTallBlock), 0, R.st, X, W, (int64_t)R.b->dim, ncol, R.partial(),
+                       &R.dev()->stopped);
+    return splits;
 }
 
+// Cholesky QR applied twice to W in place (W = Q Rout).
 template <int P>
-int update(const BlockRun &R, const double *X, int nblk, const std::vector<double> &M, double *W) {
-    HM_HIP(hipMemcpyAsync(R.mats(), M.data(), sizeof(double) * M.size(), hipMemcpyHostToDevice,
-                          R.st));
-    hipLaunchKernelGGL((block_update_kernel<P>), dim3(generic_grid(R.b->dim)), dim3(kBlock), 0,
-                       R.st, X, R.mats(), nblk, (int64_t)R.b->dim, W);
-    HM_HIP(hipGetLastError());
-    return HM_OK;
-}
-
-// Cholesky QR applied twice to W in place; Rout = R2 R1.  Returns HM_ERANGE
-// (not an error for the caller: breakdown) if W is numerically rank deficient
-// or its largest squared column norm is at most `floor2`.
-template <int P>
-int cholqr2(const BlockRun &R, double *W, double tol, double floor2, std::vector<double> &Rout) {
-    std::vector<double> G, R1, R2;
+void cholqr2(const BlockRun &R, double *W, int k, double *Rout) {
     for (int pass = 0; pass < 2; ++pass) {
-        HM_TRY(dots<P>(R, W, 1, W, G));
-        if (pass == 0) {
-            double dmax = 0.0;
-            for (int i = 0; i < P; ++i) dmax = std::max(dmax, G[(size_t)i * P + i]);
-            if (!(dmax > floor2)) return HM_ERANGE;
-        }
-        for (int i = 0; i < P; ++i)   // symmetrize the rounding of the two triangles
-            for (int j = i + 1; j < P; ++j)
-                G[(size_t)i * P + j] = G[(size_t)j * P + i] =
-                    0.5 * (G[(size_t)i * P + j] + G[(size_t)j * P + i]);
-        std::vector<double> &Rk = pass == 0 ? R1 : R2;
-        if (!cholesky_upper(G, P, pass == 0 ? tol : 1e-14, Rk)) return HM_ERANGE;
-        HM_HIP(hipMemcpyAsync(R.mats(), Rk.data(), sizeof(double) * P * P,
-                              hipMemcpyHostToDevice, R.st));
+        const int splits = dots<P>(R, W, 1, W);
+        hipLaunchKernelGGL((block_cholesky_kernel<P>), dim3(1), dim3(kTallBlock), 0, R.st,
+                           R.partial(), splits, R.dots(), R.R(pass), R.R(0), pass, k,
+                           pass == 1 ? Rout : nullptr, R.dev());
         hipLaunchKernelGGL((block_trsm_kernel<P>), dim3(generic_grid(R.b->dim)), dim3(kBlock), 0,
-                           R.st, R.mats(), (int64_t)R.b->dim, W);
-        HM_HIP(hipGetLastError());
+                           R.st, R.R(pass), (int64_t)R.b->dim, W, R.dev());
     }
-    Rout.assign((size_t)P * P, 0.0);
-    for (int i = 0; i < P; ++i)
-        for (int j = 0; j < P; ++j) {
-            double s = 0.0;
-            for (int k = 0; k < P; ++k) s += R2[(size_t)i * P + k] * R1[(size_t)k * P + j];
-            Rout[(size_t)i * P + j] = s;
-        }
-    return HM_OK;
 }
 
 template <typename I, int Bb, int P>
 int run_block(BlockRun &R, const double *X0, double *Aout, double *Bout, int *done) {
     const Basis *b = R.b;
-    const size_t blk = (size_t)b->dim * P * sizeof(double);
+    const size_t blk = (size_t)b->dim * P * sizeof(double), pp = (size_t)P * P;
     const size_t lds = ((prefix_bytes(b) + 15) / 16) * 16 + (b->two_s + 2) * sizeof(double);
     const int grid = generic_grid(b->dim);
-    const double tol = 1e-12;
     // V_0 R_0 = X0
     HM_HIP(hipMemcpyAsync(R.V(0), X0, blk, hipMemcpyDeviceToDevice, R.st));
-    std::vector<double> Rq, Ak, C, Bprev;
-    double scale = 0.0;   // running max |entry| of the A and B blocks
-    int rc = cholqr2<P>(R, R.V(0), tol, 0.0, Rq);
-    if (rc == HM_ERANGE) return fail(HM_EINVAL, "start block is rank deficient");
-    HM_TRY(rc);
-    *done = 0;
+    hipLaunchKernelGGL(block_init, dim3(1), dim3(1), 0, R.st, R.dev());
+    cholqr2<P>(R, R.V(0), -1, nullptr);
     for (int k = 0; k < R.steps; ++k) {
         double *W = R.V(k + 1);
         hipLaunchKernelGGL((block_hx_kernel<I, Bb, P>), dim3(grid), dim3(kBlock), lds, R.st,
                            (const I *)b->d_prefix, b->d_ladder, R.c->dev, R.c->nb, b->N, b->A,
-                           b->two_s, (I)b->dim, R.V(k), W);
-        HM_HIP(hipGetLastError());
-        if (k > 0) {   // W -= V_{k-1} B_{k-1}^T
-            std::vector<double> Bt((size_t)P * P);
-            for (int i = 0; i < P; ++i)
-                for (int j = 0; j < P; ++j) Bt[(size_t)i * P + j] = Bprev[(size_t)j * P + i];
-            HM_TRY(update<P>(R, R.V(k - 1), 1, Bt, W));
-        }
-        HM_TRY(dots<P>(R, R.V(k), 1, W, Ak));
-        HM_TRY(update<P>(R, R.V(k), 1, Ak, W));
-        for (int i = 0; i < P; ++i)
-            for (int j = 0; j < P; ++j) {
-                const double a = 0.5 * (Ak[(size_t)i * P + j] + Ak[(size_t)j * P + i]);
-                Aout[((size_t)k * P + i) * P + j] = a;
-                scale = std::max(scale, std::fabs(a));
-            }
+                           b->two_s, (I)b->dim, R.V(k), k > 0 ? R.V(k - 1) : (double *)nullptr,
+                           k > 0 ? R.B(k - 1) : (double *)nullptr, W, R.dev());
+        // twice W -= sum_j V_j (V_j^T W); the first pass's V_k^T W is A_k
         for (int pass = 0; pass < 2; ++pass) {
-            HM_TRY(dots<P>(R, R.V(0), k + 1, W, C));
-            HM_TRY(update<P>(R, R.V(0), k + 1, C, W));
+            const int nout = (k + 1) * P * P, splits = dots<P>(R, R.V(0), k + 1, W);
+            hipLaunchKernelGGL(block_dots_finish, dim3((nout + 63) / 64), dim3(kTallBlock), 0,
+                               R.st, R.partial(), splits, nout, R.dots(), R.dev());
+            hipLaunchKernelGGL((block_update_kernel<P>), dim3(grid), dim3(kBlock), 0, R.st,
+                               R.V(0), R.dots(), k + 1, (int64_t)b->dim, W,
+                               pass == 0 ? R.A(k) : (double *)nullptr, R.dev());
         }
-        *done = k + 1;
-        if (k + 1 == R.steps) break;
-        // breakdown when what is left of W is at rounding level of the
-        // recurrence's scale: the block Krylov space is exhausted
-        rc = cholqr2<P>(R, W, tol, (1e-12 * scale) * (1e-12 * scale), Bprev);
-        if (rc == HM_ERANGE) break;
-        HM_TRY(rc);
-        for (size_t t = 0; t < (size_t)P * P; ++t) {
-            Bout[(size_t)k * P * P + t] = Bprev[t];
-            scale = std::max(scale, std::fabs(Bprev[t]));
+        if (k + 1 < R.steps) cholqr2<P>(R, W, k, R.B(k));
+        HM_HIP(hipGetLastError());
+        // a run that has stopped only launches empty kernels: look now and then
+        if (k % kStopCheck == kStopCheck - 1 && k + 1 < R.steps) {
+            int stopped = 0;
+            HM_HIP(hipMemcpyAsync(&stopped, &R.dev()->stopped, sizeof stopped,
+                                  hipMemcpyDeviceToHost, R.st));
+            HM_HIP(hipStreamSynchronize(R.st));
+            if (stopped) break;
         }
     }
+    // the state and the blocks in one copy
+    const size_t head = R.L.A - R.L.dev;
+    std::vector<unsigned char> host(head + 2 * sizeof(double) * R.steps * pp);
+    HM_HIP(hipMemcpyAsync(host.data(), R.w + R.L.dev, host.size(), hipMemcpyDeviceToHost, R.st));
     HM_HIP(hipStreamSynchronize(R.st));
+    BlockDev dev;
+    std::memcpy(&dev, host.data(), sizeof dev);
+    if (dev.stopped < 0) return fail(HM_EINVAL, "start block is rank deficient");
+    const int n = *done = dev.stopped > 0 ? dev.stopped : R.steps;
+    const double *A = (const double *)(host.data() + head), *B = A + (size_t)R.steps * pp;
+    std::copy(A, A + n * pp, Aout);
+    std::copy(B, B + (n - 1) * pp, Bout);
     return HM_OK;
 }
 
