@@ -167,7 +167,11 @@ int hm_rank_dev(hm_basis h, const uint64_t *d_state, int64_t n,
  * entry of y is written by exactly one GPU lane and no atomics are used.
  * d_x, d_y: device arrays of dim elements of type `dtype` (HM_F64 or HM_F32);
  * they must not overlap.  With HM_F32 the matrix elements are rounded to
- * FP32 once and applied in FP32.  Asynchronous on `stream`.
+ * FP32 once and applied in FP32.  The automatic choice of kernel is the block
+ * kernel of the spin (s = 1/2, or s >= 1 up to 15/2) where its tables fit,
+ * else the generic digit kernel.  The block kernels build device tables for a
+ * coupling list on its first use (and element type, for s >= 1).  Asynchronous
+ * on `stream`.
  * HM_EINVAL: bad J (see above), null pointers, unknown dtype, d_x == d_y.
  * ------------------------------------------------------------------------- */
 int hm_apply(hm_basis h, const double *J, const void *d_x, void *d_y,

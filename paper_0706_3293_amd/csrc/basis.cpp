@@ -35,6 +35,7 @@ Basis::~Basis() {
     if (d_ladder) (void)hipFree(d_ladder);
     couplings.clear();   // each Couplings frees its device arrays
     if (half_tables && half_tables_free) half_tables_free(half_tables);
+    if (digit_tables && digit_tables_free) digit_tables_free(digit_tables);
 }
 
 static int bits_for(int two_s) {
@@ -262,6 +263,7 @@ int hm_basis_init(int32_t N, int32_t two_s, int32_t two_M, hm_basis *out) {
     b.ladder.assign(two_s + 2, 0.0);
     for (int a = 1; a <= two_s; ++a)
         b.ladder[a] = std::sqrt((double)a * (double)(two_s - a + 1));
+    b.digit = hm::choose_digit_split(&b);
     *out = h;
     return HM_OK;
 }

@@ -80,6 +80,16 @@ constexpr size_t kCouplingCacheEntries = 4;
 // of sites 1..k; decoding walks k = N..1 and picks the digit whose block holds
 // the remaining offset.
 // ---------------------------------------------------------------------------
+
+// Split of the block kernel for s >= 1 into K low sites and the rest (K = 0:
+// the generic kernel runs): blocks a wave takes together, rows of the largest
+// block, blocks and groups of blocks.
+struct DigitSplit {
+    int K = 0, R = 1, smax = 0;
+    bool flat = false;                  // one lane per row instead of a wave per R blocks
+    int64_t n_blocks = 0, n_groups = 0;
+};
+
 struct Basis {
     int N = 0, two_s = 0, A = 0, bits = 0;
     int64_t dim = 0;
@@ -111,6 +121,11 @@ struct Basis {
     int half_ipw = 0;        // work items per wave that size the grid (0: default grid)
     void *half_tables = nullptr;
     void (*half_tables_free)(void *) = nullptr;
+    // block kernel for s >= 1: the split (fixed at creation) and its tables
+    // (first use)
+    DigitSplit digit;
+    void *digit_tables = nullptr;
+    void (*digit_tables_free)(void *) = nullptr;
     // instantiated graphs of Lanczos step loops, most recently used first,
     // with the key of everything a capture bakes in (see lanczos.hip)
     struct Graph {
@@ -163,6 +178,10 @@ int hx_partial_count(const Basis *b, int kernel);      // partial slots needed
 int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel,
               const HxPass &pass, hipStream_t st);
 int choose_kernel(const Basis *b, const Couplings *c, int requested);
+// Builds what kernel `kernel` needs on the device for these couplings (ahead
+// of a graph capture, where nothing may be allocated).
+int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel);
+DigitSplit choose_digit_split(const Basis *b);
 // Ablation kernels of hm_apply_kernel: 3 = successor sweep, 4 = column scatter.
 int launch_hx_ablation(const Basis *b, const Couplings *c, int dtype, int kernel,
                        const void *x, void *y, hipStream_t st);

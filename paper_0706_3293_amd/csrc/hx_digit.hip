@@ -1,0 +1,1130 @@
+// Block kernel for the row-gather H x with s >= 1 (Sec. 4, Eq. (E-4-b)).
+//
+// The generic kernel decodes every row by an N-step digit walk and encodes
+// every target by another, so it is bound by vector instructions and the LDS
+// latency of the walks (5.2 M rows of the 16-site spin-1 ring, FP32: 250 us,
+// 3 % of the copy rate).  Here a state is split into its low K digits L and
+// its high N - K digits h.  The basis order is that of the numbers
+// sum_u a_u (2s+1)^u, so the rows with one h form a contiguous block, ordered
+// like the low words of their digit sum: index = Off(h) + rankL(L).
+//   * a bond inside the low word moves within the block: the ranks its two
+//     moves lead to are tabulated per low word, the targets are read from the
+//     block's copy in LDS;
+//   * a bond inside the high word moves all rows of a block to the same rows
+//     of another block, so the gathers are coalesced; the target blocks and
+//     matrix elements of the moves a high word allows are tabulated per
+//     (basis, couplings) in bond order;
+//   * a straddling bond takes the target block from one table and the rank
+//     from the other.
+// A wave takes R blocks of one digit-sum class (the low-word work is done once
+// for R rows), copies them to its LDS slice, interleaved, so that one LDS read
+// serves the R rows, and goes over them 64 rows at a time.  Every row adds its
+// bonds in list order, as row_hx (hx_row.h) does; the diagonal element is the
+// sum of a low-word part, a high-word part (both tabulated, summed in FP64)
+// and the straddling bonds.
+#include <algorithm>
+#include <cstring>
+#include <vector>
+
+#include "device_common.h"
+#include "hm_internal.h"
+
+namespace hm {
+
+int launch_hx_generic(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
+                      hipStream_t st);
+
+constexpr int kDigitMaxWords = 16384;        // low words
+constexpr size_t kDigitMaxLds = 64 * 1024;
+constexpr size_t kDigitMaxTables = (size_t)8 << 30;
+constexpr int64_t kDigitMaxGrid = 16384;     // workgroups of one launch
+constexpr uint32_t kNoBlock = 0xFFFFFFFFu;   // padding slot of a group of blocks
+
+// Up to four bonds with their first site in the low word, consecutive in the
+// bond list and all of one kind.
+template <typename T>
+struct DigitOp {
+    int32_t n;           // bonds in use: 1, 2 or 4 (straddling: 1)
+    int32_t straddle;    // -1: both sites in the low word, else its slot in the block table
+    int32_t first;       // index of the first bond (its table and matrix elements)
+    int32_t sv;          // straddling: bit position of the digit in the high word
+    T mJ4;               // straddling: -J/4
+};
+
+// Entry of the low-word table for one bond: the ranks of the two moves
+// (kRankBits bits each) and an index of the digits.
+//   low:         moves a_u - 1, a_v + 1 and the other (the slice's zero entry
+//                where the digits do not allow one), index a_u (2s+1) + a_v
+//   straddling:  moves a_u - 1 and a_u + 1 (the own rank where the low digit
+//                does not allow one), index a_u
+constexpr int kRankBits = 12;
+constexpr int kDigitMaxSize = (1 << kRankBits) - 1;
+
+// Four moves of a block's high word.
+template <typename T, typename I>
+struct DigitMoves {
+    I off[4];            // first rows of the target blocks
+    T cf[4];             // matrix elements
+};
+
+// One block: its packed high digits, its first row, and the start and size of
+// its digit-sum class among the low words.
+template <typename I>
+struct DigitBlock {
+    uint64_t hword;
+    I off;
+    int32_t cs, size, pad;
+};
+
+// Tables of the split that depend on the basis only.
+struct DigitTables {
+    int K = 0, R = 1, nclass = 0, smax = 0, words = 0;
+    int64_t n_blocks = 0, n_groups = 0;
+    std::vector<uint16_t> rank;      // low word's rank in its class, by number
+    std::vector<uint16_t> word;      // low-word numbers by class start + rank
+    std::vector<int32_t> cls;        // [class][2]: start in `word`, size
+    void *blocks = nullptr;          // DigitBlock<I> in memory order
+    uint32_t *groups = nullptr;      // [n_groups][R] blocks of one class
+    uint32_t *rowblk = nullptr;      // block of every row (one lane per row)
+    void *mem = nullptr;             // the allocation that holds them
+};
+
+static void free_digit(void *p) {
+    auto *t = (DigitTables *)p;
+    if (!t) return;
+    if (t->mem) (void)hipFree(t->mem);
+    delete t;
+}
+
+// Tables of one coupling list in one element type.
+struct DigitBonds {
+    void *ops = nullptr;             // DigitOp<T>, n_ops of them
+    void *cf = nullptr;              // [nF][(2s+1)^2][2] matrix elements of the two moves
+    uint32_t *low = nullptr;         // [nF][words] low-word table (class start + rank)
+    void *dlow = nullptr;            // [words] diagonal part of the low-word bonds
+    void *moves = nullptr;           // [block][mw / 4] DigitMoves<T, I>
+    uint32_t *mcnt = nullptr;        // [block] moves the block's high word allows
+    void *dhigh = nullptr;           // [block] diagonal part of the high-word bonds
+    void *strad = nullptr;           // [block][nS][2] target blocks of the straddling moves
+    int n_ops = 0, nF = 0, nS = 0, mw = 0;           // mw: moves of a row, padded to fours
+    void *mem = nullptr;                             // the allocation that holds them
+};
+struct DigitBondSet {
+    DigitBonds by_type[2];
+    bool have[2] = {false, false};
+};
+static void free_digit_bonds(void *p) {
+    auto *s = (DigitBondSet *)p;
+    if (!s) return;
+    for (auto &b : s->by_type)
+        if (b.mem) (void)hipFree(b.mem);
+    delete s;
+}
+
+template <typename T, typename I>
+struct DigitArgs {
+    const DigitBlock<I> *blocks;
+    const uint32_t *groups;
+    const uint32_t *rowblk;          // block of every row (one lane per row)
+    const DigitOp<T> *ops;
+    const T *cf;
+    const uint32_t *low;
+    const T *dlow;
+    const DigitMoves<T, I> *moves;
+    const uint32_t *mcnt;
+    const T *dhigh;
+    const I *strad;
+    uint32_t n_groups, run;          // run: consecutive groups of one XCD
+    int n_ops, nF, nS, mq, words, smax, two_s, mask;   // mq: move pieces of a row
+};
+
+template <typename T> using Const = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ const Const<T> *as_const(const T *p) {
+    return (const Const<T> *)p;
+}
+
+// Element i of a wave-uniform base.  With 32-bit indices the vectors are
+// smaller than 4 GiB, so the address is the scalar base and a 32-bit byte
+// offset: one vector instruction per gather, where a scalar 64-bit base per
+// target block took three or four and spilled scalar registers.
+template <typename T, typename I>
+__device__ __forceinline__ T load_at(const T *__restrict__ base, I i) {
+    if constexpr (sizeof(I) == 4)
+        return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
+                                            i * (uint32_t)sizeof(T));
+    else
+        return base[i];
+}
+
+// R consecutive elements of LDS (16-byte reads where they fit).
+template <typename T, int R>
+__device__ __forceinline__ void lds_row(const T *p, T (&v)[R]) {
+    typedef T VR __attribute__((ext_vector_type(R)));
+    const VR t = *reinterpret_cast<const VR *>(p);
+#pragma unroll
+    for (int m = 0; m < R; ++m) v[m] = t[m];
+}
+template <>
+__device__ __forceinline__ void lds_row<float, 1>(const float *p, float (&v)[1]) { v[0] = *p; }
+template <>
+__device__ __forceinline__ void lds_row<double, 1>(const double *p, double (&v)[1]) { v[0] = *p; }
+
+// W low-word bonds at once: the table entries, then the R rows' reads and
+// products in bond order.  A move that the digits do not allow reads the
+// slice's zero entry (its matrix element is zero as well).
+template <int W, typename T, int R>
+__device__ __forceinline__ void low_bonds(const uint32_t *__restrict__ low, int words, const T *cf,
+                                          int WW, const T *xs, T (&off)[R]) {
+    constexpr uint32_t kMask = (1u << kRankBits) - 1u;
+    uint32_t e[W];
+    T x1[W][R], x2[W][R], c[W][2];
+#pragma unroll
+    for (int q = 0; q < W; ++q) e[q] = low[(size_t)q * words];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        lds_row<T, R>(xs + (e[q] & kMask) * R, x1[q]);
+        lds_row<T, R>(xs + ((e[q] >> kRankBits) & kMask) * R, x2[q]);
+        lds_row<T, 2>(cf + (q * WW * WW + (int)(e[q] >> (2 * kRankBits))) * 2, c[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q)
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            off[m] += c[q][0] * x1[q][m];
+            off[m] += c[q][1] * x2[q][m];
+        }
+}
+
+template <typename T, typename I, int R, bool DOT, bool STORE>
+__global__ __launch_bounds__(kBlock) void hx_digit_kernel(
+    const DigitArgs<T, I> g, const T *__restrict__ x, T *__restrict__ y,
+    const T *__restrict__ prev, const double *__restrict__ sigma_p,
+    const double *__restrict__ cprev_p, double *__restrict__ partial, T *__restrict__ store,
+    const int *__restrict__ stopped) {
+    if (stopped && *stopped) return;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double red[16];
+    const int WW = g.two_s + 1;
+    const int ncf = g.nF * WW * WW * 2;
+    T *cf = reinterpret_cast<T *>(smem);
+    T *xs = reinterpret_cast<T *>(smem + ((size_t)ncf * sizeof(T) + 31) / 32 * 32) +
+            (size_t)(threadIdx.x >> 6) * R * (g.smax + 1);
+    for (int t = threadIdx.x; t < ncf; t += blockDim.x) cf[t] = g.cf[t];
+    __syncthreads();
+
+    const double sigma = sigma_p ? *sigma_p : 1.0;
+    const double cprev = cprev_p ? *cprev_p : 0.0;
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int two_s = g.two_s;
+    // XCDs (workgroup b runs on XCD b % 8) take turns on runs of g.run groups
+    uint32_t stride = gridDim.x * nw, wl = blockIdx.x * nw + (threadIdx.x >> 6), x8 = 0;
+    const bool by_xcd = gridDim.x % kXcds == 0;
+    if (by_xcd) {
+        x8 = blockIdx.x % kXcds;
+        stride = (gridDim.x / kXcds) * nw;
+        wl = (blockIdx.x / kXcds) * nw + (threadIdx.x >> 6);
+    }
+    wl = __builtin_amdgcn_readfirstlane(wl);
+    x8 = __builtin_amdgcn_readfirstlane(x8);
+    // the tables are read-only for the whole launch: through the constant
+    // address space the wave-uniform reads are scalar loads
+    const Const<uint32_t> *groups = as_const(g.groups);
+    const Const<DigitBlock<I>> *blocks = as_const(g.blocks);
+    const Const<DigitOp<T>> *ops = as_const(g.ops);
+    const Const<uint32_t> *mcnt = as_const(g.mcnt);
+    const Const<DigitMoves<T, I>> *moves = as_const(g.moves);
+    const Const<I> *strad = as_const(g.strad);
+    const Const<T> *dhigh = as_const(g.dhigh);
+    if (lane < R) xs[g.smax * R + lane] = 0;
+    double dot = 0.0;
+    for (uint32_t l = wl;; l += stride) {
+        const uint32_t it =
+            by_xcd ? (l / g.run) * (kXcds * g.run) + x8 * g.run + l % g.run : l;
+        if (it >= g.n_groups) break;
+        uint32_t hb[R];
+        bool valid[R];
+        I off0[R];
+        uint64_t hw[R];
+#pragma unroll
+        for (int m = 0; m < R; ++m) hb[m] = groups[(size_t)it * R + m];
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            valid[m] = hb[m] != kNoBlock;
+            if (!valid[m]) hb[m] = hb[0];            // padding slots shadow slot 0
+            off0[m] = blocks[hb[m]].off;
+            hw[m] = blocks[hb[m]].hword;
+        }
+        const int cs = blocks[hb[0]].cs, S = blocks[hb[0]].size;
+        int nmin = 1 << 30, nmax = 0, nm[R];
+        T dh[R];
+        const Const<DigitMoves<T, I>> *mrow[R];
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            nm[m] = (int)mcnt[hb[m]];
+            nmax = max(nmax, nm[m]);
+            nmin = min(nmin, nm[m]);
+            dh[m] = dhigh[hb[m]];
+            mrow[m] = moves + (size_t)hb[m] * g.mq;
+        }
+        // copy the blocks to LDS.  The slice is private to the wave and a
+        // wave's LDS accesses complete in program order; the wave barriers
+        // keep the compiler from moving accesses across.
+        __builtin_amdgcn_wave_barrier();
+        for (int r = lane; r < S; r += 64) {
+            T v[R];
+#pragma unroll
+            for (int m = 0; m < R; ++m) v[m] = load_at(x, off0[m] + (I)r);
+#pragma unroll
+            for (int m = 0; m < R; ++m) xs[r * R + m] = v[m];
+        }
+        __builtin_amdgcn_wave_barrier();
+        for (int r1 = 0; r1 < S; r1 += 64) {
+            const bool live = r1 + lane < S;
+            const int r = live ? r1 + lane : 0;       // dead lanes shadow row 0
+            const uint32_t *__restrict__ low = g.low + cs + r;
+            const T dl = g.dlow[cs + r];
+            T xi[R], diag[R], off[R];
+            lds_row<T, R>(xs + r * R, xi);
+#pragma unroll
+            for (int m = 0; m < R; ++m) {
+                diag[m] = dl + dh[m];
+                off[m] = 0;
+            }
+            // bonds with their first site in the low word, in list order
+            for (int o = 0; o < g.n_ops; ++o) {
+                const Const<DigitOp<T>> &op = ops[o];
+                const T *cfb = cf + op.first * (WW * WW * 2);
+                const uint32_t *__restrict__ lo = low + (size_t)op.first * g.words;
+                if (op.straddle < 0) {
+                    // four bonds at once where the R rows' reads fit the registers
+                    if constexpr (R * sizeof(T) <= 16) {
+                        if (op.n == 4) {
+                            low_bonds<4, T, R>(lo, g.words, cfb, WW, xs, off);
+                            continue;
+                        }
+                    } else if (op.n == 4) {
+                        low_bonds<2, T, R>(lo, g.words, cfb, WW, xs, off);
+                        low_bonds<2, T, R>(lo + 2 * (size_t)g.words, g.words,
+                                           cfb + 2 * WW * WW * 2, WW, xs, off);
+                        continue;
+                    }
+                    if (op.n == 2) low_bonds<2, T, R>(lo, g.words, cfb, WW, xs, off);
+                    else low_bonds<1, T, R>(lo, g.words, cfb, WW, xs, off);
+                    continue;
+                }
+                const uint32_t e = lo[0], rk1 = e & ((1u << kRankBits) - 1u);
+                const uint32_t rk2 = (e >> kRankBits) & ((1u << kRankBits) - 1u);
+                const int au = (int)(e >> (2 * kRankBits));
+                const T sJ = op.mJ4 * (T)(two_s - 2 * au);
+                T g1[R], g2[R], c[R][2];
+#pragma unroll
+                for (int m = 0; m < R; ++m) {
+                    // the high digit is wave-uniform, the low one per lane
+                    const int av = (int)((hw[m] >> op.sv) & g.mask);
+                    const Const<I> *so = strad + ((size_t)hb[m] * g.nS + op.straddle) * 2;
+                    const bool a1 = au >= 1 && av < two_s, a2 = av >= 1 && au < two_s;
+                    const T v1 = load_at(x, a1 ? so[0] + (I)rk1 : off0[m] + (I)r);
+                    const T v2 = load_at(x, a2 ? so[1] + (I)rk2 : off0[m] + (I)r);
+                    lds_row<T, 2>(cfb + (au * WW + av) * 2, c[m]);
+                    diag[m] += sJ * (T)(two_s - 2 * av);
+                    g1[m] = a1 ? v1 : (T)0;
+                    g2[m] = a2 ? v2 : (T)0;
+                }
+#pragma unroll
+                for (int m = 0; m < R; ++m) {
+                    off[m] += c[m][0] * g1[m];
+                    off[m] += c[m][1] * g2[m];
+                }
+            }
+            // bonds inside the high word: the moves the blocks allow,
+            // coalesced, four of each of the R blocks at once; past the
+            // shortest list, finished ones go on with their own block and add
+            // nothing
+            int q0 = 0;
+            for (; q0 + 4 <= nmin; q0 += 4) {
+                T xj[R][4];
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) xj[m][q] = load_at(x, mrow[m][q0 / 4].off[q] + (I)r);
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) off[m] += mrow[m][q0 / 4].cf[q] * xj[m][q];
+            }
+            for (; q0 < nmax; q0 += 4) {
+                T xj[R][4];
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) xj[m][q] = load_at(x, mrow[m][q0 / 4].off[q] + (I)r);
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        off[m] += mrow[m][q0 / 4].cf[q] * (q0 + q < nm[m] ? xj[m][q] : (T)0);
+            }
+#pragma unroll
+            for (int m = 0; m < R; ++m) {
+                if (live && valid[m]) {
+                    const I row = off0[m] + (I)r;
+                    const T hv = diag[m] * xi[m] + off[m];
+                    double w = sigma * (double)hv;
+                    if (prev) w -= cprev * (double)prev[row];
+                    const T wt = (T)w;
+                    y[row] = wt;
+                    if constexpr (DOT) dot += (double)wt * (sigma * (double)xi[m]);
+                    if constexpr (STORE) store[row] = (T)(sigma * (double)xi[m]);
+                }
+            }
+        }
+    }
+    if constexpr (DOT) {
+        const double s = block_sum(dot, red);
+        if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    }
+}
+
+// The same rows where blocks are short (sectors far from M = 0 have blocks of a
+// few rows, which would leave most lanes of a wave per block idle): one lane
+// per row, whatever its block.  The block of a row comes from a table, and the
+// block's own tables are read per lane, broadcast among the lanes of one
+// block; low-word targets are gathered from memory instead of LDS.
+template <int W, typename T, typename I>
+__device__ __forceinline__ void flat_low_bonds(const uint32_t *__restrict__ low, int words,
+                                               const T *cf, int WW, uint32_t zero,
+                                               const T *__restrict__ x, I off0, I row, T &off) {
+    constexpr uint32_t kMask = (1u << kRankBits) - 1u;
+    uint32_t e[W];
+    T x1[W], x2[W], c[W][2];
+#pragma unroll
+    for (int q = 0; q < W; ++q) e[q] = low[(size_t)q * words];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        const uint32_t i1 = e[q] & kMask, i2 = (e[q] >> kRankBits) & kMask;
+        const T v1 = load_at(x, i1 != zero ? off0 + (I)i1 : row);
+        const T v2 = load_at(x, i2 != zero ? off0 + (I)i2 : row);
+        lds_row<T, 2>(cf + (q * WW * WW + (int)(e[q] >> (2 * kRankBits))) * 2, c[q]);
+        x1[q] = i1 != zero ? v1 : (T)0;
+        x2[q] = i2 != zero ? v2 : (T)0;
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        off += c[q][0] * x1[q];
+        off += c[q][1] * x2[q];
+    }
+}
+
+template <typename T, typename I, bool DOT, bool STORE>
+__global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
+    const DigitArgs<T, I> g, I dim, const T *__restrict__ x, T *__restrict__ y,
+    const T *__restrict__ prev, const double *__restrict__ sigma_p,
+    const double *__restrict__ cprev_p, double *__restrict__ partial, T *__restrict__ store,
+    const int *__restrict__ stopped) {
+    if (stopped && *stopped) return;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double red[16];
+    const int WW = g.two_s + 1, two_s = g.two_s;
+    T *cf = reinterpret_cast<T *>(smem);
+    for (int t = threadIdx.x; t < g.nF * WW * WW * 2; t += blockDim.x) cf[t] = g.cf[t];
+    __syncthreads();
+    const double sigma = sigma_p ? *sigma_p : 1.0;
+    const double cprev = cprev_p ? *cprev_p : 0.0;
+    const Const<DigitOp<T>> *ops = as_const(g.ops);
+    I first, last;
+    block_rows<I>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, dim, first, last);
+    double dot = 0.0;
+    for (I row = first + threadIdx.x; row < last; row += blockDim.x) {
+        const uint32_t hb = g.rowblk[row];
+        const DigitBlock<I> blk = g.blocks[hb];
+        const uint32_t r = (uint32_t)(row - blk.off);
+        const uint32_t *__restrict__ low = g.low + blk.cs + r;
+        const T xi = x[row];
+        T diag = g.dlow[blk.cs + r] + g.dhigh[hb], off = 0;
+        for (int o = 0; o < g.n_ops; ++o) {
+            const Const<DigitOp<T>> &op = ops[o];
+            const T *cfb = cf + op.first * (WW * WW * 2);
+            const uint32_t *__restrict__ lo = low + (size_t)op.first * g.words;
+            if (op.straddle < 0) {
+                if (op.n == 4)
+                    flat_low_bonds<4, T, I>(lo, g.words, cfb, WW, g.smax, x, blk.off, row, off);
+                else if (op.n == 2)
+                    flat_low_bonds<2, T, I>(lo, g.words, cfb, WW, g.smax, x, blk.off, row, off);
+                else
+                    flat_low_bonds<1, T, I>(lo, g.words, cfb, WW, g.smax, x, blk.off, row, off);
+                continue;
+            }
+            const uint32_t e = lo[0], rk1 = e & ((1u << kRankBits) - 1u);
+            const uint32_t rk2 = (e >> kRankBits) & ((1u << kRankBits) - 1u);
+            const int au = (int)(e >> (2 * kRankBits));
+            const int av = (int)((blk.hword >> op.sv) & g.mask);
+            const I *__restrict__ so = g.strad + ((size_t)hb * g.nS + op.straddle) * 2;
+            const bool a1 = au >= 1 && av < two_s, a2 = av >= 1 && au < two_s;
+            const I o1 = so[0], o2 = so[1];
+            const T v1 = load_at(x, a1 ? o1 + (I)rk1 : row), v2 = load_at(x, a2 ? o2 + (I)rk2 : row);
+            T c[2];
+            lds_row<T, 2>(cfb + (au * WW + av) * 2, c);
+            const T sJ = op.mJ4 * (T)(two_s - 2 * au);
+            diag += sJ * (T)(two_s - 2 * av);
+            off += c[0] * (a1 ? v1 : (T)0);
+            off += c[1] * (a2 ? v2 : (T)0);
+        }
+        const DigitMoves<T, I> *__restrict__ mv = g.moves + (size_t)hb * g.mq;
+        const int n = (int)g.mcnt[hb];
+        for (int q0 = 0; q0 < n; q0 += 4) {
+            const DigitMoves<T, I> m = mv[q0 / 4];
+            T xj[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) xj[q] = load_at(x, m.off[q] + (I)r);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) off += m.cf[q] * (q0 + q < n ? xj[q] : (T)0);
+        }
+        const T hv = diag * xi + off;
+        double w = sigma * (double)hv;
+        if (prev) w -= cprev * (double)prev[row];
+        const T wt = (T)w;
+        y[row] = wt;
+        if constexpr (DOT) dot += (double)wt * (sigma * (double)xi);
+        if constexpr (STORE) store[row] = (T)(sigma * (double)xi);
+    }
+    if constexpr (DOT) {
+        const double s = block_sum(dot, red);
+        if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Tables (built on the device; the host enumerates the blocks)
+// ---------------------------------------------------------------------------
+// First row of the block of high word hw: the high sites' terms of the
+// encoding sum (PI: type of the prefix table).
+template <typename I, typename PI>
+__device__ __forceinline__ I block_offset(const PI *__restrict__ P, uint64_t hw, int N, int K,
+                                          int A, int two_s, int bits, uint32_t mask) {
+    I o = 0;
+    int Ak = A;
+    for (int k = N; k > K; --k) {
+        const int a = (int)((hw >> ((k - 1 - K) * bits)) & mask);
+        o += (I)P[((size_t)(k - 1) * (A + 1) + Ak) * (two_s + 1) + a];
+        Ak -= a;
+    }
+    return o;
+}
+
+// Block of every row: one wave per block.
+template <typename I>
+__global__ __launch_bounds__(kBlock) void digit_row_blocks(const DigitBlock<I> *__restrict__ blocks,
+                                                           int64_t n, uint32_t *__restrict__ rowblk) {
+    const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
+    for (int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6; i < n; i += nw)
+        for (int r = threadIdx.x & 63; r < blocks[i].size; r += 64)
+            rowblk[(size_t)blocks[i].off + r] = (uint32_t)i;
+}
+
+// Rows of the block tables: the allowed high-word moves in bond order (first
+// a_u - 1, a_v + 1, then the other; padded with the own block and 0), the
+// diagonal part, and the target blocks of the straddling bonds' two moves (the
+// own block where the high digit does not allow one).  The matrix elements
+// have the roundings of row_hx.
+template <typename T, typename I, typename PI>
+__global__ __launch_bounds__(kBlock) void digit_rows(
+    const PI *__restrict__ P, const DigitBlock<I> *__restrict__ blocks, int64_t n, int N, int K,
+    int A, int two_s, int bits, uint32_t mask, const BondDev *__restrict__ bonds, int nb,
+    const double *__restrict__ ladder, int nS, int mw, DigitMoves<T, I> *__restrict__ moves,
+    uint32_t *__restrict__ mcnt, T *__restrict__ dhigh, I *__restrict__ strad) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t hw = blocks[i].hword;
+        const I own = blocks[i].off;
+        DigitMoves<T, I> *row = moves + (size_t)i * (mw / 4);
+        auto put = [&](int c, I o, T f) {
+            row[c / 4].off[c % 4] = o;
+            row[c / 4].cf[c % 4] = f;
+        };
+        int c = 0, s = 0;
+        double d = 0.0;
+        for (int b = 0; b < nb; ++b) {
+            const int u = bonds[b].u, v = bonds[b].v;
+            if (v < K) continue;
+            const int sv = (v - K) * bits, av = (int)((hw >> sv) & mask);
+            const uint64_t ev = 1ull << sv;
+            if (u < K) {
+                I *o = strad + ((size_t)i * nS + s) * 2;
+                o[0] = av < two_s ? block_offset<I, PI>(P, hw + ev, N, K, A, two_s, bits, mask) : own;
+                o[1] = av >= 1 ? block_offset<I, PI>(P, hw - ev, N, K, A, two_s, bits, mask) : own;
+                ++s;
+                continue;
+            }
+            const int su = (u - K) * bits, au = (int)((hw >> su) & mask);
+            const uint64_t eu = 1ull << su;
+            const T mJ2 = (T)bonds[b].mJ2;
+            if (au >= 1 && av < two_s)
+                put(c++, block_offset<I, PI>(P, hw - eu + ev, N, K, A, two_s, bits, mask),
+                    mJ2 * (T)ladder[au] * (T)ladder[av + 1]);
+            if (av >= 1 && au < two_s)
+                put(c++, block_offset<I, PI>(P, hw + eu - ev, N, K, A, two_s, bits, mask),
+                    mJ2 * (T)ladder[av] * (T)ladder[au + 1]);
+            d += bonds[b].mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
+        }
+        mcnt[i] = (uint32_t)c;
+        dhigh[i] = (T)d;
+        for (; c < mw; ++c) put(c, own, (T)0);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Host side
+// ---------------------------------------------------------------------------
+namespace {
+
+// Whether a vector of doubles stays below 4 GiB: 32-bit indices and byte offsets.
+bool small_index(const Basis *b) { return b->dim < ((int64_t)1 << 29); }
+
+int64_t ipow(int64_t b, int e) {
+    int64_t r = 1;
+    for (int i = 0; i < e; ++i) r *= b;
+    return r;
+}
+
+// Blocks of a split at K low sites: by digit sum of the low word, the number
+// of rows of a block and of blocks.
+void split_counts(const Basis *b, int K, std::vector<int64_t> &size, std::vector<int64_t> &blocks) {
+    const int nh = b->N - K;
+    size.assign((size_t)K * b->two_s + 1, 0);
+    blocks.assign(size.size(), 0);
+    for (int a = 0; a <= K * b->two_s; ++a) {
+        size[a] = b->count(K, a);
+        const int ah = b->A - a;
+        blocks[a] = ah < 0 || ah > nh * b->two_s ? 0 : b->count(nh, ah);
+    }
+}
+
+// LDS of a workgroup: matrix elements of the front bonds, R blocks per wave.
+size_t digit_lds(const Basis *b, int R, int smax, int nF, size_t es) {
+    const size_t W = (size_t)b->two_s + 1;
+    return ((size_t)nF * W * W * 2 * es + 31) / 32 * 32 +
+           (size_t)(kBlock / 64) * R * (smax + 1) * es;
+}
+
+// Device arrays of one table set in one allocation: those with host contents
+// first, uploaded in one copy, then those that kernels fill.
+struct Arena {
+    std::vector<unsigned char> host;
+    size_t total = 0;
+    template <typename V> size_t add(const std::vector<V> &v) {
+        const size_t at = total, bytes = v.size() * sizeof(V);
+        total = (total + bytes + 255) / 256 * 256;
+        host.resize(total);
+        if (bytes) std::memcpy(host.data() + at, v.data(), bytes);
+        return at;
+    }
+    size_t reserve(size_t bytes) {
+        const size_t at = total;
+        total = (total + bytes + 255) / 256 * 256;
+        return at;
+    }
+    hipError_t upload(void **mem) const {
+        hipError_t e = hipMalloc(mem, total + 256);
+        if (e == hipSuccess && !host.empty())
+            e = hipMemcpy(*mem, host.data(), host.size(), hipMemcpyHostToDevice);
+        return e;
+    }
+};
+
+void count_bonds(const Couplings *c, int K, int *nF, int *nH, int *nS) {
+    *nF = *nH = *nS = 0;
+    for (const BondDev &d : c->host) {
+        if (d.u >= K) ++*nH;
+        else {
+            ++*nF;
+            if (d.v >= K) ++*nS;
+        }
+    }
+}
+
+size_t digit_table_bytes(const Basis *b, const DigitSplit &s, const Couplings *c, size_t es) {
+    int nF, nH, nS;
+    count_bonds(c, s.K, &nF, &nH, &nS);
+    const size_t is = small_index(b) ? 4 : 8, bs = 32;
+    return (size_t)s.n_blocks *
+               ((2 * (size_t)nH + 3) * (is + es) + 4 + es + 2 * (size_t)nS * is + bs) +
+           (s.flat ? (size_t)b->dim * sizeof(uint32_t) : 0);
+}
+
+}  // namespace
+
+// How the rows are split.  A wave per R blocks pays once a wave's lanes are
+// mostly in use and there are enough blocks to fill the chip; below that one
+// lane per row is faster.  Measured (us per H x of nearest-neighbour rings,
+// FP64 / FP32; wave per blocks, lane per row, generic kernel):
+//   s = 1,   16 sites, M = 0,  5,196,627 rows:   95 / 60,  121 / 100,  261 / 250
+//   s = 1,   18 sites, M = 3, 30,759,120 rows:  590 / 387, 824 / 604, 1662 / 1590
+//   s = 3/2, 12 sites, M = 0,  1,703,636 rows:   37 / 27,   43 / 34,    79 / 75
+//   s = 1,   16 sites, M = 5,  1,665,456 rows:   53 / 35,   44 / 37,    95 / 91
+//   s = 1,   20 sites, M = 13,   484,500 rows:   62 / 34,   21 / 16,    48 / 46
+//   s = 1,   14 sites, M = 0,    616,227 rows:   25 / 13,   18 / 12,    39 / 38
+// so one lane per row below kFlatRows rows and where fewer than kFlatUse of a
+// wave's lanes would have a row.
+constexpr int64_t kFlatRows = (int64_t)1 << 20;
+constexpr double kFlatUse = 0.6;
+constexpr int kFlatWords = 4096;     // most low words with one lane per row
+
+DigitSplit choose_digit_split(const Basis *b) {
+    // waves of a launch go in rounds of kSlots (4 per SIMD); a wave's time is
+    // that of its group (tables, copy to LDS) plus that of its 64-row chunks,
+    // which grows with the rows per lane
+    constexpr double kSlots = 4096.0;
+    DigitSplit best, flat;
+    if (b->two_s < 2 || b->two_s > 15) return best;
+    double best_t = 0.0, best_use = 0.0;
+    std::vector<int64_t> size, blocks;
+    for (int K = 1; K < b->N && ipow(b->two_s + 1, K) <= kDigitMaxWords; ++K) {
+        split_counts(b, K, size, blocks);
+        for (int R : {1, 2, 4}) {
+            DigitSplit s;
+            s.K = K;
+            s.R = R;
+            double work = 0.0, longest = 0.0, lanes = 0.0;
+            for (size_t a = 0; a < size.size(); ++a) {
+                if (!blocks[a]) continue;
+                s.smax = (int)std::min<int64_t>(std::max<int64_t>(s.smax, size[a]), kDigitMaxSize);
+                const int64_t n = (blocks[a] + R - 1) / R, chunks = (size[a] + 63) / 64;
+                const double t = 1.0 + (double)chunks * (0.5 + 0.25 * R);
+                s.n_blocks += blocks[a];
+                s.n_groups += n;
+                work += (double)n * t;
+                lanes += (double)blocks[a] * (double)chunks * 64.0;
+                longest = std::max(longest, t);
+            }
+            if (s.smax >= kDigitMaxSize || s.n_blocks >= ((int64_t)1 << 31)) continue;
+            if (R == 1 && ipow(b->two_s + 1, K) <= kFlatWords) {
+                flat = s;
+                flat.flat = true;
+            }
+            if ((size_t)(kBlock / 64) * R * (s.smax + 1) * 8 > 36 * 1024) continue;
+            const double t = std::max(longest, work / kSlots);
+            if (best.K == 0 || t < best_t) {
+                best = s;
+                best_t = t;
+                best_use = (double)b->dim / lanes;
+            }
+        }
+    }
+    if (flat.K && (b->dim < kFlatRows || best.K == 0 || best_use < kFlatUse)) return flat;
+    return best;
+}
+
+// Whether the block kernel for s >= 1 runs these couplings (c null: whether it
+// can run on this basis at all): its LDS and its tables fit the budgets.
+bool digit_fits(const Basis *b, const Couplings *c) {
+    const DigitSplit &s = b->digit;
+    if (s.K == 0) return false;
+    if (!c) return true;
+    int nF, nH, nS;
+    count_bonds(c, s.K, &nF, &nH, &nS);
+    return digit_lds(b, s.flat ? 0 : s.R, s.smax, nF, 8) <= kDigitMaxLds &&
+           digit_table_bytes(b, s, c, 8) <= kDigitMaxTables;
+}
+
+// Workgroups for n_groups waves of work: one group per wave up to a grid far
+// beyond the resident workgroups, so that the dispatcher evens out groups of
+// unequal size (18 sites, s = 1, M = 3, 30.8 M rows, FP32: 483 us on 2048
+// workgroups, 417 on 4096, 391 on 16384 and 392 on 65536).
+static int grid_of(int64_t n_groups) {
+    int64_t g = std::min<int64_t>((n_groups + kBlock / 64 - 1) / (kBlock / 64), kDigitMaxGrid);
+    if (g >= kXcds) g -= g % kXcds;
+    return (int)std::max<int64_t>(g, 1);
+}
+
+int hx_digit_grid(const Basis *b) {
+    return b->digit.flat ? grid_of((b->dim + 63) / 64) : grid_of(b->digit.n_groups);
+}
+
+// The high words in memory order, an odometer over their digits (site N - 1
+// most significant) that keeps those whose low word has a digit sum in range,
+// and the groups of R blocks of one class.
+template <typename I>
+static int put_blocks(const Basis *b, DigitTables *t) {
+    const int nh = b->N - t->K, two_s = b->two_s, A = b->A, R = t->R;
+    const int hmin = std::max(0, A - t->K * two_s), hmax = std::min(A, nh * two_s);
+    std::vector<DigitBlock<I>> blocks;
+    std::vector<uint8_t> cls_of;
+    blocks.reserve(t->n_blocks);
+    cls_of.reserve(t->n_blocks);
+    std::vector<int> dig(nh, 0);
+    uint64_t packed = 0, off = 0;
+    auto set = [&](int i, int a) {
+        packed += (uint64_t)(int64_t)(a - dig[i]) << (i * b->bits);
+        dig[i] = a;
+    };
+    auto lowest = [&](int upto, int sum) {   // smallest digits of sites 0..upto-1 with that sum
+        for (int i = 0; i < upto; ++i) {
+            const int a = std::min(sum, two_s);
+            set(i, a);
+            sum -= a;
+        }
+    };
+    lowest(nh, hmin);
+    int hsum = hmin;
+    for (;;) {
+        const int a = A - hsum;
+        DigitBlock<I> blk{};
+        blk.hword = packed;
+        blk.off = (I)off;
+        blk.cs = t->cls[2 * a];
+        blk.size = t->cls[2 * a + 1];
+        blocks.push_back(blk);
+        cls_of.push_back((uint8_t)a);
+        off += (uint64_t)blk.size;
+        // successor: raise the lowest site whose raise leaves a sum that the
+        // sites below it can bring into range
+        int i = 0, below = 0;
+        for (; i < nh; ++i) {
+            const int rest = hsum - below - dig[i];          // sites above i
+            if (dig[i] < two_s && rest + dig[i] + 1 <= hmax) {
+                const int need = std::max(0, hmin - rest - dig[i] - 1);
+                if (need <= i * two_s) {
+                    set(i, dig[i] + 1);
+                    hsum = rest + dig[i] + need;
+                    lowest(i, need);
+                    break;
+                }
+            }
+            below += dig[i];
+        }
+        if (i == nh) break;
+    }
+    if ((int64_t)blocks.size() != t->n_blocks || (int64_t)off != b->dim)
+        return fail(HM_EINVAL, "internal: %zu blocks with %llu rows, expected %lld with %lld",
+                    blocks.size(), (unsigned long long)off, (long long)t->n_blocks,
+                    (long long)b->dim);
+    std::vector<uint32_t> groups;
+    if (!b->digit.flat) {
+        // a class's blocks go in groups of R in order; a group takes its place
+        // by its first block, so the sweep follows memory order
+        std::vector<uint32_t> open(t->nclass, 0), seen(t->nclass, 0);
+        groups.reserve(t->n_groups * R);
+        for (size_t i = 0; i < blocks.size(); ++i) {
+            const int a = cls_of[i];
+            if (seen[a]++ % R == 0) {
+                open[a] = (uint32_t)groups.size();
+                groups.insert(groups.end(), R, kNoBlock);
+            }
+            groups[open[a] + (seen[a] - 1) % R] = (uint32_t)i;
+        }
+        if ((int64_t)groups.size() != t->n_groups * R)
+            return fail(HM_EINVAL, "internal: %zu group entries, expected %lld", groups.size(),
+                        (long long)t->n_groups * R);
+    }
+    Arena arena;
+    const size_t o_blocks = arena.add(blocks), o_groups = arena.add(groups);
+    const size_t o_rows = arena.reserve(b->digit.flat ? (size_t)b->dim * sizeof(uint32_t) : 0);
+    const hipError_t e = arena.upload(&t->mem);
+    if (e != hipSuccess)
+        return fail(e == hipErrorOutOfMemory ? HM_ENOMEM : HM_EDEVICE, "block kernel tables: %s",
+                    hipGetErrorString(e));
+    unsigned char *m = (unsigned char *)t->mem;
+    t->blocks = m + o_blocks;
+    t->groups = (uint32_t *)(m + o_groups);
+    t->rowblk = (uint32_t *)(m + o_rows);
+    if (b->digit.flat) {
+        hipLaunchKernelGGL(digit_row_blocks<I>, dim3(kMaxGrid), dim3(kBlock), 0, nullptr,
+                           (const DigitBlock<I> *)t->blocks, t->n_blocks, t->rowblk);
+        HM_HIP(hipGetLastError());
+    }
+    return HM_OK;
+}
+
+static int digit_prepare(Basis *b, DigitTables **out) {
+    if (b->digit_tables) {
+        *out = (DigitTables *)b->digit_tables;
+        return HM_OK;
+    }
+    const DigitSplit &sp = b->digit;
+    const int K = sp.K, W = b->two_s + 1, words = (int)ipow(W, K);
+    auto *t = new DigitTables;
+    t->K = K;
+    t->R = sp.R;
+    t->words = words;
+    t->smax = sp.smax;
+    t->n_blocks = sp.n_blocks;
+    t->n_groups = sp.n_groups;
+    t->nclass = K * b->two_s + 1;
+    // low words, ascending within every digit sum
+    t->cls.resize(2 * (size_t)t->nclass);
+    for (int a = 0, s = 0; a < t->nclass; ++a) {
+        t->cls[2 * a] = s;
+        t->cls[2 * a + 1] = (int)b->count(K, a);
+        s += t->cls[2 * a + 1];
+    }
+    t->rank.resize(words);
+    t->word.resize(words);
+    std::vector<int> fill(t->nclass, 0);
+    for (int n = 0; n < words; ++n) {
+        int a = 0;
+        for (int q = n; q > 0; q /= W) a += q % W;
+        t->rank[n] = (uint16_t)fill[a];
+        t->word[t->cls[2 * a] + fill[a]] = (uint16_t)n;
+        ++fill[a];
+    }
+    const int rc = small_index(b) ? put_blocks<uint32_t>(b, t) : put_blocks<uint64_t>(b, t);
+    if (rc != HM_OK) {
+        free_digit(t);
+        return rc;
+    }
+    b->digit_tables = t;
+    b->digit_tables_free = free_digit;
+    *out = t;
+    return HM_OK;
+}
+
+template <typename T, typename I, typename PI>
+static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTables *t,
+                              DigitBonds *d) {
+    const int K = t->K, W = b->two_s + 1, words = t->words, two_s = b->two_s;
+    int nH = 0;
+    count_bonds(c, K, &d->nF, &nH, &d->nS);
+    d->mw = (2 * nH + 3) / 4 * 4;
+    // runs of low-word bonds in fours, twos and ones
+    std::vector<DigitOp<T>> ops;
+    std::vector<T> cf;
+    std::vector<const BondDev *> front;
+    for (const BondDev &bd : c->host)
+        if (bd.u < K) front.push_back(&bd);
+    int ns = 0;
+    for (size_t i = 0; i < front.size();) {
+        DigitOp<T> op{};
+        op.first = (int)i;
+        op.mJ4 = (T)front[i]->mJ4;
+        size_t n = 1;
+        if (front[i]->v >= K) {
+            op.straddle = ns++;
+            op.sv = (front[i]->v - K) * b->bits;
+        } else {
+            op.straddle = -1;
+            while (n < 4 && i + n < front.size() && front[i + n]->v < K) ++n;
+            if (n == 3) n = 2;
+        }
+        op.n = (int)n;
+        ops.push_back(op);
+        i += n;
+    }
+    d->n_ops = (int)ops.size();
+    // per front bond the matrix elements, with the roundings of row_hx, and
+    // per low word the ranks its moves lead to; per low word the diagonal part
+    std::vector<uint32_t> low(front.size() * words);
+    std::vector<double> dsum(words, 0.0);
+    const uint32_t zero = (uint32_t)t->smax;
+    std::vector<uint8_t> dig((size_t)K * words);      // digits of the low words
+    for (int i = 0; i < words; ++i)
+        for (int u = 0, n = t->word[i]; u < K; ++u, n /= W) dig[(size_t)u * words + i] = n % W;
+    for (size_t f = 0; f < front.size(); ++f) {
+        const BondDev &bd = *front[f];
+        const T mJ2 = (T)bd.mJ2;
+        for (int au = 0; au < W; ++au)
+            for (int av = 0; av < W; ++av) {
+                const T one = mJ2 * (T)b->ladder[au], two = mJ2 * (T)b->ladder[av];
+                cf.push_back(one * (T)b->ladder[av + 1]);
+                cf.push_back(two * (T)b->ladder[au + 1]);
+            }
+        const int wu = (int)ipow(W, bd.u), wv = bd.v < K ? (int)ipow(W, bd.v) : 0;
+        const uint8_t *du = &dig[(size_t)bd.u * words];
+        const uint8_t *dv = bd.v < K ? &dig[(size_t)bd.v * words] : nullptr;
+        for (int i = 0; i < words; ++i) {
+            const int n = t->word[i], au = du[i];
+            uint32_t r1, r2, e;
+            if (dv) {
+                const int av = dv[i];
+                r1 = au >= 1 && av < two_s ? t->rank[n - wu + wv] : zero;
+                r2 = av >= 1 && au < two_s ? t->rank[n + wu - wv] : zero;
+                e = (uint32_t)(au * W + av);
+                dsum[i] += bd.mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
+            } else {
+                r1 = au >= 1 ? t->rank[n - wu] : t->rank[n];
+                r2 = au < two_s ? t->rank[n + wu] : t->rank[n];
+                e = (uint32_t)au;
+            }
+            // (a class without blocks may be larger than the field, and is not used)
+            constexpr uint32_t kMask = (1u << kRankBits) - 1u;
+            low[f * words + i] = (r1 & kMask) | (r2 & kMask) << kRankBits | e << (2 * kRankBits);
+        }
+    }
+    std::vector<T> dlow(dsum.begin(), dsum.end());
+    const size_t nblk = (size_t)t->n_blocks;
+    Arena arena;
+    const size_t o_ops = arena.add(ops), o_cf = arena.add(cf), o_low = arena.add(low);
+    const size_t o_dlow = arena.add(dlow);
+    const size_t o_moves = arena.reserve(nblk * (d->mw / 4) * sizeof(DigitMoves<T, I>));
+    const size_t o_mcnt = arena.reserve(nblk * sizeof(uint32_t));
+    const size_t o_dhigh = arena.reserve(nblk * sizeof(T));
+    const size_t o_strad = arena.reserve(nblk * d->nS * 2 * sizeof(I));
+    hipError_t e = arena.upload(&d->mem);
+    if (e != hipSuccess) return e;
+    unsigned char *m = (unsigned char *)d->mem;
+    d->ops = m + o_ops;
+    d->cf = m + o_cf;
+    d->low = (uint32_t *)(m + o_low);
+    d->dlow = m + o_dlow;
+    d->moves = m + o_moves;
+    d->mcnt = (uint32_t *)(m + o_mcnt);
+    d->dhigh = m + o_dhigh;
+    d->strad = m + o_strad;
+    const int grid = (int)std::min<int64_t>((t->n_blocks + kBlock - 1) / kBlock, kMaxGrid);
+    hipLaunchKernelGGL((digit_rows<T, I, PI>), dim3(grid), dim3(kBlock), 0, nullptr,
+                       (const PI *)b->d_prefix, (const DigitBlock<I> *)t->blocks, t->n_blocks, b->N,
+                       K, b->A, two_s, b->bits, (1u << b->bits) - 1u, c->dev, c->nb, b->d_ladder,
+                       d->nS, d->mw, (DigitMoves<T, I> *)d->moves, d->mcnt, (T *)d->dhigh,
+                       (I *)d->strad);
+    e = hipGetLastError();
+    // other streams may use the tables from now on
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    return e;
+}
+
+template <typename T>
+static hipError_t build_bonds_t(const Basis *b, const Couplings *c, const DigitTables *t,
+                                DigitBonds *d) {
+    if (small_index(b)) return build_bonds<T, uint32_t, uint32_t>(b, c, t, d);
+    if (b->idx32) return build_bonds<T, uint64_t, uint32_t>(b, c, t, d);
+    return build_bonds<T, uint64_t, uint64_t>(b, c, t, d);
+}
+
+// The tables of these couplings in this element type, built on first use.
+static int digit_get(Basis *b, const Couplings *c, int dtype, hipStream_t st, DigitTables **tout,
+                     const DigitBonds **bout) {
+    std::lock_guard<std::mutex> lock(b->mu);
+    HM_TRY(device_prepare(b));
+    auto *cc = const_cast<Couplings *>(c);
+    if (!cc->half) {
+        cc->half = new DigitBondSet;
+        cc->half_free = free_digit_bonds;
+    }
+    auto *set = (DigitBondSet *)cc->half;
+    const int k = dtype == HM_F64 ? 0 : 1;
+    if (!set->have[k]) {
+        // nothing may be allocated while the stream is capturing
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (st && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+            cap != hipStreamCaptureStatusNone)
+            return HM_ENOMEM;
+    }
+    DigitTables *t = nullptr;
+    HM_TRY(digit_prepare(b, &t));
+    if (!set->have[k]) {
+        DigitBonds d;
+        hipError_t e;
+        if (dtype == HM_F64) e = build_bonds_t<double>(b, c, t, &d);
+        else e = build_bonds_t<float>(b, c, t, &d);
+        if (e != hipSuccess) {
+            if (d.mem) (void)hipFree(d.mem);
+            return fail(e == hipErrorOutOfMemory ? HM_ENOMEM : HM_EDEVICE,
+                        "block kernel bonds: %s", hipGetErrorString(e));
+        }
+        set->by_type[k] = d;
+        set->have[k] = true;
+    }
+    *tout = t;
+    *bout = &set->by_type[k];
+    return HM_OK;
+}
+
+// Builds the tables ahead of a run.
+int digit_prepare_tables(Basis *b, const Couplings *c, int dtype) {
+    DigitTables *t = nullptr;
+    const DigitBonds *d = nullptr;
+    return digit_get(b, c, dtype, nullptr, &t, &d);
+}
+
+template <typename T, typename I, int R>
+static void launch_digit_r(const DigitTables *t, const DigitArgs<T, I> &g, size_t lds,
+                           const HxPass &p, hipStream_t st) {
+    const int grid = grid_of(t->n_groups);
+    const T *x = (const T *)p.x, *pr = (const T *)p.p;
+    T *y = (T *)p.y, *store = (T *)p.store;
+#define HM_LAUNCH(D, S)                                                                        \
+    hipLaunchKernelGGL((hx_digit_kernel<T, I, R, D, S>), dim3(grid), dim3(kBlock), lds, st, g, \
+                       x, y, pr, p.sigma, p.cprev, p.partial, store, p.stopped)
+    const bool dot = p.partial != nullptr, sto = store != nullptr;
+    if (!dot && !sto) HM_LAUNCH(false, false);
+    else if (dot && !sto) HM_LAUNCH(true, false);
+    else if (!dot && sto) HM_LAUNCH(false, true);
+    else HM_LAUNCH(true, true);
+#undef HM_LAUNCH
+}
+
+template <typename T, typename I>
+static void launch_digit_t(const Basis *b, const DigitTables *t, const DigitBonds *d,
+                           const HxPass &p, hipStream_t st) {
+    DigitArgs<T, I> g{};
+    g.blocks = (const DigitBlock<I> *)t->blocks;
+    g.groups = t->groups;
+    g.ops = (const DigitOp<T> *)d->ops;
+    g.cf = (const T *)d->cf;
+    g.low = d->low;
+    g.dlow = (const T *)d->dlow;
+    g.moves = (const DigitMoves<T, I> *)d->moves;
+    g.mcnt = d->mcnt;
+    g.dhigh = (const T *)d->dhigh;
+    g.strad = (const I *)d->strad;
+    g.n_ops = d->n_ops;
+    g.n_groups = (uint32_t)t->n_groups;
+    // runs of 64 groups once every XCD gets many of them, else of one
+    // workgroup's four, so that few groups still spread over the XCDs
+    g.run = t->n_groups >= 8192 ? 64 : kBlock / 64;
+    g.nF = d->nF;
+    g.nS = d->nS;
+    g.mq = d->mw / 4;
+    g.words = t->words;
+    g.smax = t->smax;
+    g.two_s = b->two_s;
+    g.mask = (1 << b->bits) - 1;
+    g.rowblk = t->rowblk;
+    if (b->digit.flat) {
+        const size_t cf = (size_t)d->nF * (b->two_s + 1) * (b->two_s + 1) * 2 * sizeof(T);
+        const int grid = hx_digit_grid(b);
+        const T *x = (const T *)p.x, *pr = (const T *)p.p;
+        T *y = (T *)p.y, *store = (T *)p.store;
+#define HM_LAUNCH(D, S)                                                                          \
+    hipLaunchKernelGGL((hx_digit_flat_kernel<T, I, D, S>), dim3(grid), dim3(kBlock), cf, st, g,  \
+                       (I)b->dim, x, y, pr, p.sigma, p.cprev, p.partial, store, p.stopped)
+        const bool dot = p.partial != nullptr, sto = store != nullptr;
+        if (!dot && !sto) HM_LAUNCH(false, false);
+        else if (dot && !sto) HM_LAUNCH(true, false);
+        else if (!dot && sto) HM_LAUNCH(false, true);
+        else HM_LAUNCH(true, true);
+#undef HM_LAUNCH
+        return;
+    }
+    const size_t lds = digit_lds(b, t->R, t->smax, d->nF, sizeof(T));
+    if (t->R == 1) launch_digit_r<T, I, 1>(t, g, lds, p, st);
+    else if (t->R == 2) launch_digit_r<T, I, 2>(t, g, lds, p, st);
+    else launch_digit_r<T, I, 4>(t, g, lds, p, st);
+}
+
+int launch_hx_digit(const Basis *cb, const Couplings *c, int dtype, const HxPass &p,
+                    hipStream_t st) {
+    Basis *b = const_cast<Basis *>(cb);
+    DigitTables *t = nullptr;
+    const DigitBonds *d = nullptr;
+    const int rc = digit_get(b, c, dtype, st, &t, &d);
+    if (rc == HM_ENOMEM && !p.partial) {
+        // no memory for the tables, or a product captured before its first
+        // use: the generic kernel's sums are the same bit for bit
+        clear_error();
+        (void)hipGetLastError();
+        return launch_hx_generic(b, c, dtype, p, st);
+    }
+    HM_TRY(rc);
+    if (dtype == HM_F64) {
+        if (small_index(b)) launch_digit_t<double, uint32_t>(b, t, d, p, st);
+        else launch_digit_t<double, uint64_t>(b, t, d, p, st);
+    } else {
+        if (small_index(b)) launch_digit_t<float, uint32_t>(b, t, d, p, st);
+        else launch_digit_t<float, uint64_t>(b, t, d, p, st);
+    }
+    HM_HIP(hipGetLastError());
+    return HM_OK;
+}
+
+}  // namespace hm

@@ -34,24 +34,41 @@ int hx_half_grid(const Basis *b);
 bool half_supported(const Basis *b);
 int half_prepare_tables(Basis *b, const Couplings *c);
 bool half_fits(const Basis *b, const Couplings *c);
+int launch_hx_digit(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
+                    hipStream_t st);
+int hx_digit_grid(const Basis *b);
+int digit_prepare_tables(Basis *b, const Couplings *c, int dtype);
+bool digit_fits(const Basis *b, const Couplings *c);
 
-// 0 = automatic (the spin-1/2 block kernel when it applies to the basis and
-// its neighbour table fits the budget, else the generic digit kernel),
-// 1 = generic, 2 = block kernel (-1 if it does not apply).
+// 0 = automatic (the block kernel of the spin, where it applies to the basis
+// and its tables fit the budget, else the generic digit kernel), 1 = generic,
+// 2 = spin-1/2 block kernel (-1 if it does not apply); kKernelDigit, the block
+// kernel for s >= 1, is chosen by 0 only.
+constexpr int kKernelDigit = 5;
+
 int choose_kernel(const Basis *b, const Couplings *c, int requested) {
     if (requested == 1) return 1;
+    if (requested == 0 && b->two_s >= 2) return digit_fits(b, c) ? kKernelDigit : 1;
     const bool ok = c ? half_fits(b, c) : half_supported(b);
     if (requested == 2) return ok ? 2 : -1;
     return ok ? 2 : 1;
 }
 
 int hx_partial_count(const Basis *b, int kernel) {
-    return kernel == 2 ? hx_half_grid(b) : hx_generic_grid(b);
+    return kernel == 2 ? hx_half_grid(b) : kernel == kKernelDigit ? hx_digit_grid(b)
+                                                                  : hx_generic_grid(b);
+}
+
+int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel) {
+    if (kernel == 2) return half_prepare_tables(b, c);
+    if (kernel == kKernelDigit) return digit_prepare_tables(b, c, dtype);
+    return HM_OK;
 }
 
 int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel, const HxPass &p,
               hipStream_t st) {
     if (kernel == 2) return launch_hx_half(b, c, dtype, p, st);
+    if (kernel == kKernelDigit) return launch_hx_digit(b, c, dtype, p, st);
     return launch_hx_generic(b, c, dtype, p, st);
 }
 
@@ -109,7 +126,8 @@ static Layout layout(const Basis *b, int steps, int prec, int reorth) {
     const size_t es = prec == HM_PREC_F64 ? 8 : 4;
     L.grid_vec = vec_grid(b->dim);
     L.grid_b = pass_b_grid(b->dim, es);
-    L.nparts = std::max({kMaxGrid, L.grid_b, half_supported(b) ? hx_half_grid(b) : 0});
+    L.nparts = std::max({kMaxGrid, L.grid_b, half_supported(b) ? hx_half_grid(b) : 0,
+                         b->digit.K > 0 ? hx_digit_grid(b) : 0});
     size_t partial_len = (size_t)L.nparts;
     if (reorth) partial_len = std::max(partial_len, (size_t)L.grid_vec * (size_t)steps);
     size_t off = 0;
@@ -928,9 +946,16 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     const Couplings *c = cref.get();
     const bool small = o->kernel == 3 || (o->kernel == 0 && !g_timing && !o->full_reorth &&
                                           b->dim * (int64_t)std::max(c->nb, 1) <= kSmallAutoWork);
-    const int kernel = small ? 1 : choose_kernel(b, c, o->kernel);
+    int kernel = small ? 1 : choose_kernel(b, c, o->kernel);
     if (kernel < 0) return fail(HM_ERANGE, "block kernel tables too large for these couplings");
-    if (kernel == 2) HM_TRY(half_prepare_tables(b, c));
+    const int prc = prepare_kernel(b, c, o->precision == HM_PREC_F64 ? HM_F64 : HM_F32, kernel);
+    if (prc == HM_ENOMEM && kernel == kKernelDigit) {
+        kernel = 1;                   // the same sums without tables
+        clear_error();
+        (void)hipGetLastError();
+    } else {
+        HM_TRY(prc);
+    }
     Run R{};
     R.small = small ? 1 : 0;
     R.b = b;
