@@ -338,7 +338,7 @@ int dots(const BlockRun &R, const double *X, int nblk, const double *W) {
     hipLaunchKernelGGL((tall_dots_kernel<double, P>),
                        dim3(splits, (ncol + tall_cols<P>() - 1) / tall_cols<P>()),
                        dim3(kTallBlock), 0, R.st, X, W, (int64_t)R.b->dim, ncol, R.partial(),
-                       &R.dev()->stopped);
+                       &R.dev()->stopped, (const double *)nullptr, TallSub<double>{});
     return splits;
 }
 

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/hm.h"
+#include "lanczos_dev.h"
 
 namespace hm {
 
@@ -151,27 +152,23 @@ int64_t host_rank(const Basis *b, const uint8_t *digits);
 // ---------------------------------------------------------------------------
 // Kernel launchers (defined in the .hip translation units).
 // ---------------------------------------------------------------------------
-struct LzDev;   // device-side Lanczos scalars (see lanczos.cpp)
-
 int launch_unrank(const Basis *b, const int64_t *d_idx, int64_t n,
                   uint64_t *d_state, hipStream_t st);
 int launch_rank(const Basis *b, const uint64_t *d_state, int64_t n,
                 int64_t *d_idx, hipStream_t st);
 
 // Arguments of the fused H x pass used by hm_apply and by Lanczos.
-//   y_i = sigma * (H x)_i - c * p_i,  sigma/c read from device scalars when
-//   scal != nullptr (Lanczos) or taken as 1/0 otherwise (plain apply);
+//   y_i = sigma * (H x)_i - c * p_i,  sigma and c from the run's step (1 and 0
+//   for a plain product);
 //   optional: partial[blk] = sum over the workgroup's rows of y_i sigma x_i
 //             (FP64), store[i] = sigma * x_i (normalized Lanczos vector).
 struct HxPass {
     const void *x = nullptr;
     void *y = nullptr;
     const void *p = nullptr;            // previous vector (nullptr: none)
-    const double *sigma = nullptr;      // device scalar (nullptr: 1)
-    const double *cprev = nullptr;      // device scalar (nullptr: 0)
+    LzStep step;                        // scalars of the step, stop flag
     double *partial = nullptr;          // per-workgroup FP64 partial sums
     void *store = nullptr;              // optional normalized copy
-    const int *stopped = nullptr;       // device flag: skip when nonzero
 };
 
 int hx_partial_count(const Basis *b, int kernel);      // partial slots needed

@@ -20,8 +20,8 @@
 // for R rows), copies them to its LDS slice, interleaved, so that one LDS read
 // serves the R rows, and goes over them 64 rows at a time.  Every row adds its
 // bonds in list order, as row_hx (hx_row.h) does; the diagonal element is the
-// sum of a low-word part, a high-word part (both tabulated, summed in FP64)
-// and the straddling bonds.
+// sum of a low-word part, a high-word part (both tabulated, summed in FP64 from
+// the same -J/4 in the vectors' type) and the straddling bonds.
 #include <algorithm>
 #include <cstring>
 #include <vector>
@@ -48,7 +48,7 @@ struct DigitOp {
     int32_t straddle;    // -1: both sites in the low word, else its slot in the block table
     int32_t first;       // index of the first bond (its table and matrix elements)
     int32_t sv;          // straddling: bit position of the digit in the high word
-    T mJ4;               // straddling: -J/4
+    T mJ4[4];            // -J/4
 };
 
 // Entry of the low-word table for one bond: the ranks of the two moves
@@ -105,8 +105,11 @@ struct DigitBonds {
     void *moves = nullptr;           // [block][mw / 4] DigitMoves<T, I>
     uint32_t *mcnt = nullptr;        // [block] moves the block's high word allows
     void *dhigh = nullptr;           // [block] diagonal part of the high-word bonds
+    void *kdiag = nullptr;           // [block][nH] (2 m_u)(2 m_v) of the high-word bonds and
+    void *hJ4 = nullptr;             // [nH] their -J/4 (FP32, one lane per row; nH padded to
+                                     // fours with zeros)
     void *strad = nullptr;           // [block][nS][2] target blocks of the straddling moves
-    int n_ops = 0, nF = 0, nS = 0, mw = 0;           // mw: moves of a row, padded to fours
+    int n_ops = 0, nF = 0, nS = 0, nH = 0, mw = 0;   // mw: moves of a row, padded to fours
     void *mem = nullptr;                             // the allocation that holds them
 };
 struct DigitBondSet {
@@ -133,9 +136,11 @@ struct DigitArgs {
     const DigitMoves<T, I> *moves;
     const uint32_t *mcnt;
     const T *dhigh;
+    const T *kdiag;
+    const T *hJ4;
     const I *strad;
     uint32_t n_groups, run;          // run: consecutive groups of one XCD
-    int n_ops, nF, nS, mq, words, smax, two_s, mask;   // mq: move pieces of a row
+    int n_ops, nF, nS, nH, mq, words, smax, two_s, mask;   // mq: move pieces of a row
 };
 
 template <typename T> using Const = const __attribute__((address_space(4))) T;
@@ -199,12 +204,13 @@ __device__ __forceinline__ void low_bonds(const uint32_t *__restrict__ low, int 
 template <typename T, typename I, int R, bool DOT, bool STORE>
 __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
     const DigitArgs<T, I> g, const T *__restrict__ x, T *__restrict__ y,
-    const T *__restrict__ prev, const double *__restrict__ sigma_p,
-    const double *__restrict__ cprev_p, double *__restrict__ partial, T *__restrict__ store,
-    const int *__restrict__ stopped) {
-    if (stopped && *stopped) return;
+    const T *__restrict__ prev, const LzStep step, double *__restrict__ partial,
+    T *__restrict__ store) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[16];
+    __shared__ double red[kLzLds];
+    double sigma_v, cprev_v;
+    if (!lz_begin(step, red, sigma_v, cprev_v)) return;
+    const double sigma = uniform(sigma_v), cprev = uniform(cprev_v);   // scalar registers
     const int WW = g.two_s + 1;
     const int ncf = g.nF * WW * WW * 2;
     T *cf = reinterpret_cast<T *>(smem);
@@ -213,8 +219,6 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
     for (int t = threadIdx.x; t < ncf; t += blockDim.x) cf[t] = g.cf[t];
     __syncthreads();
 
-    const double sigma = sigma_p ? *sigma_p : 1.0;
-    const double cprev = cprev_p ? *cprev_p : 0.0;
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     const int two_s = g.two_s;
     // XCDs (workgroup b runs on XCD b % 8) take turns on runs of g.run groups
@@ -316,7 +320,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
                 const uint32_t e = lo[0], rk1 = e & ((1u << kRankBits) - 1u);
                 const uint32_t rk2 = (e >> kRankBits) & ((1u << kRankBits) - 1u);
                 const int au = (int)(e >> (2 * kRankBits));
-                const T sJ = op.mJ4 * (T)(two_s - 2 * au);
+                const T sJ = op.mJ4[0] * (T)(two_s - 2 * au);
                 T g1[R], g2[R], c[R][2];
 #pragma unroll
                 for (int m = 0; m < R; ++m) {
@@ -384,6 +388,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
         const double s = block_sum(dot, red);
         if (threadIdx.x == 0) partial[blockIdx.x] = s;
     }
+    lz_end(step, red, sigma, cprev);
 }
 
 // The same rows where blocks are short (sectors far from M = 0 have blocks of a
@@ -391,10 +396,17 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
 // per row, whatever its block.  The block of a row comes from a table, and the
 // block's own tables are read per lane, broadcast among the lanes of one
 // block; low-word targets are gathered from memory instead of LDS.
+//
+// In FP32 the diagonal element is summed bond by bond in list order with the
+// roundings of row_hx, so that the result is the generic kernel's bit for bit:
+// an FP32 Lanczos run in a subspace this small does not average the roundings
+// of its rows out (8135 rows: coefficients 1e-8 apart).
 template <int W, typename T, typename I>
 __device__ __forceinline__ void flat_low_bonds(const uint32_t *__restrict__ low, int words,
-                                               const T *cf, int WW, uint32_t zero,
-                                               const T *__restrict__ x, I off0, I row, T &off) {
+                                               const T *cf, const T *kt, int WW, uint32_t zero,
+                                               const T *__restrict__ x, I off0, I row,
+                                               const Const<DigitOp<T>> &op, int q0, T &diag,
+                                               T &off) {
     constexpr uint32_t kMask = (1u << kRankBits) - 1u;
     uint32_t e[W];
     T x1[W], x2[W], c[W][2];
@@ -413,24 +425,28 @@ __device__ __forceinline__ void flat_low_bonds(const uint32_t *__restrict__ low,
     for (int q = 0; q < W; ++q) {
         off += c[q][0] * x1[q];
         off += c[q][1] * x2[q];
+        if constexpr (sizeof(T) == 4) diag += op.mJ4[q0 + q] * kt[e[q] >> (2 * kRankBits)];
     }
 }
 
 template <typename T, typename I, bool DOT, bool STORE>
 __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
     const DigitArgs<T, I> g, I dim, const T *__restrict__ x, T *__restrict__ y,
-    const T *__restrict__ prev, const double *__restrict__ sigma_p,
-    const double *__restrict__ cprev_p, double *__restrict__ partial, T *__restrict__ store,
-    const int *__restrict__ stopped) {
-    if (stopped && *stopped) return;
+    const T *__restrict__ prev, const LzStep step, double *__restrict__ partial,
+    T *__restrict__ store) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[16];
+    __shared__ double red[kLzLds];
+    double sigma_v, cprev_v;
+    if (!lz_begin(step, red, sigma_v, cprev_v)) return;
+    const double sigma = uniform(sigma_v), cprev = uniform(cprev_v);   // scalar registers
     const int WW = g.two_s + 1, two_s = g.two_s;
-    T *cf = reinterpret_cast<T *>(smem);
+    T *cf = reinterpret_cast<T *>(smem), *kt = cf + g.nF * WW * WW * 2;
     for (int t = threadIdx.x; t < g.nF * WW * WW * 2; t += blockDim.x) cf[t] = g.cf[t];
+    if constexpr (sizeof(T) == 4)        // (2 m_u)(2 m_v) by the index of the digits
+        for (int t = threadIdx.x; t < WW * WW; t += blockDim.x)
+            kt[t] = (T)((two_s - 2 * (t / WW)) * (two_s - 2 * (t % WW)));
     __syncthreads();
-    const double sigma = sigma_p ? *sigma_p : 1.0;
-    const double cprev = cprev_p ? *cprev_p : 0.0;
+    const Const<T> *hJ4 = as_const(g.hJ4);
     const Const<DigitOp<T>> *ops = as_const(g.ops);
     I first, last;
     block_rows<I>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, dim, first, last);
@@ -441,18 +457,22 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
         const uint32_t r = (uint32_t)(row - blk.off);
         const uint32_t *__restrict__ low = g.low + blk.cs + r;
         const T xi = x[row];
-        T diag = g.dlow[blk.cs + r] + g.dhigh[hb], off = 0;
+        T diag = 0, off = 0;
+        if constexpr (sizeof(T) == 8) diag = g.dlow[blk.cs + r] + g.dhigh[hb];
         for (int o = 0; o < g.n_ops; ++o) {
             const Const<DigitOp<T>> &op = ops[o];
             const T *cfb = cf + op.first * (WW * WW * 2);
             const uint32_t *__restrict__ lo = low + (size_t)op.first * g.words;
             if (op.straddle < 0) {
                 if (op.n == 4)
-                    flat_low_bonds<4, T, I>(lo, g.words, cfb, WW, g.smax, x, blk.off, row, off);
+                    flat_low_bonds<4, T, I>(lo, g.words, cfb, kt, WW, g.smax, x, blk.off, row,
+                                            op, 0, diag, off);
                 else if (op.n == 2)
-                    flat_low_bonds<2, T, I>(lo, g.words, cfb, WW, g.smax, x, blk.off, row, off);
+                    flat_low_bonds<2, T, I>(lo, g.words, cfb, kt, WW, g.smax, x, blk.off, row,
+                                            op, 0, diag, off);
                 else
-                    flat_low_bonds<1, T, I>(lo, g.words, cfb, WW, g.smax, x, blk.off, row, off);
+                    flat_low_bonds<1, T, I>(lo, g.words, cfb, kt, WW, g.smax, x, blk.off, row,
+                                            op, 0, diag, off);
                 continue;
             }
             const uint32_t e = lo[0], rk1 = e & ((1u << kRankBits) - 1u);
@@ -465,8 +485,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
             const T v1 = load_at(x, a1 ? o1 + (I)rk1 : row), v2 = load_at(x, a2 ? o2 + (I)rk2 : row);
             T c[2];
             lds_row<T, 2>(cfb + (au * WW + av) * 2, c);
-            const T sJ = op.mJ4 * (T)(two_s - 2 * au);
-            diag += sJ * (T)(two_s - 2 * av);
+            diag += op.mJ4[0] * (T)((two_s - 2 * au) * (two_s - 2 * av));
             off += c[0] * (a1 ? v1 : (T)0);
             off += c[1] * (a2 ? v2 : (T)0);
         }
@@ -480,6 +499,17 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
 #pragma unroll
             for (int q = 0; q < 4; ++q) off += m.cf[q] * (q0 + q < n ? xj[q] : (T)0);
         }
+        if constexpr (sizeof(T) == 4) {
+            const float4 *__restrict__ kd =
+                reinterpret_cast<const float4 *>(g.kdiag + (size_t)hb * g.nH);
+            for (int b = 0; b < g.nH; b += 4) {
+                const float4 k4 = kd[b / 4];
+                diag += hJ4[b] * k4.x;
+                diag += hJ4[b + 1] * k4.y;
+                diag += hJ4[b + 2] * k4.z;
+                diag += hJ4[b + 3] * k4.w;
+            }
+        }
         const T hv = diag * xi + off;
         double w = sigma * (double)hv;
         if (prev) w -= cprev * (double)prev[row];
@@ -492,6 +522,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
         const double s = block_sum(dot, red);
         if (threadIdx.x == 0) partial[blockIdx.x] = s;
     }
+    lz_end(step, red, sigma, cprev);
 }
 
 // ---------------------------------------------------------------------------
@@ -532,7 +563,8 @@ __global__ __launch_bounds__(kBlock) void digit_rows(
     const PI *__restrict__ P, const DigitBlock<I> *__restrict__ blocks, int64_t n, int N, int K,
     int A, int two_s, int bits, uint32_t mask, const BondDev *__restrict__ bonds, int nb,
     const double *__restrict__ ladder, int nS, int mw, DigitMoves<T, I> *__restrict__ moves,
-    uint32_t *__restrict__ mcnt, T *__restrict__ dhigh, I *__restrict__ strad) {
+    uint32_t *__restrict__ mcnt, T *__restrict__ dhigh, int nH, T *__restrict__ kdiag,
+    T *__restrict__ hJ4, I *__restrict__ strad) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t hw = blocks[i].hword;
@@ -542,7 +574,7 @@ __global__ __launch_bounds__(kBlock) void digit_rows(
             row[c / 4].off[c % 4] = o;
             row[c / 4].cf[c % 4] = f;
         };
-        int c = 0, s = 0;
+        int c = 0, s = 0, h = 0;
         double d = 0.0;
         for (int b = 0; b < nb; ++b) {
             const int u = bonds[b].u, v = bonds[b].v;
@@ -565,7 +597,17 @@ __global__ __launch_bounds__(kBlock) void digit_rows(
             if (av >= 1 && au < two_s)
                 put(c++, block_offset<I, PI>(P, hw + eu - ev, N, K, A, two_s, bits, mask),
                     mJ2 * (T)ladder[av] * (T)ladder[au + 1]);
-            d += bonds[b].mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
+            const int k = (two_s - 2 * au) * (two_s - 2 * av);
+            d += (double)(T)bonds[b].mJ4 * (double)k;
+            if (kdiag) {
+                kdiag[(size_t)i * nH + h] = (T)k;
+                if (i == 0) hJ4[h] = (T)bonds[b].mJ4;
+                ++h;
+            }
+        }
+        for (; kdiag && h < nH; ++h) {
+            kdiag[(size_t)i * nH + h] = 0;
+            if (i == 0) hJ4[h] = 0;
         }
         mcnt[i] = (uint32_t)c;
         dhigh[i] = (T)d;
@@ -603,7 +645,7 @@ void split_counts(const Basis *b, int K, std::vector<int64_t> &size, std::vector
 // LDS of a workgroup: matrix elements of the front bonds, R blocks per wave.
 size_t digit_lds(const Basis *b, int R, int smax, int nF, size_t es) {
     const size_t W = (size_t)b->two_s + 1;
-    return ((size_t)nF * W * W * 2 * es + 31) / 32 * 32 +
+    return ((2 * (size_t)nF + 1) * W * W * es + 31) / 32 * 32 +
            (size_t)(kBlock / 64) * R * (smax + 1) * es;
 }
 
@@ -648,7 +690,7 @@ size_t digit_table_bytes(const Basis *b, const DigitSplit &s, const Couplings *c
     count_bonds(c, s.K, &nF, &nH, &nS);
     const size_t is = small_index(b) ? 4 : 8, bs = 32;
     return (size_t)s.n_blocks *
-               ((2 * (size_t)nH + 3) * (is + es) + 4 + es + 2 * (size_t)nS * is + bs) +
+               ((2 * (size_t)nH + 3) * (is + es) + 4 + (nH + 4) * es + 2 * (size_t)nS * is + bs) +
            (s.flat ? (size_t)b->dim * sizeof(uint32_t) : 0);
 }
 
@@ -896,7 +938,6 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
     for (size_t i = 0; i < front.size();) {
         DigitOp<T> op{};
         op.first = (int)i;
-        op.mJ4 = (T)front[i]->mJ4;
         size_t n = 1;
         if (front[i]->v >= K) {
             op.straddle = ns++;
@@ -907,6 +948,7 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
             if (n == 3) n = 2;
         }
         op.n = (int)n;
+        for (size_t q = 0; q < n; ++q) op.mJ4[q] = (T)front[i + q]->mJ4;
         ops.push_back(op);
         i += n;
     }
@@ -939,7 +981,7 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
                 r1 = au >= 1 && av < two_s ? t->rank[n - wu + wv] : zero;
                 r2 = av >= 1 && au < two_s ? t->rank[n + wu - wv] : zero;
                 e = (uint32_t)(au * W + av);
-                dsum[i] += bd.mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
+                dsum[i] += (double)(T)bd.mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
             } else {
                 r1 = au >= 1 ? t->rank[n - wu] : t->rank[n];
                 r2 = au < two_s ? t->rank[n + wu] : t->rank[n];
@@ -958,6 +1000,10 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
     const size_t o_moves = arena.reserve(nblk * (d->mw / 4) * sizeof(DigitMoves<T, I>));
     const size_t o_mcnt = arena.reserve(nblk * sizeof(uint32_t));
     const size_t o_dhigh = arena.reserve(nblk * sizeof(T));
+    const bool chain = b->digit.flat && sizeof(T) == 4;
+    d->nH = chain ? (nH + 3) / 4 * 4 : 0;
+    const size_t o_kdiag = arena.reserve(nblk * d->nH * sizeof(T));
+    const size_t o_hJ4 = arena.reserve(d->nH * sizeof(T));
     const size_t o_strad = arena.reserve(nblk * d->nS * 2 * sizeof(I));
     hipError_t e = arena.upload(&d->mem);
     if (e != hipSuccess) return e;
@@ -969,13 +1015,15 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
     d->moves = m + o_moves;
     d->mcnt = (uint32_t *)(m + o_mcnt);
     d->dhigh = m + o_dhigh;
+    d->kdiag = chain ? m + o_kdiag : nullptr;
+    d->hJ4 = m + o_hJ4;
     d->strad = m + o_strad;
     const int grid = (int)std::min<int64_t>((t->n_blocks + kBlock - 1) / kBlock, kMaxGrid);
     hipLaunchKernelGGL((digit_rows<T, I, PI>), dim3(grid), dim3(kBlock), 0, nullptr,
                        (const PI *)b->d_prefix, (const DigitBlock<I> *)t->blocks, t->n_blocks, b->N,
                        K, b->A, two_s, b->bits, (1u << b->bits) - 1u, c->dev, c->nb, b->d_ladder,
                        d->nS, d->mw, (DigitMoves<T, I> *)d->moves, d->mcnt, (T *)d->dhigh,
-                       (I *)d->strad);
+                       d->nH, (T *)d->kdiag, (T *)d->hJ4, (I *)d->strad);
     e = hipGetLastError();
     // other streams may use the tables from now on
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
@@ -1044,7 +1092,7 @@ static void launch_digit_r(const DigitTables *t, const DigitArgs<T, I> &g, size_
     T *y = (T *)p.y, *store = (T *)p.store;
 #define HM_LAUNCH(D, S)                                                                        \
     hipLaunchKernelGGL((hx_digit_kernel<T, I, R, D, S>), dim3(grid), dim3(kBlock), lds, st, g, \
-                       x, y, pr, p.sigma, p.cprev, p.partial, store, p.stopped)
+                       x, y, pr, p.step, p.partial, store)
     const bool dot = p.partial != nullptr, sto = store != nullptr;
     if (!dot && !sto) HM_LAUNCH(false, false);
     else if (dot && !sto) HM_LAUNCH(true, false);
@@ -1066,6 +1114,8 @@ static void launch_digit_t(const Basis *b, const DigitTables *t, const DigitBond
     g.moves = (const DigitMoves<T, I> *)d->moves;
     g.mcnt = d->mcnt;
     g.dhigh = (const T *)d->dhigh;
+    g.kdiag = (const T *)d->kdiag;
+    g.hJ4 = (const T *)d->hJ4;
     g.strad = (const I *)d->strad;
     g.n_ops = d->n_ops;
     g.n_groups = (uint32_t)t->n_groups;
@@ -1074,6 +1124,7 @@ static void launch_digit_t(const Basis *b, const DigitTables *t, const DigitBond
     g.run = t->n_groups >= 8192 ? 64 : kBlock / 64;
     g.nF = d->nF;
     g.nS = d->nS;
+    g.nH = d->nH;
     g.mq = d->mw / 4;
     g.words = t->words;
     g.smax = t->smax;
@@ -1081,13 +1132,13 @@ static void launch_digit_t(const Basis *b, const DigitTables *t, const DigitBond
     g.mask = (1 << b->bits) - 1;
     g.rowblk = t->rowblk;
     if (b->digit.flat) {
-        const size_t cf = (size_t)d->nF * (b->two_s + 1) * (b->two_s + 1) * 2 * sizeof(T);
+        const size_t W = (size_t)b->two_s + 1, cf = (2 * (size_t)d->nF + 1) * W * W * sizeof(T);
         const int grid = hx_digit_grid(b);
         const T *x = (const T *)p.x, *pr = (const T *)p.p;
         T *y = (T *)p.y, *store = (T *)p.store;
 #define HM_LAUNCH(D, S)                                                                          \
     hipLaunchKernelGGL((hx_digit_flat_kernel<T, I, D, S>), dim3(grid), dim3(kBlock), cf, st, g,  \
-                       (I)b->dim, x, y, pr, p.sigma, p.cprev, p.partial, store, p.stopped)
+                       (I)b->dim, x, y, pr, p.step, p.partial, store)
         const bool dot = p.partial != nullptr, sto = store != nullptr;
         if (!dot && !sto) HM_LAUNCH(false, false);
         else if (dot && !sto) HM_LAUNCH(true, false);

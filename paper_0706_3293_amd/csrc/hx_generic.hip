@@ -18,11 +18,12 @@ __global__ __launch_bounds__(kBlock) void hx_generic_kernel(
     const I *__restrict__ gprefix, const double *__restrict__ gladder,
     const BondDev *__restrict__ bonds, int nb, int N, int A, int two_s, I dim,
     const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ prev,
-    const double *__restrict__ sigma_p, const double *__restrict__ cprev_p,
-    double *__restrict__ partial, T *__restrict__ store, const int *__restrict__ stopped) {
-    if (stopped && *stopped) return;
+    const LzStep step, double *__restrict__ partial, T *__restrict__ store) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[16];
+    __shared__ double red[kLzLds];
+    double sigma_v, cprev_v;
+    if (!lz_begin(step, red, sigma_v, cprev_v)) return;
+    const double sigma = uniform(sigma_v), cprev = uniform(cprev_v);   // scalar registers
     const int plen = N * (A + 1) * (two_s + 1);
     I *P = reinterpret_cast<I *>(smem);
     const size_t pbytes = ((plen * sizeof(I) + 15) / 16) * 16;
@@ -35,8 +36,6 @@ __global__ __launch_bounds__(kBlock) void hx_generic_kernel(
     __syncthreads();
     const Prefix<I> pv{P, A + 1, two_s + 1};
 
-    const double sigma = sigma_p ? *sigma_p : 1.0;
-    const double cprev = cprev_p ? *cprev_p : 0.0;
     const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
     I first, last;
     block_rows<I>(lb, gridDim.x, dim, first, last);
@@ -60,6 +59,7 @@ __global__ __launch_bounds__(kBlock) void hx_generic_kernel(
         const double s = block_sum(dot, red);
         if (threadIdx.x == 0) partial[blockIdx.x] = s;
     }
+    lz_end(step, red, sigma, cprev);
 }
 
 template <typename I, int B>
@@ -152,8 +152,7 @@ static void launch_hx_t(const Basis *b, const Couplings *c, const HxPass &p, int
 #define HM_LAUNCH(D, S, TB)                                                                 \
     hipLaunchKernelGGL((hx_generic_kernel<T, I, B, D, S, TB>), dim3(grid), dim3(kBlock),    \
                        TB ? lds_tab : lds, st, pref, b->d_ladder, c->dev, c->nb, b->N, b->A, \
-                       b->two_s, (I)b->dim, x, y, pr, p.sigma, p.cprev, p.partial, store,  \
-                       p.stopped)
+                       b->two_s, (I)b->dim, x, y, pr, p.step, p.partial, store)
     if (tab) {
         if (!dot && !sto) HM_LAUNCH(false, false, true);
         else if (dot && !sto) HM_LAUNCH(true, false, true);

@@ -137,6 +137,20 @@ __device__ __forceinline__ T load_at(const T *__restrict__ base, uint32_t byte_o
     return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + byte_off);
 }
 
+// Copies a table of n = 2^K 16-bit entries to LDS, 16 bytes per load: two bytes
+// at a time, the two tables of K = 12 were 32 dependent rounds that cost a
+// workgroup several microseconds, most of the launch for 13,000 rows.
+__device__ __forceinline__ void stage_tables(const uint16_t *__restrict__ src, uint16_t *dst,
+                                             int n) {
+    if (n < 8) {
+        for (int t = threadIdx.x; t < n; t += blockDim.x) dst[t] = src[t];
+        return;
+    }
+    const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
+    uint4 *d4 = reinterpret_cast<uint4 *>(dst);
+    for (int t = threadIdx.x; t < n / 8; t += blockDim.x) d4[t] = s4[t];
+}
+
 // Visits slots [0, n) of a run of 8-slot groups (n wave-uniform) in pieces
 // of at most MaxW (8 or 4) slots: pieces of MaxW, then at most one piece of
 // 4 and pieces of 2, each inside one group; f(std::integral_constant<int, W>,
@@ -157,33 +171,40 @@ __device__ __forceinline__ void for_pieces(int n, F &&f) {
     for (; k < n; k += 2) f(std::integral_constant<int, 2>{}, k);
 }
 
-template <typename T> __device__ __forceinline__ T coef(const BondGroup &g, int q);
-template <> __device__ __forceinline__ float coef<float>(const BondGroup &g, int q) {
+// Read-only tables seen through the constant address space: wave-uniform reads
+// are scalar loads whatever the kernel stores in between.  (Through plain
+// pointers, a store that might alias them makes every such read a vector load
+// per lane: twice the time of the N = 28 pass in FP64.)
+template <typename T>
+using Const = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ const Const<T> *as_const(const T *p) {
+    return (const Const<T> *)p;
+}
+template <typename T> __device__ __forceinline__ T coefc(const Const<BondGroup> &g, int q);
+template <> __device__ __forceinline__ float coefc<float>(const Const<BondGroup> &g, int q) {
     return g.c32[q];
 }
-template <> __device__ __forceinline__ double coef<double>(const BondGroup &g, int q) {
+template <> __device__ __forceinline__ double coefc<double>(const Const<BondGroup> &g, int q) {
     return g.c64[q];
 }
 
 template <typename T, typename I, int R, bool DOT, bool STORE>
 __global__ __launch_bounds__(256) void hx_half_kernel(
     const HalfArgs<I> g, const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ prev,
-    const double *__restrict__ sigma_p, const double *__restrict__ cprev_p,
-    double *__restrict__ partial, T *__restrict__ store, const int *__restrict__ stopped) {
-    if (stopped && *stopped) return;
+    const LzStep step, double *__restrict__ partial, T *__restrict__ store) {
     extern __shared__ __align__(16) uint16_t lds16[];
-    __shared__ double red[16];
+    __shared__ double red[kLzLds];
+    double sigma_v, cprev_v;
+    if (!lz_begin(step, red, sigma_v, cprev_v)) return;
+    const double sigma = uniform(sigma_v), cprev = uniform(cprev_v);   // scalar registers
     const int nlow = 1 << g.K;
     uint16_t *rankL = lds16;
     uint16_t *unrankL = lds16 + nlow;
-    for (int t = threadIdx.x; t < nlow; t += blockDim.x) {
-        rankL[t] = g.rankL[t];
-        unrankL[t] = g.unrankL[t];
-    }
+    stage_tables(g.rankL, rankL, nlow);
+    stage_tables(g.unrankL, unrankL, nlow);
     __syncthreads();
 
-    const double sigma = sigma_p ? *sigma_p : 1.0;
-    const double cprev = cprev_p ? *cprev_p : 0.0;
     const T shift = (T)g.shift;
     const int lane = threadIdx.x & 63;
     const int nw = blockDim.x >> 6;
@@ -199,9 +220,11 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
     wl = __builtin_amdgcn_readfirstlane(wl);
     x8 = __builtin_amdgcn_readfirstlane(x8);
     stride = __builtin_amdgcn_readfirstlane(stride);
-    const BondGroup *__restrict__ gl = g.groups;
-    const BondGroup *__restrict__ gh = g.groups + g.nLg;
-    const BondGroup *__restrict__ gs = g.groups + g.nLg + g.nHg;
+    const Const<BondGroup> *gl = as_const(g.groups), *gh = gl + g.nLg, *gs = gh + g.nHg;
+    const Const<uint32_t> *items = as_const(g.items), *hgroups = as_const(g.hgroups);
+    const Const<uint32_t> *hcnt = as_const(g.hcnt);
+    const Const<uint16_t> *hidx = as_const(g.hidx);
+    const Const<I> *offs = as_const(g.off), *nbr = as_const(g.nbr);
     // widest slot piece: 4 in FP32 (fewer registers, more waves: N=32 R=4
     // pass 15.2 -> 14.6 ms, N=36 H x 267 -> 260 ms), 8 in FP64 (R=1 28.7 ms
     // with pieces of 8, 31.9 ms with pieces of 4)
@@ -210,8 +233,8 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
     for (uint32_t l = wl;; l += stride) {
         const uint32_t it = by_xcd ? sweep_item(l, x8) : l;
         if (it >= g.n_items) break;
-        const uint32_t item = g.items[it];
-        const uint32_t *__restrict__ hg = g.hgroups + (size_t)(item >> 8) * R;
+        const uint32_t item = items[it];
+        const Const<uint32_t> *hg = hgroups + (size_t)(item >> 8) * R;
         uint32_t hs[R];
         bool valid[R];
 #pragma unroll
@@ -228,22 +251,22 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
         const int r = live ? r0 : 0;              // dead lanes shadow row 0 of the block
         const uint32_t L = unrankL[g.class_start[aL] + r];
         I off[R];
-        const I *__restrict__ nb[R];
+        const Const<I> *nb[R];
         T xi[R], acc[R];
         // offsets inside a block are byte offsets from a wave-uniform block
         // base, so loads take the scalar-base + 32-bit-offset address form
         const uint32_t r_bytes = (uint32_t)r * (uint32_t)sizeof(T);
 #pragma unroll
         for (int m = 0; m < R; ++m) {
-            off[m] = g.off[hs[m]];
-            nb[m] = g.nbr + (size_t)hs[m] * g.width;
+            off[m] = offs[hs[m]];
+            nb[m] = nbr + (size_t)hs[m] * g.width;
             xi[m] = load_at(x + off[m], r_bytes);
             acc[m] = 0;
         }
         // bonds inside the low word: the test and rankL(L ^ m) once per lane
         for_pieces<kW>(g.nL, [&](auto Wc, int k) {
             constexpr int W = decltype(Wc)::value;
-            const BondGroup &G = gl[k / kGroup];
+            const Const<BondGroup> &G = gl[k / kGroup];
             const int q0 = W == kGroup ? 0 : k % kGroup;
             uint32_t mk[W], idx[W];
 #pragma unroll
@@ -260,7 +283,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
 #pragma unroll
                 for (int q = 0; q < W; ++q) xj[q] = load_at(xb, idx[q]);
 #pragma unroll
-                for (int q = 0; q < W; ++q) acc[m] += coef<T>(G, q0 + q) * (xj[q] - xi[m]);
+                for (int q = 0; q < W; ++q) acc[m] += coefc<T>(G, q0 + q) * (xj[q] - xi[m]);
             }
         });
         // bonds inside the high word that flip for h_m (compacted rows of the
@@ -271,12 +294,12 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
         // with 8 rows per lane that costs too many registers, and the rows
         // go one after another.  The sums are the same either way.
         if constexpr (R <= 4) {
-            const uint16_t *__restrict__ bi[R];
+            const Const<uint16_t> *bi[R];
             int nmax = 0;
 #pragma unroll
             for (int m = 0; m < R; ++m) {
-                nmax = max(nmax, (int)g.hcnt[hs[m]]);
-                bi[m] = g.hidx + (size_t)hs[m] * (g.nHg * kGroup);
+                nmax = max(nmax, (int)hcnt[hs[m]]);
+                bi[m] = hidx + (size_t)hs[m] * (g.nHg * kGroup);
             }
             for_pieces<kW>(nmax, [&](auto Wc, int k) {
                 constexpr int W = decltype(Wc)::value;
@@ -290,14 +313,14 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
 #pragma unroll
                     for (int q = 0; q < W; ++q) {
                         const uint32_t b = bi[m][k + q];
-                        acc[m] += coef<T>(gh[b >> 3], b & 7) * (xj[m][q] - xi[m]);
+                        acc[m] += coefc<T>(gh[b >> 3], b & 7) * (xj[m][q] - xi[m]);
                     }
             });
         } else {
 #pragma unroll
             for (int m = 0; m < R; ++m) {
-                const int nf = (int)g.hcnt[hs[m]];
-                const uint16_t *__restrict__ bi = g.hidx + (size_t)hs[m] * (g.nHg * kGroup);
+                const int nf = (int)hcnt[hs[m]];
+                const Const<uint16_t> *bi = hidx + (size_t)hs[m] * (g.nHg * kGroup);
                 for_pieces<kW>(nf, [&](auto Wc, int k) {
                     constexpr int W = decltype(Wc)::value;
                     T xj[W];
@@ -306,7 +329,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
 #pragma unroll
                     for (int q = 0; q < W; ++q) {
                         const uint32_t b = bi[k + q];
-                        acc[m] += coef<T>(gh[b >> 3], b & 7) * (xj[q] - xi[m]);
+                        acc[m] += coefc<T>(gh[b >> 3], b & 7) * (xj[q] - xi[m]);
                     }
                 });
             }
@@ -314,7 +337,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
         // bonds with one site in each word: uniform high bit, per-lane low bit
         for_pieces<kW>(g.nS, [&](auto Wc, int k) {
             constexpr int W = decltype(Wc)::value;
-            const BondGroup &G = gs[k / kGroup];
+            const Const<BondGroup> &G = gs[k / kGroup];
             const int q0 = W == kGroup ? 0 : k % kGroup;
             uint32_t ml[W], lb[W], rk[W];
 #pragma unroll
@@ -326,7 +349,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
             }
 #pragma unroll
             for (int m = 0; m < R; ++m) {
-                const I *__restrict__ nbs = nb[m] + g.nHg * kGroup + k;
+                const Const<I> *nbs = nb[m] + g.nHg * kGroup + k;
                 const I own = off[m] + (I)r;
                 T xj[W];
 #pragma unroll
@@ -338,7 +361,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
                     xj[q] = x[lb[q] == want ? nbs[q] + (I)rk[q] : own];
                 }
 #pragma unroll
-                for (int q = 0; q < W; ++q) acc[m] += coef<T>(G, q0 + q) * (xj[q] - xi[m]);
+                for (int q = 0; q < W; ++q) acc[m] += coefc<T>(G, q0 + q) * (xj[q] - xi[m]);
             }
         });
 #pragma unroll
@@ -359,21 +382,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
         const double s = block_sum(dot, red);
         if (threadIdx.x == 0) partial[blockIdx.x] = s;
     }
-}
-
-// Read-only tables seen through the constant address space.
-template <typename T>
-using Const = const __attribute__((address_space(4))) T;
-template <typename T>
-__device__ __forceinline__ const Const<T> *as_const(const T *p) {
-    return (const Const<T> *)p;
-}
-template <typename T> __device__ __forceinline__ T coefc(const Const<BondGroup> &g, int q);
-template <> __device__ __forceinline__ float coefc<float>(const Const<BondGroup> &g, int q) {
-    return g.c32[q];
-}
-template <> __device__ __forceinline__ double coefc<double>(const Const<BondGroup> &g, int q) {
-    return g.c64[q];
+    lz_end(step, red, sigma, cprev);
 }
 
 // Staged variant.  Work item = one group of R high words of one popcount
@@ -558,18 +567,17 @@ __device__ __forceinline__ void staged_item(const HalfArgs<I> &g, const StagedWa
 template <typename T, typename I, int R, int C, bool DOT, bool STORE>
 __global__ __launch_bounds__(256) void hx_half_staged_kernel(
     const HalfArgs<I> g, const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ prev,
-    const double *__restrict__ sigma_p, const double *__restrict__ cprev_p,
-    double *__restrict__ partial, T *__restrict__ store, const int *__restrict__ stopped) {
-    if (stopped && *stopped) return;
+    const LzStep step, double *__restrict__ partial, T *__restrict__ store) {
     extern __shared__ __align__(16) uint16_t lds16[];
-    __shared__ double red[16];
+    __shared__ double red[kLzLds];
+    double sigma_v, cprev_v;
+    if (!lz_begin(step, red, sigma_v, cprev_v)) return;
+    const double sigma = uniform(sigma_v), cprev = uniform(cprev_v);   // scalar registers
     const int nlow = 1 << g.K;
     uint16_t *rankL = lds16;
     uint16_t *unrankL = lds16 + nlow;
-    for (int t = threadIdx.x; t < nlow; t += blockDim.x) {
-        rankL[t] = g.rankL[t];
-        unrankL[t] = g.unrankL[t];
-    }
+    stage_tables(g.rankL, rankL, nlow);
+    stage_tables(g.unrankL, unrankL, nlow);
     __syncthreads();
 
     StagedWave<T, I> w;
@@ -589,8 +597,8 @@ __global__ __launch_bounds__(256) void hx_half_staged_kernel(
     w.y = y;
     w.prev = prev;
     w.store = store;
-    w.sigma = sigma_p ? *sigma_p : 1.0;
-    w.cprev = cprev_p ? *cprev_p : 0.0;
+    w.sigma = sigma;
+    w.cprev = cprev;
     w.shift = (T)g.shift;
     w.lane = threadIdx.x & 63;
     const int nw = blockDim.x >> 6;
@@ -642,6 +650,7 @@ __global__ __launch_bounds__(256) void hx_half_staged_kernel(
         const double s = block_sum(dot, red);
         if (threadIdx.x == 0) partial[blockIdx.x] = s;
     }
+    lz_end(step, red, sigma, cprev);
 }
 
 // ---------------------------------------------------------------------------
@@ -1006,7 +1015,7 @@ static void launch_r(const HalfTables *t, const HalfArgs<I> &g, const HxPass &p,
     T *store = (T *)p.store;
 #define HM_LAUNCH(D, S)                                                                     \
     hipLaunchKernelGGL((hx_half_kernel<T, I, R, D, S>), dim3(grid), dim3(t->block), lds, st, \
-                       g, x, y, pr, p.sigma, p.cprev, p.partial, store, p.stopped)
+                       g, x, y, pr, p.step, p.partial, store)
     const bool dot = p.partial != nullptr, sto = store != nullptr;
     if (!dot && !sto) HM_LAUNCH(false, false);
     else if (dot && !sto) HM_LAUNCH(true, false);
@@ -1027,8 +1036,7 @@ static void launch_staged(const HalfTables *t, const HalfArgs<uint32_t> &g, cons
     T *store = (T *)p.store;
 #define HM_LAUNCH(D, S)                                                                    \
     hipLaunchKernelGGL((hx_half_staged_kernel<T, uint32_t, R, C, D, S>), dim3(grid),       \
-                       dim3(t->block), lds, st, g, x, y, pr, p.sigma, p.cprev, p.partial, \
-                       store, p.stopped)
+                       dim3(t->block), lds, st, g, x, y, pr, p.step, p.partial, store)
     const bool dot = p.partial != nullptr, sto = store != nullptr;
     if (!dot && !sto) HM_LAUNCH(false, false);
     else if (dot && !sto) HM_LAUNCH(true, false);

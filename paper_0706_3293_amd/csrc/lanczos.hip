@@ -3,16 +3,19 @@
 //
 // Step k (0-based) with v_k = sigma_k r_k kept as a raw vector r_k and a
 // device scalar sigma_k:
-//   pass A  w = sigma_k (H r_k) - cprev_k r_{k-1}      [fused in the H x kernel]
+//   pass A  beta_{k-1} = |w| of step k - 1; breakdown test; sigma_k =
+//           1/beta_{k-1}, cprev_k = beta_{k-1} sigma_{k-1}
+//           w = sigma_k (H r_k) - cprev_k r_{k-1}      [fused in the H x kernel]
 //           alpha partials  <w, v_k>                   [same kernel, FP64]
-//   finish  alpha_k = sum of partials                  [one workgroup, fixed order]
-//   pass B  w -= alpha_k v_k,  partials of |w|^2       [FP64 arithmetic]
-//   [reorth twice: h = V^T w, w -= V h]
-//   finish  beta_k = |w|; breakdown test; sigma_{k+1} = 1/beta_k,
-//           cprev_{k+1} = beta_k sigma_k
+//   pass B  alpha_k = sum of partials
+//           w -= alpha_k v_k,  partials of |w|^2       [FP64 arithmetic]
+//           [ground-state pass: psi += c_k v_k]
+// or, with full reorthogonalization, twice h = V^T w, w -= V h in place of
+// pass B, whose subtraction the first of them takes over.
 // The raw buffers rotate (r_{k+1} is w), so the 1/beta normalization never
-// costs a vector pass.  All reductions are per-workgroup partials summed in a
-// fixed order: two runs with the same inputs give the same bits, which the
+// costs a vector pass.  All reductions are per-workgroup partials that the next
+// kernel sums in a fixed order (lanczos_dev.h; a kernel of one workgroup on
+// large grids): two runs with the same inputs give the same bits, which the
 // recompute pass relies on.
 #include <algorithm>
 #include <cmath>
@@ -22,6 +25,7 @@
 #include "device_common.h"
 #include "hm_internal.h"
 #include "hx_row.h"
+#include "tall_dots.h"
 
 namespace hm {
 
@@ -72,17 +76,6 @@ int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel, const H
     return launch_hx_generic(b, c, dtype, p, st);
 }
 
-// Device-side scalars of one Lanczos run.
-struct LzDev {
-    int stopped;     // steps done when a breakdown ended the run; 0 while running
-    int bad_start;   // 1 if |v0| == 0
-    double tol;
-    double scale;    // running max(|alpha_j|, beta_j)
-    double norm0;    // |v0|
-    double psi_norm;
-    unsigned ticket; // workgroups of the current fused pass B that are done
-};
-
 // One-workgroup run (below): automatic choice without reorthogonalization up
 // to kSmallAutoWork (rows x bonds) of row work per step, accepted when asked
 // for explicitly up to kSmallMaxDim rows.
@@ -90,7 +83,7 @@ constexpr int64_t kSmallAutoWork = 16384;
 constexpr int64_t kSmallMaxDim = 1 << 20;
 
 struct Layout {
-    size_t lz, alpha, beta, sigma, cprev, coef, hcoef, partial, bpart, r0, r1, r2, V, states,
+    size_t lz, alpha, beta, sigma, cprev, scale, coef, hcoef, partial, bpart, dots, r0, r1, r2, V, states,
         total;
     int grid_vec, grid_b, nparts;
 };
@@ -108,38 +101,42 @@ static int vec_grid(int64_t n) {
 // Workgroups of pass B: about 8 16-byte vectors per thread, so that long
 // vectors run on many more workgroups than fit at once and the dispatcher
 // keeps every CU busy to the end (601 M FP32 rows: 1.51 ms on 2048
-// workgroups, 1.36 ms on 65536).
+// workgroups, 1.36 ms on 65536).  Shorter vectors (up to 1024 such
+// workgroups) take two 16-byte vectors per thread on at most 1024 workgroups,
+// few enough partials for the next kernel to sum.
 constexpr int64_t kMaxGridB = 65536;
 static int pass_b_grid(int64_t n, size_t es) {
-    const int64_t per = (int64_t)(16 / es) * kBlock * 8;
+    const int64_t vec = (int64_t)(16 / es) * kBlock, per = 8 * vec;
     int64_t g = std::min<int64_t>((n + per - 1) / per, kMaxGridB);
-    g = std::max<int64_t>(g, vec_grid(n));
+    if (g <= 1024) g = std::min<int64_t>((n + 2 * vec - 1) / (2 * vec), 1024);
     if (g >= kXcds) g -= g % kXcds;
-    return (int)g;
+    return (int)std::max<int64_t>(g, 1);
 }
 
 // Workspace layout; the partial-sum area holds one entry per workgroup of
-// pass B and of whichever H x kernel may run (kMaxGrid, or the block kernel's grid when its
-// schedule asks for more), so the layout does not depend on the kernel choice.
+// whichever H x kernel may run (kMaxGrid, or a block kernel's grid when that is
+// larger), so the layout does not depend on the kernel choice.
 static Layout layout(const Basis *b, int steps, int prec, int reorth) {
     Layout L{};
     const size_t es = prec == HM_PREC_F64 ? 8 : 4;
     L.grid_vec = vec_grid(b->dim);
     L.grid_b = pass_b_grid(b->dim, es);
-    L.nparts = std::max({kMaxGrid, L.grid_b, half_supported(b) ? hx_half_grid(b) : 0,
+    L.nparts = std::max({kMaxGrid, half_supported(b) ? hx_half_grid(b) : 0,
                          b->digit.K > 0 ? hx_digit_grid(b) : 0});
-    size_t partial_len = (size_t)L.nparts;
-    if (reorth) partial_len = std::max(partial_len, (size_t)L.grid_vec * (size_t)steps);
     size_t off = 0;
+    // state, alpha, beta and sigma side by side: read back in one copy
     L.lz = off; off = align256(off + sizeof(LzDev));
     L.alpha = off; off = align256(off + sizeof(double) * steps);
     L.beta = off; off = align256(off + sizeof(double) * steps);
     L.sigma = off; off = align256(off + sizeof(double) * (steps + 1));
     L.cprev = off; off = align256(off + sizeof(double) * (steps + 1));
+    L.scale = off; off = align256(off + sizeof(double) * (steps + 1));
     L.coef = off; off = align256(off + sizeof(double) * steps);
     L.hcoef = off; off = align256(off + sizeof(double) * (steps + 1));
-    L.partial = off; off = align256(off + sizeof(double) * partial_len);
-    L.bpart = off; off = align256(off + sizeof(double) * kMaxGrid);
+    L.partial = off; off = align256(off + sizeof(double) * (size_t)L.nparts);
+    L.bpart = off; off = align256(off + sizeof(double) * (size_t)std::max(kMaxGrid, L.grid_b));
+    L.dots = off;
+    if (reorth) off = align256(off + sizeof(double) * (size_t)kTallSplits * (size_t)steps);
     L.r0 = off; off = align256(off + es * (size_t)b->dim);
     L.r1 = off; off = align256(off + es * (size_t)b->dim);
     L.r2 = off; off = align256(off + es * (size_t)b->dim);
@@ -158,9 +155,7 @@ static Layout layout(const Basis *b, int steps, int prec, int reorth) {
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kBlock) void sumsq_kernel(const T *__restrict__ x, int64_t n,
-                                                       double *__restrict__ partial,
-                                                       const int *__restrict__ stopped) {
-    if (stopped && *stopped) return;
+                                                       double *__restrict__ partial) {
     __shared__ double red[16];
     int64_t first, last;
     block_rows<int64_t>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, n, first, last);
@@ -199,39 +194,37 @@ __device__ double fixed_sum(const double *__restrict__ partial, int n, double *r
 // of that pass, up to 2^20): 16 waves, the most block_sum combines.
 constexpr int kFinishBlock = 1024;
 
-__global__ __launch_bounds__(kBlock) void finish_init(LzDev *lz, const double *partial, int n,
-                                                      double *sigma, double *cprev,
-                                                      double tol) {
-    __shared__ double red[16];
-    const double s = fixed_sum(partial, n, red);
-    if (threadIdx.x == 0) {
-        lz->stopped = 0;
-        lz->tol = tol;
-        lz->scale = 0.0;
-        lz->norm0 = sqrt(s);
-        lz->bad_start = !(s > 0.0);
-        lz->psi_norm = 0.0;
-        lz->ticket = 0;
-        sigma[0] = 1.0;
-        cprev[0] = 0.0;
-        if (lz->bad_start) lz->stopped = -1;
-    }
-}
-
+// r_0 = v0 / |v0| from the partials of |v0|^2, and the run's first scalars.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void init_write(const double *__restrict__ v0,
-                                                     T *__restrict__ r, int64_t n,
-                                                     const LzDev *__restrict__ lz) {
-    if (lz->stopped) return;
-    const double inv = 1.0 / lz->norm0;
+                                                     T *__restrict__ r, int64_t n, LzDev *lz,
+                                                     const double *__restrict__ partial, int np,
+                                                     double *sigma, double *cprev, double *scale,
+                                                     double tol) {
+    __shared__ double red[17];
+    const double s = fold_sum(partial, np, red);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        lz->bad_start = !(s > 0.0);
+        lz->stopped = 0;
+        lz->tol = tol;
+        lz->norm0 = sqrt(s);
+        lz->psi_norm = 0.0;
+        sigma[0] = s > 0.0 ? 1.0 : 0.0;
+        cprev[0] = 0.0;
+        scale[0] = 0.0;
+    }
+    if (!(s > 0.0)) return;
+    const double inv = 1.0 / sqrt(s);
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         r[i] = (T)(v0[i] * inv);
 }
 
-__global__ __launch_bounds__(kFinishBlock) void finish_alpha(LzDev *lz, const double *partial,
-                                                             int n, double *alpha, int k) {
-    if (lz->stopped) return;
+// On grids of more than kFoldMax workgroups the sums have kernels of their own.
+__global__ __launch_bounds__(kFinishBlock) void finish_alpha(const double *sigma,
+                                                             const double *partial, int n,
+                                                             double *alpha, int k) {
+    if (sigma[k] == 0.0) return;
     __shared__ double red[16];
     const double s = fixed_sum(partial, n, red);
     if (threadIdx.x == 0) alpha[k] = s;
@@ -243,15 +236,28 @@ template <> struct VecOf<float> { using type = float4; };
 template <> struct VecOf<double> { using type = double2; };
 
 // w -= alpha_k sigma_k r_k (FP64 arithmetic, one rounding), partial |w|^2.
-template <typename T>
+// apart: the H x pass's alpha partials (null: alpha_k is finished already).
+// PSI: the ground-state pass, psi += c_k v_k = c_k sigma_k r_k in FP64 (the
+// first step writes psi); r_k is read anyway, so this saves a launch and a
+// read of r_k per step.
+template <typename T, bool PSI>
 __global__ __launch_bounds__(kBlock) void pass_b(T *__restrict__ w, const T *__restrict__ r,
-                                                 int64_t n, const LzDev *__restrict__ lz,
-                                                 const double *__restrict__ alpha,
+                                                 int64_t n, const double *__restrict__ apart,
+                                                 int n_hx,
+                                                 double *__restrict__ alpha,
                                                  const double *__restrict__ sigma, int k,
-                                                 double *__restrict__ partial) {
-    if (lz->stopped) return;
-    __shared__ double red[16];
-    const double a = alpha[k] * sigma[k];
+                                                 double *__restrict__ partial,
+                                                 const double *__restrict__ coef,
+                                                 double *__restrict__ psi) {
+    if (sigma[k] == 0.0) return;
+    __shared__ double red[17];
+    const double al = apart ? fold_sum(apart, n_hx, red) : alpha[k];
+    if (apart && blockIdx.x == 0 && threadIdx.x == 0) alpha[k] = al;
+    const double sg = sigma[k], a = al * sg;
+    const double cp = PSI ? coef[k] * sg : 0.0;
+    auto add_psi = [&](int64_t i, T ri) {
+        if constexpr (PSI) psi[i] = (k > 0 ? psi[i] : 0.0) + cp * (double)ri;
+    };
     int64_t first, last;
     block_rows<int64_t>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, n, first, last);
     // 16-byte vector loads and stores over the aligned middle of the range
@@ -262,9 +268,10 @@ __global__ __launch_bounds__(kBlock) void pass_b(T *__restrict__ w, const T *__r
     const int64_t m1 = std::max(m0, last / V * V);
     double s = 0.0;
     for (int64_t i = first + threadIdx.x; i < m0; i += blockDim.x) {
-        const T wi = (T)((double)w[i] - a * (double)r[i]);
+        const T ri = r[i], wi = (T)((double)w[i] - a * (double)ri);
         w[i] = wi;
         s += (double)wi * (double)wi;
+        add_psi(i, ri);
     }
     Vec *wv = reinterpret_cast<Vec *>(w);
     const Vec *rv = reinterpret_cast<const Vec *>(r);
@@ -280,186 +287,129 @@ __global__ __launch_bounds__(kBlock) void pass_b(T *__restrict__ w, const T *__r
             s += (double)we[e] * (double)we[e];
         }
         wv[j] = wj;
+#pragma unroll
+        for (int e = 0; e < V; ++e) add_psi(j * V + e, re[e]);
     }
     for (int64_t i = m1 + threadIdx.x; i < last; i += blockDim.x) {
-        const T wi = (T)((double)w[i] - a * (double)r[i]);
+        const T ri = r[i], wi = (T)((double)w[i] - a * (double)ri);
         w[i] = wi;
         s += (double)wi * (double)wi;
+        add_psi(i, ri);
     }
     s = block_sum(s, red);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(kFinishBlock) void finish_beta(LzDev *lz, const double *partial,
-                                                            int n, const double *alpha,
+// beta_k and the scalars of step k + 1 from the |w|^2 partials.
+__global__ __launch_bounds__(kFinishBlock) void finish_beta(const LzDev *lz,
+                                                            const double *partial, int n,
+                                                            const double *alpha,
                                                             double *beta, double *sigma,
-                                                            double *cprev, int k) {
-    if (lz->stopped) return;
+                                                            double *cprev, double *scale, int k) {
+    if (sigma[k] == 0.0) {
+        if (threadIdx.x == 0) sigma[k + 1] = 0.0;
+        return;
+    }
     __shared__ double red[16];
     const double s = fixed_sum(partial, n, red);
     if (threadIdx.x == 0) {
-        const double b = sqrt(s);
-        beta[k] = b;
-        const double sc = fmax(lz->scale, fmax(fabs(alpha[k]), b));
-        lz->scale = sc;
-        if (!(b > lz->tol * sc)) {
-            lz->stopped = k + 1;
-        } else {
-            sigma[k + 1] = 1.0 / b;
-            cprev[k + 1] = b * sigma[k];
-        }
+        const LzScalars c = lz_advance(lz, k + 1, s, alpha, sigma, scale);
+        beta[k] = c.beta;
+        scale[k + 1] = c.scale;
+        sigma[k + 1] = c.sigma;
+        cprev[k + 1] = c.cprev;
     }
 }
 
-// Pass B with the one-workgroup finishes folded in, for small grids (a few
-// dozen workgroups), where launches dominate a step.  Every workgroup sums
-// the H x partials (alpha_k) in the same fixed order, so all use the same
-// alpha, and applies w -= alpha_k sigma_k r_k.
-//   MODE 0: nothing more (reorthogonalization follows, then sumsq_kernel and
-//           finish_beta);
-//   MODE 2: each workgroup writes its |w|^2 partial to bpart and takes a
-//           device-scope ticket; the last one to arrive sums bpart in a fixed
-//           order and does what finish_beta does, then resets the ticket for
-//           the next step.
-// On large grids both cost more than they save (every workgroup re-reads all
-// H x partials, and the tickets are one contended atomic per workgroup), so
-// there the step keeps finish_alpha, pass_b and finish_beta.
-template <typename T, int MODE>
-__global__ __launch_bounds__(kBlock) void pass_b_fused(
-    T *__restrict__ w, const T *__restrict__ r, int64_t n, LzDev *lz,
-    const double *__restrict__ hx_partial, int n_hx, double *alpha, double *beta, double *sigma,
-    double *cprev, int k, double *bpart) {
-    if (lz->stopped) return;
-    __shared__ double red[16];
-    __shared__ double s_alpha;
-    __shared__ int s_last;
-    const double a_sum = fixed_sum(hx_partial, n_hx, red);
-    if (threadIdx.x == 0) {
-        s_alpha = a_sum;
-        if (blockIdx.x == 0) alpha[k] = a_sum;
-    }
-    __syncthreads();
-    const double al = s_alpha;
-    const double a = al * sigma[k];
-    int64_t first, last;
-    block_rows<int64_t>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, n, first, last);
-    double s = 0.0;
-    for (int64_t i = first + threadIdx.x; i < last; i += blockDim.x) {
-        const T wi = (T)((double)w[i] - a * (double)r[i]);
-        w[i] = wi;
-        s += (double)wi * (double)wi;
-    }
-    if constexpr (MODE == 2) {
-        s = block_sum(s, red);
-        if (threadIdx.x == 0) {
-            bpart[blockIdx.x] = s;
-            // the release orders the partial before the ticket; the last
-            // workgroup acquires every partial before summing them
-            const unsigned t = __hip_atomic_fetch_add(&lz->ticket, 1u, __ATOMIC_RELEASE,
-                                                      __HIP_MEMORY_SCOPE_AGENT);
-            s_last = t == gridDim.x - 1;
-            if (s_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        }
-        __syncthreads();
-        if (!s_last) return;
-        const double b2 = fixed_sum(bpart, gridDim.x, red);
-        if (threadIdx.x == 0) {
-            lz->ticket = 0;
-            const double b = sqrt(b2);
-            beta[k] = b;
-            const double sc = fmax(lz->scale, fmax(fabs(al), b));
-            lz->scale = sc;
-            if (!(b > lz->tol * sc)) {
-                lz->stopped = k + 1;
-            } else {
-                sigma[k + 1] = 1.0 / b;
-                cprev[k + 1] = b * sigma[k];
-            }
-        }
-    }
-}
+// Full reorthogonalization, second half of a pass: w -= sum_{j < nv} h_j V_j
+// with h_j summed from the dots' partials (splits x nv; h given instead: they
+// are finished already).  SUB: w - alpha_k sigma_k r_k is what the dots were
+// taken with.  sq: partials of |w|^2 (the second pass).  Each thread keeps 8
+// entries of V in flight; the sums take the vectors in order.
+constexpr int kReorthFold = 1024;    // most coefficients a workgroup sums itself
 
-// Reorthogonalization: partial[j * G + blk] = sum_i V[j][i] w_i over the slice.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void reorth_dots(const T *__restrict__ V,
-                                                      const T *__restrict__ w, int64_t n,
-                                                      int nv, double *__restrict__ partial,
-                                                      const LzDev *__restrict__ lz) {
-    if (lz->stopped) return;
-    __shared__ double red[16];
-    const int j = blockIdx.y;
-    int64_t first, last;
-    block_rows<int64_t>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, n, first, last);
-    double s = 0.0;
-    const T *Vj = V + (size_t)j * (size_t)n;
-    for (int64_t i = first + threadIdx.x; i < last; i += blockDim.x)
-        s += (double)Vj[i] * (double)w[i];
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) partial[(size_t)j * gridDim.x + blockIdx.x] = s;
-}
-
-// h_j = sum of the G partials of coefficient j: one wave per j (blockIdx.x),
-// lanes over the partials, a fixed butterfly.
-__global__ __launch_bounds__(64) void reorth_finish(const double *partial, int G, double *h,
-                                                    const LzDev *lz) {
-    if (lz->stopped) return;
-    const int j = blockIdx.x;
-    double s = 0.0;
-    for (int t = threadIdx.x; t < G; t += 64) s += partial[(size_t)j * G + t];
-    s = wave_sum(s);
-    if (threadIdx.x == 0) h[j] = s;
-}
-
-template <typename T>
+template <typename T, bool SUB>
 __global__ __launch_bounds__(kBlock) void reorth_update(const T *__restrict__ V,
                                                         T *__restrict__ w, int64_t n, int nv,
+                                                        const double *__restrict__ dots, int splits,
                                                         const double *__restrict__ h,
-                                                        const LzDev *__restrict__ lz) {
-    if (lz->stopped) return;
+                                                        const double *__restrict__ live,
+                                                        double *__restrict__ sq,
+                                                        const TallSub<T> sub) {
+    if (*live == 0.0) return;
+    __shared__ double red[17];
+    __shared__ double hs[kReorthFold];
+    double factor = 0.0;
+    if constexpr (SUB) factor = tall_factor(sub, red, false);
+    if (!h) {
+        for (int j = threadIdx.x; j < nv; j += blockDim.x) {
+            double s = 0.0;
+            for (int t = 0; t < splits; ++t) s += dots[(size_t)t * nv + j];
+            hs[j] = s;
+        }
+        __syncthreads();
+        h = hs;
+    }
+    double s = 0.0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         double acc = (double)w[i];
-        for (int j = 0; j < nv; ++j) acc -= h[j] * (double)V[(size_t)j * (size_t)n + i];
-        w[i] = (T)acc;
+        if constexpr (SUB) acc = (double)(T)(acc - factor * (double)sub.r[i]);
+        const T *__restrict__ Vi = V + i;
+        int j = 0;
+        for (; j + 8 <= nv; j += 8) {
+            T v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = Vi[(size_t)(j + q) * (size_t)n];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc -= h[j + q] * (double)v[q];
+        }
+        for (; j < nv; ++j) acc -= h[j] * (double)Vi[(size_t)j * (size_t)n];
+        const T wi = (T)acc;
+        w[i] = wi;
+        s += (double)wi * (double)wi;
+    }
+    if (sq) {
+        s = block_sum(s, red);
+        if (threadIdx.x == 0) sq[blockIdx.x] = s;
     }
 }
 
-__global__ __launch_bounds__(kBlock) void finish_psi_norm(LzDev *lz, const double *partial,
-                                                          int n) {
-    __shared__ double red[16];
-    const double s = fixed_sum(partial, n, red);
-    if (threadIdx.x == 0) lz->psi_norm = sqrt(s);
+// h_j from the partials of the dots (64 coefficients per workgroup).
+__global__ __launch_bounds__(kTallBlock) void reorth_finish(const double *__restrict__ dots,
+                                                            int splits, int nv,
+                                                            double *__restrict__ h,
+                                                            const double *__restrict__ live) {
+    if (*live == 0.0) return;
+    __shared__ double red[4][64];
+    tall_sum(dots, splits, nv, blockIdx.x * 64, h, red);
 }
 
-__global__ __launch_bounds__(kBlock) void scale_psi(double *__restrict__ psi, int64_t n,
-                                                    const LzDev *__restrict__ lz) {
-    const double nrm = lz->psi_norm;
+// Ground-state accumulation of the reorthogonalized recurrence, which has no
+// pass B to do it (the first step writes psi).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void psi_axpy(double *__restrict__ psi,
+                                                   const T *__restrict__ r, int64_t n,
+                                                   const double *__restrict__ coef,
+                                                   const double *__restrict__ sigma, int k) {
+    if (sigma[k] == 0.0) return;
+    const double a = coef[k] * sigma[k];
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        psi[i] = (k > 0 ? psi[i] : 0.0) + a * (double)r[i];
+}
+
+// psi /= |psi| from the partials of |psi|^2.
+__global__ __launch_bounds__(kBlock) void scale_psi(double *__restrict__ psi, int64_t n, LzDev *lz,
+                                                    const double *__restrict__ partial, int np) {
+    __shared__ double red[17];
+    const double nrm = sqrt(fold_sum(partial, np, red));
+    if (blockIdx.x == 0 && threadIdx.x == 0) lz->psi_norm = nrm;
     if (!(nrm > 0.0)) return;
     const double inv = 1.0 / nrm;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         psi[i] *= inv;
-}
-
-// Ground-state accumulation psi += c_k v_k = c_k sigma_k r_k in FP64.  Kept out
-// of the H x kernel so both Lanczos passes run the same recurrence kernels.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void psi_axpy(double *__restrict__ psi,
-                                                   const T *__restrict__ r, int64_t n,
-                                                   const double *__restrict__ coef,
-                                                   const double *__restrict__ sigma,
-                                                   const LzDev *__restrict__ lz) {
-    if (lz->stopped) return;
-    const double a = coef[0] * sigma[0];
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        psi[i] += a * (double)r[i];
-}
-
-__global__ void zero_f64(double *__restrict__ x, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        x[i] = 0.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -601,7 +551,6 @@ __global__ __launch_bounds__(kSmallBlock) void lanczos_small_kernel(const SmallA
         if (threadIdx.x == 0) {
             a.alpha[k] = alpha;
             a.beta[k] = beta;
-            a.lz->scale = scale;
         }
         if (!(beta > a.tol * scale)) {
             stopped = k + 1;
@@ -648,9 +597,6 @@ struct Run {
     double *psi;               // ritz pass output, else nullptr
 };
 
-// Largest grids (pass B and the H x partials) for the fused pass B.
-constexpr int kFusedMaxGrid = 64;
-
 template <typename T>
 static int enqueue_steps(Run &R, int k0, int k1, std::vector<hipEvent_t> *ev) {
     Basis *b = R.b;
@@ -658,64 +604,85 @@ static int enqueue_steps(Run &R, int k0, int k1, std::vector<hipEvent_t> *ev) {
     LzDev *lz = (LzDev *)(R.w + R.L.lz);
     double *alpha = (double *)(R.w + R.L.alpha), *beta = (double *)(R.w + R.L.beta);
     double *sigma = (double *)(R.w + R.L.sigma), *cprev = (double *)(R.w + R.L.cprev);
+    double *scale = (double *)(R.w + R.L.scale);
     double *coef = (double *)(R.w + R.L.coef), *hc = (double *)(R.w + R.L.hcoef);
     double *partial = (double *)(R.w + R.L.partial), *bpart = (double *)(R.w + R.L.bpart);
+    double *dots = (double *)(R.w + R.L.dots);
     T *buf[3] = {(T *)(R.w + R.L.r0), (T *)(R.w + R.L.r1), (T *)(R.w + R.L.r2)};
     T *V = (T *)(R.w + R.L.V);
-    const int G = R.L.grid_vec, Gb = R.L.grid_b;
+    const int G = R.L.grid_vec, Gb = R.reorth ? G : R.L.grid_b;
     const int Ghx = hx_partial_count(b, R.kernel);
     const int dtype = R.prec == HM_PREC_F64 ? HM_F64 : HM_F32;
+    // sums of few enough partials are left to the kernel that needs them
+    const bool fold_a = Ghx <= kFoldMax, fold_b = Gb <= kFoldMax;
     for (int k = k0; k < k1; ++k) {
         T *rk = buf[k % 3], *rprev = buf[(k + 2) % 3], *wn = buf[(k + 1) % 3];
         HxPass p;
         p.x = rk;
         p.y = wn;
         p.p = k > 0 ? rprev : nullptr;
-        p.sigma = sigma + k;
-        p.cprev = cprev + k;
+        p.step.lz = lz;
+        p.step.bpart = fold_b && k > 0 ? bpart : nullptr;
+        p.step.nb = Gb;
+        p.step.k = k;
+        p.step.alpha = alpha;
+        p.step.beta = beta;
+        p.step.sigma = sigma;
+        p.step.cprev = cprev;
+        p.step.scale = scale;
         p.partial = partial;
         p.store = R.reorth ? (void *)(V + (size_t)k * (size_t)n) : nullptr;
-        p.stopped = &lz->stopped;
         if (ev) HM_HIP(hipEventRecord((*ev)[2 * k], R.st));
         HM_TRY(launch_hx(b, R.c, dtype, R.kernel, p, R.st));
         if (ev) HM_HIP(hipEventRecord((*ev)[2 * k + 1], R.st));
-        if (R.psi)
-            hipLaunchKernelGGL(psi_axpy<T>, dim3(G), dim3(kBlock), 0, R.st, R.psi, rk, n,
-                               coef + k, sigma + k, lz);
-        const bool small = G <= kFusedMaxGrid && Ghx <= kFusedMaxGrid;
-        if (small && !R.reorth) {
-            // pass B with both finishes: two launches per step in all
-            hipLaunchKernelGGL((pass_b_fused<T, 2>), dim3(G), dim3(kBlock), 0, R.st, wn, rk, n,
-                               lz, partial, Ghx, alpha, beta, sigma, cprev, k, bpart);
-            continue;
-        }
-        if (small) {
-            hipLaunchKernelGGL((pass_b_fused<T, 0>), dim3(G), dim3(kBlock), 0, R.st, wn, rk, n,
-                               lz, partial, Ghx, alpha, beta, sigma, cprev, k, bpart);
-        } else {
-            hipLaunchKernelGGL(finish_alpha, dim3(1), dim3(kFinishBlock), 0, R.st, lz, partial, Ghx,
-                               alpha, k);
-            hipLaunchKernelGGL(pass_b<T>, dim3(Gb), dim3(kBlock), 0, R.st, wn, rk, n, lz, alpha,
-                               sigma, k, partial);
-        }
+        if (!fold_a)
+            hipLaunchKernelGGL(finish_alpha, dim3(1), dim3(kFinishBlock), 0, R.st, sigma, partial,
+                               Ghx, alpha, k);
+        const double *apart = fold_a ? partial : nullptr;
         if (!R.reorth) {
-            hipLaunchKernelGGL(finish_beta, dim3(1), dim3(kFinishBlock), 0, R.st, lz, partial, Gb,
-                               alpha, beta, sigma, cprev, k);
-            continue;
+            if (R.psi)
+                hipLaunchKernelGGL((pass_b<T, true>), dim3(Gb), dim3(kBlock), 0, R.st, wn, rk, n,
+                                   apart, Ghx, alpha, sigma, k, bpart, coef, R.psi);
+            else
+                hipLaunchKernelGGL((pass_b<T, false>), dim3(Gb), dim3(kBlock), 0, R.st, wn, rk, n,
+                                   apart, Ghx, alpha, sigma, k, bpart, coef, R.psi);
+        } else {
+            // beta is the norm after the second pass
+            const int nv = k + 1, splits = tall_splits<1>(n, nv);
+            const dim3 dg(splits, (nv + tall_cols<1>() - 1) / tall_cols<1>());
+            const bool fold_h = nv <= kReorthFold && splits <= 16;
+            TallSub<T> sub;
+            sub.r = rk;
+            sub.apart = apart;
+            sub.n_hx = Ghx;
+            sub.k = k;
+            sub.alpha = alpha;
+            sub.sigma = sigma;
+            if (R.psi)
+                hipLaunchKernelGGL(psi_axpy<T>, dim3(G), dim3(kBlock), 0, R.st, R.psi, rk, n, coef,
+                                   sigma, k);
+            for (int rep = 0; rep < 2; ++rep) {
+                if (rep == 0)
+                    hipLaunchKernelGGL((tall_dots_kernel<T, 1, true>), dg, dim3(kTallBlock), 0, R.st,
+                                       V, wn, n, nv, dots, (const int *)nullptr, sigma + k, sub);
+                else
+                    hipLaunchKernelGGL((tall_dots_kernel<T, 1, false>), dg, dim3(kTallBlock), 0,
+                                       R.st, V, wn, n, nv, dots, (const int *)nullptr, sigma + k, sub);
+                if (!fold_h)
+                    hipLaunchKernelGGL(reorth_finish, dim3((nv + 63) / 64), dim3(kTallBlock), 0,
+                                       R.st, dots, splits, nv, hc, sigma + k);
+                const double *h = fold_h ? nullptr : hc;
+                if (rep == 0)
+                    hipLaunchKernelGGL((reorth_update<T, true>), dim3(G), dim3(kBlock), 0, R.st, V,
+                                       wn, n, nv, dots, splits, h, sigma + k, (double *)nullptr, sub);
+                else
+                    hipLaunchKernelGGL((reorth_update<T, false>), dim3(G), dim3(kBlock), 0, R.st, V,
+                                       wn, n, nv, dots, splits, h, sigma + k, bpart, sub);
+            }
         }
-        // with full reorthogonalization beta is the norm after it
-        for (int rep = 0; rep < 2; ++rep) {
-            hipLaunchKernelGGL(reorth_dots<T>, dim3(G, k + 1), dim3(kBlock), 0, R.st, V, wn, n,
-                               k + 1, partial, lz);
-            hipLaunchKernelGGL(reorth_finish, dim3(k + 1), dim3(64), 0, R.st, partial, G, hc,
-                               lz);
-            hipLaunchKernelGGL(reorth_update<T>, dim3(G), dim3(kBlock), 0, R.st, V, wn, n,
-                               k + 1, hc, lz);
-        }
-        hipLaunchKernelGGL(sumsq_kernel<T>, dim3(G), dim3(kBlock), 0, R.st, wn, n, partial,
-                           &lz->stopped);
-        hipLaunchKernelGGL(finish_beta, dim3(1), dim3(kFinishBlock), 0, R.st, lz, partial, G, alpha,
-                           beta, sigma, cprev, k);
+        if (!fold_b || k + 1 == R.steps)
+            hipLaunchKernelGGL(finish_beta, dim3(1), dim3(kFinishBlock), 0, R.st, lz, bpart, Gb,
+                               alpha, beta, sigma, cprev, scale, k);
     }
     HM_HIP(hipGetLastError());
     return HM_OK;
@@ -724,15 +691,27 @@ static int enqueue_steps(Run &R, int k0, int k1, std::vector<hipEvent_t> *ev) {
 // Waits for the run and copies its results to the host.
 static int collect(const Run &R, double *alpha_h, double *beta_h, int *steps_done) {
     HM_HIP(hipGetLastError());
+    const size_t bytes = R.L.sigma + sizeof(double) * (R.steps + 1) - R.L.lz;
+    std::vector<unsigned char> host(bytes);
+    HM_HIP(hipMemcpyAsync(host.data(), R.w + R.L.lz, bytes, hipMemcpyDeviceToHost, R.st));
     HM_HIP(hipStreamSynchronize(R.st));
     LzDev hlz;
-    HM_HIP(hipMemcpy(&hlz, R.w + R.L.lz, sizeof hlz, hipMemcpyDeviceToHost));
+    std::memcpy(&hlz, host.data(), sizeof hlz);
     if (hlz.bad_start) return fail(HM_EINVAL, "start vector has zero norm");
-    const int done = hlz.stopped > 0 ? hlz.stopped : R.steps;
+    int done = R.steps;
+    if (R.small) {
+        if (hlz.stopped > 0) done = hlz.stopped;
+    } else {
+        const double *sigma = (const double *)(host.data() + (R.L.sigma - R.L.lz));
+        for (int k = 1; k <= R.steps; ++k)
+            if (sigma[k] == 0.0) {
+                done = k;
+                break;
+            }
+    }
     if (alpha_h)
-        HM_HIP(hipMemcpy(alpha_h, R.w + R.L.alpha, sizeof(double) * done, hipMemcpyDeviceToHost));
-    if (beta_h)
-        HM_HIP(hipMemcpy(beta_h, R.w + R.L.beta, sizeof(double) * done, hipMemcpyDeviceToHost));
+        std::memcpy(alpha_h, host.data() + (R.L.alpha - R.L.lz), sizeof(double) * done);
+    if (beta_h) std::memcpy(beta_h, host.data() + (R.L.beta - R.L.lz), sizeof(double) * done);
     if (alpha_h) std::fill(alpha_h + done, alpha_h + R.steps, 0.0);
     if (beta_h) std::fill(beta_h + done, beta_h + R.steps, 0.0);
     *steps_done = done;
@@ -852,17 +831,14 @@ static int run_lanczos(Run &R, double *alpha_h, double *beta_h, int *steps_done)
     if (R.psi) {
         HM_HIP(hipMemcpyAsync(R.w + R.L.coef, R.coef_host, sizeof(double) * R.steps,
                               hipMemcpyHostToDevice, R.st));
-        if (!R.small) hipLaunchKernelGGL(zero_f64, dim3(G), dim3(kBlock), 0, R.st, R.psi, n);
     }
     if (R.small) {
         HM_TRY(launch_small<T>(R));
         return collect(R, alpha_h, beta_h, steps_done);
     }
-    hipLaunchKernelGGL(sumsq_kernel<double>, dim3(G), dim3(kBlock), 0, R.st, R.v0, n, partial,
-                       (const int *)nullptr);
-    hipLaunchKernelGGL(finish_init, dim3(1), dim3(kBlock), 0, R.st, lz, partial, G, sigma,
-                       cprev, R.tol);
-    hipLaunchKernelGGL(init_write<T>, dim3(G), dim3(kBlock), 0, R.st, R.v0, r0, n, lz);
+    hipLaunchKernelGGL(sumsq_kernel<double>, dim3(G), dim3(kBlock), 0, R.st, R.v0, n, partial);
+    hipLaunchKernelGGL(init_write<T>, dim3(G), dim3(kBlock), 0, R.st, R.v0, r0, n, lz, partial, G,
+                       sigma, cprev, (double *)(R.w + R.L.scale), R.tol);
     HM_HIP(hipGetLastError());
 
     const bool timing = g_timing;
@@ -897,9 +873,8 @@ static int run_lanczos(Run &R, double *alpha_h, double *beta_h, int *steps_done)
     }
     if (R.psi) {
         hipLaunchKernelGGL(sumsq_kernel<double>, dim3(G), dim3(kBlock), 0, R.st, R.psi, n,
-                           partial, (const int *)nullptr);
-        hipLaunchKernelGGL(finish_psi_norm, dim3(1), dim3(kBlock), 0, R.st, lz, partial, G);
-        hipLaunchKernelGGL(scale_psi, dim3(G), dim3(kBlock), 0, R.st, R.psi, n, lz);
+                           partial);
+        hipLaunchKernelGGL(scale_psi, dim3(G), dim3(kBlock), 0, R.st, R.psi, n, lz, partial, G);
     }
     if (timing) HM_HIP(hipEventRecord(hi, R.st));
     HM_TRY(collect(R, alpha_h, beta_h, steps_done));

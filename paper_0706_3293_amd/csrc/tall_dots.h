@@ -18,6 +18,7 @@
 #pragma once
 
 #include "device_common.h"
+#include "lanczos_dev.h"
 
 namespace hm {
 
@@ -38,12 +39,40 @@ __device__ __forceinline__ void load2(const T *__restrict__ p, double &a, double
 // Columns of V one workgroup (blockIdx.y) takes.
 template <int P> constexpr int tall_cols() { return P == 1 ? 32 : 64; }
 
-// partial[split][col][c] over the rows of split blockIdx.x.
-template <typename T, int P>
+// W - alpha_k sigma_k r instead of W itself, rounded to the vectors' type (the
+// scalar recurrence's pass B, which then needs no launch of its own): alpha_k
+// is summed here from the H x pass's partials.
+template <typename T>
+struct TallSub {
+    const T *r = nullptr;            // nullptr: W as it is
+    const double *apart = nullptr;   // alpha partials (nullptr: finished already)
+    int n_hx = 0, k = 0;
+    double *alpha = nullptr;
+    const double *sigma = nullptr;
+};
+
+// alpha_k sigma_k of a TallSub; `write`: this workgroup stores alpha_k.
+template <typename T>
+__device__ __forceinline__ double tall_factor(const TallSub<T> &sub, double *red, bool write) {
+    const double al = sub.apart ? fold_sum(sub.apart, sub.n_hx, red) : sub.alpha[sub.k];
+    if (write && sub.apart && threadIdx.x == 0) sub.alpha[sub.k] = al;
+    return uniform(al * sub.sigma[sub.k]);
+}
+
+// partial[split][col][c] over the rows of split blockIdx.x.  The run has
+// stopped, and nothing is done, if *stopped != 0 or *live == 0 (null: neither).
+template <typename T, int P, bool SUB = false>
 __global__ __launch_bounds__(kTallBlock) void tall_dots_kernel(
     const T *__restrict__ V, const T *__restrict__ W, int64_t dim, int ncol,
-    double *__restrict__ partial, const int *__restrict__ stopped) {
-    if (stopped && *stopped) return;
+    double *__restrict__ partial, const int *__restrict__ stopped,
+    const double *__restrict__ live, const TallSub<T> sub) {
+    static_assert(!SUB || P == 1, "pass B belongs to the scalar recurrence");
+    if ((stopped && *stopped) || (live && *live == 0.0)) return;
+    double factor = 0.0;
+    if constexpr (SUB) {
+        __shared__ double red[17];
+        factor = tall_factor(sub, red, blockIdx.x == 0 && blockIdx.y == 0);
+    }
     constexpr int NG = 2;                          // accumulator pairs per wave
     constexpr int NA = P == 1 ? NG : 2 * NG;       // accumulators of 16 columns
     constexpr int kRows = P == 1 ? 8 : 4;          // rows of one load
@@ -87,6 +116,13 @@ __global__ __launch_bounds__(kTallBlock) void tall_dots_kernel(
                 }
                 if (wok && two) load2(wp + r, b0[u], b1[u]);
                 else if (wok && one) b0[u] = (double)wp[r];
+                if constexpr (SUB) {
+                    double r0 = 0.0, r1 = 0.0;
+                    if (wok && two) load2(sub.r + r, r0, r1);
+                    else if (wok && one) r0 = (double)sub.r[r];
+                    b0[u] = (double)(T)(b0[u] - factor * r0);
+                    b1[u] = (double)(T)(b1[u] - factor * r1);
+                }
             } else {
                 const int64_t r = base + u * kRows + kk;
                 const bool ok = r < dim;
