@@ -59,10 +59,14 @@ struct Couplings {
     // bonds regrouped for the spin-1/2 block kernel (built on first use)
     void *half = nullptr;
     void (*half_free)(void *) = nullptr;
+    // the same for the spin-1/2 kernel with one workgroup per block
+    void *wg = nullptr;
+    void (*wg_free)(void *) = nullptr;
     ~Couplings() {
-        if (dev || half) (void)hipDeviceSynchronize();
+        if (dev || half || wg) (void)hipDeviceSynchronize();
         if (dev) (void)hipFree(dev);
         if (half && half_free) half_free(half);
+        if (wg && wg_free) wg_free(wg);
     }
 };
 using CouplingsRef = std::shared_ptr<Couplings>;
@@ -122,6 +126,9 @@ struct Basis {
     int half_ipw = 0;        // work items per wave that size the grid (0: default grid)
     void *half_tables = nullptr;
     void (*half_tables_free)(void *) = nullptr;
+    // spin-1/2 kernel with one workgroup per block: tables (first use)
+    void *wg_tables = nullptr;
+    void (*wg_tables_free)(void *) = nullptr;
     // block kernel for s >= 1: the split (fixed at creation) and its tables
     // (first use)
     DigitSplit digit;
@@ -174,7 +181,7 @@ struct HxPass {
 int hx_partial_count(const Basis *b, int kernel);      // partial slots needed
 int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel,
               const HxPass &pass, hipStream_t st);
-int choose_kernel(const Basis *b, const Couplings *c, int requested);
+int choose_kernel(const Basis *b, const Couplings *c, int requested, int dtype);
 // Builds what kernel `kernel` needs on the device for these couplings (ahead
 // of a graph capture, where nothing may be allocated).
 int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel);

@@ -19,10 +19,16 @@
 // A wave takes R blocks of one digit-sum class (the low-word work is done once
 // for R rows), copies them to its LDS slice, interleaved, so that one LDS read
 // serves the R rows, and goes over them 64 rows at a time.  Every row adds its
-// bonds in list order, as row_hx (hx_row.h) does; the diagonal element is the
-// sum of a low-word part, a high-word part (both tabulated, summed in FP64 from
-// the same -J/4 in the vectors' type) and the straddling bonds.
+// bonds in list order, as row_hx (hx_row.h) does.  In FP64 the diagonal element
+// is the sum of a low-word part, a high-word part (both tabulated) and the
+// straddling bonds.  In FP32 it is summed bond by bond with the roundings of
+// row_hx, so that the result is the generic kernel's bit for bit: with equal
+// couplings those roundings are the same for many rows and do not average out
+// (coefficients of FP32-mixed runs 1e-8 apart).  Where FP32 holds all of these
+// sums exactly, the tabulated parts give the same.
 #include <algorithm>
+#include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <vector>
 
@@ -106,8 +112,7 @@ struct DigitBonds {
     uint32_t *mcnt = nullptr;        // [block] moves the block's high word allows
     void *dhigh = nullptr;           // [block] diagonal part of the high-word bonds
     void *kdiag = nullptr;           // [block][nH] (2 m_u)(2 m_v) of the high-word bonds and
-    void *hJ4 = nullptr;             // [nH] their -J/4 (FP32, one lane per row; nH padded to
-                                     // fours with zeros)
+    void *hJ4 = nullptr;             // [nH] their -J/4 (FP32; nH padded to fours with zeros)
     void *strad = nullptr;           // [block][nS][2] target blocks of the straddling moves
     int n_ops = 0, nF = 0, nS = 0, nH = 0, mw = 0;   // mw: moves of a row, padded to fours
     void *mem = nullptr;                             // the allocation that holds them
@@ -175,12 +180,22 @@ __device__ __forceinline__ void lds_row<float, 1>(const float *p, float (&v)[1])
 template <>
 __device__ __forceinline__ void lds_row<double, 1>(const double *p, double (&v)[1]) { v[0] = *p; }
 
+// (2 m_u)(2 m_v) by the index of the two digits (FP32 only).
+template <typename T>
+__device__ __forceinline__ void stage_products(T *kt, int two_s) {
+    if constexpr (sizeof(T) == 4)
+        for (int t = threadIdx.x; t < (two_s + 1) * (two_s + 1); t += blockDim.x)
+            kt[t] = (T)((two_s - 2 * (t / (two_s + 1))) * (two_s - 2 * (t % (two_s + 1))));
+}
+
 // W low-word bonds at once: the table entries, then the R rows' reads and
 // products in bond order.  A move that the digits do not allow reads the
 // slice's zero entry (its matrix element is zero as well).
 template <int W, typename T, int R>
 __device__ __forceinline__ void low_bonds(const uint32_t *__restrict__ low, int words, const T *cf,
-                                          int WW, const T *xs, T (&off)[R]) {
+                                          const T *kt, int WW, const T *xs,
+                                          const Const<DigitOp<T>> &op, int q0, bool chain,
+                                          T (&diag)[R], T (&off)[R]) {
     constexpr uint32_t kMask = (1u << kRankBits) - 1u;
     uint32_t e[W];
     T x1[W][R], x2[W][R], c[W][2];
@@ -199,6 +214,13 @@ __device__ __forceinline__ void low_bonds(const uint32_t *__restrict__ low, int 
             off[m] += c[q][0] * x1[q][m];
             off[m] += c[q][1] * x2[q][m];
         }
+    if (sizeof(T) == 4 && chain)
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            const T k = kt[e[q] >> (2 * kRankBits)];
+#pragma unroll
+            for (int m = 0; m < R; ++m) diag[m] += op.mJ4[q0 + q] * k;
+        }
 }
 
 template <typename T, typename I, int R, bool DOT, bool STORE>
@@ -213,11 +235,15 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
     const double sigma = uniform(sigma_v), cprev = uniform(cprev_v);   // scalar registers
     const int WW = g.two_s + 1;
     const int ncf = g.nF * WW * WW * 2;
-    T *cf = reinterpret_cast<T *>(smem);
-    T *xs = reinterpret_cast<T *>(smem + ((size_t)ncf * sizeof(T) + 31) / 32 * 32) +
+    T *cf = reinterpret_cast<T *>(smem), *kt = cf + ncf;
+    T *xs = reinterpret_cast<T *>(smem + ((size_t)(ncf + WW * WW) * sizeof(T) + 31) / 32 * 32) +
             (size_t)(threadIdx.x >> 6) * R * (g.smax + 1);
     for (int t = threadIdx.x; t < ncf; t += blockDim.x) cf[t] = g.cf[t];
+    stage_products(kt, g.two_s);
     __syncthreads();
+    const Const<T> *kdiag = as_const(g.kdiag), *hJ4 = as_const(g.hJ4);
+    const bool chain = sizeof(T) == 4 && g.kdiag;
+    const int nHc = chain ? g.nH : 0;
 
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     const int two_s = g.two_s;
@@ -231,6 +257,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
     }
     wl = __builtin_amdgcn_readfirstlane(wl);
     x8 = __builtin_amdgcn_readfirstlane(x8);
+    stride = __builtin_amdgcn_readfirstlane(stride);
     // the tables are read-only for the whole launch: through the constant
     // address space the wave-uniform reads are scalar loads
     const Const<uint32_t> *groups = as_const(g.groups);
@@ -243,8 +270,8 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
     if (lane < R) xs[g.smax * R + lane] = 0;
     double dot = 0.0;
     for (uint32_t l = wl;; l += stride) {
-        const uint32_t it =
-            by_xcd ? (l / g.run) * (kXcds * g.run) + x8 * g.run + l % g.run : l;
+        const uint32_t it = __builtin_amdgcn_readfirstlane(
+            by_xcd ? (l / g.run) * (kXcds * g.run) + x8 * g.run + l % g.run : l);
         if (it >= g.n_groups) break;
         uint32_t hb[R];
         bool valid[R];
@@ -287,12 +314,12 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
             const bool live = r1 + lane < S;
             const int r = live ? r1 + lane : 0;       // dead lanes shadow row 0
             const uint32_t *__restrict__ low = g.low + cs + r;
-            const T dl = g.dlow[cs + r];
+            const T dl = chain ? (T)0 : g.dlow[cs + r];
             T xi[R], diag[R], off[R];
             lds_row<T, R>(xs + r * R, xi);
 #pragma unroll
             for (int m = 0; m < R; ++m) {
-                diag[m] = dl + dh[m];
+                diag[m] = chain ? (T)0 : dl + dh[m];
                 off[m] = 0;
             }
             // bonds with their first site in the low word, in list order
@@ -304,17 +331,17 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
                     // four bonds at once where the R rows' reads fit the registers
                     if constexpr (R * sizeof(T) <= 16) {
                         if (op.n == 4) {
-                            low_bonds<4, T, R>(lo, g.words, cfb, WW, xs, off);
+                            low_bonds<4, T, R>(lo, g.words, cfb, kt, WW, xs, op, 0, chain, diag, off);
                             continue;
                         }
                     } else if (op.n == 4) {
-                        low_bonds<2, T, R>(lo, g.words, cfb, WW, xs, off);
+                        low_bonds<2, T, R>(lo, g.words, cfb, kt, WW, xs, op, 0, chain, diag, off);
                         low_bonds<2, T, R>(lo + 2 * (size_t)g.words, g.words,
-                                           cfb + 2 * WW * WW * 2, WW, xs, off);
+                                           cfb + 2 * WW * WW * 2, kt, WW, xs, op, 2, chain, diag, off);
                         continue;
                     }
-                    if (op.n == 2) low_bonds<2, T, R>(lo, g.words, cfb, WW, xs, off);
-                    else low_bonds<1, T, R>(lo, g.words, cfb, WW, xs, off);
+                    if (op.n == 2) low_bonds<2, T, R>(lo, g.words, cfb, kt, WW, xs, op, 0, chain, diag, off);
+                    else low_bonds<1, T, R>(lo, g.words, cfb, kt, WW, xs, op, 0, chain, diag, off);
                     continue;
                 }
                 const uint32_t e = lo[0], rk1 = e & ((1u << kRankBits) - 1u);
@@ -331,7 +358,8 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
                     const T v1 = load_at(x, a1 ? so[0] + (I)rk1 : off0[m] + (I)r);
                     const T v2 = load_at(x, a2 ? so[1] + (I)rk2 : off0[m] + (I)r);
                     lds_row<T, 2>(cfb + (au * WW + av) * 2, c[m]);
-                    diag[m] += sJ * (T)(two_s - 2 * av);
+                    if constexpr (sizeof(T) == 8) diag[m] += sJ * (T)(two_s - 2 * av);
+                    else diag[m] += op.mJ4[0] * (T)((two_s - 2 * au) * (two_s - 2 * av));
                     g1[m] = a1 ? v1 : (T)0;
                     g2[m] = a2 ? v2 : (T)0;
                 }
@@ -345,6 +373,16 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
             // coalesced, four of each of the R blocks at once; past the
             // shortest list, finished ones go on with their own block and add
             // nothing
+            // (the diagonal's chain takes its four bonds while the gathers are
+            // on their way)
+            auto add_diag = [&](int b) {
+#pragma unroll
+                for (int m = 0; m < R; ++m) {
+                    const Const<T> *kd = kdiag + (size_t)hb[m] * g.nH + b;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) diag[m] += hJ4[b + q] * kd[q];
+                }
+            };
             int q0 = 0;
             for (; q0 + 4 <= nmin; q0 += 4) {
                 T xj[R][4];
@@ -352,6 +390,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
                 for (int m = 0; m < R; ++m)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) xj[m][q] = load_at(x, mrow[m][q0 / 4].off[q] + (I)r);
+                if (q0 < nHc) add_diag(q0);
 #pragma unroll
                 for (int m = 0; m < R; ++m)
 #pragma unroll
@@ -363,12 +402,14 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
                 for (int m = 0; m < R; ++m)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) xj[m][q] = load_at(x, mrow[m][q0 / 4].off[q] + (I)r);
+                if (q0 < nHc) add_diag(q0);
 #pragma unroll
                 for (int m = 0; m < R; ++m)
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
                         off[m] += mrow[m][q0 / 4].cf[q] * (q0 + q < nm[m] ? xj[m][q] : (T)0);
             }
+            for (; q0 < nHc; q0 += 4) add_diag(q0);
 #pragma unroll
             for (int m = 0; m < R; ++m) {
                 if (live && valid[m]) {
@@ -396,17 +437,12 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
 // per row, whatever its block.  The block of a row comes from a table, and the
 // block's own tables are read per lane, broadcast among the lanes of one
 // block; low-word targets are gathered from memory instead of LDS.
-//
-// In FP32 the diagonal element is summed bond by bond in list order with the
-// roundings of row_hx, so that the result is the generic kernel's bit for bit:
-// an FP32 Lanczos run in a subspace this small does not average the roundings
-// of its rows out (8135 rows: coefficients 1e-8 apart).
 template <int W, typename T, typename I>
 __device__ __forceinline__ void flat_low_bonds(const uint32_t *__restrict__ low, int words,
                                                const T *cf, const T *kt, int WW, uint32_t zero,
                                                const T *__restrict__ x, I off0, I row,
-                                               const Const<DigitOp<T>> &op, int q0, T &diag,
-                                               T &off) {
+                                               const Const<DigitOp<T>> &op, int q0, bool chain,
+                                               T &diag, T &off) {
     constexpr uint32_t kMask = (1u << kRankBits) - 1u;
     uint32_t e[W];
     T x1[W], x2[W], c[W][2];
@@ -425,7 +461,7 @@ __device__ __forceinline__ void flat_low_bonds(const uint32_t *__restrict__ low,
     for (int q = 0; q < W; ++q) {
         off += c[q][0] * x1[q];
         off += c[q][1] * x2[q];
-        if constexpr (sizeof(T) == 4) diag += op.mJ4[q0 + q] * kt[e[q] >> (2 * kRankBits)];
+        if (sizeof(T) == 4 && chain) diag += op.mJ4[q0 + q] * kt[e[q] >> (2 * kRankBits)];
     }
 }
 
@@ -442,11 +478,10 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
     const int WW = g.two_s + 1, two_s = g.two_s;
     T *cf = reinterpret_cast<T *>(smem), *kt = cf + g.nF * WW * WW * 2;
     for (int t = threadIdx.x; t < g.nF * WW * WW * 2; t += blockDim.x) cf[t] = g.cf[t];
-    if constexpr (sizeof(T) == 4)        // (2 m_u)(2 m_v) by the index of the digits
-        for (int t = threadIdx.x; t < WW * WW; t += blockDim.x)
-            kt[t] = (T)((two_s - 2 * (t / WW)) * (two_s - 2 * (t % WW)));
+    stage_products(kt, two_s);
     __syncthreads();
     const Const<T> *hJ4 = as_const(g.hJ4);
+    const bool chain = sizeof(T) == 4 && g.kdiag;
     const Const<DigitOp<T>> *ops = as_const(g.ops);
     I first, last;
     block_rows<I>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, dim, first, last);
@@ -458,7 +493,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
         const uint32_t *__restrict__ low = g.low + blk.cs + r;
         const T xi = x[row];
         T diag = 0, off = 0;
-        if constexpr (sizeof(T) == 8) diag = g.dlow[blk.cs + r] + g.dhigh[hb];
+        if (!chain) diag = g.dlow[blk.cs + r] + g.dhigh[hb];
         for (int o = 0; o < g.n_ops; ++o) {
             const Const<DigitOp<T>> &op = ops[o];
             const T *cfb = cf + op.first * (WW * WW * 2);
@@ -466,13 +501,13 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
             if (op.straddle < 0) {
                 if (op.n == 4)
                     flat_low_bonds<4, T, I>(lo, g.words, cfb, kt, WW, g.smax, x, blk.off, row,
-                                            op, 0, diag, off);
+                                            op, 0, chain, diag, off);
                 else if (op.n == 2)
                     flat_low_bonds<2, T, I>(lo, g.words, cfb, kt, WW, g.smax, x, blk.off, row,
-                                            op, 0, diag, off);
+                                            op, 0, chain, diag, off);
                 else
                     flat_low_bonds<1, T, I>(lo, g.words, cfb, kt, WW, g.smax, x, blk.off, row,
-                                            op, 0, diag, off);
+                                            op, 0, chain, diag, off);
                 continue;
             }
             const uint32_t e = lo[0], rk1 = e & ((1u << kRankBits) - 1u);
@@ -499,7 +534,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
 #pragma unroll
             for (int q = 0; q < 4; ++q) off += m.cf[q] * (q0 + q < n ? xj[q] : (T)0);
         }
-        if constexpr (sizeof(T) == 4) {
+        if (sizeof(T) == 4 && chain) {
             const float4 *__restrict__ kd =
                 reinterpret_cast<const float4 *>(g.kdiag + (size_t)hb * g.nH);
             for (int b = 0; b < g.nH; b += 4) {
@@ -921,6 +956,26 @@ static int digit_prepare(Basis *b, DigitTables **out) {
     return HM_OK;
 }
 
+// Whether FP32 holds every sum of diagonal terms of these couplings exactly
+// (multiples of one power of two, the largest below 2^24 of it; couplings of 1
+// or 0.25, say): then no order of summation rounds.
+static bool exact_diagonal(const Basis *b, const Couplings *c) {
+    double sum = 0.0;
+    int low = 0;                          // smallest bit set in any -J/4
+    bool any = false;
+    for (const BondDev &bd : c->host) {
+        const float f = (float)bd.mJ4;
+        if (f == 0.0f) continue;
+        int e;
+        const float m = std::frexp(f, &e);
+        const int bit = e - 24 + __builtin_ctz((unsigned)std::abs((int)std::ldexp(m, 24)));
+        low = any ? std::min(low, bit) : bit;
+        any = true;
+        sum += std::fabs((double)f) * b->two_s * b->two_s;
+    }
+    return !any || sum <= std::ldexp(1.0, 24 + low);
+}
+
 template <typename T, typename I, typename PI>
 static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTables *t,
                               DigitBonds *d) {
@@ -1000,7 +1055,7 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
     const size_t o_moves = arena.reserve(nblk * (d->mw / 4) * sizeof(DigitMoves<T, I>));
     const size_t o_mcnt = arena.reserve(nblk * sizeof(uint32_t));
     const size_t o_dhigh = arena.reserve(nblk * sizeof(T));
-    const bool chain = b->digit.flat && sizeof(T) == 4;
+    const bool chain = sizeof(T) == 4 && !exact_diagonal(b, c);
     d->nH = chain ? (nH + 3) / 4 * 4 : 0;
     const size_t o_kdiag = arena.reserve(nblk * d->nH * sizeof(T));
     const size_t o_hJ4 = arena.reserve(d->nH * sizeof(T));

@@ -1,0 +1,644 @@
+// Spin-1/2 block kernel with one workgroup per block (Sec. 4, Eq. (E-4-b)).
+//
+// The split is that of hx_half.hip: the rows with one high word h are a
+// contiguous block of C(K, A - popcount(h)) rows, ordered like the low words.
+// The kernels there give a wave its own rows and let it walk the bonds with
+// one round of gathers after another.  For a few thousand blocks that is a
+// chain of eight or more memory round trips on a chip with a wave or two per
+// SIMD (12,870 rows: 12.8 us; 184,756 rows with all 190 bonds: 41 us), and the
+// straddling bonds gather per lane.  Here a workgroup takes one block, a row
+// per thread, and loads everything in one round: its own block, the blocks
+// that its straddling bonds reach (one per distinct high site, whatever the
+// number of bonds), all coalesced, into LDS, and the first rows of the
+// high-word targets into registers; what follows reads LDS.  Tables are laid
+// out per block, so the wave-uniform reads are one round of scalar loads too.
+// The sums take the bonds in the order of hx_half_kernel (low word, high word,
+// straddling): at the same K the results are equal bit for bit.
+#include <algorithm>
+#include <cstring>
+#include <vector>
+
+#include "device_common.h"
+#include "hm_internal.h"
+
+namespace hm {
+
+int launch_hx_generic(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
+                      hipStream_t st);
+
+constexpr int kWgMaxK = 12;
+constexpr int kWgMaxHighBits = 20;
+constexpr size_t kWgMaxLds = 64 * 1024;
+constexpr size_t kWgMaxTables = (size_t)4 << 30;
+constexpr int kWgPiece = 8;          // high-word targets of a piece
+
+// Up to eight bonds of one kind, consecutive in the bond list, read with two or
+// three wide scalar loads.  Low: m holds the two bits of every bond.
+// Straddling: the bonds share their low site (m[0] its bit), slot holds the
+// slot of every high site.
+template <typename T>
+struct WgOp {
+    int32_t n;           // bonds in use: 8, 4, 2 or 1
+    uint32_t slot[2];    // a byte each
+    int32_t pad;
+    uint32_t m[8];
+    T c[8];              // -J/2
+};
+
+struct WgTables {
+    int K = 0, threads = 256, smax = 0;
+    int64_t n_blocks = 0;
+    std::vector<uint16_t> rankL, unrankL;
+    std::vector<uint32_t> off;       // by high word
+    std::vector<uint32_t> blocks;    // high words with rows, in memory order
+    int start[kWgMaxK + 2] = {0}, size[kWgMaxK + 2] = {0};
+    void *mem = nullptr;
+    uint16_t *d_rankL = nullptr, *d_unrankL = nullptr;
+    uint32_t *d_off = nullptr, *d_blocks = nullptr;
+};
+
+static void free_wg(void *p) {
+    auto *t = (WgTables *)p;
+    if (!t) return;
+    if (t->mem) (void)hipFree(t->mem);
+    delete t;
+}
+
+struct WgBonds {
+    void *mem = nullptr;
+    void *low = nullptr, *strad = nullptr;   // WgOp<T>
+    uint32_t *vbit = nullptr;                // bit of every straddling high site
+    uint32_t *hdr = nullptr;                 // [block][hw]: off, size | start << 16, flips, bits of
+                                             // the straddling high sites by slot, then per slot:
+                                             // off, size
+    uint32_t *hoff = nullptr;                // [block][mh] target blocks of the high-word bonds
+    void *hcf = nullptr;                     // [block][mh] their -J/2
+    int nlow = 0, nstrad = 0, nslot = 0, mh = 0, hw = 0;
+};
+struct WgBondSet {
+    WgBonds by_type[2];
+    bool have[2] = {false, false};
+};
+static void free_wg_bonds(void *p) {
+    auto *s = (WgBondSet *)p;
+    if (!s) return;
+    for (auto &b : s->by_type)
+        if (b.mem) (void)hipFree(b.mem);
+    delete s;
+}
+
+template <typename T>
+struct WgArgs {
+    const uint16_t *rankL, *unrankL;
+    const WgOp<T> *low, *strad;
+    const uint32_t *hdr, *hoff;
+    const T *hcf;
+    uint32_t n_blocks, run;
+    int K, nlow, nstrad, nslot, mh, hw, stride;
+    double shift;
+};
+
+template <typename T> using Const = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ const Const<T> *as_const(const T *p) {
+    return (const Const<T> *)p;
+}
+
+// Element i of a vector below 4 GiB: scalar base and 32-bit byte offset.
+template <typename T>
+__device__ __forceinline__ T load_at(const T *__restrict__ base, uint32_t i) {
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
+                                        i * (uint32_t)sizeof(T));
+}
+
+// W low-word bonds from LDS.
+template <int W, typename T>
+__device__ __forceinline__ void wg_low(const Const<WgOp<T>> &op, uint32_t L, uint32_t r,
+                                       const uint16_t *rankL, const T *xs, T xi, T &acc) {
+    uint32_t idx[W];
+    T xj[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        const uint32_t m = op.m[q], t = rankL[L ^ m];
+        idx[q] = __popc(L & m) == 1 ? t : r;
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) xj[q] = xs[idx[q]];
+#pragma unroll
+    for (int q = 0; q < W; ++q) acc += op.c[q] * (xj[q] - xi);
+}
+
+// W straddling bonds of one low site: they flip where the low bit differs from
+// the bond's high bit, which is the same for the whole block.
+template <int W, typename T>
+__device__ __forceinline__ void wg_straddle(const Const<WgOp<T>> &op, uint32_t hmask, bool set,
+                                            uint32_t rk, uint32_t r, int stride, const T *xs, T xi,
+                                            T &acc) {
+    T xj[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        const uint32_t slot = (op.slot[q / 4] >> (8 * (q % 4))) & 0xffu;
+        const bool hset = (hmask >> slot) & 1u;
+        xj[q] = xs[set != hset ? (slot + 1) * stride + rk : r];
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) acc += op.c[q] * (xj[q] - xi);
+}
+
+template <typename T, bool DOT, bool STORE>
+__global__ __launch_bounds__(256) void hx_half_wg_kernel(
+    const WgArgs<T> g, const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ prev,
+    const LzStep step, double *__restrict__ partial, T *__restrict__ store) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double red[kLzLds];
+    T *xs = reinterpret_cast<T *>(smem);
+    uint16_t *rankL = reinterpret_cast<uint16_t *>(
+        smem + ((size_t)(1 + g.nslot) * g.stride * sizeof(T) + 15) / 16 * 16);
+    {
+        const uint4 *s4 = reinterpret_cast<const uint4 *>(g.rankL);
+        uint4 *d4 = reinterpret_cast<uint4 *>(rankL);
+        for (int t = threadIdx.x; t < (1 << g.K) / 8; t += blockDim.x) d4[t] = s4[t];
+    }
+    double sigma = 1.0, cprev = 0.0;
+    const T shift = (T)g.shift;
+    const Const<uint32_t> *hdrs = as_const(g.hdr), *hoffs = as_const(g.hoff);
+    const Const<T> *hcfs = as_const(g.hcf);
+    const Const<WgOp<T>> *low = as_const(g.low), *strad = as_const(g.strad);
+    // XCDs (workgroup b runs on XCD b % 8) take turns on runs of g.run blocks
+    const bool by_xcd = gridDim.x % kXcds == 0;
+    const uint32_t x8 = by_xcd ? blockIdx.x % kXcds : 0;
+    const uint32_t l0 = by_xcd ? blockIdx.x / kXcds : blockIdx.x;
+    const uint32_t lstep = by_xcd ? gridDim.x / kXcds : gridDim.x;
+    double dot = 0.0;
+    for (uint32_t l = l0;; l += lstep) {
+        const uint32_t it = by_xcd ? (l / g.run) * (kXcds * g.run) + x8 * g.run + l % g.run : l;
+        const bool any = it < g.n_blocks;
+        if (!any && l != l0) break;
+        const Const<uint32_t> *hdr = hdrs + (size_t)(any ? it : 0) * g.hw;
+        const uint32_t off = hdr[0], hmask = hdr[3];
+        const int S = any ? (int)(hdr[1] & 0xffffu) : 0, cs = (int)(hdr[1] >> 16);
+        const int nf = (int)hdr[2];
+        // one round of coalesced loads: this block and those its straddling
+        // bonds reach
+        for (int r = threadIdx.x; any && r < g.stride; r += blockDim.x) {
+            T v = 0;
+            if (r < S) v = load_at(x, off + (uint32_t)r);
+            for (int s0 = 0; s0 < g.nslot; s0 += 4) {
+                T t[4];
+                bool in[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    in[s] = s0 + s < g.nslot && r < (int)hdr[5 + 2 * (s0 + s)];
+                    if (in[s]) t[s] = load_at(x, hdr[4 + 2 * (s0 + s)] + (uint32_t)r);
+                }
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    if (in[s]) xs[(1 + s0 + s) * g.stride + r] = t[s];
+            }
+            if (r < S) xs[r] = v;
+        }
+        // the step's scalars while the first round is on its way
+        if (l == l0) {
+            double sg, cp;
+            if (!lz_begin(step, red, sg, cp)) return;
+            sigma = uniform(sg);
+            cprev = uniform(cp);
+            if (!any) break;
+        }
+        __syncthreads();
+        const Const<uint32_t> *hoff = hoffs + (size_t)it * g.mh;
+        const Const<T> *hcf = hcfs + (size_t)it * g.mh;
+        for (int r0 = 0; r0 < S; r0 += blockDim.x) {
+            const uint32_t r = (uint32_t)r0 + threadIdx.x;
+            if ((int)r >= S) break;
+            const uint32_t L = g.unrankL[cs + r];
+            // the first piece of high-word targets is on its way meanwhile
+            T xh[kWgPiece];
+#pragma unroll
+            for (int q = 0; q < kWgPiece; ++q) xh[q] = q < g.mh ? load_at(x, hoff[q] + r) : (T)0;
+            T pv = 0;
+            if (prev) pv = load_at(prev, off + r);
+            const T xi = xs[r];
+            T acc = 0;
+            for (int o = 0; o < g.nlow; ++o) {
+                const Const<WgOp<T>> &op = low[o];
+                if (op.n == 8) wg_low<8, T>(op, L, r, rankL, xs, xi, acc);
+                else if (op.n == 4) wg_low<4, T>(op, L, r, rankL, xs, xi, acc);
+                else if (op.n == 2) wg_low<2, T>(op, L, r, rankL, xs, xi, acc);
+                else wg_low<1, T>(op, L, r, rankL, xs, xi, acc);
+            }
+            // bonds inside the high word that flip for h (padded with the own
+            // block and coefficient 0)
+            if (nf > 0) {
+#pragma unroll
+                for (int q = 0; q < kWgPiece; ++q) acc += hcf[q] * (xh[q] - xi);
+                for (int q0 = kWgPiece; q0 < nf; q0 += kWgPiece) {
+#pragma unroll
+                    for (int q = 0; q < kWgPiece; ++q) xh[q] = load_at(x, hoff[q0 + q] + r);
+#pragma unroll
+                    for (int q = 0; q < kWgPiece; ++q) acc += hcf[q0 + q] * (xh[q] - xi);
+                }
+            }
+            // bonds with one site in each word, by low site
+            for (int o = 0; o < g.nstrad; ++o) {
+                const Const<WgOp<T>> &op = strad[o];
+                const uint32_t m1 = op.m[0], rk = rankL[L ^ m1];
+                const bool set = (L & m1) != 0;
+                if (op.n == 8) wg_straddle<8, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
+                else if (op.n == 4) wg_straddle<4, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
+                else if (op.n == 2) wg_straddle<2, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
+                else wg_straddle<1, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
+            }
+            const T hv = shift * xi + acc;
+            double w = sigma * (double)hv;
+            if (prev) w -= cprev * (double)pv;
+            const T wt = (T)w;
+            y[off + r] = wt;
+            if constexpr (DOT) dot += (double)wt * (sigma * (double)xi);
+            if constexpr (STORE) store[off + r] = (T)(sigma * (double)xi);
+        }
+        __syncthreads();       // the next block overwrites the slices
+    }
+    if constexpr (DOT) {
+        const double s = block_sum(dot, red);
+        if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    }
+    lz_end(step, red, sigma, cprev);
+}
+
+// Rows of the block tables, one thread per block.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void wg_rows(const uint32_t *__restrict__ blocks, int64_t n,
+                                                  const uint32_t *__restrict__ off, int K, int A,
+                                                  const int *__restrict__ cls,
+                                                  const BondDev *__restrict__ bonds, int nb,
+                                                  const uint32_t *__restrict__ vbit, int nslot,
+                                                  int mh, int hw, uint32_t *__restrict__ hdr,
+                                                  uint32_t *__restrict__ hoff,
+                                                  T *__restrict__ hcf) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t h = blocks[i], own = off[h];
+        const int aL = A - __popc(h);
+        uint32_t *row = hdr + (size_t)i * hw;
+        row[0] = own;
+        row[1] = (uint32_t)cls[2 * aL + 1] | (uint32_t)cls[2 * aL] << 16;
+        uint32_t hmask = 0;
+        for (int s = 0; s < nslot; ++s) {
+            const uint32_t t = h ^ vbit[s];
+            const int a = A - __popc(t);
+            const bool ok = a >= 0 && a <= K;
+            row[4 + 2 * s] = ok ? off[t] : own;
+            row[5 + 2 * s] = ok ? (uint32_t)cls[2 * a + 1] : 0u;
+            hmask |= (h & vbit[s]) ? 1u << s : 0u;
+        }
+        row[3] = hmask;
+        int c = 0;
+        for (int b = 0; b < nb; ++b) {
+            if (bonds[b].u < K) continue;
+            const uint32_t m = 1u << (bonds[b].u - K) | 1u << (bonds[b].v - K);
+            if (__popc(h & m) != 1) continue;
+            hoff[(size_t)i * mh + c] = off[h ^ m];
+            hcf[(size_t)i * mh + c] = (T)bonds[b].mJ2;
+            ++c;
+        }
+        row[2] = (uint32_t)c;
+        for (; c < mh; ++c) {
+            hoff[(size_t)i * mh + c] = own;
+            hcf[(size_t)i * mh + c] = 0;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Host side
+// ---------------------------------------------------------------------------
+static int64_t choose2(int n, int k) {
+    if (k < 0 || k > n) return 0;
+    int64_t r = 1;
+    for (int i = 1; i <= k; ++i) r = r * (n - k + i) / i;
+    return r;
+}
+
+// Low sites: blocks of at most 252 rows, a row per thread, and about as many
+// blocks as rows of one for small N.  Measured (us per FP64 Lanczos step, J1-J2
+// rings unless said, K = 8 / 9 / 10 / 11): N = 16 15.9 / 15.7 / 16.1 / 18.4;
+// N = 18 20.1 / 16.8 / 16.4 / 19.7; N = 20 27.0 / 23.7 / 22.9 / 24.5; N = 20 with
+// all bonds 47.8 / 41.0 / 36.3 / 43.5.
+static int wg_low_bits(const Basis *b) { return std::min(10, (b->N + 2) / 2); }
+
+static int64_t wg_blocks(const Basis *b) {
+    const int K = wg_low_bits(b), nh = b->N - K;
+    int64_t n = 0;
+    for (int p = 0; p <= nh; ++p)
+        if (b->A - p >= 0 && b->A - p <= K) n += choose2(nh, p);
+    return n;
+}
+
+static int wg_threads(int K) {
+    const int s = (int)choose2(K, K / 2);
+    return s <= 64 ? 64 : s <= 128 ? 128 : 256;
+}
+
+int hx_wg_grid(const Basis *b) {
+    int64_t g = std::min<int64_t>(wg_blocks(b), kMaxGrid);
+    if (g >= kXcds) g -= g % kXcds;
+    return (int)std::max<int64_t>(g, 1);
+}
+
+static void wg_counts(const Couplings *c, int K, int *nL, int *nH, int *nS, int *nslot,
+                      uint32_t *vmask) {
+    *nL = *nH = *nS = *nslot = 0;
+    *vmask = 0;
+    for (const BondDev &d : c->host) {
+        if (d.u >= K) ++*nH;
+        else if (d.v < K) ++*nL;
+        else {
+            ++*nS;
+            *vmask |= 1u << (d.v - K);
+        }
+    }
+    *nslot = __builtin_popcount(*vmask);
+}
+
+static size_t wg_lds(int K, int nslot, size_t es) {
+    return ((size_t)(1 + nslot) * choose2(K, K / 2) * es + 15) / 16 * 16 + ((size_t)2 << K);
+}
+
+// Where it is the automatic choice: FP64, up to kWgRows rows, blocks of
+// kWgRowsPerBlock rows on average, and no schedule asked for (that is one of
+// hx_half.hip's kernels).  Measured against hx_half_kernel (us per FP64 Lanczos
+// step): N = 12 13.0 / 14.3, N = 16 15.7 / 20.7, N = 18 16.4 / 19.8, N = 20 22.9 /
+// 24.7, N = 20 with all 190 bonds 36.3 / 51.7; N = 21 28 / 28, N = 22 42 / 37, N = 24
+// 118 / 108, where the wave's own rows keep enough gathers in flight; N = 28,
+// M = 10 (5 rows per block) 33 / 23.  In FP32 another K changes the order of a
+// row's sums, which FP32-mixed runs in subspaces this small show.
+constexpr int64_t kWgRows = (int64_t)1 << 18;
+constexpr int64_t kWgRowsPerBlock = 48;
+
+bool wg_fits(const Basis *b, const Couplings *c, int dtype) {
+    if (b->two_s != 1 || dtype != HM_F64 || b->N < 4 || b->dim > kWgRows) return false;
+    if (b->half_K || b->half_block || b->half_R || b->half_staging || b->half_ipw) return false;
+    const int K = wg_low_bits(b);
+    if (b->N - K > kWgMaxHighBits) return false;
+    const int64_t n = wg_blocks(b);
+    // (small N: a block holds what there is)
+    if (b->N > 16 && b->dim < kWgRowsPerBlock * n) return false;
+    if (!c) return true;
+    int nL, nH, nS, nslot;
+    uint32_t vm;
+    wg_counts(c, K, &nL, &nH, &nS, &nslot, &vm);
+    return wg_lds(K, nslot, 8) <= kWgMaxLds &&
+           (size_t)n * ((nH + 8) * 12 + 64 + 8 * nslot) <= kWgMaxTables;
+}
+
+static int wg_prepare(Basis *b, WgTables **out) {
+    if (b->wg_tables) {
+        *out = (WgTables *)b->wg_tables;
+        return HM_OK;
+    }
+    auto *t = new WgTables;
+    const int K = t->K = wg_low_bits(b), nh = b->N - K, nlow = 1 << K;
+    t->threads = wg_threads(K);
+    t->rankL.resize(nlow);
+    t->unrankL.resize(nlow);
+    std::vector<int> fill(K + 1, 0);
+    for (int a = 0, s = 0; a <= K; ++a) {
+        t->start[a] = s;
+        t->size[a] = (int)choose2(K, a);
+        s += t->size[a];
+    }
+    for (int L = 0; L < nlow; ++L) {
+        const int a = __builtin_popcount((unsigned)L);
+        t->rankL[L] = (uint16_t)fill[a];
+        t->unrankL[t->start[a] + fill[a]++] = (uint16_t)L;
+    }
+    t->smax = (int)choose2(K, K / 2);
+    t->off.assign((size_t)1 << nh, 0);
+    uint64_t o = 0;
+    for (uint32_t h = 0; h < (uint32_t)t->off.size(); ++h) {
+        const int a = b->A - __builtin_popcount(h);
+        if (a < 0 || a > K) continue;
+        t->off[h] = (uint32_t)o;
+        t->blocks.push_back(h);
+        o += (uint64_t)t->size[a];
+    }
+    if ((int64_t)o != b->dim) {
+        delete t;
+        return fail(HM_EINVAL, "internal: block sizes sum to %llu, dim %lld",
+                    (unsigned long long)o, (long long)b->dim);
+    }
+    t->n_blocks = (int64_t)t->blocks.size();
+    auto al = [](size_t v) { return (v + 255) / 256 * 256; };
+    const size_t o_un = al(nlow * 2), o_off = o_un + al(nlow * 2),
+                 o_blk = o_off + al(t->off.size() * 4), total = o_blk + al(t->blocks.size() * 4);
+    std::vector<unsigned char> host(total);
+    std::memcpy(host.data(), t->rankL.data(), nlow * 2);
+    std::memcpy(host.data() + o_un, t->unrankL.data(), nlow * 2);
+    std::memcpy(host.data() + o_off, t->off.data(), t->off.size() * 4);
+    std::memcpy(host.data() + o_blk, t->blocks.data(), t->blocks.size() * 4);
+    hipError_t e = hipMalloc(&t->mem, total);
+    if (e == hipSuccess) e = hipMemcpy(t->mem, host.data(), total, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        free_wg(t);
+        return fail(e == hipErrorOutOfMemory ? HM_ENOMEM : HM_EDEVICE, "block kernel tables: %s",
+                    hipGetErrorString(e));
+    }
+    unsigned char *m = (unsigned char *)t->mem;
+    t->d_rankL = (uint16_t *)m;
+    t->d_unrankL = (uint16_t *)(m + o_un);
+    t->d_off = (uint32_t *)(m + o_off);
+    t->d_blocks = (uint32_t *)(m + o_blk);
+    b->wg_tables = t;
+    b->wg_tables_free = free_wg;
+    *out = t;
+    return HM_OK;
+}
+
+template <typename T>
+static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t, WgBonds *d) {
+    const int K = t->K;
+    int nH;
+    uint32_t vmask;
+    int nL, nS;
+    wg_counts(c, K, &nL, &nH, &nS, &d->nslot, &vmask);
+    std::vector<uint32_t> vbit;
+    for (int v = 0; v < 32; ++v)
+        if (vmask >> v & 1) vbit.push_back(1u << v);
+    // runs of low-word bonds, and of the straddling bonds of one low site, in
+    // eights, fours, twos and ones
+    std::vector<const BondDev *> lo, st;
+    for (const BondDev &bd : c->host)
+        if (bd.u < K) (bd.v < K ? lo : st).push_back(&bd);
+    auto piece = [](size_t n) { return n >= 8 ? 8 : n >= 4 ? 4 : n >= 2 ? 2 : 1; };
+    std::vector<WgOp<T>> low, strad;
+    for (size_t i = 0; i < lo.size();) {
+        WgOp<T> op{};
+        op.n = piece(lo.size() - i);
+        for (int q = 0; q < op.n; ++q, ++i) {
+            op.m[q] = 1u << lo[i]->u | 1u << lo[i]->v;
+            op.c[q] = (T)lo[i]->mJ2;
+        }
+        low.push_back(op);
+    }
+    for (size_t i = 0; i < st.size();) {
+        size_t n = 1;
+        while (i + n < st.size() && st[i + n]->u == st[i]->u) ++n;
+        WgOp<T> op{};
+        op.n = piece(n);
+        op.m[0] = 1u << st[i]->u;
+        for (int q = 0; q < op.n; ++q, ++i) {
+            const int slot = __builtin_popcount(vmask & ((1u << (st[i]->v - K)) - 1u));
+            op.slot[q / 4] |= (uint32_t)slot << (8 * (q % 4));
+            op.c[q] = (T)st[i]->mJ2;
+        }
+        strad.push_back(op);
+    }
+    d->nlow = (int)low.size();
+    d->nstrad = (int)strad.size();
+    d->mh = (nH + kWgPiece - 1) / kWgPiece * kWgPiece;
+    d->hw = (4 + 2 * d->nslot + 3 + 8) / 4 * 4;       // slot reads go in fours
+    std::vector<int> cls(2 * (K + 1));
+    for (int a = 0; a <= K; ++a) {
+        cls[2 * a] = t->start[a];
+        cls[2 * a + 1] = t->size[a];
+    }
+    auto al = [](size_t v) { return (v + 255) / 256 * 256; };
+    size_t total = 0;
+    auto add = [&](size_t bytes) {
+        const size_t at = total;
+        total += al(bytes + 64);
+        return at;
+    };
+    const size_t nblk = (size_t)t->n_blocks;
+    const size_t o_low = add(low.size() * sizeof(WgOp<T>)),
+                 o_str = add(strad.size() * sizeof(WgOp<T>)), o_vb = add(vbit.size() * 4),
+                 o_cls = add(cls.size() * 4), hostlen = total;
+    const size_t o_hdr = add(nblk * d->hw * 4), o_hoff = add(nblk * d->mh * 4),
+                 o_hcf = add(nblk * d->mh * sizeof(T));
+    std::vector<unsigned char> host(hostlen);
+    auto put = [&](size_t at, const void *p, size_t bytes) {
+        if (bytes) std::memcpy(host.data() + at, p, bytes);
+    };
+    put(o_low, low.data(), low.size() * sizeof(WgOp<T>));
+    put(o_str, strad.data(), strad.size() * sizeof(WgOp<T>));
+    put(o_vb, vbit.data(), vbit.size() * 4);
+    put(o_cls, cls.data(), cls.size() * 4);
+    hipError_t e = hipMalloc(&d->mem, total);
+    if (e == hipSuccess) e = hipMemcpy(d->mem, host.data(), hostlen, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return e;
+    unsigned char *m = (unsigned char *)d->mem;
+    d->low = m + o_low;
+    d->strad = m + o_str;
+    d->vbit = (uint32_t *)(m + o_vb);
+    d->hdr = (uint32_t *)(m + o_hdr);
+    d->hoff = (uint32_t *)(m + o_hoff);
+    d->hcf = m + o_hcf;
+    const int grid = (int)std::min<int64_t>((t->n_blocks + kBlock - 1) / kBlock, kMaxGrid);
+    hipLaunchKernelGGL(wg_rows<T>, dim3(grid), dim3(kBlock), 0, nullptr, t->d_blocks, t->n_blocks,
+                       t->d_off, K, b->A, (const int *)(m + o_cls), c->dev, c->nb, d->vbit,
+                       d->nslot, d->mh, d->hw, d->hdr, d->hoff, (T *)d->hcf);
+    e = hipGetLastError();
+    // other streams may use the tables from now on
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    return e;
+}
+
+static int wg_get(Basis *b, const Couplings *c, int dtype, hipStream_t st, WgTables **tout,
+                  const WgBonds **bout) {
+    std::lock_guard<std::mutex> lock(b->mu);
+    HM_TRY(device_prepare(b));
+    auto *cc = const_cast<Couplings *>(c);
+    if (!cc->wg) {
+        cc->wg = new WgBondSet;
+        cc->wg_free = free_wg_bonds;
+    }
+    auto *set = (WgBondSet *)cc->wg;
+    const int k = dtype == HM_F64 ? 0 : 1;
+    if (!set->have[k]) {
+        // nothing may be allocated while the stream is capturing
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (st && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+            cap != hipStreamCaptureStatusNone)
+            return HM_ENOMEM;
+    }
+    WgTables *t = nullptr;
+    HM_TRY(wg_prepare(b, &t));
+    if (!set->have[k]) {
+        WgBonds d;
+        const hipError_t e = dtype == HM_F64 ? wg_build<double>(b, c, t, &d)
+                                             : wg_build<float>(b, c, t, &d);
+        if (e != hipSuccess) {
+            if (d.mem) (void)hipFree(d.mem);
+            return fail(e == hipErrorOutOfMemory ? HM_ENOMEM : HM_EDEVICE, "block kernel bonds: %s",
+                        hipGetErrorString(e));
+        }
+        set->by_type[k] = d;
+        set->have[k] = true;
+    }
+    *tout = t;
+    *bout = &set->by_type[k];
+    return HM_OK;
+}
+
+int wg_prepare_tables(Basis *b, const Couplings *c, int dtype) {
+    WgTables *t = nullptr;
+    const WgBonds *d = nullptr;
+    return wg_get(b, c, dtype, nullptr, &t, &d);
+}
+
+template <typename T>
+static void launch_wg_t(const Basis *b, const Couplings *c, const WgTables *t, const WgBonds *d,
+                        const HxPass &p, hipStream_t st) {
+    WgArgs<T> g{};
+    g.rankL = t->d_rankL;
+    g.unrankL = t->d_unrankL;
+    g.low = (const WgOp<T> *)d->low;
+    g.strad = (const WgOp<T> *)d->strad;
+    g.hdr = d->hdr;
+    g.hoff = d->hoff;
+    g.hcf = (const T *)d->hcf;
+    g.n_blocks = (uint32_t)t->n_blocks;
+    g.run = 1;
+    g.K = t->K;
+    g.nlow = d->nlow;
+    g.nstrad = d->nstrad;
+    g.nslot = d->nslot;
+    g.mh = d->mh;
+    g.hw = d->hw;
+    g.stride = t->smax;
+    g.shift = c->diag_shift;
+    const int grid = hx_wg_grid(b);
+    const size_t lds = wg_lds(t->K, d->nslot, sizeof(T));
+    const T *x = (const T *)p.x, *pr = (const T *)p.p;
+    T *y = (T *)p.y, *store = (T *)p.store;
+#define HM_LAUNCH(D, S)                                                                      \
+    hipLaunchKernelGGL((hx_half_wg_kernel<T, D, S>), dim3(grid), dim3(t->threads), lds, st, g, \
+                       x, y, pr, p.step, p.partial, store)
+    const bool dot = p.partial != nullptr, sto = store != nullptr;
+    if (!dot && !sto) HM_LAUNCH(false, false);
+    else if (dot && !sto) HM_LAUNCH(true, false);
+    else if (!dot && sto) HM_LAUNCH(false, true);
+    else HM_LAUNCH(true, true);
+#undef HM_LAUNCH
+}
+
+int launch_hx_wg(const Basis *cb, const Couplings *c, int dtype, const HxPass &p, hipStream_t st) {
+    Basis *b = const_cast<Basis *>(cb);
+    WgTables *t = nullptr;
+    const WgBonds *d = nullptr;
+    const int rc = wg_get(b, c, dtype, st, &t, &d);
+    if (rc == HM_ENOMEM && !p.partial) {
+        // no memory for the tables, or a product captured before its first use
+        clear_error();
+        (void)hipGetLastError();
+        return launch_hx_generic(b, c, dtype, p, st);
+    }
+    HM_TRY(rc);
+    if (dtype == HM_F64) launch_wg_t<double>(b, c, t, d, p, st);
+    else launch_wg_t<float>(b, c, t, d, p, st);
+    HM_HIP(hipGetLastError());
+    return HM_OK;
+}
+
+}  // namespace hm

@@ -43,29 +43,40 @@ int launch_hx_digit(const Basis *b, const Couplings *c, int dtype, const HxPass 
 int hx_digit_grid(const Basis *b);
 int digit_prepare_tables(Basis *b, const Couplings *c, int dtype);
 bool digit_fits(const Basis *b, const Couplings *c);
+int launch_hx_wg(const Basis *b, const Couplings *c, int dtype, const HxPass &p, hipStream_t st);
+int hx_wg_grid(const Basis *b);
+int wg_prepare_tables(Basis *b, const Couplings *c, int dtype);
+bool wg_fits(const Basis *b, const Couplings *c, int dtype);
 
 // 0 = automatic (the block kernel of the spin, where it applies to the basis
 // and its tables fit the budget, else the generic digit kernel), 1 = generic,
-// 2 = spin-1/2 block kernel (-1 if it does not apply); kKernelDigit, the block
-// kernel for s >= 1, is chosen by 0 only.
-constexpr int kKernelDigit = 5;
+// 2 = spin-1/2 block kernel (-1 if it does not apply).  Chosen by 0 only:
+// kKernelDigit, the block kernel for s >= 1, and kKernelWg, the spin-1/2
+// kernel with one workgroup per block.
+constexpr int kKernelDigit = 5, kKernelWg = 6;
 
-int choose_kernel(const Basis *b, const Couplings *c, int requested) {
+int choose_kernel(const Basis *b, const Couplings *c, int requested, int dtype) {
     if (requested == 1) return 1;
     if (requested == 0 && b->two_s >= 2) return digit_fits(b, c) ? kKernelDigit : 1;
+    if (requested == 0 && wg_fits(b, c, dtype)) return kKernelWg;
     const bool ok = c ? half_fits(b, c) : half_supported(b);
     if (requested == 2) return ok ? 2 : -1;
     return ok ? 2 : 1;
 }
 
 int hx_partial_count(const Basis *b, int kernel) {
-    return kernel == 2 ? hx_half_grid(b) : kernel == kKernelDigit ? hx_digit_grid(b)
-                                                                  : hx_generic_grid(b);
+    switch (kernel) {
+        case 2: return hx_half_grid(b);
+        case kKernelDigit: return hx_digit_grid(b);
+        case kKernelWg: return hx_wg_grid(b);
+        default: return hx_generic_grid(b);
+    }
 }
 
 int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel) {
     if (kernel == 2) return half_prepare_tables(b, c);
     if (kernel == kKernelDigit) return digit_prepare_tables(b, c, dtype);
+    if (kernel == kKernelWg) return wg_prepare_tables(b, c, dtype);
     return HM_OK;
 }
 
@@ -73,6 +84,7 @@ int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel, const H
               hipStream_t st) {
     if (kernel == 2) return launch_hx_half(b, c, dtype, p, st);
     if (kernel == kKernelDigit) return launch_hx_digit(b, c, dtype, p, st);
+    if (kernel == kKernelWg) return launch_hx_wg(b, c, dtype, p, st);
     return launch_hx_generic(b, c, dtype, p, st);
 }
 
@@ -251,13 +263,6 @@ __global__ __launch_bounds__(kBlock) void pass_b(T *__restrict__ w, const T *__r
                                                  double *__restrict__ psi) {
     if (sigma[k] == 0.0) return;
     __shared__ double red[17];
-    const double al = apart ? fold_sum(apart, n_hx, red) : alpha[k];
-    if (apart && blockIdx.x == 0 && threadIdx.x == 0) alpha[k] = al;
-    const double sg = sigma[k], a = al * sg;
-    const double cp = PSI ? coef[k] * sg : 0.0;
-    auto add_psi = [&](int64_t i, T ri) {
-        if constexpr (PSI) psi[i] = (k > 0 ? psi[i] : 0.0) + cp * (double)ri;
-    };
     int64_t first, last;
     block_rows<int64_t>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, n, first, last);
     // 16-byte vector loads and stores over the aligned middle of the range
@@ -266,19 +271,28 @@ __global__ __launch_bounds__(kBlock) void pass_b(T *__restrict__ w, const T *__r
     using Vec = typename VecOf<T>::type;
     const int64_t m0 = std::min(last, (first + V - 1) / V * V);
     const int64_t m1 = std::max(m0, last / V * V);
+    Vec *wv = reinterpret_cast<Vec *>(w);
+    const Vec *rv = reinterpret_cast<const Vec *>(r);
+    // the first loads are on their way while alpha_k is summed
+    int64_t j = m0 / V + threadIdx.x;
+    const bool have = j < m1 / V;
+    Vec w0, r0;
+    if (have) {
+        w0 = wv[j];
+        r0 = rv[j];
+    }
+    const double al = apart ? fold_sum(apart, n_hx, red) : alpha[k];
+    if (apart && blockIdx.x == 0 && threadIdx.x == 0) alpha[k] = al;
+    const double sg = sigma[k], a = al * sg;
+    const double cp = PSI ? coef[k] * sg : 0.0;
     double s = 0.0;
-    for (int64_t i = first + threadIdx.x; i < m0; i += blockDim.x) {
+    auto one = [&](int64_t i) {
         const T ri = r[i], wi = (T)((double)w[i] - a * (double)ri);
         w[i] = wi;
         s += (double)wi * (double)wi;
-        add_psi(i, ri);
-    }
-    Vec *wv = reinterpret_cast<Vec *>(w);
-    const Vec *rv = reinterpret_cast<const Vec *>(r);
-#pragma unroll 2
-    for (int64_t j = m0 / V + threadIdx.x; j < m1 / V; j += blockDim.x) {
-        Vec wj = wv[j];
-        const Vec rj = rv[j];
+        if constexpr (PSI) psi[i] = (k > 0 ? psi[i] : 0.0) + cp * (double)ri;
+    };
+    auto vec = [&](int64_t jj, Vec wj, const Vec rj) {
         T *we = reinterpret_cast<T *>(&wj);
         const T *re = reinterpret_cast<const T *>(&rj);
 #pragma unroll
@@ -286,16 +300,19 @@ __global__ __launch_bounds__(kBlock) void pass_b(T *__restrict__ w, const T *__r
             we[e] = (T)((double)we[e] - a * (double)re[e]);
             s += (double)we[e] * (double)we[e];
         }
-        wv[j] = wj;
+        wv[jj] = wj;
+        if constexpr (PSI)
 #pragma unroll
-        for (int e = 0; e < V; ++e) add_psi(j * V + e, re[e]);
-    }
-    for (int64_t i = m1 + threadIdx.x; i < last; i += blockDim.x) {
-        const T ri = r[i], wi = (T)((double)w[i] - a * (double)ri);
-        w[i] = wi;
-        s += (double)wi * (double)wi;
-        add_psi(i, ri);
-    }
+            for (int e = 0; e < V; ++e) {
+                const int64_t i = jj * V + e;
+                psi[i] = (k > 0 ? psi[i] : 0.0) + cp * (double)re[e];
+            }
+    };
+    for (int64_t i = first + threadIdx.x; i < m0; i += blockDim.x) one(i);
+    if (have) vec(j, w0, r0);
+#pragma unroll 2
+    for (j += blockDim.x; j < m1 / V; j += blockDim.x) vec(j, wv[j], rv[j]);
+    for (int64_t i = m1 + threadIdx.x; i < last; i += blockDim.x) one(i);
     s = block_sum(s, red);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
@@ -903,7 +920,7 @@ static int check_opts(const Basis *b, const hm_lanczos_opts *o) {
     if (o->kernel == 3 && b->dim > kSmallMaxDim)
         return fail(HM_ERANGE, "the one-workgroup run takes at most %lld rows",
                     (long long)kSmallMaxDim);
-    if (o->kernel != 3 && choose_kernel(b, nullptr, o->kernel) < 0)
+    if (o->kernel != 3 && choose_kernel(b, nullptr, o->kernel, HM_F64) < 0)
         return fail(HM_EINVAL, "spin-1/2 block kernel not applicable to this basis");
     return HM_OK;
 }
@@ -921,11 +938,12 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     const Couplings *c = cref.get();
     const bool small = o->kernel == 3 || (o->kernel == 0 && !g_timing && !o->full_reorth &&
                                           b->dim * (int64_t)std::max(c->nb, 1) <= kSmallAutoWork);
-    int kernel = small ? 1 : choose_kernel(b, c, o->kernel);
+    const int dtype = o->precision == HM_PREC_F64 ? HM_F64 : HM_F32;
+    int kernel = small ? 1 : choose_kernel(b, c, o->kernel, dtype);
     if (kernel < 0) return fail(HM_ERANGE, "block kernel tables too large for these couplings");
-    const int prc = prepare_kernel(b, c, o->precision == HM_PREC_F64 ? HM_F64 : HM_F32, kernel);
-    if (prc == HM_ENOMEM && kernel == kKernelDigit) {
-        kernel = 1;                   // the same sums without tables
+    const int prc = prepare_kernel(b, c, dtype, kernel);
+    if (prc == HM_ENOMEM && kernel != 2) {
+        kernel = 1;                   // the kernel without tables
         clear_error();
         (void)hipGetLastError();
     } else {

@@ -55,7 +55,11 @@ def test_rows_match_oracle(N, two_s, A, kind):
     ref = oracle.Subspace(N, two_s, A).apply(J, x)
     s = _scale(J, two_s)
     for dt, tol in ((torch.float64, 1e-13), (torch.float32, 2e-6)):
-        y = b.apply(J, torch.tensor(x, device="cuda").to(dt)).double().cpu().numpy()
+        xd = torch.tensor(x, device="cuda").to(dt)
+        y = b.apply(J, xd)
+        if dt == torch.float32:                   # the generic kernel's roundings
+            assert torch.equal(y, b.apply(J, xd, kernel=1))
+        y = y.double().cpu().numpy()
         assert np.abs(y - ref).max() <= tol * s
 
 
@@ -78,6 +82,8 @@ def test_long_blocks_match_oracle_and_generic_kernel(N, two_s, A, kind):
         y = b.apply(J, xd)
         assert np.abs(y.double().cpu().numpy()[rows] - ref).max() <= tol * s
         assert float((y - b.apply(J, xd, kernel=1)).abs().max()) <= tol * s
+        if dt == torch.float32:                   # the generic kernel's roundings
+            assert torch.equal(y, b.apply(J, xd, kernel=1))
 
 
 def test_64_bit_indices_match_generic_kernel():
