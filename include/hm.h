@@ -217,9 +217,9 @@ typedef struct hm_lanczos_opts {
                              start vector may change between calls (same
                              kernels, bitwise equal results to direct
                              launches)                                    */
-    int32_t kernel;       /* 0: automatic choice (the one-workgroup run
-                             without full_reorth when dim x bonds <=
-                             16384, else the H x kernel that suits
+    int32_t kernel;       /* 0: automatic choice (one-workgroup launches
+                             for up to 3072 rows while one compute unit is
+                             faster, else the H x kernel that suits
                              the basis); 1: generic digit kernel; 2:
                              spin-1/2 block kernel (if the basis is spin
                              1/2); 3: one-workgroup run (every step in one

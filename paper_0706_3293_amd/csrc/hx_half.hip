@@ -665,6 +665,7 @@ static int default_low_bits(int N) {
 }
 
 static int low_bits_of(const Basis *b) { return b->half_K > 0 ? b->half_K : default_low_bits(b->N); }
+int half_low_bits(const Basis *b) { return low_bits_of(b); }
 static int block_of(const Basis *b) { return b->half_block > 0 ? b->half_block : 256; }
 static int rows_of(const Basis *b) {
     if (b->half_R > 0) return b->half_R;

@@ -38,6 +38,7 @@ int hx_half_grid(const Basis *b);
 bool half_supported(const Basis *b);
 int half_prepare_tables(Basis *b, const Couplings *c);
 bool half_fits(const Basis *b, const Couplings *c);
+int half_low_bits(const Basis *b);
 int launch_hx_digit(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
                     hipStream_t st);
 int hx_digit_grid(const Basis *b);
@@ -88,15 +89,30 @@ int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel, const H
     return launch_hx_generic(b, c, dtype, p, st);
 }
 
-// One-workgroup run (below): automatic choice without reorthogonalization up
-// to kSmallAutoWork (rows x bonds) of row work per step, accepted when asked
-// for explicitly up to kSmallMaxDim rows.
-constexpr int64_t kSmallAutoWork = 16384;
+// One-workgroup runs (below).  With tables up to kTableRows rows; without, when
+// asked for explicitly, up to kSmallMaxDim rows.
+constexpr int64_t kTableRows = 3072;
 constexpr int64_t kSmallMaxDim = 1 << 20;
+constexpr int kTableCoefs = 1024;    // most reorthogonalization coefficients (LDS)
+// Most bytes of matrix elements, and of stored vectors in a step, that one
+// compute unit reads faster than a step's launches take.  One workgroup against
+// several kernels, us a step: 2,024 rows, 97,152 row-bonds FP64 10.1 / 18.7;
+// 1,716 rows, 133,848 row-bonds FP64 19.4 / 19.1, FP32 12.6 / 20.3; 60
+// reorthogonalized steps at 924 rows FP64 20 / 31, at 1,716 rows FP64 33 / 34,
+// FP32 17 / 38, at 2,024 rows FP64 41 / 38.
+constexpr int64_t kTableBytes = 768 * 1024;
+
+// Most ladder moves a row can have: every move lowers a site that is not at 0
+// and raises one that is not at 2s.
+static int64_t max_moves(const Basis *b) {
+    const int64_t down = std::min<int64_t>(b->A, b->N);
+    const int64_t up = std::min<int64_t>((int64_t)b->N * b->two_s - b->A, b->N);
+    return (std::min(down * up, (int64_t)b->N * (b->N - 1)) + 3) / 4 * 4;
+}
 
 struct Layout {
-    size_t lz, alpha, beta, sigma, cprev, scale, coef, hcoef, partial, bpart, dots, r0, r1, r2, V, states,
-        total;
+    size_t lz, alpha, beta, sigma, cprev, scale, coef, hcoef, partial, bpart, dots, r0, r1, r2, V,
+        states, mtgt, mcf, total;
     int grid_vec, grid_b, nparts;
 };
 
@@ -157,6 +173,11 @@ static Layout layout(const Basis *b, int steps, int prec, int reorth) {
     // decoded states of the one-workgroup run (any basis it may take)
     L.states = off;
     if (b->dim <= kSmallMaxDim) off = align256(off + sizeof(uint64_t) * (size_t)b->dim);
+    // move tables of the one-workgroup run
+    if (b->dim <= kTableRows) {
+        L.mtgt = off; off = align256(off + sizeof(uint16_t) * (size_t)(b->dim * max_moves(b)));
+        L.mcf = off; off = align256(off + es * (size_t)(b->dim * max_moves(b)));
+    }
     L.total = off;
     return L;
 }
@@ -432,22 +453,22 @@ __global__ __launch_bounds__(kBlock) void scale_psi(double *__restrict__ psi, in
 // ---------------------------------------------------------------------------
 // Small problems: the whole run in one workgroup.
 //
-// For a few thousand rows a step is little work, but the multi-kernel step
-// costs two launches (ten with full reorthogonalization).  Here one
-// workgroup of 1024 threads runs every step in a single launch: thread t owns
-// rows t, t + 1024, ... (the generic row of hx_row.h, on states decoded once
-// at the start and kept in the workspace), reductions are fixed
-// trees (block_sum, wave_sum), and workgroup barriers order the passes, so a
-// run is reproducible and the recompute pass repeats it bit for bit.  The
-// recurrence is the same (Paige's ordering, the same breakdown test); v_k is
-// stored normalized.  One compute unit does all the row work, so the run pays
-// off only while that work stays below the launch costs it saves.  Measured
-// against directly launched steps, without reorthogonalization: faster at 70
-// rows x 8 bonds (0.46 vs 0.65 ms, 60 steps), 924 x 12 (1.4 vs 1.7 ms, 120
-// steps) and 1107 x 7 (1.2 vs 1.7 ms, 100 steps); slower at 3432 x 14 (5.2
-// vs 2.7 ms, 150 steps) and 2024 x 48 (5.4 ms, 150 steps).  With
-// reorthogonalization, whose k-term sums run on this one workgroup, it is
-// slower already at 924 rows (7.7 vs 5.3 ms).
+// For a few thousand rows a step is little work, but its launches cost 5 us
+// each (two without, five with full reorthogonalization).  Here one workgroup
+// of 1024 threads runs every step in a single launch: thread t owns rows t,
+// t + 1024, ..., reductions are fixed trees, and workgroup barriers order the
+// passes, so a run is reproducible and the recompute pass repeats it bit for
+// bit.  The recurrence is the same (Paige's ordering, the same breakdown
+// test).  One compute unit does all the row work.
+//
+// lanczos_table_kernel (up to kTableRows rows) finds every row's moves and
+// matrix elements once at the start of the run and keeps them in the
+// workspace, v_k and w in LDS and the thread's rows in registers: at 924 rows
+// and 12 bonds a step is 5.6 us in FP64 (two launches: 13.3) and over 20
+// reorthogonalized steps 13 us (five launches: 28).  What bounds it is one
+// compute unit's reads of the move tables and of the stored vectors from L2.
+// lanczos_small_kernel (v_k stored normalized) runs larger subspaces when asked
+// for explicitly.
 // ---------------------------------------------------------------------------
 constexpr int kSmallBlock = 1024;
 
@@ -594,6 +615,259 @@ __global__ __launch_bounds__(kSmallBlock) void lanczos_small_kernel(const SmallA
     }
 }
 
+template <typename T>
+struct TableArgs {
+    const uint32_t *prefix;
+    const double *ladder;
+    const BondDev *bonds;
+    int nb, N, A, two_s, steps, reorth, n, halfK;   // halfK > 0: the arithmetic of hx_half.hip
+    double tol, shift;
+    const double *v0;
+    T *V;                    // [steps][n] normalized v_j (full reorthogonalization)
+    T *r, *rprev;            // r_k and r_{k-1} for the kernels that go on, null: none do
+    uint16_t *mtgt;          // [move][n] target rows
+    T *mcf;                  // [move][n] matrix elements
+    double *alpha, *beta, *sigma, *cprev, *scale;
+    LzDev *lz;
+    const double *coef;      // recompute pass: c_k, else nullptr
+    double *psi;
+};
+
+// Sum over the workgroup in every thread, one barrier; the caller alternates
+// between two `red`, so that a fast wave cannot overwrite what a slow one reads.
+__device__ __forceinline__ double all_sum(double v, double *red /* 16 */) {
+    v = wave_sum(v);
+    const int lane = threadIdx.x & 63;
+    if (lane == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = red[lane & 15];
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+template <typename T, int B>
+__global__ __launch_bounds__(kSmallBlock) void lanczos_table_kernel(const TableArgs<T> a) {
+    constexpr int J = (int)(kTableRows / kSmallBlock);   // rows of a thread
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double red[2][16];
+    __shared__ double hs[kTableCoefs];
+    const int n = a.n, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int plen = a.N * (a.A + 1) * (a.two_s + 1);
+    uint32_t *P = reinterpret_cast<uint32_t *>(smem);
+    T *F = reinterpret_cast<T *>(smem + ((plen * sizeof(uint32_t) + 15) / 16) * 16);
+    for (int t = tid; t < plen; t += kSmallBlock) P[t] = a.prefix[t];
+    for (int t = tid; t < a.two_s + 2; t += kSmallBlock) F[t] = (T)a.ladder[t];
+    __syncthreads();
+    const Prefix<uint32_t> pv{P, a.A + 1, a.two_s + 1};
+    // the rows' moves in the order and with the roundings of the H x kernel
+    // that the steps of larger subspaces run: row_hx's, or with halfK the
+    // spin-1/2 block kernel's (low word, high word, straddling)
+    T diag[J];
+    int cnt[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        diag[j] = 0;
+        cnt[j] = 0;
+        const int i = tid + j * kSmallBlock;
+        if (i >= n) continue;
+        const uint64_t st = unrank_state<uint32_t, B>((uint32_t)i, pv, a.N, a.A, a.two_s);
+        auto put = [&](uint32_t to, T c) {
+            a.mtgt[(size_t)cnt[j] * n + i] = (uint16_t)to;
+            a.mcf[(size_t)cnt[j] * n + i] = c;
+            ++cnt[j];
+        };
+        for (int pass = 0; pass < (a.halfK ? 3 : 1); ++pass)
+            for (int b = 0; b < a.nb; ++b) {
+                const int u = a.bonds[b].u, v = a.bonds[b].v;
+                if (a.halfK && pass != (v < a.halfK ? 0 : u >= a.halfK ? 1 : 2)) continue;
+                const T mJ4 = (T)a.bonds[b].mJ4, mJ2 = (T)a.bonds[b].mJ2;
+                const int au = digit_at<B>(st, u), av = digit_at<B>(st, v);
+                diag[j] += mJ4 * (T)((a.two_s - 2 * au) * (a.two_s - 2 * av));
+                if (au >= 1 && av < a.two_s)
+                    put((uint32_t)i + move_delta<uint32_t, B>(st, u, v, -1, pv),
+                        mJ2 * F[au] * F[av + 1]);
+                if (av >= 1 && au < a.two_s)
+                    put((uint32_t)i + move_delta<uint32_t, B>(st, u, v, +1, pv),
+                        mJ2 * F[av] * F[au + 1]);
+            }
+        while (cnt[j] % 4) put((uint32_t)i, (T)0);   // moves are read in fours
+        if (a.halfK) diag[j] = (T)a.shift;
+    }
+    __syncthreads();
+    T *vk = reinterpret_cast<T *>(smem), *ws = vk + n;   // over the prefix table
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int i = tid + j * kSmallBlock;
+        if (i < n) s += a.v0[i] * a.v0[i];
+    }
+    s = all_sum(s, red[0]);
+    if (tid == 0) {
+        a.lz->tol = a.tol;
+        a.lz->norm0 = sqrt(s);
+        a.lz->bad_start = !(s > 0.0);
+        a.lz->stopped = a.lz->bad_start ? -1 : 0;
+        a.lz->psi_norm = 0.0;
+        a.sigma[0] = s > 0.0 ? 1.0 : 0.0;
+        a.sigma[a.steps] = 0.0;
+    }
+    if (!(s > 0.0)) return;
+    const double inv0 = 1.0 / sqrt(s);
+    T vp[J], w[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        vp[j] = w[j] = 0;
+        const int i = tid + j * kSmallBlock;
+        if (i >= n) continue;
+        vk[i] = (T)(a.v0[i] * inv0);
+    }
+    __syncthreads();
+    double sigma = 1.0, cprev = 0.0, scale = 0.0;
+    int stopped = 0;
+    for (int k = 0; k < a.steps; ++k) {
+        // w = sigma_k H r_k - cprev_k r_{k-1};  alpha_k = <w, v_k>, v_k = sigma_k r_k
+        double dot = 0.0;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int i = tid + j * kSmallBlock;
+            if (i >= n) continue;
+            const T xi = vk[i];
+            T off = 0;
+            for (int t = 0; t < cnt[j]; t += 4) {
+                uint32_t to[4];
+                T c[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    to[q] = a.mtgt[(size_t)(t + q) * n + i];
+                    c[q] = a.mcf[(size_t)(t + q) * n + i];
+                }
+                if (a.halfK) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) off += c[q] * (vk[to[q]] - xi);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) off += c[q] * vk[to[q]];
+                }
+            }
+            const T hv = diag[j] * xi + off;
+            double wi = sigma * (double)hv;
+            if (k > 0) wi -= cprev * (double)vp[j];
+            w[j] = (T)wi;
+            dot += (double)w[j] * (sigma * (double)xi);
+            if (a.reorth) a.V[(size_t)k * n + i] = (T)(sigma * (double)xi);
+            if (a.psi)
+                a.psi[i] = (k > 0 ? a.psi[i] : 0.0) + a.coef[k] * sigma * (double)xi;
+        }
+        const double alpha = all_sum(dot, red[0]), as = alpha * sigma;
+        double ss = 0.0;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int i = tid + j * kSmallBlock;
+            if (i >= n) continue;
+            w[j] = (T)((double)w[j] - as * (double)vk[i]);
+            ss += (double)w[j] * (double)w[j];
+            if (a.reorth) ws[i] = w[j];
+        }
+        if (a.reorth) {
+            for (int rep = 0; rep < 2; ++rep) {
+                __syncthreads();
+                // h_c = <V_c, w>: a wave per column, 8 rows per lane in flight
+                for (int c = wid; c <= k; c += kSmallBlock / 64) {
+                    const T *__restrict__ Vc = a.V + (size_t)c * n;
+                    double d = 0.0;
+                    int i = lane;
+                    for (; i + 7 * 64 < n; i += 8 * 64) {
+                        T v[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) v[q] = Vc[i + 64 * q];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) d += (double)v[q] * (double)ws[i + 64 * q];
+                    }
+                    for (; i < n; i += 64) d += (double)Vc[i] * (double)ws[i];
+                    d = wave_sum(d);
+                    if (lane == 0) hs[c] = d;
+                }
+                __syncthreads();
+                ss = 0.0;
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const int i = tid + j * kSmallBlock;
+                    if (i >= n) continue;
+                    double acc = (double)w[j];
+                    const T *__restrict__ Vi = a.V + i;
+                    int c = 0;
+                    for (; c + 8 <= k + 1; c += 8) {
+                        T v[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) v[q] = Vi[(size_t)(c + q) * n];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) acc -= hs[c + q] * (double)v[q];
+                    }
+                    for (; c <= k; ++c) acc -= hs[c] * (double)Vi[(size_t)c * n];
+                    w[j] = (T)acc;
+                    ws[i] = w[j];
+                    ss += (double)w[j] * (double)w[j];
+                }
+            }
+        }
+        const double beta = sqrt(all_sum(ss, red[1]));
+        scale = fmax(scale, fmax(fabs(alpha), beta));
+        if (tid == 0) {
+            a.alpha[k] = alpha;
+            a.beta[k] = beta;
+        }
+        if (!(beta > a.tol * scale)) {
+            stopped = k + 1;
+            if (tid == 0) a.sigma[k + 1] = 0.0;
+            break;
+        }
+        // every wave has read r_k (the barrier of the sum above)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int i = tid + j * kSmallBlock;
+            if (i >= n) continue;
+            vp[j] = vk[i];
+            vk[i] = w[j];
+        }
+        cprev = beta * sigma;
+        sigma = 1.0 / beta;
+        if (tid == 0) a.sigma[k + 1] = sigma;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        a.lz->stopped = stopped;
+        a.cprev[a.steps] = cprev;
+        a.scale[a.steps] = scale;
+    }
+    if (a.r) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int i = tid + j * kSmallBlock;
+            if (i >= n) continue;
+            a.r[i] = vk[i];
+            a.rprev[i] = vp[j];
+        }
+        return;
+    }
+    if (a.psi) {
+        double q = 0.0;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int i = tid + j * kSmallBlock;
+            if (i < n) q += a.psi[i] * a.psi[i];
+        }
+        const double nrm = sqrt(all_sum(q, red[0]));
+        if (tid == 0) a.lz->psi_norm = nrm;
+        if (nrm > 0.0)
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int i = tid + j * kSmallBlock;
+                if (i < n) a.psi[i] /= nrm;
+            }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Host driver
 // ---------------------------------------------------------------------------
@@ -605,6 +879,9 @@ struct Run {
     Basis *b;
     const Couplings *c;
     int steps, prec, reorth, kernel, use_graph, small;
+    int table;                 // steps of lanczos_table_kernel before the step loop
+    int halfK;                 // one-workgroup run: low sites of the block kernel whose
+                               // arithmetic it takes (0: row_hx's)
     double tol;
     Layout L;
     unsigned char *w;
@@ -639,7 +916,7 @@ static int enqueue_steps(Run &R, int k0, int k1, std::vector<hipEvent_t> *ev) {
         p.y = wn;
         p.p = k > 0 ? rprev : nullptr;
         p.step.lz = lz;
-        p.step.bpart = fold_b && k > 0 ? bpart : nullptr;
+        p.step.bpart = fold_b && k > R.table ? bpart : nullptr;
         p.step.nb = Gb;
         p.step.k = k;
         p.step.alpha = alpha;
@@ -767,9 +1044,74 @@ static void launch_small_b(const Run &R) {
                        a);
 }
 
+template <typename T, int B>
+static void launch_table_b(const Run &R, int steps) {
+    const Basis *b = R.b;
+    TableArgs<T> a{};
+    a.prefix = (const uint32_t *)b->d_prefix;
+    a.ladder = b->d_ladder;
+    a.bonds = R.c->dev;
+    a.nb = R.c->nb;
+    a.N = b->N;
+    a.A = b->A;
+    a.two_s = b->two_s;
+    a.steps = steps;
+    a.reorth = R.reorth;
+    a.n = (int)b->dim;
+    a.halfK = R.halfK;
+    a.tol = R.tol;
+    a.shift = R.c->diag_shift;
+    a.v0 = R.v0;
+    a.V = (T *)(R.w + R.L.V);
+    a.mtgt = (uint16_t *)(R.w + R.L.mtgt);
+    a.mcf = (T *)(R.w + R.L.mcf);
+    if (steps < R.steps) {
+        T *buf[3] = {(T *)(R.w + R.L.r0), (T *)(R.w + R.L.r1), (T *)(R.w + R.L.r2)};
+        a.r = buf[steps % 3];
+        a.rprev = buf[(steps + 2) % 3];
+    }
+    a.alpha = (double *)(R.w + R.L.alpha);
+    a.beta = (double *)(R.w + R.L.beta);
+    a.sigma = (double *)(R.w + R.L.sigma);
+    a.cprev = (double *)(R.w + R.L.cprev);
+    a.scale = (double *)(R.w + R.L.scale);
+    a.lz = (LzDev *)(R.w + R.L.lz);
+    a.coef = R.psi ? (const double *)(R.w + R.L.coef) : nullptr;
+    a.psi = R.psi;
+    const size_t pre = ((prefix_bytes(b) + 15) / 16) * 16 + (b->two_s + 2) * sizeof(double);
+    const size_t lds = std::max(pre, 2 * sizeof(T) * (size_t)b->dim);
+    hipLaunchKernelGGL((lanczos_table_kernel<T, B>), dim3(1), dim3(kSmallBlock), lds, R.st, a);
+}
+
+// Bases that lanczos_table_kernel takes: the prefix table, the vectors and the
+// coefficients fit the 64 KB of LDS that a launch has without asking for more.
+static bool table_fits(const Basis *b) {
+    return b->dim <= kTableRows && b->idx32 && prefix_bytes(b) <= 48 * 1024;
+}
+
+// The first `steps` steps of a run.
+template <typename T>
+static int launch_table(const Run &R, int steps) {
+    switch (R.b->bits) {
+        case 1: launch_table_b<T, 1>(R, steps); break;
+        case 2: launch_table_b<T, 2>(R, steps); break;
+        case 3: launch_table_b<T, 3>(R, steps); break;
+        case 4: launch_table_b<T, 4>(R, steps); break;
+        case 5: launch_table_b<T, 5>(R, steps); break;
+        case 6: launch_table_b<T, 6>(R, steps); break;
+        case 7: launch_table_b<T, 7>(R, steps); break;
+        case 8: launch_table_b<T, 8>(R, steps); break;
+        default: return fail(HM_ERANGE, "bits per digit %d unsupported", R.b->bits);
+    }
+    HM_HIP(hipGetLastError());
+    return HM_OK;
+}
+
 template <typename T>
 static int launch_small(const Run &R) {
     HM_TRY(check_lds(R.b));
+    if (table_fits(R.b) && (!R.reorth || R.steps <= kTableCoefs))
+        return launch_table<T>(R, R.steps);
     if (!R.b->idx32) return fail(HM_ERANGE, "the one-workgroup run needs 32-bit prefix tables");
     switch (R.b->bits) {
         case 1: launch_small_b<T, uint32_t, 1>(R); break;
@@ -801,7 +1143,7 @@ static int step_graph(Run &R, hipGraphExec_t *out) {
     const std::vector<uint64_t> key = {R.c->serial, (uint64_t)(uintptr_t)R.w,
                                        (uint64_t)R.steps, (uint64_t)R.prec, (uint64_t)R.reorth,
                                        (uint64_t)R.kernel, (uint64_t)(uintptr_t)R.psi,
-                                       (uint64_t)sizeof(T)};
+                                       (uint64_t)R.table, (uint64_t)sizeof(T)};
     {
         std::lock_guard<std::mutex> lock(b->mu);
         for (auto it = b->graphs.begin(); it != b->graphs.end(); ++it)
@@ -813,7 +1155,7 @@ static int step_graph(Run &R, hipGraphExec_t *out) {
     }
     hipGraph_t graph = nullptr;
     HM_HIP(hipStreamBeginCapture(R.st, hipStreamCaptureModeThreadLocal));
-    const int rc = enqueue_steps<T>(R, 0, R.steps, nullptr);
+    const int rc = enqueue_steps<T>(R, R.table, R.steps, nullptr);
     hipError_t e = hipStreamEndCapture(R.st, &graph);
     if (rc != HM_OK) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -853,10 +1195,14 @@ static int run_lanczos(Run &R, double *alpha_h, double *beta_h, int *steps_done)
         HM_TRY(launch_small<T>(R));
         return collect(R, alpha_h, beta_h, steps_done);
     }
-    hipLaunchKernelGGL(sumsq_kernel<double>, dim3(G), dim3(kBlock), 0, R.st, R.v0, n, partial);
-    hipLaunchKernelGGL(init_write<T>, dim3(G), dim3(kBlock), 0, R.st, R.v0, r0, n, lz, partial, G,
-                       sigma, cprev, (double *)(R.w + R.L.scale), R.tol);
-    HM_HIP(hipGetLastError());
+    if (R.table) {
+        HM_TRY(launch_table<T>(R, R.table));
+    } else {
+        hipLaunchKernelGGL(sumsq_kernel<double>, dim3(G), dim3(kBlock), 0, R.st, R.v0, n, partial);
+        hipLaunchKernelGGL(init_write<T>, dim3(G), dim3(kBlock), 0, R.st, R.v0, r0, n, lz, partial,
+                           G, sigma, cprev, (double *)(R.w + R.L.scale), R.tol);
+        HM_HIP(hipGetLastError());
+    }
 
     const bool timing = g_timing;
     // timing events, destroyed on every return path
@@ -885,7 +1231,7 @@ static int run_lanczos(Run &R, double *alpha_h, double *beta_h, int *steps_done)
         HM_TRY(step_graph<T>(R, &exec));
         HM_HIP(hipGraphLaunch(exec, R.st));
     } else {
-        rc = enqueue_steps<T>(R, 0, R.steps, timing ? &ev : nullptr);
+        rc = enqueue_steps<T>(R, R.table, R.steps, timing ? &ev : nullptr);
         if (rc != HM_OK) return rc;
     }
     if (R.psi) {
@@ -925,6 +1271,17 @@ static int check_opts(const Basis *b, const hm_lanczos_opts *o) {
     return HM_OK;
 }
 
+// Steps that the automatic choice gives to lanczos_table_kernel: a number that
+// does not depend on the length of the run, so that the recompute pass of a run
+// that stopped early takes the same kernels.
+constexpr int64_t kSmallWork = 16384;
+static int table_steps(const Basis *b, int64_t work, const hm_lanczos_opts *o) {
+    const int64_t es = o->precision == HM_PREC_F64 ? 8 : 4;
+    if (!table_fits(b) || work * es > kTableBytes) return 0;
+    if (!o->full_reorth) return INT32_MAX;
+    return (int)std::min<int64_t>(kTableCoefs, kTableBytes / (b->dim * es));
+}
+
 static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t steps,
                       const hm_lanczos_opts *o, void *d_work, size_t work_bytes,
                       const double *coef, double *d_psi, double *alpha, double *beta,
@@ -936,8 +1293,9 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     CouplingsRef cref;
     HM_TRY(get_couplings(b, J, &cref));
     const Couplings *c = cref.get();
-    const bool small = o->kernel == 3 || (o->kernel == 0 && !g_timing && !o->full_reorth &&
-                                          b->dim * (int64_t)std::max(c->nb, 1) <= kSmallAutoWork);
+    const int64_t work = b->dim * (int64_t)std::max(c->nb, 1);
+    const int table = o->kernel == 0 && !g_timing ? table_steps(b, work, o) : 0;
+    const bool small = o->kernel == 3 || table >= steps;
     const int dtype = o->precision == HM_PREC_F64 ? HM_F64 : HM_F32;
     int kernel = small ? 1 : choose_kernel(b, c, o->kernel, dtype);
     if (kernel < 0) return fail(HM_ERANGE, "block kernel tables too large for these couplings");
@@ -951,6 +1309,9 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     }
     Run R{};
     R.small = small ? 1 : 0;
+    R.table = small ? 0 : table;
+    if (table > 0 && (o->full_reorth || work > kSmallWork) && half_supported(b))
+        R.halfK = half_low_bits(b);
     R.b = b;
     R.c = c;
     R.steps = steps;
