@@ -287,7 +287,7 @@ def _extra_spin1_chains_batched(out):
     import torch
 
     from paper_0706_3293_amd import Basis, BatchedProblem, inputs
-    # 64 spin-1 chains x 16 start vectors x 80 steps, one persistent launch,
+    # 64 spin-1 chains x 16 start vectors x 80 steps, one batched run,
     # in the default schedule and in the one the autotuner picks
     from paper_0706_3293_amd import autotune
     inst = inputs.batched_instances(lambda n: Basis(n, two_s=2, two_M=0).dim, count=64)

@@ -368,9 +368,9 @@ int hm_bond_corr_noalloc(hm_basis h, const int32_t *uv, int32_t nb,
 
 /* ---------------------------------------------------------------------------
  * Batched Lanczos: ninst independent problems, each with nvec start vectors,
- * solved together in FP32-mixed precision by one persistent (cooperative)
- * kernel launch that runs all steps; the multi-vector product H X shares one
- * decoding and one encoding per row among the nvec vectors.
+ * solved together in FP32-mixed precision, every pass of a step one launch for
+ * all of them; the multi-vector product H X shares one decoding and one encoding
+ * per row among the nvec vectors.
  *   bases[k]     basis handle of instance k (any mix of N, s, M; states are
  *                packed with the digit width of the largest spin in the
  *                batch, so N_k * bits(s_max) <= 64 for every k);
@@ -382,11 +382,11 @@ int hm_bond_corr_noalloc(hm_basis h, const int32_t *uv, int32_t nb,
  *   E0           host array [ninst][nvec];
  *   steps_done   host array [ninst][nvec].
  * Each (instance, vector) pair runs its own recurrence; a breakdown stops
- * only that pair.  Schedule: the rows are cut into 256-row items and the
- * persistent workgroups take `chunk` consecutive items at a time (1..64, 0 =
- * 4), with `wg_per_cu` workgroups resident per compute unit (1..8, capped by
- * occupancy; 0 = 4).  Every sum has a fixed order for a given schedule, so a
- * run is reproducible; the autotuner picks the schedule per workload.
+ * only that pair.  Schedule: the rows are cut into 256-row items, a workgroup
+ * takes `chunk` consecutive items at a time (1..64; 0 = 1, or 2 above 8192
+ * items), and `wg_per_cu` (1..8) workgroups per compute unit take all of them in
+ * turn (0: one workgroup per chunk).  Every sum has a fixed order for a given
+ * chunk, so a run is reproducible; the autotuner picks the schedule per workload.
  * d_work: device workspace of at least hm_lanczos_batched_workspace bytes.
  * Synchronizes `stream`.  HM_EINVAL: bad arguments or schedule.  HM_ERANGE:
  * an instance with N_k * bits(s_max) > 64, a dimension of 2^32 or more, or a

@@ -6,7 +6,7 @@ include/hm.h); this package is its thin Python binding:
   Basis            subspace H(M), host/device encoding and decoding, H x,
                    Lanczos, ground-state recompute, bond correlations
   GroundStateEnergy  torch.autograd.Function for E0(J) with dE0/dJ = -<s.s>
-  lanczos_batched  many instances and start vectors in one persistent launch
+  lanczos_batched  many instances and start vectors in one run
   magnetization_curve, ftl_thermodynamics
                    E0(M) over all sectors and finite-temperature Lanczos sums
 """

@@ -1,5 +1,5 @@
 """Autotuners for the spin-1/2 block kernel's schedule and the batched
-persistent Lanczos launch.
+Lanczos run.
 
 For a given problem (N, M, couplings, element type) every candidate schedule
 (low bits K, workgroup size, rows per lane, work split) is built on a fresh basis handle
@@ -160,10 +160,9 @@ def tuned_basis(N, J, two_M=0, dtype=torch.float32, **kw):
     return b, sched
 
 
-# --- batched persistent Lanczos -------------------------------------------
+# --- batched Lanczos ------------------------------------------------------
 # (items per chunk, workgroups per compute unit): the first is the default
-BATCH_CANDIDATES = [(4, 4)] + [(c, w) for w in (4, 2, 8, 1) for c in (1, 2, 4, 8, 16)
-                               if (c, w) != (4, 4)]
+BATCH_CANDIDATES = [(0, 0)] + [(c, w) for w in (4, 2, 8, 1) for c in (1, 2, 4, 8, 16)]
 
 
 def _batch_key(bases, nvec, steps):
@@ -173,7 +172,7 @@ def _batch_key(bases, nvec, steps):
 
 
 def tune_batched(bases, Js, V0s, steps, reps=2, cache=DEFAULT_CACHE, verbose=False):
-    """Best (chunk, workgroups per CU) of the batched persistent Lanczos for
+    """Best (chunk, workgroups per CU) of the batched Lanczos for
     this set of instances (their shapes, the number of start vectors and
     steps), timed over whole runs; cached like the block kernel's schedules."""
     import time

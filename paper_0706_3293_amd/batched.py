@@ -1,5 +1,5 @@
 """Batched Lanczos over many (basis, couplings, start vectors) instances in one
-persistent launch (hm_lanczos_batched): argument marshalling only."""
+run (hm_lanczos_batched): argument marshalling only."""
 import ctypes
 from dataclasses import dataclass
 

@@ -142,8 +142,18 @@ int device_prepare(Basis *b) {
     return HM_OK;
 }
 
-// Bonds of J (u < v, J_uv != 0) in row-major upper-triangle order, uploaded
-// once per distinct J.  The handle keeps the kCouplingCacheEntries most
+int list_bonds(const Basis *b, const double *J, BondDev *out) {
+    const int N = b->N;
+    int nb = 0;
+    for (int u = 0; u < N; ++u)
+        for (int v = u + 1; v < N; ++v) {
+            const double x = J[(size_t)u * N + v];
+            if (x != 0.0) out[nb++] = BondDev{u, v, -0.25 * x, -0.5 * x};
+        }
+    return nb;
+}
+
+// Bonds of J, uploaded once per distinct J.  The handle keeps the kCouplingCacheEntries most
 // recently used lists; older ones are dropped (and freed once no running call
 // holds them), so loops over many distinct J keep device memory bounded.
 int get_couplings(Basis *b, const double *J, CouplingsRef *out) {
@@ -162,19 +172,10 @@ int get_couplings(Basis *b, const double *J, CouplingsRef *out) {
     static std::atomic<uint64_t> next_serial{1};
     auto c = std::make_shared<Couplings>();
     c->serial = next_serial.fetch_add(1);
-    for (int u = 0; u < N; ++u)
-        for (int v = u + 1; v < N; ++v) {
-            double x = J[(size_t)u * N + v];
-            if (x == 0.0) continue;
-            BondDev bd;
-            bd.u = u;
-            bd.v = v;
-            bd.mJ4 = -0.25 * x;
-            bd.mJ2 = -0.5 * x;
-            c->host.push_back(bd);
-            c->diag_shift += bd.mJ4;
-        }
-    c->nb = (int)c->host.size();
+    c->host.resize((size_t)N * (N - 1) / 2);
+    c->nb = list_bonds(b, J, c->host.data());
+    c->host.resize(c->nb);
+    for (const BondDev &bd : c->host) c->diag_shift += bd.mJ4;
     if (c->nb > 0) {
         HM_HIP(hipMalloc(&c->dev, c->host.size() * sizeof(BondDev)));
         HM_HIP(hipMemcpy(c->dev, c->host.data(), c->host.size() * sizeof(BondDev),

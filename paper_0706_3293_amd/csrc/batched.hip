@@ -1,24 +1,23 @@
 // Batched Lanczos: many independent problems (basis, couplings) with up to 16
-// start vectors each, all steps in one persistent cooperative launch.
+// start vectors each, every step one set of launches for all of them.
 //
 // Vectors are stored in FP32 as [dim][NV] rows (NV = 1, 2, 4, 8 or 16), so the
 // multi-vector product H X decodes each basis state and encodes each target
 // once (Sec. 3.1, 3.2) and gathers the NV entries of a target row with
 // contiguous 16-byte loads; with 8 or 16 vectors a row is spread over 2 or 4
-// lanes, which share its decoding and bond work.  Dots and norms are FP64.  Each (instance,
-// vector) pair runs its own recurrence (Paige's ordering, as hm_lanczos):
+// lanes.  Dots and norms are FP64.  Each (instance, vector) pair runs its own
+// recurrence (Paige's ordering, as hm_lanczos):
 //
-//   init  norms of the start vectors, r_0 = v0 / |v0|            (2 barriers)
-//   step  A:  w = sigma H r - cprev r_prev, alpha partials per item and vector
-//         A': alpha per pair, one wave per pair summing the instance's item
-//             partials in a fixed order
+//   init  norms of the start vectors, r_0 = v0 / |v0|              (3 launches)
+//   step  A:  w = sigma H r - cprev r_prev, alpha partials
+//         A': alpha per pair
 //         B:  w -= alpha sigma r, |w|^2 partials
 //         B': beta, breakdown test, sigma and cprev of the next step
-// Work items are 256-row tiles of one instance; persistent workgroups take
-// chunks of consecutive items in a fixed order and reduce once per run of
-// items of one instance, so every sum has a fixed order for a given grid.  The grid
-// barrier is a counter and a generation word with a bounded spin: a wave that
-// waits too long raises an abort flag and every wave leaves the kernel.
+// Work items are 256-row tiles of one instance; a workgroup takes chunks of
+// consecutive items and reduces once per run of items of one instance, so every
+// sum has a fixed order for a given chunk.  Launches order the passes: a launch
+// of a few microseconds costs less than a barrier over the whole grid (8, 15 and
+// 28 us on 256, 512 and 1024 workgroups), and the grid need not be resident.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -31,7 +30,6 @@ namespace hm {
 constexpr int kBatchBlock = 256;
 constexpr int kBatchMaxVec = 16;
 constexpr size_t kBatchPrefixLds = 24 * 1024;
-constexpr long long kSpinLimit = 1ll << 22;
 
 struct InstDesc {
     int N, A, two_s, nb;
@@ -48,80 +46,38 @@ struct Item {
     uint32_t inst, row0;
 };
 
-// A bond as the pass-A loop reads it from LDS: sites packed u | v << 16.
-struct LdsBond {
-    int32_t uv;
-    float mJ4;
-    double mJ2;
-};
-constexpr int kStageWaves = 16;   // per-wave partial slots (workgroup <= 1024 threads)
-constexpr int kChunkDefault = 4;  // items a workgroup takes at a time (default)
-constexpr int kWgPerCuDefault = 4; // resident workgroups per compute unit (default)
+constexpr int kStageWaves = kBatchBlock / 64;
 
-// Arrival counter, generation word and abort flag on separate 128-byte lines,
-// so the polling of gen does not contend with the arrivals on count.
-struct GridBar {
-    unsigned count;
-    unsigned pad0[31];
-    unsigned gen;
-    unsigned pad1[31];
-    int abort;
-    int pad2[31];
-};
+// Items a workgroup takes at a time by default: one while the batch has few (the
+// workgroups balance better), two later (half the reductions).  us for 8 steps
+// with chunk 1 / 2 / 4: 2,700 items 900 / 963 / 1004; 4,600 items 617 / 619 / 716;
+// 16,600 items 2171 / 1964 / 2045; 43,800 items 13131 / 12903 / 13001.
+constexpr int kFewItems = 8192;
+static int default_chunk(int n_items) { return n_items <= kFewItems ? 1 : 2; }
 
 struct BatchArgs {
     const InstDesc *inst;
     const Item *items;
     int ninst, n_items, nvec, steps;
     double tol;
-    GridBar *bar;
     float *r[3];
-    double *partial;           // [n_items][NV]
+    double *partial;           // [n_items][NV], the first item of a segment holds its sum
     double *alpha, *beta;      // [npairs][steps]
+    double *E0;                // [npairs]
     double *sigma, *cprev;     // [npairs][steps + 1]
     double *scale, *norm0;     // [npairs]
     int *stopped;              // [npairs]: steps done at breakdown, 0 while running
     int max_prefix;            // entries of the largest prefix table
-    int max_bonds;             // bonds of the largest coupling list
     int chunk;                 // items a workgroup takes at a time
 };
 
-// Grid-wide barrier; returns false if the run was aborted (timeout).  One
-// agent-scope release on arrival (the workgroup barrier before it orders the
-// other waves' writes), relaxed polling of the generation word, and one
-// agent-scope acquire fence after the wait.  Acquire loads in the polling loop
-// would invalidate the caches on every iteration; measured alone, this form
-// takes 8, 15 and 28 us per barrier on 256, 512 and 1024 workgroups against
-// 44, 41 and 81 us with acquire polling.
-__device__ bool grid_barrier(GridBar *bar, unsigned nblocks, int *lds_ok) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int ok = __hip_atomic_load(&bar->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
-        const unsigned g = __hip_atomic_load(&bar->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const unsigned arrived = __hip_atomic_fetch_add(&bar->count, 1u, __ATOMIC_RELEASE,
-                                                        __HIP_MEMORY_SCOPE_AGENT);
-        if (arrived == nblocks - 1) {
-            __hip_atomic_store(&bar->count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_fetch_add(&bar->gen, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            long long spins = 0;
-            while (ok && __hip_atomic_load(&bar->gen, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT) == g) {
-                __builtin_amdgcn_s_sleep(2);
-                if (++spins > kSpinLimit) {
-                    __hip_atomic_store(&bar->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    ok = 0;
-                }
-                if ((spins & 1023) == 0 &&
-                    __hip_atomic_load(&bar->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                    ok = 0;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        *lds_ok = ok;
-    }
-    __syncthreads();
-    return *lds_ok != 0;
+// Read-only tables through the constant address space: the kernels store through
+// pointers that may alias them, which would turn their uniform reads into
+// vector loads per lane.
+template <typename T> using Const = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ const Const<T> *as_const(const T *p) {
+    return (const Const<T> *)p;
 }
 
 template <int NV>
@@ -154,60 +110,16 @@ __device__ __forceinline__ void store_row(float *__restrict__ p, const float (&v
     }
 }
 
-// Per-item FP64 partials of NV columns: a fixed butterfly per column inside
-// each wave, then thread q < NV adds the wave sums of column q in wave order.
-template <int NV>
-__device__ __forceinline__ void item_partials(double (&v)[NV], double *stage, double *out) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) v[q] += __shfl_xor(v[q], off, 64);
-    }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) stage[wid * NV + q] = v[q];
-    }
-    __syncthreads();
-    if (threadIdx.x < NV) {
-        double s = 0.0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += stage[w * NV + threadIdx.x];
-        out[threadIdx.x] = s;
-    }
-    __syncthreads();
-}
-
 // Lanes per row in the two row passes: with 8 or 16 vectors a row is split
 // over NV/4 lanes of 4 vectors (16 bytes) each, so the lanes of a wave read
-// whole 64-byte rows together (a 64-lane load touches 16 lines, not 64).  The
-// lanes of a row share its bond work (each takes every G-th bond of a batch)
-// and pass the targets and coefficients around with quad permutes.
+// whole 64-byte rows together (a 64-lane load touches 16 lines, not 64).
 template <int NV>
 constexpr int lanes_per_row() { return NV >= 8 ? NV / 4 : 1; }
 
-// Value of lane t of this lane's group of G consecutive lanes (G = 2 or 4;
-// groups never straddle a quad), by a DPP quad permute.
-template <int G>
-__device__ __forceinline__ uint32_t group_lane(uint32_t v, int t) {
-    if constexpr (G == 4) {
-        switch (t) {   // quad_perm [t, t, t, t]
-            case 0: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x00, 0xf, 0xf, false);
-            case 1: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x55, 0xf, 0xf, false);
-            case 2: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xaa, 0xf, 0xf, false);
-            default: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xff, 0xf, 0xf, false);
-        }
-    } else {
-        switch (t) {   // quad_perm [t, t, 2 + t, 2 + t]
-            case 0: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xa0, 0xf, 0xf, false);
-            default: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xf5, 0xf, 0xf, false);
-        }
-    }
-}
-
-// item_partials when G lanes share a row: lane l holds the V = NV / G columns
-// starting at (l % G) V.  A fixed butterfly over the lanes of one column group
-// (offsets 32 down to G), then thread q < NV adds the wave sums of column q in
-// wave order.  G = 1 is item_partials.
+// FP64 partials of NV columns when G lanes share a row: lane l holds the
+// V = NV / G columns starting at (l % G) V.  A fixed butterfly over the lanes of
+// one column group (offsets 32 down to G), then thread q < NV adds the wave sums
+// of column q in wave order.
 template <int NV, int G>
 __device__ __forceinline__ void item_partials_g(double (&v)[NV / G], double *stage,
                                                 double *out) {
@@ -231,373 +143,494 @@ __device__ __forceinline__ void item_partials_g(double (&v)[NV / G], double *sta
     __syncthreads();
 }
 
-// Sum of column q of the item partials [first, first + count): lane l adds
-// items l, l + 64, ... in order, then a fixed butterfly over the lanes.  Every
-// lane of the wave returns the same value.
-template <int NV>
-__device__ __forceinline__ double pair_sum(const double *__restrict__ partial, uint32_t first,
-                                           uint32_t count, int q) {
-    const uint32_t lane = threadIdx.x & 63;
-    double s = 0.0;
-    for (uint32_t t = lane; t < count; t += 64) s += partial[(size_t)(first + t) * NV + q];
-    return wave_sum(s);
+// Row differences of the two ladder moves of bond (u, v) in one walk over the
+// prefix table: dn = 1 lowers u and raises v, up = 1 raises u and lowers v; with
+// 0 (a move that is not allowed) the difference is 0 and every read is the row's
+// own entry.
+template <int B>
+__device__ __forceinline__ void pair_deltas(uint64_t st, int u, int v, int dn, int up,
+                                            const Prefix<uint32_t> &P, uint32_t &d_dn,
+                                            uint32_t &d_up) {
+    int Ap = digit_sum_upto<B>(st, u);
+    const int au = digit_at<B>(st, u);
+    uint32_t base = P.at(u + 1, Ap, au);
+    d_dn = P.at(u + 1, Ap - dn, au - dn) - base;
+    d_up = P.at(u + 1, Ap + up, au + up) - base;
+    for (int p = u + 1; p < v; ++p) {
+        const int ap = digit_at<B>(st, p);
+        Ap += ap;
+        base = P.at(p + 1, Ap, ap);
+        d_dn += P.at(p + 1, Ap - dn, ap) - base;
+        d_up += P.at(p + 1, Ap + up, ap) - base;
+    }
+    const int av = digit_at<B>(st, v);
+    Ap += av;
+    base = P.at(v + 1, Ap, av);
+    d_dn += P.at(v + 1, Ap, av + dn) - base;
+    d_up += P.at(v + 1, Ap, av - up) - base;
 }
 
-template <int NV, int B>
-__global__ __launch_bounds__(kBatchBlock) void batched_lanczos_kernel(BatchArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int ok_flag;
-    __shared__ double sc_sigma[NV], sc_c[NV], sc_a[NV];
-    // instance in LDS (pass A): the kernel writes through pointers that may
-    // alias the descriptors, so uniform reads of them from global memory
-    // would be vector loads per lane; LDS broadcasts are cheap
-    __shared__ int s_N, s_A, s_two_s, s_nb;
-    __shared__ uint32_t s_dim, s_vec_off, s_item_end;
-    __shared__ uint32_t sb_dim, sb_vec_off, sb_item_end;   // pass B's instance
-    uint32_t *P = reinterpret_cast<uint32_t *>(smem);
-    double *F = reinterpret_cast<double *>(smem + ((a.max_prefix * 4 + 15) / 16) * 16);
-    double *stage = F + 32;
-    LdsBond *Bd = reinterpret_cast<LdsBond *>(stage + kStageWaves * NV);
-    const unsigned nblocks = gridDim.x;
-    const int npairs = a.ninst * NV;
-    // per-pair reductions: one wave per (instance, vector) pair
-    const int gwave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-    const int nwaves = (int)((gridDim.x * blockDim.x) >> 6);
-    const bool lane0 = (threadIdx.x & 63) == 0;
-    // Workgroups take chunks of a.chunk consecutive items, chunk c going to
-    // workgroup c % grid, so the grid sweeps the items roughly in order (a
-    // narrow working set for the gathers).  Within a chunk, consecutive items
-    // of one instance form a segment: threads add their rows' FP64
-    // contributions over the segment and the workgroup reduces once per
-    // segment, into the slot of the segment's first item.  All other slots
-    // stay zero, so the per-pair sums over an instance's slots keep a fixed
-    // order for a given grid.
-    const int kChunk = a.chunk;
-    const int n_chunks = (a.n_items + kChunk - 1) / kChunk;
-    for (int c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-        const int i0 = c * kChunk, i1 = min(i0 + kChunk, a.n_items);
-        for (int t = threadIdx.x; t < (i1 - i0) * NV; t += blockDim.x)
-            a.partial[(size_t)i0 * NV + t] = 0.0;
-    }
+// Chunks of a.chunk consecutive items.  Within a chunk, consecutive items of one
+// instance form a segment: threads add their rows' FP64 contributions over the
+// segment and the workgroup reduces once per segment, into the slot of the
+// segment's first item.
+__device__ __forceinline__ int chunk_count(const BatchArgs &a) {
+    return (a.n_items + a.chunk - 1) / a.chunk;
+}
 
-    // ---- init: |v0| partials per segment --------------------------------
-    {
-        double s[NV];
+// Chunk of position t: workgroups t, t + 8, ... run on one XCD, which so sweeps a
+// range of consecutive chunks and finds most gathered rows in its own L2.
+__device__ __forceinline__ int chunk_at(int t, int n) {
+    const int q = n / kXcds, rem = n % kXcds, x = t % kXcds;
+    return x * q + min(x, rem) + t / kXcds;
+}
+
+// item -> (instance, first row): the instance is the last one that starts at or
+// before the item.
+__global__ __launch_bounds__(kBatchBlock) void batch_items_kernel(BatchArgs a, Item *items) {
+    const uint32_t it = blockIdx.x * kBatchBlock + threadIdx.x;
+    if (it >= (uint32_t)a.n_items) return;
+    int lo = 0, hi = a.ninst;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        if (a.inst[mid].item_first <= it) lo = mid;
+        else hi = mid;
+    }
+    items[it] = Item{(uint32_t)lo, (it - a.inst[lo].item_first) * kBatchBlock};
+}
+
+// |v0|^2 partials per segment.  Thread t takes column t % NV of the rows
+// t / NV, t / NV + 256 / NV, ..., so that a wave reads consecutive entries.
+template <int NV>
+__global__ __launch_bounds__(kBatchBlock) void batch_norm_kernel(BatchArgs a) {
+    __shared__ double stage[kStageWaves * NV];
+    const int n_chunks = chunk_count(a), q = threadIdx.x % NV;
+    const uint32_t r0 = threadIdx.x / NV;
+    double s[1] = {0.0};
+    for (int t = blockIdx.x; t < n_chunks; t += gridDim.x) {
+        const int c = chunk_at(t, n_chunks), i0 = c * a.chunk, i1 = min(i0 + a.chunk, a.n_items);
+        int seg = i0;
+        for (int it = i0; it < i1; ++it) {
+            const Const<InstDesc> &d = as_const(a.inst)[as_const(a.items)[it].inst];
+            const uint32_t i = as_const(a.items)[it].row0 + r0, dim = d.dim;
+            const double *v0 = d.v0;
+            double v[NV];
 #pragma unroll
-        for (int q = 0; q < NV; ++q) s[q] = 0.0;
-        for (int c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-            const int i0 = c * kChunk, i1 = min(i0 + kChunk, a.n_items);
-            int seg = i0;
-            for (int it = i0; it < i1; ++it) {
-                const Item itm = a.items[it];
-                const InstDesc &d = a.inst[itm.inst];
-                const uint32_t i = itm.row0 + threadIdx.x;
-                if (i < d.dim) {
-    #pragma unroll
-                    for (int q = 0; q < NV; ++q) {
-                        const double v = q < a.nvec ? d.v0[(size_t)i * a.nvec + q] : 0.0;
-                        s[q] += v * v;
-                    }
-                }
-                if (it + 1 == i1 || (uint32_t)(it + 1) == d.item_first + d.item_count) {
-                    item_partials<NV>(s, stage, a.partial + (size_t)seg * NV);
-    #pragma unroll
-                    for (int q = 0; q < NV; ++q) s[q] = 0.0;
-                    seg = it + 1;
-                }
+            for (int t = 0; t < NV; ++t) {
+                const uint32_t row = i + t * (kBatchBlock / NV);
+                v[t] = row < dim && q < a.nvec ? v0[(size_t)row * a.nvec + q] : 0.0;
+            }
+#pragma unroll
+            for (int t = 0; t < NV; ++t) s[0] += v[t] * v[t];
+            if (it + 1 == i1 || (uint32_t)(it + 1) == d.item_first + d.item_count) {
+                item_partials_g<NV, NV>(s, stage, a.partial + (size_t)seg * NV);
+                s[0] = 0.0;
+                seg = it + 1;
             }
         }
     }
-    if (!grid_barrier(a.bar, nblocks, &ok_flag)) return;
-    for (int p = gwave; p < npairs; p += nwaves) {
-        const InstDesc &d = a.inst[p / NV];
-        const int q = p % NV;
-        const double s = pair_sum<NV>(a.partial, d.item_first, d.item_count, q);
-        if (!lane0) continue;
-        const bool live = q < a.nvec && s > 0.0;
-        a.norm0[p] = sqrt(s);
+}
+
+// r_0 = v0 / |v0|, threads as above.
+template <int NV>
+__global__ __launch_bounds__(kBatchBlock) void batch_start_kernel(BatchArgs a) {
+    const int q = threadIdx.x % NV;
+    const uint32_t r0 = threadIdx.x / NV;
+    for (int it = blockIdx.x; it < a.n_items; it += gridDim.x) {
+        const int inst = as_const(a.items)[it].inst;
+        const Const<InstDesc> &d = as_const(a.inst)[inst];
+        const uint32_t i = as_const(a.items)[it].row0 + r0, dim = d.dim;
+        const double *v0 = d.v0;
+        float *out = a.r[0] + (size_t)d.vec_off * NV + q;
+        const bool live = q < a.nvec && a.stopped[inst * NV + q] == 0;
+        const double norm = a.norm0[inst * NV + q];
+        double v[NV];
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const uint32_t row = i + t * (kBatchBlock / NV);
+            v[t] = live && row < dim ? v0[(size_t)row * a.nvec + q] : 0.0;
+        }
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const uint32_t row = i + t * (kBatchBlock / NV);
+            if (row < dim) out[(size_t)row * NV] = live ? (float)(v[t] / norm) : 0.0f;
+        }
+    }
+}
+
+// The sums of one instance's segments, and what follows from them for its NV
+// pairs: the start norms (kInit), alpha_k (kAlpha), or beta_k, the breakdown test
+// and the scalars of step k + 1 (kBeta).  One workgroup per instance: thread t
+// adds the slots t / NV, t / NV + 1024 / NV, ... of column t % NV, 8 loads in
+// flight; then a fixed tree.
+enum { kInit, kAlpha, kBeta };
+constexpr int kPairBlock = 1024;
+
+template <int NV, int MODE>
+__global__ __launch_bounds__(kPairBlock) void batch_pairs_kernel(BatchArgs a, int k) {
+    __shared__ double stage[kPairBlock / 64 * NV];
+    const int inst = blockIdx.x;
+    const int first = (int)a.inst[inst].item_first, count = (int)a.inst[inst].item_count;
+    const int c0 = first / a.chunk, slots = (first + count - 1) / a.chunk - c0 + 1;
+    const int q = threadIdx.x % NV;
+    auto slot = [&](int s) {
+        return a.partial[(size_t)(s == 0 ? first : (c0 + s) * a.chunk) * NV + q];
+    };
+    constexpr int U = 8, S = kPairBlock / NV;
+    double sum = 0.0;
+    int s = threadIdx.x / NV;
+    for (; s + (U - 1) * S < slots; s += U * S) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = slot(s + u * S);
+#pragma unroll
+        for (int u = 0; u < U; ++u) sum += v[u];
+    }
+    for (; s < slots; s += S) sum += slot(s);
+#pragma unroll
+    for (int off = 32; off >= NV; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if ((threadIdx.x & 63) < NV) stage[threadIdx.x / 64 * NV + q] = sum;
+    __syncthreads();
+    if (threadIdx.x >= NV) return;
+    sum = 0.0;
+    for (int w = 0; w < kPairBlock / 64; ++w) sum += stage[w * NV + q];
+    const int p = inst * NV + q;
+    const size_t o = (size_t)p * (a.steps + 1);
+    if (MODE == kInit) {
+        const bool live = q < a.nvec && sum > 0.0;
+        a.norm0[p] = sqrt(sum);
         a.scale[p] = 0.0;
         a.stopped[p] = live ? 0 : -1;
-        a.sigma[(size_t)p * (a.steps + 1)] = live ? 1.0 : 0.0;
-        a.cprev[(size_t)p * (a.steps + 1)] = 0.0;
-    }
-    if (!grid_barrier(a.bar, nblocks, &ok_flag)) return;
-    for (int it = blockIdx.x; it < a.n_items; it += gridDim.x) {
-        const Item itm = a.items[it];
-        const InstDesc &d = a.inst[itm.inst];
-        const uint32_t i = itm.row0 + threadIdx.x;
-        if (i < d.dim) {
-            float v[NV];
-#pragma unroll
-            for (int q = 0; q < NV; ++q) {
-                const int p = itm.inst * NV + q;
-                v[q] = (q < a.nvec && a.stopped[p] == 0)
-                           ? (float)(d.v0[(size_t)i * a.nvec + q] / a.norm0[p]) : 0.0f;
-            }
-            store_row<NV>(a.r[0] + ((size_t)d.vec_off + i) * NV, v);
-        }
-    }
-    if (!grid_barrier(a.bar, nblocks, &ok_flag)) return;
-
-    // row passes: G lanes per row, this lane's V columns start at gq
-    constexpr int G = lanes_per_row<NV>(), V = NV / G;
-    const int gl = (int)(threadIdx.x % G), gq = gl * V;
-    int loaded = -1;   // instance whose tables are in LDS
-    for (int k = 0; k < a.steps; ++k) {
-        const float *__restrict__ rk = a.r[k % 3];
-        const float *__restrict__ rp = a.r[(k + 2) % 3];
-        float *__restrict__ w = a.r[(k + 1) % 3];
-        // ---- A: w = sigma H r_k - cprev r_{k-1}; alpha partials ----------
-        double dacc[V];
-#pragma unroll
-        for (int q = 0; q < V; ++q) dacc[q] = 0.0;
-        int sc_loaded = -1;
-        for (int c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-            const int i0 = c * kChunk, i1 = min(i0 + kChunk, a.n_items);
-            int seg = i0;
-            for (int it = i0; it < i1; ++it) {
-                const Item itm = a.items[it];
-                // a new instance starts a segment; the previous segment ended with
-                // a workgroup barrier, so nobody still reads what is replaced here
-                if ((int)itm.inst != sc_loaded) {
-                    if ((int)itm.inst != loaded) {
-                        const InstDesc &d = a.inst[itm.inst];
-                        const int plen = d.N * (d.A + 1) * (d.two_s + 1);
-                        for (int t = threadIdx.x; t < plen; t += blockDim.x) P[t] = d.prefix[t];
-                        for (int t = threadIdx.x; t < d.two_s + 2; t += blockDim.x) F[t] = d.ladder[t];
-                        for (int t = threadIdx.x; t < d.nb; t += blockDim.x) {
-                            const BondDev bd = d.bonds[t];
-                            Bd[t] = LdsBond{bd.u | (bd.v << 16), (float)bd.mJ4, bd.mJ2};
-                        }
-                        if (threadIdx.x == 0) {
-                            s_N = d.N;
-                            s_A = d.A;
-                            s_two_s = d.two_s;
-                            s_nb = d.nb;
-                            s_dim = d.dim;
-                            s_vec_off = d.vec_off;
-                            s_item_end = d.item_first + d.item_count;
-                        }
-                        loaded = itm.inst;
-                    }
-                    if (threadIdx.x < NV) {
-                        const int p = itm.inst * NV + threadIdx.x;
-                        sc_sigma[threadIdx.x] = a.sigma[(size_t)p * (a.steps + 1) + k];
-                        sc_c[threadIdx.x] = a.cprev[(size_t)p * (a.steps + 1) + k];
-                    }
-                    sc_loaded = itm.inst;
-                    __syncthreads();
-                }
-                const int iN = __builtin_amdgcn_readfirstlane(s_N);
-                const int iA = __builtin_amdgcn_readfirstlane(s_A);
-                const int two_s = __builtin_amdgcn_readfirstlane(s_two_s);
-                const int nb = __builtin_amdgcn_readfirstlane(s_nb);
-                const uint32_t dim = __builtin_amdgcn_readfirstlane(s_dim);
-                const uint32_t vec_off = __builtin_amdgcn_readfirstlane(s_vec_off);
-                const uint32_t item_end = __builtin_amdgcn_readfirstlane(s_item_end);
-                const Prefix<uint32_t> pv{P, iA + 1, two_s + 1};
-                const float *__restrict__ xr = rk + (size_t)vec_off * NV;
-                // lane gl of a group decodes the group's row of sub-iteration gl,
-                // so each row is decoded once; the state is passed around below
-                const uint32_t i_mine = itm.row0 + gl * (kBatchBlock / G) + threadIdx.x / G;
-                const uint64_t st_mine =
-                    i_mine < dim ? unrank_state<uint32_t, B>(i_mine, pv, iN, iA, two_s) : 0;
-                for (int sub = 0; sub < G; ++sub) {
-                    const uint32_t i = itm.row0 + sub * (kBatchBlock / G) + threadIdx.x / G;
-                    if (i >= dim) continue;   // the G lanes of a row leave together
-                    uint64_t st = st_mine;
-                    if constexpr (G > 1)
-                        st = (uint64_t)group_lane<G>((uint32_t)st_mine, sub) |
-                             ((uint64_t)group_lane<G>((uint32_t)(st_mine >> 32), sub) << 32);
-                    float xi[V], acc[V];
-                    load_row<V>(xr + (size_t)i * NV + gq, xi);
-    #pragma unroll
-                    for (int q = 0; q < V; ++q) acc[q] = 0.0f;
-                    float diag = 0.0f;
-                    // moves in batches: targets and coefficients first (a move that
-                    // is not allowed reads the own row with coefficient 0), then all
-                    // row loads of the batch, then the products in bond order, so
-                    // kMoves row gathers are in flight together.  With G > 1 lane
-                    // gl of a row finds the moves of bonds gl*BPL .. gl*BPL+BPL-1
-                    // of the batch and the group shares them.
-                    constexpr int kMoves = G > 1 ? 8 : 16;
-                    constexpr int BPL = kMoves / 2 / G;      // bonds per lane and batch
-                    for (int b0 = 0; b0 < nb; b0 += kMoves / 2) {
-                        uint32_t jo[2 * BPL];
-                        float co[2 * BPL];
-    #pragma unroll
-                        for (int t = 0; t < BPL; ++t) {
-                            jo[2 * t] = jo[2 * t + 1] = i;
-                            co[2 * t] = co[2 * t + 1] = 0.0f;
-                            const int b = b0 + gl * BPL + t;
-                            if (b < nb) {
-                                const LdsBond bd = Bd[b];
-                                const int u = bd.uv & 0xffff, v = bd.uv >> 16;
-                                const double mJ2 = bd.mJ2;
-                                const int au = digit_at<B>(st, u), av = digit_at<B>(st, v);
-                                diag += bd.mJ4 * (float)((two_s - 2 * au) * (two_s - 2 * av));
-                                if (au >= 1 && av < two_s) {
-                                    jo[2 * t] = i + move_delta<uint32_t, B>(st, u, v, -1, pv);
-                                    co[2 * t] = (float)(mJ2 * F[au] * F[av + 1]);
-                                }
-                                if (av >= 1 && au < two_s) {
-                                    jo[2 * t + 1] = i + move_delta<uint32_t, B>(st, u, v, +1, pv);
-                                    co[2 * t + 1] = (float)(mJ2 * F[av] * F[au + 1]);
-                                }
-                            }
-                        }
-                        uint32_t jm[kMoves];
-                        float cm[kMoves];
-                        if constexpr (G == 1) {
-    #pragma unroll
-                            for (int m = 0; m < kMoves; ++m) {
-                                jm[m] = jo[m];
-                                cm[m] = co[m];
-                            }
-                        } else {
-    #pragma unroll
-                            for (int src = 0; src < G; ++src)
-    #pragma unroll
-                                for (int m = 0; m < 2 * BPL; ++m) {
-                                    jm[src * 2 * BPL + m] = group_lane<G>(jo[m], src);
-                                    cm[src * 2 * BPL + m] = __uint_as_float(
-                                        group_lane<G>(__float_as_uint(co[m]), src));
-                                }
-                        }
-                        float xj[kMoves][V];
-    #pragma unroll
-                        for (int m = 0; m < kMoves; ++m)
-                            load_row<V>(xr + (size_t)jm[m] * NV + gq, xj[m]);
-    #pragma unroll
-                        for (int m = 0; m < kMoves; ++m)
-    #pragma unroll
-                            for (int q = 0; q < V; ++q) acc[q] += cm[m] * xj[m][q];
-                    }
-                    if constexpr (G > 1) {
-                        // the diagonal: each lane summed its own bonds; add the
-                        // group's parts in lane order (same value in every lane)
-                        const uint32_t db = __float_as_uint(diag);
-                        float dsum = 0.0f;
-    #pragma unroll
-                        for (int src = 0; src < G; ++src)
-                            dsum += __uint_as_float(group_lane<G>(db, src));
-                        diag = dsum;
-                    }
-                    float prv[V];
-                    if (k > 0) load_row<V>(rp + ((size_t)vec_off + i) * NV + gq, prv);
-                    float out[V];
-    #pragma unroll
-                    for (int q = 0; q < V; ++q) {
-                        const double hv = (double)(diag * xi[q] + acc[q]);
-                        double wq = sc_sigma[gq + q] * hv;
-                        if (k > 0) wq -= sc_c[gq + q] * (double)prv[q];
-                        out[q] = (float)wq;
-                        dacc[q] += (double)out[q] * (sc_sigma[gq + q] * (double)xi[q]);
-                    }
-                    store_row<V>(w + ((size_t)vec_off + i) * NV + gq, out);
-                }
-                if (it + 1 == i1 || (uint32_t)(it + 1) == item_end) {
-                    item_partials_g<NV, G>(dacc, stage, a.partial + (size_t)seg * NV);
-    #pragma unroll
-                    for (int q = 0; q < V; ++q) dacc[q] = 0.0;
-                    seg = it + 1;
-                }
-            }
-        }
-        if (!grid_barrier(a.bar, nblocks, &ok_flag)) return;
-        // ---- A': alpha per pair --------------------------------------------
-        for (int p = gwave; p < npairs; p += nwaves) {
-            const InstDesc &d = a.inst[p / NV];
-            const double s = pair_sum<NV>(a.partial, d.item_first, d.item_count, p % NV);
-            if (lane0) a.alpha[(size_t)p * a.steps + k] = s;
-        }
-        if (!grid_barrier(a.bar, nblocks, &ok_flag)) return;
-        // ---- B: w -= alpha sigma r_k; |w|^2 partials -----------------------
-        double ss[V];
-#pragma unroll
-        for (int q = 0; q < V; ++q) ss[q] = 0.0;
-        sc_loaded = -1;
-        for (int c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-            const int i0 = c * kChunk, i1 = min(i0 + kChunk, a.n_items);
-            int seg = i0;
-            for (int it = i0; it < i1; ++it) {
-                const Item itm = a.items[it];
-                if ((int)itm.inst != sc_loaded) {
-                    if (threadIdx.x < NV) {
-                        const int p = itm.inst * NV + threadIdx.x;
-                        sc_a[threadIdx.x] = a.alpha[(size_t)p * a.steps + k] *
-                                            a.sigma[(size_t)p * (a.steps + 1) + k];
-                    }
-                    if (threadIdx.x == 0) {
-                        const InstDesc &d = a.inst[itm.inst];
-                        sb_dim = d.dim;
-                        sb_vec_off = d.vec_off;
-                        sb_item_end = d.item_first + d.item_count;
-                    }
-                    sc_loaded = itm.inst;
-                    __syncthreads();
-                }
-                const uint32_t dim = __builtin_amdgcn_readfirstlane(sb_dim);
-                const uint32_t vec_off = __builtin_amdgcn_readfirstlane(sb_vec_off);
-                const uint32_t item_end = __builtin_amdgcn_readfirstlane(sb_item_end);
-                for (int sub = 0; sub < G; ++sub) {
-                    const uint32_t i = itm.row0 + sub * (kBatchBlock / G) + threadIdx.x / G;
-                    if (i >= dim) continue;
-                    const size_t row = ((size_t)vec_off + i) * NV + gq;
-                    float wv[V], rv[V];
-                    load_row<V>(w + row, wv);
-                    load_row<V>(rk + row, rv);
-    #pragma unroll
-                    for (int q = 0; q < V; ++q) {
-                        wv[q] = (float)((double)wv[q] - sc_a[gq + q] * (double)rv[q]);
-                        ss[q] += (double)wv[q] * (double)wv[q];
-                    }
-                    store_row<V>(w + row, wv);
-                }
-                if (it + 1 == i1 || (uint32_t)(it + 1) == item_end) {
-                    item_partials_g<NV, G>(ss, stage, a.partial + (size_t)seg * NV);
-    #pragma unroll
-                    for (int q = 0; q < V; ++q) ss[q] = 0.0;
-                    seg = it + 1;
-                }
-            }
-        }
-        if (!grid_barrier(a.bar, nblocks, &ok_flag)) return;
-        // ---- B': beta, breakdown, next sigma / cprev -----------------------
-        for (int p = gwave; p < npairs; p += nwaves) {
-            const InstDesc &d = a.inst[p / NV];
-            const double s = pair_sum<NV>(a.partial, d.item_first, d.item_count, p % NV);
-            if (!lane0) continue;
-            const double b = sqrt(s);
-            const size_t o = (size_t)p * (a.steps + 1);
-            if (a.stopped[p] != 0) {
-                a.beta[(size_t)p * a.steps + k] = 0.0;
-                a.sigma[o + k + 1] = 0.0;
-                a.cprev[o + k + 1] = 0.0;
-                continue;
-            }
-            a.beta[(size_t)p * a.steps + k] = b;
+        a.sigma[o] = live ? 1.0 : 0.0;
+        a.cprev[o] = 0.0;
+    } else if (MODE == kAlpha) {
+        a.alpha[(size_t)p * a.steps + k] = sum;
+    } else {
+        double b = sqrt(sum), sigma = 0.0, cprev = 0.0;
+        if (a.stopped[p] != 0) {
+            b = 0.0;
+        } else {
             const double sc = fmax(a.scale[p], fmax(fabs(a.alpha[(size_t)p * a.steps + k]), b));
             a.scale[p] = sc;
             if (!(b > a.tol * sc)) {
                 a.stopped[p] = k + 1;
-                a.sigma[o + k + 1] = 0.0;
-                a.cprev[o + k + 1] = 0.0;
             } else {
-                a.sigma[o + k + 1] = 1.0 / b;
-                a.cprev[o + k + 1] = b * a.sigma[o + k];
+                sigma = 1.0 / b;
+                cprev = b * a.sigma[o + k];
             }
         }
-        if (!grid_barrier(a.bar, nblocks, &ok_flag)) return;
+        a.beta[(size_t)p * a.steps + k] = b;
+        a.sigma[o + k + 1] = sigma;
+        a.cprev[o + k + 1] = cprev;
     }
+}
+
+// Pass A.  A wave takes 64 rows of an item in two phases.  First every lane
+// decodes a row and walks the bonds, writing the moves that are allowed into the
+// row's list in LDS (kList moves; a bond that may not fit any more empties the
+// lists first).  Then the G lanes of a row read its list and gather the target
+// rows, 8 in flight.  Only allowed moves are gathered (spin 1, 14 sites: 12 of
+// 26).  Bound by decoding and encoding: 2,100 vector instructions per 64 rows,
+// 60 % of what the units can issue, with 4 waves per SIMD (lists and registers).
+// 64 spin-1 chains of 8 to 14 sites, 11.2 M rows of 16 vectors: 1.09 ms (2.0 TB/s
+// of the 2.15 GB that have to move), a step 1.54 ms; with every move gathered
+// (coefficient 0 for the others) and one barrier per pass a step took 2.3 ms.
+constexpr int kList = 16;
+
+template <int NV, int B>
+__global__ __launch_bounds__(kBatchBlock) void batch_hx_kernel(BatchArgs a, int k) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double sc_sigma[NV], sc_c[NV];
+    // the lists of a wave's rows: move m of row r at [m * 64 + r]
+    __shared__ uint2 lists[kBatchBlock / 64][kList * 64];
+    __shared__ double stage[kStageWaves * NV];
+    uint32_t *P = reinterpret_cast<uint32_t *>(smem);
+    double *F = reinterpret_cast<double *>(smem + ((a.max_prefix * 4 + 15) / 16) * 16);
+    // G lanes per row, this lane's V columns start at gq
+    constexpr int G = lanes_per_row<NV>(), V = NV / G;
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int gq = lane % G * V;
+    uint2 *L = lists[wid];
+    const float *__restrict__ rk = a.r[k % 3];
+    const float *__restrict__ rp = a.r[(k + 2) % 3];
+    float *__restrict__ w = a.r[(k + 1) % 3];
+    double dacc[V];
+#pragma unroll
+    for (int q = 0; q < V; ++q) dacc[q] = 0.0;
+    int loaded = -1;   // instance whose tables are in LDS
+    const int n_chunks = chunk_count(a);
+    for (int t = blockIdx.x; t < n_chunks; t += gridDim.x) {
+        const int c = chunk_at(t, n_chunks), i0 = c * a.chunk, i1 = min(i0 + a.chunk, a.n_items);
+        int seg = i0;
+        for (int it = i0; it < i1; ++it) {
+            const int inst = as_const(a.items)[it].inst;
+            const Const<InstDesc> &d = as_const(a.inst)[inst];
+            const int iN = d.N, iA = d.A, two_s = d.two_s, nb = d.nb;
+            const uint32_t dim = d.dim, vec_off = d.vec_off;
+            // a new instance starts a segment; the previous segment ended with
+            // a workgroup barrier, so nobody still reads what is replaced here
+            if (inst != loaded) {
+                const uint32_t *prefix = d.prefix;
+                const double *ladder = d.ladder;
+                const int plen = iN * (iA + 1) * (two_s + 1);
+                for (int t = threadIdx.x; t < plen; t += kBatchBlock) P[t] = prefix[t];
+                for (int t = threadIdx.x; t < two_s + 2; t += kBatchBlock) F[t] = ladder[t];
+                if (threadIdx.x < NV) {
+                    const int p = inst * NV + threadIdx.x;
+                    sc_sigma[threadIdx.x] = a.sigma[(size_t)p * (a.steps + 1) + k];
+                    sc_c[threadIdx.x] = a.cprev[(size_t)p * (a.steps + 1) + k];
+                }
+                loaded = inst;
+                __syncthreads();
+            }
+            const Const<BondDev> *bonds = as_const((const BondDev *)d.bonds);
+            const Prefix<uint32_t> pv{P, iA + 1, two_s + 1};
+            const float *__restrict__ xr = rk + (size_t)vec_off * NV;
+            const uint32_t base = as_const(a.items)[it].row0 + wid * 64;
+            if (base < dim) {
+                const uint32_t i = base + lane;
+                const bool live = i < dim;
+                const uint64_t st = live ? unrank_state<uint32_t, B>(i, pv, iN, iA, two_s) : 0;
+                // the diagonal in G partial sums, bond b in number (b % 4) G / 4
+                float dg[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) dg[g] = 0.0f;
+                float acc[G][V];
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+#pragma unroll
+                    for (int q = 0; q < V; ++q) acc[g][q] = 0.0f;
+                int cnt = 0;
+                // gathers the listed moves of sub-row g (row g * 64 / G + lane / G
+                // of the wave), in list order
+                auto gather = [&](int g) {
+                    const int r = g * (64 / G) + lane / G;
+                    const int n = G == 1 ? cnt : __shfl(cnt, r, 64);
+                    for (int m = 0; m < n; m += 8) {
+                        uint2 e[8];
+                        float xj[8][V];
+                        const bool more = m + 4 < n;
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) e[t] = L[(m + t) % kList * 64 + r];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            load_row<V>(xr + (size_t)e[t].x * NV + gq, xj[t]);
+                        if (more)
+#pragma unroll
+                            for (int t = 4; t < 8; ++t)
+                                load_row<V>(xr + (size_t)e[t].x * NV + gq, xj[t]);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+#pragma unroll
+                            for (int q = 0; q < V; ++q)
+                                acc[g][q] += __uint_as_float(e[t].y) * xj[t][q];
+                        if (more)
+#pragma unroll
+                            for (int t = 4; t < 8; ++t)
+#pragma unroll
+                                for (int q = 0; q < V; ++q)
+                                    acc[g][q] += __uint_as_float(e[t].y) * xj[t][q];
+                    }
+                };
+                // lists filled up to a multiple of 4 and seen by the whole wave
+                auto close = [&]() {
+                    while (cnt & 3) L[cnt++ * 64 + lane] = make_uint2(i, 0u);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                };
+                for (int b = 0; b < nb; ++b) {
+                    if (__any(cnt > kList - 2)) {
+                        close();
+#pragma unroll
+                        for (int g = 0; g < G; ++g) gather(g);
+                        __builtin_amdgcn_wave_barrier();
+                        cnt = 0;
+                    }
+                    const int u = bonds[b].u, v = bonds[b].v;
+                    const double mJ2 = bonds[b].mJ2;
+                    const float mJ4 = (float)bonds[b].mJ4;
+                    const int au = digit_at<B>(st, u), av = digit_at<B>(st, v);
+                    const float z = (float)((two_s - 2 * au) * (two_s - 2 * av));
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+                        if ((b & 3) * G / 4 == g) dg[g] += mJ4 * z;
+                    const int dn = live && au >= 1 && av < two_s;
+                    const int up = live && av >= 1 && au < two_s;
+                    uint32_t d_dn, d_up;
+                    pair_deltas<B>(st, u, v, dn, up, pv, d_dn, d_up);
+                    if (dn)
+                        L[cnt++ * 64 + lane] = make_uint2(
+                            i + d_dn, __float_as_uint((float)(mJ2 * F[au] * F[av + 1])));
+                    if (up)
+                        L[cnt++ * 64 + lane] = make_uint2(
+                            i + d_up, __float_as_uint((float)(mJ2 * F[av] * F[au + 1])));
+                }
+                close();
+                float diag = 0.0f;
+                if constexpr (G == 1) {
+                    diag = dg[0];
+                } else {
+#pragma unroll
+                    for (int g = 0; g < G; ++g) diag += dg[g];
+                }
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int r = g * (64 / G) + lane / G;
+                    const float dr = G == 1 ? diag : __shfl(diag, r, 64);
+                    const uint32_t ir = base + r;
+                    const bool rl = ir < dim;
+                    float xi[V], prv[V];
+                    const size_t row = ((size_t)vec_off + ir) * NV + gq;
+                    if (rl) {
+                        load_row<V>(rk + row, xi);
+                        if (k > 0) load_row<V>(rp + row, prv);
+                    }
+                    gather(g);
+                    if (rl) {
+                        float out[V];
+#pragma unroll
+                        for (int q = 0; q < V; ++q) {
+                            const double hv = (double)(dr * xi[q] + acc[g][q]);
+                            double wq = sc_sigma[gq + q] * hv;
+                            if (k > 0) wq -= sc_c[gq + q] * (double)prv[q];
+                            out[q] = (float)wq;
+                            dacc[q] += (double)out[q] * (sc_sigma[gq + q] * (double)xi[q]);
+                        }
+                        store_row<V>(w + row, out);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (it + 1 == i1 || (uint32_t)(it + 1) == d.item_first + d.item_count) {
+                item_partials_g<NV, G>(dacc, stage, a.partial + (size_t)seg * NV);
+#pragma unroll
+                for (int q = 0; q < V; ++q) dacc[q] = 0.0;
+                seg = it + 1;
+            }
+        }
+    }
+}
+
+// Pass B: w -= alpha sigma r_k; |w|^2 partials.  Bound by memory.
+template <int NV>
+__global__ __launch_bounds__(kBatchBlock) void batch_update_kernel(BatchArgs a, int k) {
+    constexpr int G = lanes_per_row<NV>(), V = NV / G;
+    __shared__ double sc_a[NV];
+    __shared__ double stage[kStageWaves * NV];
+    const int gq = (int)(threadIdx.x % G) * V;
+    const float *__restrict__ rk = a.r[k % 3];
+    float *__restrict__ w = a.r[(k + 1) % 3];
+    double ss[V];
+#pragma unroll
+    for (int q = 0; q < V; ++q) ss[q] = 0.0;
+    int loaded = -1;
+    const int n_chunks = chunk_count(a);
+    for (int t = blockIdx.x; t < n_chunks; t += gridDim.x) {
+        const int c = chunk_at(t, n_chunks), i0 = c * a.chunk, i1 = min(i0 + a.chunk, a.n_items);
+        int seg = i0;
+        for (int it = i0; it < i1; ++it) {
+            const int inst = as_const(a.items)[it].inst;
+            const uint32_t row0 = as_const(a.items)[it].row0;
+            const Const<InstDesc> &d = as_const(a.inst)[inst];
+            const uint32_t dim = d.dim, vec_off = d.vec_off;
+            if (inst != loaded) {
+                if (threadIdx.x < NV) {
+                    const int p = inst * NV + threadIdx.x;
+                    sc_a[threadIdx.x] = a.alpha[(size_t)p * a.steps + k] *
+                                        a.sigma[(size_t)p * (a.steps + 1) + k];
+                }
+                loaded = inst;
+                __syncthreads();
+            }
+            float wv[G][V], rv[G][V];
+#pragma unroll
+            for (int sub = 0; sub < G; ++sub) {
+                const uint32_t i = row0 + sub * (kBatchBlock / G) + threadIdx.x / G;
+                if (i >= dim) continue;
+                const size_t row = ((size_t)vec_off + i) * NV + gq;
+                load_row<V>(w + row, wv[sub]);
+                load_row<V>(rk + row, rv[sub]);
+            }
+#pragma unroll
+            for (int sub = 0; sub < G; ++sub) {
+                const uint32_t i = row0 + sub * (kBatchBlock / G) + threadIdx.x / G;
+                if (i >= dim) continue;
+#pragma unroll
+                for (int q = 0; q < V; ++q) {
+                    wv[sub][q] = (float)((double)wv[sub][q] - sc_a[gq + q] * (double)rv[sub][q]);
+                    ss[q] += (double)wv[sub][q] * (double)wv[sub][q];
+                }
+                store_row<V>(w + ((size_t)vec_off + i) * NV + gq, wv[sub]);
+            }
+            if (it + 1 == i1 || (uint32_t)(it + 1) == d.item_first + d.item_count) {
+                item_partials_g<NV, G>(ss, stage, a.partial + (size_t)seg * NV);
+#pragma unroll
+                for (int q = 0; q < V; ++q) ss[q] = 0.0;
+                seg = it + 1;
+            }
+        }
+    }
+}
+
+// E0 of every pair: the lowest eigenvalue of its tridiagonal matrix by Sturm
+// counts, one wave per pair.  The lanes count at 64 points inside the bracket, so
+// a round narrows it 65 times (bisection one pair after the other on the host
+// took 2.6 us a pair at 8 steps); rounds go on until no number lies between the
+// ends.
+__global__ __launch_bounds__(kBatchBlock) void batch_ground_kernel(BatchArgs a, int npairs) {
+    const int p = __builtin_amdgcn_readfirstlane(
+        blockIdx.x * (kBatchBlock / 64) + (threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    if (p >= npairs) return;
+    const double *al = a.alpha + (size_t)p * a.steps, *be = a.beta + (size_t)p * a.steps;
+    const int stop = a.stopped[p], n = stop > 0 ? stop : stop < 0 ? 0 : a.steps;
+    double lo = 1e300, hi = -1e300;
+    for (int i = lane; i < n; i += 64) {
+        const double d = (i > 0 ? fabs(be[i - 1]) : 0.0) + (i + 1 < n ? fabs(be[i]) : 0.0);
+        lo = fmin(lo, al[i] - d);
+        hi = fmax(hi, al[i] + d);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, off, 64));
+        hi = fmax(hi, __shfl_xor(hi, off, 64));
+    }
+    const double span = fmax(fabs(lo), fabs(hi));
+    lo -= 1e-12 * span + 1e-300;
+    hi += 1e-12 * span + 1e-300;
+    for (int round = 0; round < 2000 && n > 0; ++round) {
+        const double mid = 0.5 * (lo + hi);
+        if (!(mid > lo && mid < hi)) break;
+        const double x = fmin(fmax(lo + (hi - lo) * ((lane + 1) / 65.0), lo), hi);
+        bool below = false;   // an eigenvalue below x
+        double q = 1.0, bb = 0.0;
+        for (int i = 0; i < n; ++i) {
+            q = (al[i] - x) - bb / q;
+            if (q == 0.0) q = -1e-300;
+            below |= q < 0.0;
+            bb = be[i] * be[i];
+        }
+        const uint64_t m = __ballot(below);
+        const int f = m ? __ffsll((unsigned long long)m) - 1 : 64;   // first point above E0
+        const double below_f = __shfl(x, f > 0 ? f - 1 : 0, 64), at_f = __shfl(x, f & 63, 64);
+        const double lo1 = f > 0 ? below_f : lo, hi1 = f < 64 ? at_f : hi;
+        if (lo1 == lo && hi1 == hi) {   // the points rounded to the ends
+            break;
+        }
+        lo = lo1;
+        hi = hi1;
+    }
+    if (lane == 0) a.E0[p] = 0.5 * (lo + hi);
 }
 
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
 struct BatchLayout {
-    size_t desc, items, bar, alpha, beta, sigma, cprev, scale, norm0, stopped, partial, r0, r1,
-        r2, total;
+    size_t desc, bonds, items, E0, stopped, alpha, beta, sigma, cprev, scale, norm0, partial, r0,
+        r1, r2, total;
     int n_items, NV, bits;
     uint64_t rows;
 };
@@ -639,17 +672,21 @@ static int batch_layout(int ninst, const hm_basis *bases, int nvec, int steps, B
     }
     if (L->rows >= ((uint64_t)1 << 32)) return fail(HM_ERANGE, "too many rows in the batch");
     const size_t npairs = (size_t)ninst * L->NV;
-    size_t off = 0;
-    L->desc = off; off = al256(off + sizeof(InstDesc) * ninst);
+    size_t off = 0, nb = 0;
+    for (int k = 0; k < ninst; ++k) nb += (size_t)bases[k]->impl.N * (bases[k]->impl.N - 1) / 2;
+    // descriptors and bonds side by side (one copy to the device), and E0,
+    // stopped, alpha and beta (one copy back)
+    L->desc = off; off += sizeof(InstDesc) * ninst;
+    L->bonds = off; off = al256(off + sizeof(BondDev) * nb);
     L->items = off; off = al256(off + sizeof(Item) * L->n_items);
-    L->bar = off; off = al256(off + sizeof(GridBar));
-    L->alpha = off; off = al256(off + sizeof(double) * npairs * steps);
+    L->E0 = off; off += sizeof(double) * npairs;
+    L->stopped = off; off = al256(off + sizeof(int) * npairs);
+    L->alpha = off; off += sizeof(double) * npairs * steps;
     L->beta = off; off = al256(off + sizeof(double) * npairs * steps);
     L->sigma = off; off = al256(off + sizeof(double) * npairs * (steps + 1));
     L->cprev = off; off = al256(off + sizeof(double) * npairs * (steps + 1));
     L->scale = off; off = al256(off + sizeof(double) * npairs);
     L->norm0 = off; off = al256(off + sizeof(double) * npairs);
-    L->stopped = off; off = al256(off + sizeof(int) * npairs);
     L->partial = off; off = al256(off + sizeof(double) * (size_t)L->n_items * L->NV);
     const size_t vb = sizeof(float) * (size_t)L->rows * L->NV;
     L->r0 = off; off = al256(off + vb);
@@ -659,41 +696,45 @@ static int batch_layout(int ninst, const hm_basis *bases, int nvec, int steps, B
     return HM_OK;
 }
 
+// Every launch of a run.  The grid holds wg_per_cu workgroups per compute unit
+// (0: as many workgroups as there are chunks, left to the dispatcher).
 template <int NV, int B>
-static int launch_batched(BatchArgs &args, size_t lds, int wg_per_cu, hipStream_t st,
-                          int *grid_out) {
-    auto kern = batched_lanczos_kernel<NV, B>;
-    int dev = 0, per_cu = 0;
-    HM_HIP(hipGetDevice(&dev));
-    hipDeviceProp_t prop;
-    HM_HIP(hipGetDeviceProperties(&prop, dev));
-    HM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBatchBlock, lds));
-    if (per_cu < 1) return fail(HM_ERANGE, "batched kernel does not fit on a compute unit");
-    // every workgroup of a cooperative launch must be resident at once
-    int grid = std::min(per_cu, wg_per_cu) * prop.multiProcessorCount;
-    grid = std::min(grid, std::max(args.n_items, 1));
-    *grid_out = grid;
-    void *params[] = {&args};
-    HM_HIP(hipLaunchCooperativeKernel((const void *)kern, dim3(grid), dim3(kBatchBlock), params,
-                                      (unsigned)lds, st));
+static int launch_batched(const BatchArgs &a, size_t lds, int wg_per_cu, hipStream_t st) {
+    const int chunks = (a.n_items + a.chunk - 1) / a.chunk;
+    int grid = chunks;
+    if (wg_per_cu > 0) {
+        int dev = 0, cus = 0;
+        HM_HIP(hipGetDevice(&dev));
+        HM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        grid = std::min(grid, wg_per_cu * cus);
+    }
+    const dim3 g(grid), t(kBatchBlock), gp(a.ninst), tp(kPairBlock);
+    const int npairs = a.ninst * NV, gw = (npairs + kBatchBlock / 64 - 1) / (kBatchBlock / 64);
+    hipLaunchKernelGGL(batch_items_kernel, dim3((a.n_items + kBatchBlock - 1) / kBatchBlock), t, 0,
+                       st, a, const_cast<Item *>(a.items));
+    hipLaunchKernelGGL(batch_norm_kernel<NV>, g, t, 0, st, a);
+    hipLaunchKernelGGL((batch_pairs_kernel<NV, kInit>), gp, tp, 0, st, a, 0);
+    hipLaunchKernelGGL(batch_start_kernel<NV>, dim3(std::min(a.n_items, 1 << 16)), t, 0, st, a);
+    for (int k = 0; k < a.steps; ++k) {
+        hipLaunchKernelGGL((batch_hx_kernel<NV, B>), g, t, lds, st, a, k);
+        hipLaunchKernelGGL((batch_pairs_kernel<NV, kAlpha>), gp, tp, 0, st, a, k);
+        hipLaunchKernelGGL(batch_update_kernel<NV>, g, t, 0, st, a, k);
+        hipLaunchKernelGGL((batch_pairs_kernel<NV, kBeta>), gp, tp, 0, st, a, k);
+    }
+    hipLaunchKernelGGL(batch_ground_kernel, dim3(gw), t, 0, st, a, npairs);
+    HM_HIP(hipGetLastError());
     return HM_OK;
 }
 
 template <int NV>
-static int dispatch_bits(int bits, BatchArgs &args, size_t lds, int wg, hipStream_t st, int *grid) {
+static int dispatch_bits(int bits, const BatchArgs &args, size_t lds, int wg, hipStream_t st) {
     switch (bits) {
-        case 1: return launch_batched<NV, 1>(args, lds, wg, st, grid);
-        case 2: return launch_batched<NV, 2>(args, lds, wg, st, grid);
-        case 3: return launch_batched<NV, 3>(args, lds, wg, st, grid);
-        case 4: return launch_batched<NV, 4>(args, lds, wg, st, grid);
+        case 1: return launch_batched<NV, 1>(args, lds, wg, st);
+        case 2: return launch_batched<NV, 2>(args, lds, wg, st);
+        case 3: return launch_batched<NV, 3>(args, lds, wg, st);
+        case 4: return launch_batched<NV, 4>(args, lds, wg, st);
         default: return fail(HM_ERANGE, "batched kernel supports up to 4 bits per digit");
     }
-}
-
-__global__ void zero_bar(GridBar *bar) {
-    bar->count = 0;
-    bar->gen = 0;
-    bar->abort = 0;
 }
 
 }  // namespace hm
@@ -720,51 +761,53 @@ int hm_lanczos_batched(int32_t ninst, const hm_basis *bases, const double *const
     hm::clear_error();
     if (!J || !d_v0 || !d_work || !alpha || !beta || !E0 || !steps_done)
         return fail(HM_EINVAL, "null argument");
-    if (chunk == 0) chunk = hm::kChunkDefault;
-    if (wg_per_cu == 0) wg_per_cu = hm::kWgPerCuDefault;
-    if (chunk < 1 || chunk > 64) return fail(HM_EINVAL, "chunk %d outside 1..64", chunk);
-    if (wg_per_cu < 1 || wg_per_cu > 8)
-        return fail(HM_EINVAL, "workgroups per compute unit %d outside 1..8", wg_per_cu);
+    if (chunk < 0 || chunk > 64) return fail(HM_EINVAL, "chunk %d outside 0..64", chunk);
+    if (wg_per_cu < 0 || wg_per_cu > 8)
+        return fail(HM_EINVAL, "workgroups per compute unit %d outside 0..8", wg_per_cu);
     hm::BatchLayout L;
     HM_TRY(hm::batch_layout(ninst, bases, nvec, steps, &L));
     if (work_bytes < L.total)
         return fail(HM_EWORKSPACE, "workspace %zu bytes < required %zu", work_bytes, L.total);
     unsigned char *w = (unsigned char *)d_work;
     hipStream_t st = (hipStream_t)stream;
-    std::vector<hm::InstDesc> desc(ninst);
-    std::vector<hm::CouplingsRef> crefs(ninst);   // held until the run returns
-    std::vector<hm::Item> items;
-    uint32_t vec_off = 0;
-    int max_prefix = 0, max_bonds = 0;
+    // descriptors and bond lists, built here and not in the handles' caches, which
+    // hold fewer lists than a batch may bring
+    std::vector<unsigned char> up(L.items - L.desc);
+    hm::InstDesc *desc = (hm::InstDesc *)up.data();
+    hm::BondDev *bonds = (hm::BondDev *)(up.data() + (L.bonds - L.desc));
+    const hm::BondDev *d_bonds = (const hm::BondDev *)(w + L.bonds);
+    uint32_t vec_off = 0, item_first = 0;
+    int max_prefix = 0;
     for (int k = 0; k < ninst; ++k) {
         hm::Basis *b = &bases[k]->impl;
         if (!d_v0[k]) return fail(HM_EINVAL, "start vectors of instance %d are null", k);
-        HM_TRY(hm::get_couplings(b, J[k], &crefs[k]));   // validates J, prepares the device
-        const hm::Couplings *c = crefs[k].get();
+        HM_TRY(hm::validate_J(b, J[k]));
+        {
+            std::lock_guard<std::mutex> lock(b->mu);
+            HM_TRY(hm::device_prepare(b));
+        }
+        const int nb = hm::list_bonds(b, J[k], bonds);
         hm::InstDesc &d = desc[k];
         d.N = b->N;
         d.A = b->A;
         d.two_s = b->two_s;
-        d.nb = c->nb;
+        d.nb = nb;
         d.dim = (uint32_t)b->dim;
         d.vec_off = vec_off;
-        d.item_first = (uint32_t)items.size();
-        for (uint32_t r0 = 0; r0 < d.dim; r0 += hm::kBatchBlock) items.push_back({(uint32_t)k, r0});
-        d.item_count = (uint32_t)items.size() - d.item_first;
+        d.item_first = item_first;
+        d.item_count = (d.dim + hm::kBatchBlock - 1) / hm::kBatchBlock;
         d.prefix = (const uint32_t *)b->d_prefix;
         d.ladder = b->d_ladder;
-        d.bonds = c->dev;
+        d.bonds = d_bonds;
         d.v0 = d_v0[k];
         vec_off += d.dim;
+        item_first += d.item_count;
+        bonds += nb;
+        d_bonds += nb;
         max_prefix = std::max(max_prefix, (int)b->prefix_len());
-        max_bonds = std::max(max_bonds, c->nb);
     }
-    HM_HIP(hipMemcpyAsync(w + L.desc, desc.data(), sizeof(hm::InstDesc) * ninst,
+    HM_HIP(hipMemcpyAsync(w + L.desc, up.data(), (unsigned char *)bonds - up.data(),
                           hipMemcpyHostToDevice, st));
-    HM_HIP(hipMemcpyAsync(w + L.items, items.data(), sizeof(hm::Item) * items.size(),
-                          hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(hm::zero_bar, dim3(1), dim3(1), 0, st, (hm::GridBar *)(w + L.bar));
-    HM_HIP(hipGetLastError());
     hm::BatchArgs a{};
     a.inst = (const hm::InstDesc *)(w + L.desc);
     a.items = (const hm::Item *)(w + L.items);
@@ -773,44 +816,38 @@ int hm_lanczos_batched(int32_t ninst, const hm_basis *bases, const double *const
     a.nvec = nvec;
     a.steps = steps;
     a.tol = breakdown_tol > 0 ? breakdown_tol : 1e-6;   // FP32 vectors: FP32 noise floor
-    a.bar = (hm::GridBar *)(w + L.bar);
     a.r[0] = (float *)(w + L.r0);
     a.r[1] = (float *)(w + L.r1);
     a.r[2] = (float *)(w + L.r2);
     a.partial = (double *)(w + L.partial);
     a.alpha = (double *)(w + L.alpha);
     a.beta = (double *)(w + L.beta);
+    a.E0 = (double *)(w + L.E0);
     a.sigma = (double *)(w + L.sigma);
     a.cprev = (double *)(w + L.cprev);
     a.scale = (double *)(w + L.scale);
     a.norm0 = (double *)(w + L.norm0);
     a.stopped = (int *)(w + L.stopped);
     a.max_prefix = max_prefix;
-    a.max_bonds = max_bonds;
-    a.chunk = chunk;
-    const size_t lds = ((size_t)(max_prefix * 4 + 15) / 16) * 16 + 32 * sizeof(double) +
-                       (size_t)hm::kStageWaves * L.NV * sizeof(double) +
-                       (size_t)max_bonds * sizeof(hm::LdsBond);
+    a.chunk = chunk > 0 ? chunk : hm::default_chunk(L.n_items);
+    const size_t lds = ((size_t)(max_prefix * 4 + 15) / 16) * 16 + 32 * sizeof(double);
     const int bits = L.bits;
-    int grid = 0, rc;
+    int rc;
     switch (L.NV) {
-        case 1: rc = hm::dispatch_bits<1>(bits, a, lds, wg_per_cu, st, &grid); break;
-        case 2: rc = hm::dispatch_bits<2>(bits, a, lds, wg_per_cu, st, &grid); break;
-        case 4: rc = hm::dispatch_bits<4>(bits, a, lds, wg_per_cu, st, &grid); break;
-        case 8: rc = hm::dispatch_bits<8>(bits, a, lds, wg_per_cu, st, &grid); break;
-        default: rc = hm::dispatch_bits<16>(bits, a, lds, wg_per_cu, st, &grid); break;
+        case 1: rc = hm::dispatch_bits<1>(bits, a, lds, wg_per_cu, st); break;
+        case 2: rc = hm::dispatch_bits<2>(bits, a, lds, wg_per_cu, st); break;
+        case 4: rc = hm::dispatch_bits<4>(bits, a, lds, wg_per_cu, st); break;
+        case 8: rc = hm::dispatch_bits<8>(bits, a, lds, wg_per_cu, st); break;
+        default: rc = hm::dispatch_bits<16>(bits, a, lds, wg_per_cu, st); break;
     }
     if (rc != HM_OK) return rc;
+    std::vector<unsigned char> down(L.sigma - L.E0);
+    HM_HIP(hipMemcpyAsync(down.data(), w + L.E0, down.size(), hipMemcpyDeviceToHost, st));
     HM_HIP(hipStreamSynchronize(st));
-    hm::GridBar bar;
-    HM_HIP(hipMemcpy(&bar, w + L.bar, sizeof bar, hipMemcpyDeviceToHost));
-    if (bar.abort) return fail(HM_EDEVICE, "batched kernel: grid barrier timed out");
-    const size_t npairs = (size_t)ninst * L.NV;
-    std::vector<double> al(npairs * steps), be(npairs * steps);
-    std::vector<int> stop(npairs);
-    HM_HIP(hipMemcpy(al.data(), w + L.alpha, sizeof(double) * al.size(), hipMemcpyDeviceToHost));
-    HM_HIP(hipMemcpy(be.data(), w + L.beta, sizeof(double) * be.size(), hipMemcpyDeviceToHost));
-    HM_HIP(hipMemcpy(stop.data(), w + L.stopped, sizeof(int) * npairs, hipMemcpyDeviceToHost));
+    const double *e0 = (const double *)down.data();
+    const int *stop = (const int *)(down.data() + (L.stopped - L.E0));
+    const double *al = (const double *)(down.data() + (L.alpha - L.E0));
+    const double *be = (const double *)(down.data() + (L.beta - L.E0));
     for (int k = 0; k < ninst; ++k)
         for (int q = 0; q < nvec; ++q) {
             const size_t p = (size_t)k * L.NV + q, o = ((size_t)k * nvec + q) * steps;
@@ -821,7 +858,7 @@ int hm_lanczos_batched(int32_t ninst, const hm_basis *bases, const double *const
                 beta[o + s] = s < done ? be[p * steps + s] : 0.0;
             }
             steps_done[k * nvec + q] = done;
-            HM_TRY(hm_tridiag_lowest(done, alpha + o, beta + o, &E0[k * nvec + q], nullptr));
+            E0[k * nvec + q] = e0[p];
         }
     return HM_OK;
 }

@@ -151,6 +151,9 @@ constexpr size_t kGraphCacheEntries = 4;
 int device_prepare(Basis *b);                      // device tables + device check
 int get_couplings(Basis *b, const double *J, CouplingsRef *out);
 int validate_J(const Basis *b, const double *J);
+// Bonds of J (u < v, J_uv != 0) in row-major upper-triangle order, at most
+// N(N-1)/2 of them; returns their number.
+int list_bonds(const Basis *b, const double *J, BondDev *out);
 
 // Host codec (Sec. 3.1 / 3.2), used by hm_unrank / hm_rank.
 void host_unrank(const Basis *b, int64_t i, uint8_t *digits);

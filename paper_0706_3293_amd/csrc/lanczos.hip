@@ -621,6 +621,7 @@ struct TableArgs {
     const double *ladder;
     const BondDev *bonds;
     int nb, N, A, two_s, steps, reorth, n, halfK;   // halfK > 0: the arithmetic of hx_half.hip
+    int normed;              // v_k kept normalized (sigma_k = 1), as lanczos_small_kernel does
     double tol, shift;
     const double *v0;
     T *V;                    // [steps][n] normalized v_j (full reorthogonalization)
@@ -823,15 +824,16 @@ __global__ __launch_bounds__(kSmallBlock) void lanczos_table_kernel(const TableA
             break;
         }
         // every wave has read r_k (the barrier of the sum above)
+        const double inv = 1.0 / beta;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int i = tid + j * kSmallBlock;
             if (i >= n) continue;
             vp[j] = vk[i];
-            vk[i] = w[j];
+            vk[i] = a.normed ? (T)((double)w[j] * inv) : w[j];
         }
         cprev = beta * sigma;
-        sigma = 1.0 / beta;
+        if (!a.normed) sigma = inv;
         if (tid == 0) a.sigma[k + 1] = sigma;
         __syncthreads();
     }
@@ -880,6 +882,7 @@ struct Run {
     const Couplings *c;
     int steps, prec, reorth, kernel, use_graph, small;
     int table;                 // steps of lanczos_table_kernel before the step loop
+    int normed;                // one-workgroup run: v_k kept normalized
     int halfK;                 // one-workgroup run: low sites of the block kernel whose
                                // arithmetic it takes (0: row_hx's)
     double tol;
@@ -1059,6 +1062,7 @@ static void launch_table_b(const Run &R, int steps) {
     a.reorth = R.reorth;
     a.n = (int)b->dim;
     a.halfK = R.halfK;
+    a.normed = R.normed;
     a.tol = R.tol;
     a.shift = R.c->diag_shift;
     a.v0 = R.v0;
@@ -1310,6 +1314,8 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     Run R{};
     R.small = small ? 1 : 0;
     R.table = small ? 0 : table;
+    // FP32 roundings of the shortest runs, and of those asked for
+    R.normed = o->kernel == 3 || (!o->full_reorth && work <= kSmallWork);
     if (table > 0 && (o->full_reorth || work > kSmallWork) && half_supported(b))
         R.halfK = half_low_bits(b);
     R.b = b;

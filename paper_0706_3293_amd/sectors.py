@@ -5,9 +5,9 @@ H(M) (Sec. 2); a magnetization curve needs the lowest energy of each one.  By
 the spin-flip symmetry a_u -> 2s - a_u the sectors M and -M share their
 spectrum, so only M >= 0 (A = Ns - M = 0 .. floor(Ns)) is computed.
 
-Every sector of one coupling matrix is one instance of the batched persistent
-Lanczos (hm_lanczos_batched): all sectors and start vectors run in a single
-launch.  For finite temperature, each (sector, start vector) run gives Ritz
+Every sector of one coupling matrix is one instance of the batched
+Lanczos (hm_lanczos_batched): every pass of a step is one launch for all sectors
+and start vectors.  For finite temperature, each (sector, start vector) run gives Ritz
 values theta_j and Gauss weights |<r|y_j>|^2 (hm_tridiag_ritz), and
 
     Z_M ~ (D_M / R) sum_r sum_j |<r|y_j>|^2 exp(-theta_j / T)
@@ -78,7 +78,7 @@ def magnetization_curve(N: int, two_s: int, J, steps: int, nvec: int = 1, seed: 
                         V0s=None, tol: float = 0.0, method: str = "auto") -> MagnetizationCurve:
     """E0 of every sector M >= 0 (FP32 vectors, FP64 coefficients and sums).
 
-    method "batched": all sectors and start vectors in one persistent launch
+    method "batched": all sectors and start vectors in one batched run
     (hm_lanczos_batched); "single": one hm_lanczos run per sector and start
     vector, which for s = 1/2 runs the block H x kernel; "auto": single for
     s = 1/2, batched otherwise.  V0s: optional list of (nvec, dim) start
