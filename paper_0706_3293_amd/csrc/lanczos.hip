@@ -959,12 +959,13 @@ static int enqueue_steps(Run &R, int k0, int k1, std::vector<hipEvent_t> *ev) {
                 hipLaunchKernelGGL(psi_axpy<T>, dim3(G), dim3(kBlock), 0, R.st, R.psi, rk, n, coef,
                                    sigma, k);
             for (int rep = 0; rep < 2; ++rep) {
-                if (rep == 0)
-                    hipLaunchKernelGGL((tall_dots_kernel<T, 1, true>), dg, dim3(kTallBlock), 0, R.st,
-                                       V, wn, n, nv, dots, (const int *)nullptr, sigma + k, sub);
-                else
-                    hipLaunchKernelGGL((tall_dots_kernel<T, 1, false>), dg, dim3(kTallBlock), 0,
-                                       R.st, V, wn, n, nv, dots, (const int *)nullptr, sigma + k, sub);
+                const auto dots_kernel =
+                    nv <= 16 ? (rep == 0 ? tall_dots_kernel<T, 1, true, 1>
+                                         : tall_dots_kernel<T, 1, false, 1>)
+                             : (rep == 0 ? tall_dots_kernel<T, 1, true, 2>
+                                         : tall_dots_kernel<T, 1, false, 2>);
+                hipLaunchKernelGGL(dots_kernel, dg, dim3(kTallBlock), 0, R.st, V, wn, n, nv, dots,
+                                   (const int *)nullptr, sigma + k, sub);
                 if (!fold_h)
                     hipLaunchKernelGGL(reorth_finish, dim3((nv + 63) / 64), dim3(kTallBlock), 0,
                                        R.st, dots, splits, nv, hc, sigma + k);

@@ -29,11 +29,10 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 // Two consecutive elements at any element-aligned address.
 template <typename T>
-__device__ __forceinline__ void load2(const T *__restrict__ p, double &a, double &b) {
-    typedef T V2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));
-    const V2 v = *reinterpret_cast<const V2 *>(p);
-    a = (double)v.x;
-    b = (double)v.y;
+using Two = T __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+template <typename T>
+__device__ __forceinline__ Two<T> load2(const T *__restrict__ p) {
+    return *reinterpret_cast<const Two<T> *>(p);
 }
 
 // Columns of V one workgroup (blockIdx.y) takes.
@@ -61,22 +60,24 @@ __device__ __forceinline__ double tall_factor(const TallSub<T> &sub, double *red
 
 // partial[split][col][c] over the rows of split blockIdx.x.  The run has
 // stopped, and nothing is done, if *stopped != 0 or *live == 0 (null: neither).
-template <typename T, int P, bool SUB = false>
+// NG = 1 takes at most 16 columns of the scalar recurrence, with twice the rows
+// in flight (92,378 rows, up to 8 columns, FP32: 8.8 -> 5.7 us, with pass B and
+// alpha 12.4 -> 7.6).
+template <typename T, int P, bool SUB = false, int NG = 2>
 __global__ __launch_bounds__(kTallBlock) void tall_dots_kernel(
     const T *__restrict__ V, const T *__restrict__ W, int64_t dim, int ncol,
     double *__restrict__ partial, const int *__restrict__ stopped,
     const double *__restrict__ live, const TallSub<T> sub) {
-    static_assert(!SUB || P == 1, "pass B belongs to the scalar recurrence");
+    static_assert((!SUB && NG == 2) || P == 1, "scalar recurrence");
     if ((stopped && *stopped) || (live && *live == 0.0)) return;
     double factor = 0.0;
     if constexpr (SUB) {
         __shared__ double red[17];
         factor = tall_factor(sub, red, blockIdx.x == 0 && blockIdx.y == 0);
     }
-    constexpr int NG = 2;                          // accumulator pairs per wave
     constexpr int NA = P == 1 ? NG : 2 * NG;       // accumulators of 16 columns
     constexpr int kRows = P == 1 ? 8 : 4;          // rows of one load
-    constexpr int U = 4;                           // loads of a column in flight
+    constexpr int U = 8 / NG;                      // loads of a column in flight
     __shared__ double stage[4][16 * NA][P];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int i = lane & 15, kk = lane >> 4;
@@ -102,34 +103,53 @@ __global__ __launch_bounds__(kTallBlock) void tall_dots_kernel(
     for (int64_t s = s0; s < s1; ++s) {
         const int64_t base = s * kStep + wid * (U * kRows);
         double a0[U][NG], a1[U][NG], b0[U], b1[U];
+        if constexpr (P == 1) {
+            // all loads first, rows past the end read from inside: the values
+            // are converted and combined, and a branch around a load would wait
+            // for it there
+            Two<T> va[U][NG], vw[U], vr[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            b0[u] = b1[u] = 0.0;
-            if constexpr (P == 1) {
+            for (int u = 0; u < U; ++u) {
+                const int64_t r = base + u * kRows + 2 * kk;
+                const int64_t rr = max(min(r, dim - 2), (int64_t)0);
+#pragma unroll
+                for (int g = 0; g < NG; ++g) va[u][g] = load2(vp[g] + rr);
+                vw[u] = load2(wp + rr);
+                if constexpr (SUB) vr[u] = load2(sub.r + rr);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
                 const int64_t r = base + u * kRows + 2 * kk;
                 const bool two = r + 1 < dim, one = r < dim;
+                const bool at = two || dim == 1;   // the pair that was read starts at r
 #pragma unroll
                 for (int g = 0; g < NG; ++g) {
-                    a0[u][g] = a1[u][g] = 0.0;
-                    if (vok[g] && two) load2(vp[g] + r, a0[u][g], a1[u][g]);
-                    else if (vok[g] && one) a0[u][g] = (double)vp[g][r];
+                    a0[u][g] = vok[g] && one ? (double)(at ? va[u][g].x : va[u][g].y) : 0.0;
+                    a1[u][g] = vok[g] && two ? (double)va[u][g].y : 0.0;
                 }
-                if (wok && two) load2(wp + r, b0[u], b1[u]);
-                else if (wok && one) b0[u] = (double)wp[r];
+                b0[u] = (double)(at ? vw[u].x : vw[u].y);
+                b1[u] = (double)vw[u].y;
                 if constexpr (SUB) {
-                    double r0 = 0.0, r1 = 0.0;
-                    if (wok && two) load2(sub.r + r, r0, r1);
-                    else if (wok && one) r0 = (double)sub.r[r];
-                    b0[u] = (double)(T)(b0[u] - factor * r0);
-                    b1[u] = (double)(T)(b1[u] - factor * r1);
+                    b0[u] = (double)(T)(b0[u] - factor * (double)(at ? vr[u].x : vr[u].y));
+                    b1[u] = (double)(T)(b1[u] - factor * (double)vr[u].y);
                 }
-            } else {
+                b0[u] = wok && one ? b0[u] : 0.0;
+                b1[u] = wok && two ? b1[u] : 0.0;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                b0[u] = 0.0;
                 const int64_t r = base + u * kRows + kk;
                 const bool ok = r < dim;
 #pragma unroll
                 for (int g = 0; g < NG; ++g) {
                     a0[u][g] = a1[u][g] = 0.0;
-                    if (vok[g] && ok) load2(vp[g] + r * P, a0[u][g], a1[u][g]);
+                    if (vok[g] && ok) {
+                        const Two<T> v = load2(vp[g] + r * P);
+                        a0[u][g] = (double)v.x;
+                        a1[u][g] = (double)v.y;
+                    }
                 }
                 if (wok && ok) b0[u] = (double)wp[r * P];
             }
