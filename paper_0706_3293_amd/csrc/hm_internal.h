@@ -58,14 +58,16 @@ struct Couplings {
     double diag_shift = 0.0;  // sum_b mJ4 (used by the spin-1/2 kernel)
     // bonds regrouped for the spin-1/2 block kernel (built on first use)
     void *half = nullptr;
+    void *staged = nullptr;   // for the automatic FP64 split
     void (*half_free)(void *) = nullptr;
     // the same for the spin-1/2 kernel with one workgroup per block
     void *wg = nullptr;
     void (*wg_free)(void *) = nullptr;
     ~Couplings() {
-        if (dev || half || wg) (void)hipDeviceSynchronize();
+        if (dev || half || staged || wg) (void)hipDeviceSynchronize();
         if (dev) (void)hipFree(dev);
         if (half && half_free) half_free(half);
+        if (staged && half_free) half_free(staged);
         if (wg && wg_free) wg_free(wg);
     }
 };
@@ -125,6 +127,7 @@ struct Basis {
     int half_staging = 0;    // 0 automatic, 1 chunked items, 2 staged blocks
     int half_ipw = 0;        // work items per wave that size the grid (0: default grid)
     void *half_tables = nullptr;
+    void *staged_tables = nullptr;   // those of the automatic FP64 split
     void (*half_tables_free)(void *) = nullptr;
     // spin-1/2 kernel with one workgroup per block: tables (first use)
     void *wg_tables = nullptr;

@@ -75,7 +75,6 @@ struct HalfTables {
     int K = 0, block = 256, R = 1, C = 0;   // C > 0: staged blocks of 64 C entries
     int ipw = 0;                            // items per wave that size the grid (0: default)
     int64_t n_items = 0, n_groups = 0;
-    std::vector<uint64_t> off_host;
     uint16_t *d_rankL = nullptr, *d_unrankL = nullptr;
     void *d_off = nullptr;            // uint32 or uint64 per high word
     uint32_t *d_hgroups = nullptr;    // n_groups x R high words
@@ -664,20 +663,6 @@ static int default_low_bits(int N) {
     return K;
 }
 
-static int low_bits_of(const Basis *b) { return b->half_K > 0 ? b->half_K : default_low_bits(b->N); }
-int half_low_bits(const Basis *b) { return low_bits_of(b); }
-static int block_of(const Basis *b) { return b->half_block > 0 ? b->half_block : 256; }
-static int rows_of(const Basis *b) {
-    if (b->half_R > 0) return b->half_R;
-    return b->dim >= ((int64_t)1 << 22) ? 4 : 1;
-}
-
-bool half_supported(const Basis *b) {
-    if (b->two_s != 1) return false;
-    const int K = low_bits_of(b);
-    return K <= kHalfMaxK && K <= b->N && b->N - K <= kHalfMaxHighBits;
-}
-
 static int64_t binom(int n, int k) {
     if (k < 0 || k > n) return 0;
     int64_t r = 1;
@@ -685,9 +670,34 @@ static int64_t binom(int n, int k) {
     return r;
 }
 
+// How the rows are split: low sites, rows per lane, threads per workgroup, items
+// per wave that size the grid (0: default grid), staged blocks or chunked items.
+struct HalfSplit {
+    int K, R, block, ipw;
+    bool staged;
+};
+
+// The split of the handle's schedule.
+static HalfSplit split_of(const Basis *b) {
+    HalfSplit s;
+    s.K = b->half_K > 0 ? b->half_K : default_low_bits(b->N);
+    s.R = b->half_R > 0 ? b->half_R : b->dim >= ((int64_t)1 << 22) ? 4 : 1;
+    s.block = b->half_block > 0 ? b->half_block : 256;
+    s.ipw = b->half_ipw;
+    s.staged = b->half_staging == 2;
+    return s;
+}
+int half_low_bits(const Basis *b) { return split_of(b).K; }
+
+bool half_supported(const Basis *b) {
+    if (b->two_s != 1) return false;
+    const int K = split_of(b).K;
+    return K <= kHalfMaxK && K <= b->N && b->N - K <= kHalfMaxHighBits;
+}
+
 // Number of (high-word group, 64-row chunk) items, from the block sizes.
-static int64_t item_count(const Basis *b) {
-    const int K = low_bits_of(b), nh = b->N - K, R = rows_of(b);
+static int64_t item_count(const Basis *b, const HalfSplit &sp) {
+    const int K = sp.K, nh = b->N - K, R = sp.R;
     int64_t n = 0;
     for (int ph = 0; ph <= nh; ++ph) {
         const int aL = b->A - ph;
@@ -704,22 +714,14 @@ static int staged_entries(int K) {
     return smax <= 128 ? 2 : (smax <= 256 ? 4 : (smax <= 512 ? 8 : 0));
 }
 
-static bool staged_possible(const Basis *b) {
-    const int C = staged_entries(low_bits_of(b)), R = rows_of(b);
-    return C > 0 && b->idx32 && R <= (C == 8 ? 2 : 4);
-}
-
-// Whether the staged work split runs (a function of the basis and its
-// schedule only, so workspace sizes can be computed before the tables).
-static bool staged_of(const Basis *b) {
-    if (b->half_staging == 1) return false;
-    if (b->half_staging == 2) return true;
-    return false;
+static bool staged_possible(const Basis *b, const HalfSplit &sp) {
+    const int C = staged_entries(sp.K);
+    return C > 0 && b->idx32 && sp.R <= (C == 8 ? 2 : 4);
 }
 
 // Number of high-word groups (work items of the staged split).
-static int64_t group_count(const Basis *b) {
-    const int K = low_bits_of(b), nh = b->N - K, R = rows_of(b);
+static int64_t group_count(const Basis *b, const HalfSplit &sp) {
+    const int K = sp.K, nh = b->N - K, R = sp.R;
     int64_t n = 0;
     for (int ph = 0; ph <= nh; ++ph) {
         const int aL = b->A - ph;
@@ -749,10 +751,46 @@ static int grid_for_items(int64_t n_items, int block, int ipw) {
     return (int)g;
 }
 
-// Workgroups of the block kernel (= FP64 partial sums it writes).
-int hx_half_grid(const Basis *b) {
-    return grid_for_items(staged_of(b) ? group_count(b) : item_count(b), block_of(b), b->half_ipw);
+static int grid_of(const Basis *b, const HalfSplit &sp) {
+    return grid_for_items(sp.staged ? group_count(b, sp) : item_count(b, sp), sp.block, sp.ipw);
 }
+
+// The automatic FP64 split of large, well-filled subspaces without a schedule:
+// staged blocks of 10 low sites.  From about 1 M rows they fill the chip, and
+// while the blocks hold more than kStagedFill rows on average (at most 252, four
+// 64-row slices) few lanes idle and a block's rows come from LDS.  us of one
+// FP64 H x, chunked -> staged (rows, rows per block):
+//   J1-J2 rings: 0.74 M, 57:  28.3 -> 33.0 (not taken)
+//                1.35 M, 165: 43.5 -> 34.2
+//                1.96 M, 123: 62.6 -> 50.1
+//                5.31 M, 91:  139 -> 138 (not taken)
+//                40.1 M, 154: 1271 -> 961
+//                155 M, 150:  5250 -> 3986
+//   all-to-all:  2.70 M, 165: 407 -> 404
+//                40.1 M, 154: 9062 -> 8089
+// In FP32 the order of a row's sum shows in the coefficients, so it stays.  One
+// item per wave while there are few (all-to-all, 16,354: 404 us, 450 with 4), 4 to
+// share a workgroup's tables later (J1-J2 ring, 2 M: 4.48 ms, 4.92 with one).
+constexpr int64_t kStagedMinRows = (int64_t)1 << 20;
+constexpr int64_t kStagedFill = 110;
+static HalfSplit staged_split(const Basis *b) {
+    HalfSplit s{10, 1, 256, 1, true};
+    if (group_count(b, s) > (1 << 15)) s.ipw = 4;
+    return s;
+}
+
+static bool staged_pays(const Basis *b) {
+    if (b->half_K || b->half_block || b->half_R || b->half_staging || b->half_ipw) return false;
+    if (b->two_s != 1 || !b->idx32 || b->dim < kStagedMinRows) return false;
+    const HalfSplit s = staged_split(b);
+    const int nh = b->N - s.K;
+    return nh >= 1 && nh <= kHalfMaxHighBits && b->dim >= kStagedFill * group_count(b, s);
+}
+
+// Workgroups of the block kernel (= FP64 partial sums it writes) in the handle's
+// split, and in the automatic FP64 split (0 where it is not taken).
+int hx_half_grid(const Basis *b) { return grid_of(b, split_of(b)); }
+int hx_staged_grid(const Basis *b) { return staged_pays(b) ? grid_of(b, staged_split(b)) : 0; }
 
 static hipError_t upload(void **dst, const void *src, size_t bytes) {
     hipError_t e = hipMalloc(dst, bytes);
@@ -760,27 +798,29 @@ static hipError_t upload(void **dst, const void *src, size_t bytes) {
     return e;
 }
 
-static int half_prepare(Basis *b, HalfTables **out) {
+static int half_prepare(Basis *b, bool staged, HalfTables **out) {
     std::lock_guard<std::mutex> lock(b->mu);
     HM_TRY(device_prepare(b));
-    if (b->half_tables) {
-        *out = (HalfTables *)b->half_tables;
+    void *&slot = staged ? b->staged_tables : b->half_tables;
+    if (slot) {
+        *out = (HalfTables *)slot;
         return HM_OK;
     }
     const int N = b->N, A = b->A;
-    const int K = low_bits_of(b), R = rows_of(b);
+    const HalfSplit sp = staged ? staged_split(b) : split_of(b);
+    const int K = sp.K, R = sp.R;
     if (K > kHalfMaxK || N - K > kHalfMaxHighBits || K < 1 || K > N)
         return fail(HM_EINVAL, "block kernel: low bits K=%d unsupported for N=%d", K, N);
-    if (staged_of(b) && !staged_possible(b))
+    if (sp.staged && !staged_possible(b, sp))
         return fail(HM_EINVAL,
                     "staged block kernel needs C(K, K/2) <= 512, 32-bit indices and at most "
                     "4 rows per lane (2 when K = 11); K=%d, R=%d", K, R);
     auto *t = new HalfTables;
     t->K = K;
     t->R = R;
-    t->block = block_of(b);
-    t->C = staged_of(b) ? staged_entries(K) : 0;
-    t->ipw = b->half_ipw;
+    t->block = sp.block;
+    t->C = sp.staged ? staged_entries(K) : 0;
+    t->ipw = sp.ipw;
     const int nlow = 1 << K;
     std::vector<uint16_t> rankL(nlow), unrankL(nlow);
     std::vector<int> fill(K + 1, 0);
@@ -797,22 +837,15 @@ static int half_prepare(Basis *b, HalfTables **out) {
     }
     const int nh = N - K;
     const int64_t nhigh = (int64_t)1 << nh;
-    t->off_host.assign(nhigh, 0);
+    // blocks lie in the order of their high words
+    std::vector<uint64_t> off(nhigh, 0);
     std::vector<std::vector<uint32_t>> by_class(nh + 1);
     int64_t expect = 0;
     for (int64_t h = 0; h < nhigh; ++h) {
         const int ph = __builtin_popcountll((unsigned long long)h);
         const int aL = A - ph;
         if (aL < 0 || aL > K) continue;
-        uint64_t o = 0;
-        int t_idx = aL;
-        for (int q = 0; q < nh; ++q)
-            if ((h >> q) & 1) o += (uint64_t)binom(K + q, ++t_idx);
-        if ((int64_t)o != expect) {
-            free_half(t);
-            return fail(HM_EINVAL, "internal: block offsets out of order at h=%lld", (long long)h);
-        }
-        t->off_host[h] = o;
+        off[h] = (uint64_t)expect;
         expect += t->class_size[aL];
         by_class[ph].push_back((uint32_t)h);
     }
@@ -823,12 +856,13 @@ static int half_prepare(Basis *b, HalfTables **out) {
     }
     // groups of R high words of one popcount class, ordered by the offset of
     // their first block so the sweep follows memory order
-    struct Grp { uint64_t key; int ph; size_t start; };
+    struct Grp { uint32_t first; int ph; size_t start; };
     std::vector<Grp> grps;
     for (int ph = 0; ph <= nh; ++ph)
         for (size_t s = 0; s < by_class[ph].size(); s += R)
-            grps.push_back({t->off_host[by_class[ph][s]], ph, s});
-    std::sort(grps.begin(), grps.end(), [](const Grp &a, const Grp &b) { return a.key < b.key; });
+            grps.push_back({by_class[ph][s], ph, s});
+    std::sort(grps.begin(), grps.end(),
+              [](const Grp &a, const Grp &b) { return a.first < b.first; });
     std::vector<uint32_t> hgroups, items;
     hgroups.reserve(grps.size() * R);
     for (size_t gi = 0; gi < grps.size(); ++gi) {
@@ -838,33 +872,37 @@ static int half_prepare(Basis *b, HalfTables **out) {
             hgroups.push_back(s < cls.size() ? cls[s] : kNoHigh);
         }
         const int S = t->class_size[A - grps[gi].ph];
-        for (int c = 0; c * 64 < S; ++c) items.push_back(((uint32_t)gi << 8) | (uint32_t)c);
+        if (!sp.staged)
+            for (int c = 0; c * 64 < S; ++c) items.push_back(((uint32_t)gi << 8) | (uint32_t)c);
     }
-    if ((int64_t)items.size() != item_count(b) || grps.size() >= ((size_t)1 << 24)) {
-        free_half(t);
-        return fail(HM_EINVAL, "internal: %zu items, expected %lld", items.size(),
-                    (long long)item_count(b));
-    }
-    t->n_items = (int64_t)items.size();
+    t->n_items = sp.staged ? 0 : (int64_t)items.size();
     t->n_groups = (int64_t)grps.size();
+    const bool whole = sp.staged ? t->n_groups == group_count(b, sp)
+                                 : t->n_items == item_count(b, sp);
+    if (!whole || grps.size() >= ((size_t)1 << 24)) {
+        free_half(t);
+        return fail(HM_EINVAL, "internal: %zu items, %zu groups", items.size(), grps.size());
+    }
     hipError_t e = upload((void **)&t->d_rankL, rankL.data(), nlow * sizeof(uint16_t));
     if (e == hipSuccess) e = upload((void **)&t->d_unrankL, unrankL.data(), nlow * sizeof(uint16_t));
     if (e == hipSuccess) {
         if (b->idx32) {
-            std::vector<uint32_t> o32(t->off_host.begin(), t->off_host.end());
+            std::vector<uint32_t> o32(off.begin(), off.end());
             e = upload(&t->d_off, o32.data(), o32.size() * sizeof(uint32_t));
         } else {
-            e = upload(&t->d_off, t->off_host.data(), t->off_host.size() * sizeof(uint64_t));
+            e = upload(&t->d_off, off.data(), off.size() * sizeof(uint64_t));
         }
     }
     if (e == hipSuccess)
         e = upload((void **)&t->d_hgroups, hgroups.data(), hgroups.size() * sizeof(uint32_t));
-    if (e == hipSuccess) e = upload((void **)&t->d_items, items.data(), items.size() * sizeof(uint32_t));
+    if (e == hipSuccess && !items.empty())
+        e = upload((void **)&t->d_items, items.data(), items.size() * sizeof(uint32_t));
     if (e != hipSuccess) {
         free_half(t);
-        return fail(HM_EDEVICE, "block kernel tables: %s", hipGetErrorString(e));
+        return fail(staged && e == hipErrorOutOfMemory ? HM_ENOMEM : HM_EDEVICE,
+                    "block kernel tables: %s", hipGetErrorString(e));
     }
-    b->half_tables = t;
+    slot = t;
     b->half_tables_free = free_half;
     *out = t;
     return HM_OK;
@@ -910,13 +948,48 @@ static size_t neighbour_bytes(const Basis *b, const Couplings *c, int K) {
            (width * (b->idx32 ? 4 : 8) + hwidth * sizeof(uint16_t) + sizeof(uint32_t));
 }
 
-static int half_bonds(Basis *b, const Couplings *c, const HalfTables *t,
+// Neighbour table of a high word: compacted high-word part (target blocks of the
+// bonds that flip, then the own block), straddling part Off(h ^ m2).
+template <typename I>
+__global__ __launch_bounds__(256) void half_neighbours_kernel(
+    const I *__restrict__ off, const BondGroup *__restrict__ groups, int64_t nhigh, int K, int A,
+    int nLg, int nHg, int nSg, I *__restrict__ nbr, uint32_t *__restrict__ hcnt,
+    uint16_t *__restrict__ hidx) {
+    const int width = (nHg + nSg) * kGroup, hwidth = nHg * kGroup;
+    for (int64_t h = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; h < nhigh;
+         h += (int64_t)gridDim.x * blockDim.x) {
+        I *__restrict__ row = nbr + (size_t)h * width;
+        uint16_t *__restrict__ irow = hidx + (size_t)h * hwidth;
+        const int aL = A - __popcll((unsigned long long)h);
+        const bool live = aL >= 0 && aL <= K;
+        const I own = off[h];
+        int n = 0;
+        for (int k = 0; k < hwidth; ++k) {
+            const uint32_t m = groups[nLg + k / kGroup].m1[k % kGroup];
+            if (live && __popc((uint32_t)h & m) == 1) {
+                row[n] = off[h ^ m];
+                irow[n++] = (uint16_t)k;
+            }
+        }
+        hcnt[h] = (uint32_t)n;
+        for (int s = n; s < hwidth; ++s) {
+            row[s] = own;
+            irow[s] = (uint16_t)width;   // the group of zero coefficients
+        }
+        for (int k = 0; k < nSg * kGroup; ++k)
+            row[hwidth + k] =
+                live ? off[h ^ groups[nLg + nHg + k / kGroup].m2[k % kGroup]] : (I)0;
+    }
+}
+
+static int half_bonds(Basis *b, const Couplings *c, const HalfTables *t, bool staged,
                       const HalfBonds **out) {
     const int K = t->K;
     std::lock_guard<std::mutex> lock(b->mu);
     auto *cc = const_cast<Couplings *>(c);
-    if (cc->half && ((HalfBonds *)cc->half)->K == K) {
-        *out = (const HalfBonds *)cc->half;
+    void *&slot = staged ? cc->staged : cc->half;
+    if (slot && ((HalfBonds *)slot)->K == K) {
+        *out = (const HalfBonds *)slot;
         return HM_OK;
     }
     if (neighbour_bytes(b, c, K) > kMaxNeighbourBytes)
@@ -946,35 +1019,9 @@ static int half_bonds(Basis *b, const Couplings *c, const HalfTables *t,
     to_groups(st, groups);
     const int nSg = (int)groups.size() - nLg - nHg;
     groups.push_back(BondGroup{});    // all coefficients 0: the padding of compacted rows
-    const int width = (nHg + nSg) * kGroup, hwidth = nHg * kGroup;
-    const uint16_t zero_slot = (uint16_t)((nHg + nSg) * kGroup);   // relative to the high groups
     const int64_t nhigh = (int64_t)1 << (b->N - K);
-    // neighbour table: compacted high-word part (target blocks of the bonds
-    // that flip, then the own block), straddling part Off(h ^ m2)
-    std::vector<uint64_t> nbr((size_t)nhigh * width, 0);
-    std::vector<uint32_t> hcnt((size_t)nhigh, 0);
-    std::vector<uint16_t> hidx((size_t)nhigh * hwidth, zero_slot);
-    for (int64_t h = 0; h < nhigh; ++h) {
-        const int aL = b->A - __builtin_popcountll((unsigned long long)h);
-        if (aL < 0 || aL > K) continue;
-        uint64_t *row = &nbr[(size_t)h * width];
-        uint16_t *irow = &hidx[(size_t)h * hwidth];
-        int n = 0;
-        for (int k = 0; k < nHg; ++k)
-            for (int q = 0; q < kGroup; ++q) {
-                const uint32_t m = groups[nLg + k].m1[q];
-                if (__builtin_popcountll((unsigned long long)(h & m)) == 1) {
-                    row[n] = t->off_host[h ^ m];
-                    irow[n] = (uint16_t)(k * kGroup + q);
-                    ++n;
-                }
-            }
-        hcnt[h] = (uint32_t)n;
-        for (int s2 = n; s2 < hwidth; ++s2) row[s2] = t->off_host[h];
-        for (int k = 0; k < nSg; ++k)
-            for (int q = 0; q < kGroup; ++q)
-                row[(nHg + k) * kGroup + q] = t->off_host[h ^ groups[nLg + nHg + k].m2[q]];
-    }
+    const size_t width = (size_t)(nHg + nSg) * kGroup, hwidth = (size_t)nHg * kGroup;
+    const size_t es = b->idx32 ? sizeof(uint32_t) : sizeof(uint64_t);
     auto *hb = new HalfBonds;
     hb->K = K;
     hb->nLg = nLg;
@@ -982,25 +1029,32 @@ static int half_bonds(Basis *b, const Couplings *c, const HalfTables *t,
     hb->nSg = nSg;
     hb->nL = (int)lo.size();
     hb->nS = (int)st.size();
-    hipError_t e = hipSuccess;
-    if (!groups.empty()) e = upload((void **)&hb->groups, groups.data(), groups.size() * sizeof(BondGroup));
-    if (e == hipSuccess && !nbr.empty()) {
-        if (b->idx32) {
-            std::vector<uint32_t> n32(nbr.begin(), nbr.end());
-            e = upload(&hb->nbr, n32.data(), n32.size() * sizeof(uint32_t));
-        } else {
-            e = upload(&hb->nbr, nbr.data(), nbr.size() * sizeof(uint64_t));
-        }
+    hipError_t e = upload((void **)&hb->groups, groups.data(), groups.size() * sizeof(BondGroup));
+    if (e == hipSuccess && width) e = hipMalloc(&hb->nbr, (size_t)nhigh * width * es);
+    if (e == hipSuccess) e = hipMalloc((void **)&hb->hcnt, (size_t)nhigh * sizeof(uint32_t));
+    if (e == hipSuccess && hwidth)
+        e = hipMalloc((void **)&hb->hidx, (size_t)nhigh * hwidth * sizeof(uint16_t));
+    if (e == hipSuccess) {
+        const dim3 grid((unsigned)std::min<int64_t>((nhigh + 255) / 256, 1 << 16)), block(256);
+        if (b->idx32)
+            hipLaunchKernelGGL(half_neighbours_kernel<uint32_t>, grid, block, 0, nullptr,
+                               (const uint32_t *)t->d_off, hb->groups, nhigh, K, b->A, nLg, nHg,
+                               nSg, (uint32_t *)hb->nbr, hb->hcnt, hb->hidx);
+        else
+            hipLaunchKernelGGL(half_neighbours_kernel<uint64_t>, grid, block, 0, nullptr,
+                               (const uint64_t *)t->d_off, hb->groups, nhigh, K, b->A, nLg, nHg,
+                               nSg, (uint64_t *)hb->nbr, hb->hcnt, hb->hidx);
+        e = hipGetLastError();
+        // other streams may use the table from now on
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     }
-    if (e == hipSuccess) e = upload((void **)&hb->hcnt, hcnt.data(), hcnt.size() * sizeof(uint32_t));
-    if (e == hipSuccess && !hidx.empty())
-        e = upload((void **)&hb->hidx, hidx.data(), hidx.size() * sizeof(uint16_t));
     if (e != hipSuccess) {
         free_half_bonds(hb);
-        return fail(HM_EDEVICE, "block kernel bonds: %s", hipGetErrorString(e));
+        return fail(staged && e == hipErrorOutOfMemory ? HM_ENOMEM : HM_EDEVICE,
+                    "block kernel bonds: %s", hipGetErrorString(e));
     }
-    if (cc->half && cc->half_free) cc->half_free(cc->half);
-    cc->half = hb;
+    if (slot && cc->half_free) cc->half_free(slot);
+    slot = hb;
     cc->half_free = free_half_bonds;
     *out = hb;
     return HM_OK;
@@ -1107,25 +1161,39 @@ static void launch_t(const HalfTables *t, const HalfBonds *hb, const Basis *b, d
 
 // Builds the tables and the regrouped bonds (also ahead of a graph capture:
 // no allocation may happen while a stream is capturing).
-int half_prepare_tables(Basis *b, const Couplings *c) {
+int half_prepare_tables(Basis *b, const Couplings *c, bool staged) {
     HalfTables *t = nullptr;
-    HM_TRY(half_prepare(b, &t));
+    HM_TRY(half_prepare(b, staged, &t));
     const HalfBonds *hb = nullptr;
-    return half_bonds(b, c, t, &hb);
+    return half_bonds(b, c, t, staged, &hb);
 }
 
 // Whether the block kernel can run these couplings (neighbour table budget).
 bool half_fits(const Basis *b, const Couplings *c) {
-    return half_supported(b) && neighbour_bytes(b, c, low_bits_of(b)) <= kMaxNeighbourBytes;
+    return half_supported(b) && neighbour_bytes(b, c, split_of(b).K) <= kMaxNeighbourBytes;
 }
 
-int launch_hx_half(const Basis *cb, const Couplings *c, int dtype, const HxPass &p,
+// Whether the automatic FP64 split is taken: its neighbour table may have the
+// size of two vectors.
+bool staged_fits(const Basis *b, const Couplings *c, int dtype) {
+    return dtype == HM_F64 && staged_pays(b) &&
+           neighbour_bytes(b, c, staged_split(b).K) <=
+               std::min(kMaxNeighbourBytes, (size_t)b->dim * 2 * sizeof(double));
+}
+
+int launch_hx_half(const Basis *cb, const Couplings *c, int dtype, bool staged, const HxPass &p,
                    hipStream_t st) {
     Basis *b = const_cast<Basis *>(cb);
     HalfTables *t = nullptr;
-    HM_TRY(half_prepare(b, &t));
     const HalfBonds *hb = nullptr;
-    HM_TRY(half_bonds(b, c, t, &hb));
+    int rc = half_prepare(b, staged, &t);
+    if (rc == HM_OK) rc = half_bonds(b, c, t, staged, &hb);
+    if (rc == HM_ENOMEM && staged && !p.partial) {   // a plain product: the handle's split
+        clear_error();
+        (void)hipGetLastError();
+        return launch_hx_half(b, c, dtype, false, p, st);
+    }
+    HM_TRY(rc);
     if (dtype == HM_F64) {
         if (b->idx32) launch_t<double, uint32_t>(t, hb, b, c->diag_shift, p, st);
         else launch_t<double, uint64_t>(t, hb, b, c->diag_shift, p, st);

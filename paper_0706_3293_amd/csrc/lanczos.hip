@@ -32,12 +32,14 @@ namespace hm {
 int launch_hx_generic(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
                       hipStream_t st);
 int hx_generic_grid(const Basis *b);
-int launch_hx_half(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
+int launch_hx_half(const Basis *b, const Couplings *c, int dtype, bool staged, const HxPass &p,
                    hipStream_t st);
 int hx_half_grid(const Basis *b);
+int hx_staged_grid(const Basis *b);
 bool half_supported(const Basis *b);
-int half_prepare_tables(Basis *b, const Couplings *c);
+int half_prepare_tables(Basis *b, const Couplings *c, bool staged);
 bool half_fits(const Basis *b, const Couplings *c);
+bool staged_fits(const Basis *b, const Couplings *c, int dtype);
 int half_low_bits(const Basis *b);
 int launch_hx_digit(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
                     hipStream_t st);
@@ -52,14 +54,16 @@ bool wg_fits(const Basis *b, const Couplings *c, int dtype);
 // 0 = automatic (the block kernel of the spin, where it applies to the basis
 // and its tables fit the budget, else the generic digit kernel), 1 = generic,
 // 2 = spin-1/2 block kernel (-1 if it does not apply).  Chosen by 0 only:
-// kKernelDigit, the block kernel for s >= 1, and kKernelWg, the spin-1/2
-// kernel with one workgroup per block.
-constexpr int kKernelDigit = 5, kKernelWg = 6;
+// kKernelDigit, the block kernel for s >= 1, kKernelWg, the spin-1/2 kernel with
+// one workgroup per block, and kKernelStaged, the spin-1/2 block kernel in its
+// automatic FP64 split.
+constexpr int kKernelDigit = 5, kKernelWg = 6, kKernelStaged = 7;
 
 int choose_kernel(const Basis *b, const Couplings *c, int requested, int dtype) {
     if (requested == 1) return 1;
     if (requested == 0 && b->two_s >= 2) return digit_fits(b, c) ? kKernelDigit : 1;
     if (requested == 0 && wg_fits(b, c, dtype)) return kKernelWg;
+    if (requested == 0 && c && staged_fits(b, c, dtype)) return kKernelStaged;
     const bool ok = c ? half_fits(b, c) : half_supported(b);
     if (requested == 2) return ok ? 2 : -1;
     return ok ? 2 : 1;
@@ -70,12 +74,14 @@ int hx_partial_count(const Basis *b, int kernel) {
         case 2: return hx_half_grid(b);
         case kKernelDigit: return hx_digit_grid(b);
         case kKernelWg: return hx_wg_grid(b);
+        case kKernelStaged: return hx_staged_grid(b);
         default: return hx_generic_grid(b);
     }
 }
 
 int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel) {
-    if (kernel == 2) return half_prepare_tables(b, c);
+    if (kernel == 2 || kernel == kKernelStaged)
+        return half_prepare_tables(b, c, kernel == kKernelStaged);
     if (kernel == kKernelDigit) return digit_prepare_tables(b, c, dtype);
     if (kernel == kKernelWg) return wg_prepare_tables(b, c, dtype);
     return HM_OK;
@@ -83,7 +89,8 @@ int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel) {
 
 int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel, const HxPass &p,
               hipStream_t st) {
-    if (kernel == 2) return launch_hx_half(b, c, dtype, p, st);
+    if (kernel == 2 || kernel == kKernelStaged)
+        return launch_hx_half(b, c, dtype, kernel == kKernelStaged, p, st);
     if (kernel == kKernelDigit) return launch_hx_digit(b, c, dtype, p, st);
     if (kernel == kKernelWg) return launch_hx_wg(b, c, dtype, p, st);
     return launch_hx_generic(b, c, dtype, p, st);
@@ -149,7 +156,7 @@ static Layout layout(const Basis *b, int steps, int prec, int reorth) {
     const size_t es = prec == HM_PREC_F64 ? 8 : 4;
     L.grid_vec = vec_grid(b->dim);
     L.grid_b = pass_b_grid(b->dim, es);
-    L.nparts = std::max({kMaxGrid, half_supported(b) ? hx_half_grid(b) : 0,
+    L.nparts = std::max({kMaxGrid, half_supported(b) ? hx_half_grid(b) : 0, hx_staged_grid(b),
                          b->digit.K > 0 ? hx_digit_grid(b) : 0});
     size_t off = 0;
     // state, alpha, beta and sigma side by side: read back in one copy
@@ -1304,7 +1311,13 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     const int dtype = o->precision == HM_PREC_F64 ? HM_F64 : HM_F32;
     int kernel = small ? 1 : choose_kernel(b, c, o->kernel, dtype);
     if (kernel < 0) return fail(HM_ERANGE, "block kernel tables too large for these couplings");
-    const int prc = prepare_kernel(b, c, dtype, kernel);
+    int prc = prepare_kernel(b, c, dtype, kernel);
+    if (prc == HM_ENOMEM && kernel == kKernelStaged) {
+        kernel = 2;                   // the handle's split
+        clear_error();
+        (void)hipGetLastError();
+        prc = prepare_kernel(b, c, dtype, kernel);
+    }
     if (prc == HM_ENOMEM && kernel != 2) {
         kernel = 1;                   // the kernel without tables
         clear_error();
