@@ -106,6 +106,104 @@ __global__ __launch_bounds__(kBlock) void rank_kernel(const I *__restrict__ gpre
     }
 }
 
+// Codec of spins 1/2.  The walk over all sites (unrank_kernel, rank_kernel) is
+// bound by its vector instructions, 8 a site.  Decoding walks the sites above the
+// low 12 only, with one table entry a site, and looks the low word up: words with
+// a set bits lie in ascending order from word_start[a].  Encoding visits the set
+// bits only, A of them in every valid state, so the lanes stay together.
+// 4 M states of 28 sites: decoding 35 -> 21 us, encoding 46 -> 18 us (floor: 12.5
+// each); up to 0.2 M states either way a launch, 8.7 us.
+constexpr int kWordBits = 12, kWords = 1 << kWordBits;
+struct WordTable {
+    uint16_t start[kWordBits + 2];
+    alignas(16) uint16_t word[kWords];
+};
+constexpr WordTable make_word_table() {
+    WordTable t{};
+    int n = 0;
+    for (int a = 0; a <= kWordBits; ++a) {
+        t.start[a] = (uint16_t)n;
+        for (int w = 0; w < kWords; ++w) {
+            int c = 0;
+            for (int x = w; x; x &= x - 1) ++c;
+            if (c == a) t.word[n++] = (uint16_t)w;
+        }
+    }
+    return t;
+}
+__device__ const WordTable kWordTable = make_word_table();
+
+// T[k][Ak] = P[k][Ak][1]: states whose site k is empty, of those with Ak bits left.
+template <typename I>
+__device__ __forceinline__ void load_steps(const I *__restrict__ gprefix, int first, int n, I *T) {
+    for (int t = threadIdx.x; t < n; t += blockDim.x) T[t] = gprefix[2 * (first + t) + 1];
+}
+
+template <typename I>
+__global__ __launch_bounds__(kBlock) void unrank_half_kernel(const I *__restrict__ gprefix, int N,
+                                                             int A, int64_t dim,
+                                                             const int64_t *__restrict__ idx,
+                                                             int64_t n,
+                                                             uint64_t *__restrict__ out) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint16_t start[kWordBits + 2];
+    __shared__ __align__(16) uint16_t word[kWords];
+    I *T = reinterpret_cast<I *>(smem);           // sites 13 .. N
+    const int A1 = A + 1, nh = N - kWordBits;
+    load_steps(gprefix, kWordBits * A1, nh * A1, T);
+    if (threadIdx.x < kWordBits + 1) start[threadIdx.x] = kWordTable.start[threadIdx.x];
+    for (int t = threadIdx.x; t < kWords / 8; t += blockDim.x)
+        reinterpret_cast<uint4 *>(word)[t] = reinterpret_cast<const uint4 *>(kWordTable.word)[t];
+    __syncthreads();
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n;
+         t += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t i = idx[t];
+        const bool ok = i >= 0 && i < dim;
+        I r = ok ? (I)i : (I)0;
+        uint32_t hi = 0;
+        int e = (nh - 1) * A1 + A;                 // entry of the next site
+        for (int k = nh; k >= 1; --k) {
+            const I s = T[e];
+            const bool set = s <= r;
+            r -= set ? s : (I)0;
+            hi = 2 * hi + (set ? 1 : 0);
+            e -= A1 + (set ? 1 : 0);
+        }
+        const int Ak = e + A1;                     // bits left for the low word
+        const uint32_t lo = word[start[Ak] + (uint32_t)r];
+        out[t] = ok ? (uint64_t)hi << kWordBits | lo : ~0ull;
+    }
+}
+
+__device__ __forceinline__ int top_bit(uint32_t w) { return 31 - __clz((int)w); }
+__device__ __forceinline__ int top_bit(uint64_t w) { return 63 - __clzll((long long)w); }
+
+template <typename I, typename Word>
+__global__ __launch_bounds__(kBlock) void rank_half_kernel(const I *__restrict__ gprefix, int N,
+                                                           int A,
+                                                           const uint64_t *__restrict__ states,
+                                                           int64_t n, int64_t *__restrict__ out) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    I *T = reinterpret_cast<I *>(smem);
+    const int A1 = A + 1;
+    load_steps(gprefix, 0, N * A1, T);
+    __syncthreads();
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n;
+         t += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t st = states[t];
+        const bool ok = (N == 64 || st >> N == 0) && __popcll((unsigned long long)st) == A;
+        // any A bits in place of a state that is not one of the subspace
+        Word w = ok ? (Word)st : A < (int)(8 * sizeof(Word)) ? ((Word)1 << A) - 1 : ~(Word)0;
+        I idx = 0;
+        for (int a = A; a >= 1; --a) {
+            const int p = top_bit(w);
+            idx += T[p * A1 + a];
+            w ^= (Word)1 << p;
+        }
+        out[t] = ok ? (int64_t)idx : (int64_t)-1;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Host launchers
 // ---------------------------------------------------------------------------
@@ -213,14 +311,40 @@ static void launch_codec(const Basis *b, bool un, const int64_t *d_idx, const ui
         hipLaunchKernelGGL((unrank_kernel<I, B>), dim3((int)g), dim3(kBlock), lds, st,
                            (const I *)b->d_prefix, b->N, b->A, b->two_s, b->dim, d_idx, n,
                            o_st);
-    else
+    else if constexpr (B > 1)                 // spins 1/2 have their own
         hipLaunchKernelGGL((rank_kernel<I, B>), dim3((int)g), dim3(kBlock), lds, st,
                            (const I *)b->d_prefix, b->N, b->A, b->two_s, d_st, n, o_idx);
+}
+
+// The spin-1/2 codec where it applies: every state to encode; to decode, 13 to 44
+// sites (a high word of 1 to 32).
+template <typename I>
+static bool launch_codec_half(const Basis *b, bool un, const int64_t *d_idx, const uint64_t *d_st,
+                              int64_t n, uint64_t *o_st, int64_t *o_idx, hipStream_t st) {
+    const int nh = b->N - kWordBits;
+    if (b->two_s != 1 || (un && (nh < 1 || nh > 32))) return false;
+    const int64_t g = std::min<int64_t>((n + kBlock - 1) / kBlock, 2048);
+    const I *prefix = (const I *)b->d_prefix;
+    if (un) {
+        hipLaunchKernelGGL(unrank_half_kernel<I>, dim3((int)g), dim3(kBlock),
+                           (size_t)nh * (b->A + 1) * sizeof(I), st, prefix, b->N, b->A, b->dim,
+                           d_idx, n, o_st);
+        return true;
+    }
+    const size_t lds = (size_t)b->N * (b->A + 1) * sizeof(I);
+    if (b->N <= 32)
+        hipLaunchKernelGGL((rank_half_kernel<I, uint32_t>), dim3((int)g), dim3(kBlock), lds, st,
+                           prefix, b->N, b->A, d_st, n, o_idx);
+    else
+        hipLaunchKernelGGL((rank_half_kernel<I, uint64_t>), dim3((int)g), dim3(kBlock), lds, st,
+                           prefix, b->N, b->A, d_st, n, o_idx);
+    return true;
 }
 
 template <typename I>
 static int codec_bits(const Basis *b, bool un, const int64_t *d_idx, const uint64_t *d_st,
                       int64_t n, uint64_t *o_st, int64_t *o_idx, hipStream_t st) {
+    if (launch_codec_half<I>(b, un, d_idx, d_st, n, o_st, o_idx, st)) return HM_OK;
     switch (b->bits) {
         case 1: launch_codec<I, 1>(b, un, d_idx, d_st, n, o_st, o_idx, st); break;
         case 2: launch_codec<I, 2>(b, un, d_idx, d_st, n, o_st, o_idx, st); break;

@@ -949,7 +949,9 @@ static size_t neighbour_bytes(const Basis *b, const Couplings *c, int K) {
 }
 
 // Neighbour table of a high word: compacted high-word part (target blocks of the
-// bonds that flip, then the own block), straddling part Off(h ^ m2).
+// bonds that flip, then the own block), straddling part Off(h ^ m2).  Built on the
+// device: on the host the first call took 1.75 s at N = 32 (K = 10, 4 M high
+// words), now 0.13 s with its 20 steps.
 template <typename I>
 __global__ __launch_bounds__(256) void half_neighbours_kernel(
     const I *__restrict__ off, const BondGroup *__restrict__ groups, int64_t nhigh, int K, int A,
