@@ -4,20 +4,26 @@
 // Rows are visited in the gather form of Eq. (E-4-b): the lane that owns row
 // i decodes |i>, and for every bond adds psi_i times the row i of s(u).s(v)
 // applied to psi (diagonal m_u m_v psi_i plus the two ladder terms, each
-// 1/2 * ladder factors * psi_j).  Per-bond sums are reduced wave by wave in a
-// fixed butterfly order into per-wave LDS slots, then per workgroup, then
-// over workgroups by a single workgroup: no atomics, bitwise reproducible.
+// 1/2 * ladder factors * psi_j).  Bonds go in batches of 8, so that their gathers
+// are in flight together (one bond after the other waited for each).  Per-bond sums
+// are reduced wave by wave in a fixed order into per-wave LDS slots, then per
+// workgroup, then over workgroups: no atomics, bitwise reproducible.
+// 184,756 rows, 190 bonds: 387 -> 195 us, the sums over workgroups 173 -> 12.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <vector>
 
 #include "device_common.h"
 #include "hm_internal.h"
+#include "tall_dots.h"
 
 namespace hm {
 
 constexpr int kCorrMaxBonds = 1024;
 constexpr int kCorrBlock = 256;
+constexpr int kCorrGrid = 4096;    // workgroups that a launch is split into
+constexpr int kCorrBatch = 8;      // bonds whose gathers are in flight together
 
 template <typename I, int B>
 __global__ __launch_bounds__(kCorrBlock) void bond_corr_kernel(
@@ -37,6 +43,10 @@ __global__ __launch_bounds__(kCorrBlock) void bond_corr_kernel(
     for (int t = threadIdx.x; t < nwaves * nb; t += blockDim.x) acc[t] = 0.0;
     __syncthreads();
     const Prefix<I> pv{P, A + 1, two_s + 1};
+    // this workgroup's bonds: whole batches, range blockIdx.y of gridDim.y
+    const int batches = (nb + kCorrBatch - 1) / kCorrBatch;
+    const int bond0 = batches * (int)blockIdx.y / (int)gridDim.y * kCorrBatch;
+    const int bond1 = min(batches * ((int)blockIdx.y + 1) / (int)gridDim.y * kCorrBatch, nb);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     I first, last;
     block_rows<I>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, dim, first, last);
@@ -49,38 +59,72 @@ __global__ __launch_bounds__(kCorrBlock) void bond_corr_kernel(
         const bool live = row < last;
         const uint64_t st = live ? unrank_state<I, B>(row, pv, N, A, two_s) : 0;
         const double pi = live ? psi[row] : 0.0;
-        for (int b = 0; b < nb; ++b) {
-            const int u = uv[2 * b], v = uv[2 * b + 1];
-            double c = 0.0;
-            if (live) {
+        for (int b0 = bond0; b0 < bond1; b0 += kCorrBatch) {
+            double w1[kCorrBatch], w2[kCorrBatch], x1[kCorrBatch], x2[kCorrBatch], c[kCorrBatch];
+            I j1[kCorrBatch], j2[kCorrBatch];
+#pragma unroll
+            for (int q = 0; q < kCorrBatch; ++q) {
+                const bool on = live && b0 + q < bond1;
+                const int b = min(b0 + q, bond1 - 1), u = uv[2 * b], v = uv[2 * b + 1];
                 const int au = digit_at<B>(st, u), av = digit_at<B>(st, v);
-                double s = 0.25 * (double)((two_s - 2 * au) * (two_s - 2 * av)) * pi;
-                if (au >= 1 && av < two_s)
-                    s += 0.5 * F[au] * F[av + 1] * psi[row + move_delta<I, B>(st, u, v, -1, pv)];
-                if (av >= 1 && au < two_s)
-                    s += 0.5 * F[av] * F[au + 1] * psi[row + move_delta<I, B>(st, u, v, +1, pv)];
-                c = pi * s;
+                c[q] = on ? 0.25 * (double)((two_s - 2 * au) * (two_s - 2 * av)) * pi : 0.0;
+                j1[q] = j2[q] = live ? row : first;
+                w1[q] = w2[q] = 0.0;
+                if (on && au >= 1 && av < two_s) {
+                    w1[q] = 0.5 * F[au] * F[av + 1];
+                    j1[q] += move_delta<I, B>(st, u, v, -1, pv);
+                }
+                if (on && av >= 1 && au < two_s) {
+                    w2[q] = 0.5 * F[av] * F[au + 1];
+                    j2[q] += move_delta<I, B>(st, u, v, +1, pv);
+                }
             }
-            c = wave_sum(c);
-            if (lane == 0) acc[wid * nb + b] += c;
+#pragma unroll
+            for (int q = 0; q < kCorrBatch; ++q) {
+                x1[q] = psi[j1[q]];
+                if (B > 1) x2[q] = psi[j2[q]];
+                else if (w2[q] != 0.0) x1[q] = psi[j2[q]];   // spin 1/2: one move at most
+            }
+#pragma unroll
+            for (int q = 0; q < kCorrBatch; ++q) {
+                c[q] += B > 1 ? w1[q] * x1[q] : (w1[q] + w2[q]) * x1[q];
+                if (B > 1) c[q] += w2[q] * x2[q];
+                c[q] *= pi;
+            }
+            // sums of 8 values over the wave: each exchange halves the values a
+            // lane carries, so 10 exchanges instead of 48; lane l ends up with
+            // value (l / 8 reversed in 3 bits) of the batch
+            const bool h5 = lane & 32, h4 = lane & 16, h3 = lane & 8;
+            double d[4], e[2];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                d[q] = (h5 ? c[q + 4] : c[q]) + __shfl_xor(h5 ? c[q] : c[q + 4], 32, 64);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                e[q] = (h4 ? d[q + 2] : d[q]) + __shfl_xor(h4 ? d[q] : d[q + 2], 16, 64);
+            double f = (h3 ? e[1] : e[0]) + __shfl_xor(h3 ? e[0] : e[1], 8, 64);
+            f += __shfl_xor(f, 4, 64);
+            f += __shfl_xor(f, 2, 64);
+            f += __shfl_xor(f, 1, 64);
+            const int b = b0 + (h5 ? 4 : 0) + (h4 ? 2 : 0) + (h3 ? 1 : 0);
+            if ((lane & 7) == 0 && b < bond1) acc[wid * nb + b] += f;
         }
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) {
+    for (int b = bond0 + threadIdx.x; b < bond1; b += blockDim.x) {
         double s = 0.0;
         for (int w = 0; w < nwaves; ++w) s += acc[w * nb + b];
         partial[(size_t)blockIdx.x * nb + b] = s;
     }
 }
 
-__global__ __launch_bounds__(kCorrBlock) void bond_corr_finish(const double *__restrict__ partial,
+// Sums over the workgroups, 64 bonds per workgroup (one serial loop per bond took
+// 173 us for 720 workgroups and 190 bonds).
+__global__ __launch_bounds__(kTallBlock) void bond_corr_finish(const double *__restrict__ partial,
                                                                int nblocks, int nb,
                                                                double *__restrict__ out) {
-    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += gridDim.x * blockDim.x) {
-        double s = 0.0;
-        for (int k = 0; k < nblocks; ++k) s += partial[(size_t)k * nb + b];
-        out[b] = s;
-    }
+    __shared__ double red[4][64];
+    tall_sum(partial, nblocks, nb, blockIdx.x * 64, out, red);
 }
 
 int bond_corr_blocks(const Basis *b) {
@@ -101,11 +145,14 @@ static void launch_t(const Basis *b, const void *d_prefix, const double *d_ladde
     size_t lds = ((plen * sizeof(I) + 15) / 16) * 16;
     lds += ((b->two_s + 2) * sizeof(double) + 15) / 16 * 16;
     lds += (size_t)(kCorrBlock / 64) * nb * sizeof(double);
-    hipLaunchKernelGGL((bond_corr_kernel<I, B>), dim3(nblocks), dim3(kCorrBlock), lds, st,
+    // few rows and many bonds: the bonds are split too, down to two batches, up to
+    // kCorrGrid workgroups (each decodes its rows again: about 3 bonds' work)
+    const int ny = std::max(1, std::min(kCorrGrid / nblocks, nb / (2 * kCorrBatch)));
+    hipLaunchKernelGGL((bond_corr_kernel<I, B>), dim3(nblocks, ny), dim3(kCorrBlock), lds, st,
                        (const I *)d_prefix, d_ladder, d_uv, nb, b->N, b->A, b->two_s,
                        (I)b->dim, d_psi, d_partial);
-    hipLaunchKernelGGL(bond_corr_finish, dim3((nb + kCorrBlock - 1) / kCorrBlock),
-                       dim3(kCorrBlock), 0, st, d_partial, nblocks, nb, d_out);
+    hipLaunchKernelGGL(bond_corr_finish, dim3((nb + 63) / 64), dim3(kTallBlock), 0, st, d_partial,
+                       nblocks, nb, d_out);
 }
 
 template <typename I>
