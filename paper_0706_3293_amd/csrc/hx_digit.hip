@@ -92,6 +92,7 @@ struct DigitTables {
     void *blocks = nullptr;          // DigitBlock<I> in memory order
     uint32_t *groups = nullptr;      // [n_groups][R] blocks of one class
     uint32_t *rowblk = nullptr;      // block of every row (one lane per row)
+    uint16_t *d_rank = nullptr, *d_word = nullptr;   // device copies of rank and word
     void *mem = nullptr;             // the allocation that holds them
 };
 
@@ -896,6 +897,7 @@ static int put_blocks(const Basis *b, DigitTables *t) {
     }
     Arena arena;
     const size_t o_blocks = arena.add(blocks), o_groups = arena.add(groups);
+    const size_t o_rank = arena.add(t->rank), o_word = arena.add(t->word);
     const size_t o_rows = arena.reserve(b->digit.flat ? (size_t)b->dim * sizeof(uint32_t) : 0);
     const hipError_t e = arena.upload(&t->mem);
     if (e != hipSuccess)
@@ -905,6 +907,8 @@ static int put_blocks(const Basis *b, DigitTables *t) {
     t->blocks = m + o_blocks;
     t->groups = (uint32_t *)(m + o_groups);
     t->rowblk = (uint32_t *)(m + o_rows);
+    t->d_rank = (uint16_t *)(m + o_rank);
+    t->d_word = (uint16_t *)(m + o_word);
     if (b->digit.flat) {
         hipLaunchKernelGGL(digit_row_blocks<I>, dim3(kMaxGrid), dim3(kBlock), 0, nullptr,
                            (const DigitBlock<I> *)t->blocks, t->n_blocks, t->rowblk);
@@ -976,6 +980,48 @@ static bool exact_diagonal(const Basis *b, const Couplings *c) {
     return !any || sum <= std::ldexp(1.0, 24 + low);
 }
 
+// The low-word table: per bond of a low site (the first nF of the list, which is
+// sorted by u) and low word, the ranks that its two moves lead to (smax where a move
+// is not allowed; with the other site in the high word, the rank with u alone
+// changed) and the entry of its matrix elements; and per low word the diagonal part
+// of the bonds inside it.  Built on the host it made the first product with new
+// couplings 135 us at 1,107 rows and 155 at 73,789; now 80 and 95 (25 afterwards).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void digit_low(const BondDev *__restrict__ bonds, int nF, int K,
+                                                    int two_s, int words, int smax,
+                                                    const uint16_t *__restrict__ rank,
+                                                    const uint16_t *__restrict__ word,
+                                                    uint32_t *__restrict__ low,
+                                                    T *__restrict__ dlow) {
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= words) return;
+    const int W = two_s + 1, n = word[i];
+    constexpr uint32_t kMask = (1u << kRankBits) - 1u;
+    double dsum = 0.0;
+    for (int f = 0; f < nF; ++f) {
+        const int u = bonds[f].u, v = bonds[f].v;
+        int wu = 1, wv = 1;
+        for (int q = 0; q < u; ++q) wu *= W;
+        const int au = n / wu % W;
+        uint32_t r1, r2, e;
+        if (v < K) {
+            for (int q = 0; q < v; ++q) wv *= W;
+            const int av = n / wv % W;
+            r1 = au >= 1 && av < two_s ? rank[n - wu + wv] : smax;
+            r2 = av >= 1 && au < two_s ? rank[n + wu - wv] : smax;
+            e = (uint32_t)(au * W + av);
+            dsum += (double)(T)bonds[f].mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
+        } else {
+            r1 = au >= 1 ? rank[n - wu] : rank[n];
+            r2 = au < two_s ? rank[n + wu] : rank[n];
+            e = (uint32_t)au;
+        }
+        // (a class without blocks may be larger than the field, and is not used)
+        low[(size_t)f * words + i] = (r1 & kMask) | (r2 & kMask) << kRankBits | e << (2 * kRankBits);
+    }
+    dlow[i] = (T)dsum;
+}
+
 template <typename T, typename I, typename PI>
 static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTables *t,
                               DigitBonds *d) {
@@ -1008,50 +1054,21 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
         i += n;
     }
     d->n_ops = (int)ops.size();
-    // per front bond the matrix elements, with the roundings of row_hx, and
-    // per low word the ranks its moves lead to; per low word the diagonal part
-    std::vector<uint32_t> low(front.size() * words);
-    std::vector<double> dsum(words, 0.0);
-    const uint32_t zero = (uint32_t)t->smax;
-    std::vector<uint8_t> dig((size_t)K * words);      // digits of the low words
-    for (int i = 0; i < words; ++i)
-        for (int u = 0, n = t->word[i]; u < K; ++u, n /= W) dig[(size_t)u * words + i] = n % W;
-    for (size_t f = 0; f < front.size(); ++f) {
-        const BondDev &bd = *front[f];
-        const T mJ2 = (T)bd.mJ2;
+    // per front bond the matrix elements, with the roundings of row_hx
+    for (const BondDev *bd : front) {
+        const T mJ2 = (T)bd->mJ2;
         for (int au = 0; au < W; ++au)
             for (int av = 0; av < W; ++av) {
                 const T one = mJ2 * (T)b->ladder[au], two = mJ2 * (T)b->ladder[av];
                 cf.push_back(one * (T)b->ladder[av + 1]);
                 cf.push_back(two * (T)b->ladder[au + 1]);
             }
-        const int wu = (int)ipow(W, bd.u), wv = bd.v < K ? (int)ipow(W, bd.v) : 0;
-        const uint8_t *du = &dig[(size_t)bd.u * words];
-        const uint8_t *dv = bd.v < K ? &dig[(size_t)bd.v * words] : nullptr;
-        for (int i = 0; i < words; ++i) {
-            const int n = t->word[i], au = du[i];
-            uint32_t r1, r2, e;
-            if (dv) {
-                const int av = dv[i];
-                r1 = au >= 1 && av < two_s ? t->rank[n - wu + wv] : zero;
-                r2 = av >= 1 && au < two_s ? t->rank[n + wu - wv] : zero;
-                e = (uint32_t)(au * W + av);
-                dsum[i] += (double)(T)bd.mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
-            } else {
-                r1 = au >= 1 ? t->rank[n - wu] : t->rank[n];
-                r2 = au < two_s ? t->rank[n + wu] : t->rank[n];
-                e = (uint32_t)au;
-            }
-            // (a class without blocks may be larger than the field, and is not used)
-            constexpr uint32_t kMask = (1u << kRankBits) - 1u;
-            low[f * words + i] = (r1 & kMask) | (r2 & kMask) << kRankBits | e << (2 * kRankBits);
-        }
     }
-    std::vector<T> dlow(dsum.begin(), dsum.end());
-    const size_t nblk = (size_t)t->n_blocks;
     Arena arena;
-    const size_t o_ops = arena.add(ops), o_cf = arena.add(cf), o_low = arena.add(low);
-    const size_t o_dlow = arena.add(dlow);
+    const size_t o_ops = arena.add(ops), o_cf = arena.add(cf);
+    const size_t o_low = arena.reserve(front.size() * words * sizeof(uint32_t));
+    const size_t o_dlow = arena.reserve((size_t)words * sizeof(T));
+    const size_t nblk = (size_t)t->n_blocks;
     const size_t o_moves = arena.reserve(nblk * (d->mw / 4) * sizeof(DigitMoves<T, I>));
     const size_t o_mcnt = arena.reserve(nblk * sizeof(uint32_t));
     const size_t o_dhigh = arena.reserve(nblk * sizeof(T));
@@ -1073,6 +1090,9 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
     d->kdiag = chain ? m + o_kdiag : nullptr;
     d->hJ4 = m + o_hJ4;
     d->strad = m + o_strad;
+    hipLaunchKernelGGL(digit_low<T>, dim3((words + kBlock - 1) / kBlock), dim3(kBlock), 0, nullptr,
+                       c->dev, d->nF, K, two_s, words, t->smax, t->d_rank, t->d_word, d->low,
+                       (T *)d->dlow);
     const int grid = (int)std::min<int64_t>((t->n_blocks + kBlock - 1) / kBlock, kMaxGrid);
     hipLaunchKernelGGL((digit_rows<T, I, PI>), dim3(grid), dim3(kBlock), 0, nullptr,
                        (const PI *)b->d_prefix, (const DigitBlock<I> *)t->blocks, t->n_blocks, b->N,
