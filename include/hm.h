@@ -219,9 +219,13 @@ typedef struct hm_lanczos_opts {
                              kernels, bitwise equal results to direct
                              launches)                                    */
     int32_t kernel;       /* 0: automatic choice (one-workgroup launches
-                             for up to 3072 rows while one compute unit is
-                             faster, else the H x kernel that suits
-                             the basis); 1: generic digit kernel; 2:
+                             for up to 3072 rows: with full_reorth while
+                             one compute unit is faster, without it when
+                             dim x bonds <= 16384; else the H x kernel that
+                             suits the basis.  Without full_reorth, and up
+                             to 2^20 rows (s = 1/2 in FP64) or 2^19 (s >= 1),
+                             the coefficients are bit for bit those of
+                             kernel 3, 2 or 1); 1: generic digit kernel; 2:
                              spin-1/2 block kernel (if the basis is spin
                              1/2); 3: one-workgroup run (every step in one
                              launch of a single 1024-thread workgroup with

@@ -55,7 +55,7 @@ int hm_apply(hm_basis h, const double *J, const void *d_x, void *d_y, int32_t dt
     hm::HxPass p;
     p.x = d_x;
     p.y = d_y;
-    return hm::launch_hx(b, c, dtype, hm::choose_kernel(b, c, 0, dtype), p, (hipStream_t)stream);
+    return hm::launch_hx(b, c, dtype, hm::choose_kernel(b, c, 0, dtype, false), p, (hipStream_t)stream);
 }
 
 // Variant of hm_apply that forces one H x kernel (1: generic digits, 2: the
@@ -73,7 +73,7 @@ int hm_apply_kernel(hm_basis h, const double *J, const void *d_x, void *d_y, int
     HM_TRY(hm::get_couplings(b, J, &cref));
     const hm::Couplings *c = cref.get();
     if (kernel >= 3) return hm::launch_hx_ablation(b, c, dtype, kernel, d_x, d_y, (hipStream_t)stream);
-    const int k = hm::choose_kernel(b, c, kernel, dtype);
+    const int k = hm::choose_kernel(b, c, kernel, dtype, false);
     if (k < 0) return fail(HM_EINVAL, "kernel %d not applicable", kernel);
     hm::HxPass p;
     p.x = d_x;

@@ -22,6 +22,18 @@ __device__ __forceinline__ int xcd_logical_block(int b, int grid) {
     return (b % kXcds) * (grid / kXcds) + b / kXcds;
 }
 
+// Persistent sweep over the items of the spin-1/2 block kernel (grid a multiple
+// of 8; workgroup b runs on XCD b % 8): the XCDs take turns on runs of kSweepRun
+// consecutive items, so all eight work in the same region of x at any time and
+// gathers that reach far share the Infinity Cache, while a run keeps neighbouring
+// blocks within one XCD's L2.  Local index l of XCD x8 (its waves stride through l
+// together) maps to item (l / run) * 8 run + x8 run + l % run.
+constexpr uint32_t kSweepRun = 64;
+
+__device__ __forceinline__ uint32_t sweep_item(uint32_t l, uint32_t x8) {
+    return (l / kSweepRun) * (kXcds * kSweepRun) + x8 * kSweepRun + l % kSweepRun;
+}
+
 // Rows [first, last) of logical workgroup lb when `dim` rows are split into
 // `grid` contiguous ranges.
 template <typename I>

@@ -187,7 +187,7 @@ struct HxPass {
 int hx_partial_count(const Basis *b, int kernel);      // partial slots needed
 int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel,
               const HxPass &pass, hipStream_t st);
-int choose_kernel(const Basis *b, const Couplings *c, int requested, int dtype);
+int choose_kernel(const Basis *b, const Couplings *c, int requested, int dtype, bool plain_run);
 // Builds what kernel `kernel` needs on the device for these couplings (ahead
 // of a graph capture, where nothing may be allocated).
 int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel);

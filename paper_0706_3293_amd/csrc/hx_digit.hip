@@ -30,6 +30,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 #include <vector>
 
 #include "device_common.h"
@@ -181,12 +182,11 @@ __device__ __forceinline__ void lds_row<float, 1>(const float *p, float (&v)[1])
 template <>
 __device__ __forceinline__ void lds_row<double, 1>(const double *p, double (&v)[1]) { v[0] = *p; }
 
-// (2 m_u)(2 m_v) by the index of the two digits (FP32 only).
+// (2 m_u)(2 m_v) by the index of the two digits.
 template <typename T>
 __device__ __forceinline__ void stage_products(T *kt, int two_s) {
-    if constexpr (sizeof(T) == 4)
-        for (int t = threadIdx.x; t < (two_s + 1) * (two_s + 1); t += blockDim.x)
-            kt[t] = (T)((two_s - 2 * (t / (two_s + 1))) * (two_s - 2 * (t % (two_s + 1))));
+    for (int t = threadIdx.x; t < (two_s + 1) * (two_s + 1); t += blockDim.x)
+        kt[t] = (T)((two_s - 2 * (t / (two_s + 1))) * (two_s - 2 * (t % (two_s + 1))));
 }
 
 // W low-word bonds at once: the table entries, then the R rows' reads and
@@ -215,7 +215,7 @@ __device__ __forceinline__ void low_bonds(const uint32_t *__restrict__ low, int 
             off[m] += c[q][0] * x1[q][m];
             off[m] += c[q][1] * x2[q][m];
         }
-    if (sizeof(T) == 4 && chain)
+    if (chain)
 #pragma unroll
         for (int q = 0; q < W; ++q) {
             const T k = kt[e[q] >> (2 * kRankBits)];
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
     stage_products(kt, g.two_s);
     __syncthreads();
     const Const<T> *kdiag = as_const(g.kdiag), *hJ4 = as_const(g.hJ4);
-    const bool chain = sizeof(T) == 4 && g.kdiag;
+    const bool chain = g.kdiag != nullptr;
     const int nHc = chain ? g.nH : 0;
 
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
@@ -348,7 +348,6 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
                 const uint32_t e = lo[0], rk1 = e & ((1u << kRankBits) - 1u);
                 const uint32_t rk2 = (e >> kRankBits) & ((1u << kRankBits) - 1u);
                 const int au = (int)(e >> (2 * kRankBits));
-                const T sJ = op.mJ4[0] * (T)(two_s - 2 * au);
                 T g1[R], g2[R], c[R][2];
 #pragma unroll
                 for (int m = 0; m < R; ++m) {
@@ -359,8 +358,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
                     const T v1 = load_at(x, a1 ? so[0] + (I)rk1 : off0[m] + (I)r);
                     const T v2 = load_at(x, a2 ? so[1] + (I)rk2 : off0[m] + (I)r);
                     lds_row<T, 2>(cfb + (au * WW + av) * 2, c[m]);
-                    if constexpr (sizeof(T) == 8) diag[m] += sJ * (T)(two_s - 2 * av);
-                    else diag[m] += op.mJ4[0] * (T)((two_s - 2 * au) * (two_s - 2 * av));
+                    diag[m] += op.mJ4[0] * (T)((two_s - 2 * au) * (two_s - 2 * av));
                     g1[m] = a1 ? v1 : (T)0;
                     g2[m] = a2 ? v2 : (T)0;
                 }
@@ -462,7 +460,7 @@ __device__ __forceinline__ void flat_low_bonds(const uint32_t *__restrict__ low,
     for (int q = 0; q < W; ++q) {
         off += c[q][0] * x1[q];
         off += c[q][1] * x2[q];
-        if (sizeof(T) == 4 && chain) diag += op.mJ4[q0 + q] * kt[e[q] >> (2 * kRankBits)];
+        if (chain) diag += op.mJ4[q0 + q] * kt[e[q] >> (2 * kRankBits)];
     }
 }
 
@@ -482,7 +480,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
     stage_products(kt, two_s);
     __syncthreads();
     const Const<T> *hJ4 = as_const(g.hJ4);
-    const bool chain = sizeof(T) == 4 && g.kdiag;
+    const bool chain = g.kdiag != nullptr;
     const Const<DigitOp<T>> *ops = as_const(g.ops);
     I first, last;
     block_rows<I>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, dim, first, last);
@@ -535,15 +533,13 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
 #pragma unroll
             for (int q = 0; q < 4; ++q) off += m.cf[q] * (q0 + q < n ? xj[q] : (T)0);
         }
-        if (sizeof(T) == 4 && chain) {
-            const float4 *__restrict__ kd =
-                reinterpret_cast<const float4 *>(g.kdiag + (size_t)hb * g.nH);
+        if (chain) {
+            typedef T V4 __attribute__((ext_vector_type(4)));
+            const V4 *__restrict__ kd = reinterpret_cast<const V4 *>(g.kdiag + (size_t)hb * g.nH);
             for (int b = 0; b < g.nH; b += 4) {
-                const float4 k4 = kd[b / 4];
-                diag += hJ4[b] * k4.x;
-                diag += hJ4[b + 1] * k4.y;
-                diag += hJ4[b + 2] * k4.z;
-                diag += hJ4[b + 3] * k4.w;
+                const V4 k4 = kd[b / 4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) diag += hJ4[b + q] * k4[q];
             }
         }
         const T hv = diag * xi + off;
@@ -826,6 +822,8 @@ static int grid_of(int64_t n_groups) {
     return (int)std::max<int64_t>(g, 1);
 }
 
+// One lane per row: up to 2048 workgroups of 256 rows this is the generic kernel's
+// grid, so a run has that kernel's partial sums too.
 int hx_digit_grid(const Basis *b) {
     return b->digit.flat ? grid_of((b->dim + 63) / 64) : grid_of(b->digit.n_groups);
 }
@@ -973,24 +971,26 @@ static int digit_prepare(Basis *b, DigitTables **out) {
     return HM_OK;
 }
 
-// Whether FP32 holds every sum of diagonal terms of these couplings exactly
-// (multiples of one power of two, the largest below 2^24 of it; couplings of 1
-// or 0.25, say): then no order of summation rounds.
+// Whether T holds every sum of diagonal terms of these couplings exactly
+// (multiples of one power of two, the largest below 2^24 or 2^53 of it; couplings
+// of 1 or 0.25, say): then no order of summation rounds.
+template <typename T>
 static bool exact_diagonal(const Basis *b, const Couplings *c) {
+    constexpr int kBits = std::numeric_limits<T>::digits;
     double sum = 0.0;
     int low = 0;                          // smallest bit set in any -J/4
     bool any = false;
     for (const BondDev &bd : c->host) {
-        const float f = (float)bd.mJ4;
-        if (f == 0.0f) continue;
+        const T f = (T)bd.mJ4;
+        if (f == (T)0) continue;
         int e;
-        const float m = std::frexp(f, &e);
-        const int bit = e - 24 + __builtin_ctz((unsigned)std::abs((int)std::ldexp(m, 24)));
+        const double m = std::frexp((double)f, &e);
+        const int bit = e - kBits + __builtin_ctzll((uint64_t)std::fabs(std::ldexp(m, kBits)));
         low = any ? std::min(low, bit) : bit;
         any = true;
         sum += std::fabs((double)f) * b->two_s * b->two_s;
     }
-    return !any || sum <= std::ldexp(1.0, 24 + low);
+    return !any || sum < std::ldexp(1.0, kBits + low);
 }
 
 // The low-word table: per bond of a low site (the first nF of the list, which is
@@ -1085,7 +1085,7 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
     const size_t o_moves = arena.reserve(nblk * (d->mw / 4) * sizeof(DigitMoves<T, I>));
     const size_t o_mcnt = arena.reserve(nblk * sizeof(uint32_t));
     const size_t o_dhigh = arena.reserve(nblk * sizeof(T));
-    const bool chain = sizeof(T) == 4 && !exact_diagonal(b, c);
+    const bool chain = !exact_diagonal<T>(b, c);
     d->nH = chain ? (nH + 3) / 4 * 4 : 0;
     const size_t o_kdiag = arena.reserve(nblk * d->nH * sizeof(T));
     const size_t o_hJ4 = arena.reserve(d->nH * sizeof(T));
@@ -1247,7 +1247,7 @@ int launch_hx_digit(const Basis *cb, const Couplings *c, int dtype, const HxPass
     DigitTables *t = nullptr;
     const DigitBonds *d = nullptr;
     const int rc = digit_get(b, c, dtype, st, &t, &d);
-    if (rc == HM_ENOMEM && !p.partial) {
+    if (rc == HM_ENOMEM && !p.step.sigma) {
         // no memory for the tables, or a product captured before its first
         // use: the generic kernel's sums are the same bit for bit
         clear_error();

@@ -44,18 +44,6 @@ constexpr uint32_t kNoHigh = 0xFFFFFFFFu;      // padding slot of a high-word gr
 constexpr size_t kMaxNeighbourBytes = (size_t)8 << 30;
 constexpr int64_t kMaxHalfGrid = 1 << 20;   // workgroups (and FP64 partials) of one launch
 
-// Persistent sweep over the items (grid a multiple of 8; workgroup b runs on
-// XCD b % 8): the XCDs take turns on runs of kSweepRun consecutive items, so
-// all eight work in the same region of x at any time and gathers that reach
-// far share the Infinity Cache, while a run keeps neighbouring blocks within
-// one XCD's L2.  Local index l of XCD x8 (its waves stride through l
-// together) maps to item (l / run) * 8 run + x8 run + l % run.
-constexpr uint32_t kSweepRun = 64;
-
-__device__ __forceinline__ uint32_t sweep_item(uint32_t l, uint32_t x8) {
-    return (l / kSweepRun) * (kXcds * kSweepRun) + x8 * kSweepRun + l % kSweepRun;
-}
-
 // Eight bonds of one group, structure-of-arrays so one group is fetched with
 // a few wide scalar loads.
 //   low group:        m1 = bits u, v of the low word
@@ -790,6 +778,18 @@ static bool staged_pays(const Basis *b) {
 // Workgroups of the block kernel (= FP64 partial sums it writes) in the handle's
 // split, and in the automatic FP64 split (0 where it is not taken).
 int hx_half_grid(const Basis *b) { return grid_of(b, split_of(b)); }
+
+// Most items that a wave of the handle's (chunked) split takes in turn: the XCDs
+// take turns on runs of kSweepRun items, so small grids leave most of them idle.
+int hx_half_chain(const Basis *b) {
+    const HalfSplit s = split_of(b);
+    const int64_t n = item_count(b, s), all = kXcds * kSweepRun;
+    const int grid = grid_of(b, s);
+    const bool by_xcd = grid % kXcds == 0;
+    const int64_t most = by_xcd ? n / all * kSweepRun + std::min<int64_t>(n % all, kSweepRun) : n;
+    const int64_t waves = (int64_t)(by_xcd ? grid / kXcds : grid) * (s.block / 64);
+    return (int)((most + waves - 1) / waves);
+}
 int hx_staged_grid(const Basis *b) { return staged_pays(b) ? grid_of(b, staged_split(b)) : 0; }
 
 static hipError_t upload(void **dst, const void *src, size_t bytes) {
@@ -1190,7 +1190,7 @@ int launch_hx_half(const Basis *cb, const Couplings *c, int dtype, bool staged, 
     const HalfBonds *hb = nullptr;
     int rc = half_prepare(b, staged, &t);
     if (rc == HM_OK) rc = half_bonds(b, c, t, staged, &hb);
-    if (rc == HM_ENOMEM && staged && !p.partial) {   // a plain product: the handle's split
+    if (rc == HM_ENOMEM && staged && !p.step.sigma) {   // a plain product: the handle's split
         clear_error();
         (void)hipGetLastError();
         return launch_hx_half(b, c, dtype, false, p, st);

@@ -12,8 +12,17 @@
 // number of bonds), all coalesced, into LDS, and the first rows of the
 // high-word targets into registers; what follows reads LDS.  Tables are laid
 // out per block, so the wave-uniform reads are one round of scalar loads too.
-// The sums take the bonds in the order of hx_half_kernel (low word, high word,
-// straddling): at the same K the results are equal bit for bit.
+// The sums take the bonds in the order of hx_half_kernel in its own split at K0 low
+// sites (bonds below K0 in list order, bonds above, straddling ones), whatever the
+// split here, so the rows are equal bit for bit.  With K < K0 low sites a bond of
+// any kind here may belong to any of the three there: first low and straddling
+// bonds mixed (v < K0), then two lists of high-word bonds around the straddling
+// ones with v >= K0.
+//
+// A Lanczos run without reorthogonalization takes its dots from wg_dots_kernel,
+// item by item as hx_half_kernel's waves add them: past convergence such a run
+// amplifies its roundings (all-to-all model, 20 sites, 300 steps: to 4e-9 of
+// dE0/dJ), so rows and dots keep one order.
 #include <algorithm>
 #include <cstring>
 #include <vector>
@@ -25,6 +34,9 @@ namespace hm {
 
 int launch_hx_generic(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
                       hipStream_t st);
+
+int half_low_bits(const Basis *b);
+int hx_half_grid(const Basis *b);
 
 constexpr int kWgMaxK = 12;
 constexpr int kWgMaxHighBits = 20;
@@ -40,7 +52,7 @@ template <typename T>
 struct WgOp {
     int32_t n;           // bonds in use: 8, 4, 2 or 1
     uint32_t slot[2];    // a byte each
-    int32_t pad;
+    int32_t straddle;    // 0: both sites in the low word
     uint32_t m[8];
     T c[8];              // -J/2
 };
@@ -55,6 +67,8 @@ struct WgTables {
     void *mem = nullptr;
     uint16_t *d_rankL = nullptr, *d_unrankL = nullptr;
     uint32_t *d_off = nullptr, *d_blocks = nullptr;
+    uint2 *d_items = nullptr;        // hx_half_kernel's items: first row, rows
+    int n_items = 0;
 };
 
 static void free_wg(void *p) {
@@ -66,14 +80,14 @@ static void free_wg(void *p) {
 
 struct WgBonds {
     void *mem = nullptr;
-    void *low = nullptr, *strad = nullptr;   // WgOp<T>
+    void *front = nullptr, *strad = nullptr; // WgOp<T>: below K0, straddling K0
     uint32_t *vbit = nullptr;                // bit of every straddling high site
     uint32_t *hdr = nullptr;                 // [block][hw]: off, size | start << 16, flips, bits of
                                              // the straddling high sites by slot, then per slot:
-                                             // off, size
-    uint32_t *hoff = nullptr;                // [block][mh] target blocks of the high-word bonds
-    void *hcf = nullptr;                     // [block][mh] their -J/2
-    int nlow = 0, nstrad = 0, nslot = 0, mh = 0, hw = 0;
+                                             // off, size (flips: of the two lists, 16 bits each)
+    uint32_t *hoff = nullptr;                // [block][mh] target blocks of the high-word bonds,
+    void *hcf = nullptr;                     // [block][mh] their -J/2: mh1 of the first list
+    int nfront = 0, nstrad = 0, nslot = 0, mh1 = 0, mh = 0, hw = 0;
 };
 struct WgBondSet {
     WgBonds by_type[2];
@@ -90,11 +104,11 @@ static void free_wg_bonds(void *p) {
 template <typename T>
 struct WgArgs {
     const uint16_t *rankL, *unrankL;
-    const WgOp<T> *low, *strad;
+    const WgOp<T> *front, *strad;
     const uint32_t *hdr, *hoff;
     const T *hcf;
     uint32_t n_blocks, run;
-    int K, nlow, nstrad, nslot, mh, hw, stride;
+    int K, nfront, nstrad, nslot, mh1, mh, hw, stride;
     double shift;
 };
 
@@ -163,7 +177,7 @@ __global__ __launch_bounds__(256) void hx_half_wg_kernel(
     const T shift = (T)g.shift;
     const Const<uint32_t> *hdrs = as_const(g.hdr), *hoffs = as_const(g.hoff);
     const Const<T> *hcfs = as_const(g.hcf);
-    const Const<WgOp<T>> *low = as_const(g.low), *strad = as_const(g.strad);
+    const Const<WgOp<T>> *front = as_const(g.front), *strad = as_const(g.strad);
     // XCDs (workgroup b runs on XCD b % 8) take turns on runs of g.run blocks
     const bool by_xcd = gridDim.x % kXcds == 0;
     const uint32_t x8 = by_xcd ? blockIdx.x % kXcds : 0;
@@ -177,7 +191,7 @@ __global__ __launch_bounds__(256) void hx_half_wg_kernel(
         const Const<uint32_t> *hdr = hdrs + (size_t)(any ? it : 0) * g.hw;
         const uint32_t off = hdr[0], hmask = hdr[3];
         const int S = any ? (int)(hdr[1] & 0xffffu) : 0, cs = (int)(hdr[1] >> 16);
-        const int nf = (int)hdr[2];
+        const int nf = (int)(hdr[2] & 0xffffu), nc = (int)(hdr[2] >> 16);
         // one round of coalesced loads: this block and those its straddling
         // bonds reach
         for (int r = threadIdx.x; any && r < g.stride; r += blockDim.x) {
@@ -212,43 +226,48 @@ __global__ __launch_bounds__(256) void hx_half_wg_kernel(
             const uint32_t r = (uint32_t)r0 + threadIdx.x;
             if ((int)r >= S) break;
             const uint32_t L = g.unrankL[cs + r];
-            // the first piece of high-word targets is on its way meanwhile
-            T xh[kWgPiece];
+            // the first pieces of high-word targets are on their way meanwhile
+            T xh[kWgPiece], xc[kWgPiece];
 #pragma unroll
-            for (int q = 0; q < kWgPiece; ++q) xh[q] = q < g.mh ? load_at(x, hoff[q] + r) : (T)0;
+            for (int q = 0; q < kWgPiece; ++q) xh[q] = q < g.mh1 ? load_at(x, hoff[q] + r) : (T)0;
+#pragma unroll
+            for (int q = 0; q < kWgPiece; ++q)
+                xc[q] = g.mh1 + q < g.mh ? load_at(x, hoff[g.mh1 + q] + r) : (T)0;
             T pv = 0;
             if (prev) pv = load_at(prev, off + r);
             const T xi = xs[r];
             T acc = 0;
-            for (int o = 0; o < g.nlow; ++o) {
-                const Const<WgOp<T>> &op = low[o];
-                if (op.n == 8) wg_low<8, T>(op, L, r, rankL, xs, xi, acc);
-                else if (op.n == 4) wg_low<4, T>(op, L, r, rankL, xs, xi, acc);
-                else if (op.n == 2) wg_low<2, T>(op, L, r, rankL, xs, xi, acc);
-                else wg_low<1, T>(op, L, r, rankL, xs, xi, acc);
-            }
-            // bonds inside the high word that flip for h (padded with the own
-            // block and coefficient 0)
-            if (nf > 0) {
-#pragma unroll
-                for (int q = 0; q < kWgPiece; ++q) acc += hcf[q] * (xh[q] - xi);
-                for (int q0 = kWgPiece; q0 < nf; q0 += kWgPiece) {
-#pragma unroll
-                    for (int q = 0; q < kWgPiece; ++q) xh[q] = load_at(x, hoff[q0 + q] + r);
-#pragma unroll
-                    for (int q = 0; q < kWgPiece; ++q) acc += hcf[q0 + q] * (xh[q] - xi);
-                }
-            }
-            // bonds with one site in each word, by low site
-            for (int o = 0; o < g.nstrad; ++o) {
-                const Const<WgOp<T>> &op = strad[o];
+            auto straddle = [&](const Const<WgOp<T>> &op) {
                 const uint32_t m1 = op.m[0], rk = rankL[L ^ m1];
                 const bool set = (L & m1) != 0;
                 if (op.n == 8) wg_straddle<8, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
                 else if (op.n == 4) wg_straddle<4, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
                 else if (op.n == 2) wg_straddle<2, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
                 else wg_straddle<1, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
+            };
+            // high-word bonds that flip for h, n of them from place `at` of the
+            // block's list (padded with the own block and coefficient 0); the first
+            // piece is loaded
+            auto high = [&](int at, int n, T (&xj)[kWgPiece]) {
+                for (int q0 = 0; q0 < n; q0 += kWgPiece) {
+                    if (q0 > 0)
+#pragma unroll
+                        for (int q = 0; q < kWgPiece; ++q) xj[q] = load_at(x, hoff[at + q0 + q] + r);
+#pragma unroll
+                    for (int q = 0; q < kWgPiece; ++q) acc += hcf[at + q0 + q] * (xj[q] - xi);
+                }
+            };
+            for (int o = 0; o < g.nfront; ++o) {
+                const Const<WgOp<T>> &op = front[o];
+                if (op.straddle) straddle(op);
+                else if (op.n == 8) wg_low<8, T>(op, L, r, rankL, xs, xi, acc);
+                else if (op.n == 4) wg_low<4, T>(op, L, r, rankL, xs, xi, acc);
+                else if (op.n == 2) wg_low<2, T>(op, L, r, rankL, xs, xi, acc);
+                else wg_low<1, T>(op, L, r, rankL, xs, xi, acc);
             }
+            high(0, nf, xh);
+            for (int o = 0; o < g.nstrad; ++o) straddle(strad[o]);
+            high(g.mh1, nc, xc);
             const T hv = shift * xi + acc;
             double w = sigma * (double)hv;
             if (prev) w -= cprev * (double)pv;
@@ -266,14 +285,57 @@ __global__ __launch_bounds__(256) void hx_half_wg_kernel(
     lz_end(step, red, sigma, cprev);
 }
 
+// <w, v_k> as hx_half_kernel adds it: a wave's lanes go through its items in turn,
+// a row each.  Needs the pass that wrote w and the step's scalars to be over.  A
+// launch of 4 us, for what the rows' kernel saves (20 sites, 190 bonds: H x 41 ->
+// 25 us).
+__global__ __launch_bounds__(kBlock) void wg_dots_kernel(const uint2 *__restrict__ items,
+                                                         uint32_t n_items,
+                                                         const double *__restrict__ w,
+                                                         const double *__restrict__ x,
+                                                         const double *__restrict__ sigma_k,
+                                                         double *__restrict__ partial) {
+    const double sigma = *sigma_k;
+    if (sigma == 0.0) return;
+    __shared__ double red[16];
+    const bool by_xcd = gridDim.x % kXcds == 0;
+    const uint32_t x8 = by_xcd ? blockIdx.x % kXcds : 0, nw = kBlock / 64;
+    const uint32_t wl = __builtin_amdgcn_readfirstlane(
+        (by_xcd ? blockIdx.x / kXcds : blockIdx.x) * nw + (threadIdx.x >> 6));
+    const uint32_t stride = (by_xcd ? gridDim.x / kXcds : gridDim.x) * nw;
+    const uint32_t lane = threadIdx.x & 63;
+    const Const<uint2> *it = as_const(items);
+    double dot = 0.0;
+    constexpr int U = 4;                          // items in flight
+    for (uint32_t l = wl;; l += U * stride) {
+        if ((by_xcd ? sweep_item(l, x8) : l) >= n_items) break;
+        double a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t lu = l + u * stride, i = by_xcd ? sweep_item(lu, x8) : lu;
+            const uint32_t row0 = i < n_items ? it[i].x : 0, rows = i < n_items ? it[i].y : 0;
+            const uint32_t row = lane < rows ? row0 + lane : 0;
+            const double wr = w[row], xr = x[row];
+            a[u] = lane < rows ? wr : 0.0;
+            b[u] = lane < rows ? sigma * xr : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) dot = __builtin_fma(a[u], b[u], dot);
+    }
+    const double s = block_sum(dot, red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+}
+
 // Rows of the block tables, one thread per block.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void wg_rows(const uint32_t *__restrict__ blocks, int64_t n,
-                                                  const uint32_t *__restrict__ off, int K, int A,
+                                                  const uint32_t *__restrict__ off, int K, int K0,
+                                                  int A,
                                                   const int *__restrict__ cls,
                                                   const BondDev *__restrict__ bonds, int nb,
                                                   const uint32_t *__restrict__ vbit, int nslot,
-                                                  int mh, int hw, uint32_t *__restrict__ hdr,
+                                                  int mh1, int mh, int hw,
+                                                  uint32_t *__restrict__ hdr,
                                                   uint32_t *__restrict__ hoff,
                                                   T *__restrict__ hcf) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
@@ -293,20 +355,23 @@ __global__ __launch_bounds__(kBlock) void wg_rows(const uint32_t *__restrict__ b
             hmask |= (h & vbit[s]) ? 1u << s : 0u;
         }
         row[3] = hmask;
-        int c = 0;
+        // the bonds that straddle K0 in the second list
+        int c[2] = {0, 0};
         for (int b = 0; b < nb; ++b) {
             if (bonds[b].u < K) continue;
             const uint32_t m = 1u << (bonds[b].u - K) | 1u << (bonds[b].v - K);
             if (__popc(h & m) != 1) continue;
-            hoff[(size_t)i * mh + c] = off[h ^ m];
-            hcf[(size_t)i * mh + c] = (T)bonds[b].mJ2;
-            ++c;
+            const int list = bonds[b].u < K0 && bonds[b].v >= K0;
+            const size_t at = (size_t)i * mh + (list ? mh1 + c[1]++ : c[0]++);
+            hoff[at] = off[h ^ m];
+            hcf[at] = (T)bonds[b].mJ2;
         }
-        row[2] = (uint32_t)c;
-        for (; c < mh; ++c) {
-            hoff[(size_t)i * mh + c] = own;
-            hcf[(size_t)i * mh + c] = 0;
-        }
+        row[2] = (uint32_t)c[0] | (uint32_t)c[1] << 16;
+        for (int list = 0; list < 2; ++list)
+            for (int q = (list ? mh1 : 0) + c[list]; q < (list ? mh : mh1); ++q) {
+                hoff[(size_t)i * mh + q] = own;
+                hcf[(size_t)i * mh + q] = 0;
+            }
     }
 }
 
@@ -389,7 +454,7 @@ bool wg_fits(const Basis *b, const Couplings *c, int dtype) {
     uint32_t vm;
     wg_counts(c, K, &nL, &nH, &nS, &nslot, &vm);
     return wg_lds(K, nslot, 8) <= kWgMaxLds &&
-           (size_t)n * ((nH + 8) * 12 + 64 + 8 * nslot) <= kWgMaxTables;
+           (size_t)n * ((nH + 16) * 12 + 64 + 8 * nslot) <= kWgMaxTables;
 }
 
 static int wg_prepare(Basis *b, WgTables **out) {
@@ -429,14 +494,26 @@ static int wg_prepare(Basis *b, WgTables **out) {
                     (unsigned long long)o, (long long)b->dim);
     }
     t->n_blocks = (int64_t)t->blocks.size();
+    // the items of hx_half_kernel: 64 rows of a block of its split
+    const int K0 = half_low_bits(b);
+    std::vector<uint2> items;
+    uint32_t row = 0;
+    for (uint32_t h = 0; h < 1u << (b->N - K0); ++h) {
+        const int S = (int)choose2(K0, b->A - __builtin_popcount(h));
+        for (int c = 0; c < S; c += 64) items.push_back(uint2{row + c, (uint32_t)std::min(64, S - c)});
+        row += S;
+    }
+    t->n_items = (int)items.size();
     auto al = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t o_un = al(nlow * 2), o_off = o_un + al(nlow * 2),
-                 o_blk = o_off + al(t->off.size() * 4), total = o_blk + al(t->blocks.size() * 4);
+                 o_blk = o_off + al(t->off.size() * 4), o_it = o_blk + al(t->blocks.size() * 4),
+                 total = o_it + al(items.size() * sizeof(uint2));
     std::vector<unsigned char> host(total);
     std::memcpy(host.data(), t->rankL.data(), nlow * 2);
     std::memcpy(host.data() + o_un, t->unrankL.data(), nlow * 2);
     std::memcpy(host.data() + o_off, t->off.data(), t->off.size() * 4);
     std::memcpy(host.data() + o_blk, t->blocks.data(), t->blocks.size() * 4);
+    std::memcpy(host.data() + o_it, items.data(), items.size() * sizeof(uint2));
     hipError_t e = hipMalloc(&t->mem, total);
     if (e == hipSuccess) e = hipMemcpy(t->mem, host.data(), total, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
@@ -449,6 +526,7 @@ static int wg_prepare(Basis *b, WgTables **out) {
     t->d_unrankL = (uint16_t *)(m + o_un);
     t->d_off = (uint32_t *)(m + o_off);
     t->d_blocks = (uint32_t *)(m + o_blk);
+    t->d_items = (uint2 *)(m + o_it);
     b->wg_tables = t;
     b->wg_tables_free = free_wg;
     *out = t;
@@ -467,36 +545,44 @@ static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t
         if (vmask >> v & 1) vbit.push_back(1u << v);
     // runs of low-word bonds, and of the straddling bonds of one low site, in
     // eights, fours, twos and ones
-    std::vector<const BondDev *> lo, st;
-    for (const BondDev &bd : c->host)
-        if (bd.u < K) (bd.v < K ? lo : st).push_back(&bd);
-    auto piece = [](size_t n) { return n >= 8 ? 8 : n >= 4 ? 4 : n >= 2 ? 2 : 1; };
-    std::vector<WgOp<T>> low, strad;
-    for (size_t i = 0; i < lo.size();) {
-        WgOp<T> op{};
-        op.n = piece(lo.size() - i);
-        for (int q = 0; q < op.n; ++q, ++i) {
-            op.m[q] = 1u << lo[i]->u | 1u << lo[i]->v;
-            op.c[q] = (T)lo[i]->mJ2;
-        }
-        low.push_back(op);
+    const int K0 = half_low_bits(b);
+    std::vector<const BondDev *> below, across;      // first site low; second below K0, or not
+    int nH2 = 0;
+    for (const BondDev &bd : c->host) {
+        if (bd.u < K) (bd.v < K0 ? below : across).push_back(&bd);
+        else if (bd.u < K0 && bd.v >= K0) ++nH2;
     }
-    for (size_t i = 0; i < st.size();) {
-        size_t n = 1;
-        while (i + n < st.size() && st[i + n]->u == st[i]->u) ++n;
-        WgOp<T> op{};
-        op.n = piece(n);
-        op.m[0] = 1u << st[i]->u;
-        for (int q = 0; q < op.n; ++q, ++i) {
-            const int slot = __builtin_popcount(vmask & ((1u << (st[i]->v - K)) - 1u));
-            op.slot[q / 4] |= (uint32_t)slot << (8 * (q % 4));
-            op.c[q] = (T)st[i]->mJ2;
+    auto pieces = [&](const std::vector<const BondDev *> &v) {
+        std::vector<WgOp<T>> ops;
+        for (size_t i = 0; i < v.size();) {
+            const bool straddle = v[i]->v >= K;
+            size_t n = 1;
+            while (i + n < v.size() && (v[i + n]->v >= K) == straddle &&
+                   (!straddle || v[i + n]->u == v[i]->u))
+                ++n;
+            WgOp<T> op{};
+            op.n = n >= 8 ? 8 : n >= 4 ? 4 : n >= 2 ? 2 : 1;
+            op.straddle = straddle;
+            if (straddle) op.m[0] = 1u << v[i]->u;
+            for (int q = 0; q < op.n; ++q, ++i) {
+                op.c[q] = (T)v[i]->mJ2;
+                if (!straddle) {
+                    op.m[q] = 1u << v[i]->u | 1u << v[i]->v;
+                    continue;
+                }
+                const int slot = __builtin_popcount(vmask & ((1u << (v[i]->v - K)) - 1u));
+                op.slot[q / 4] |= (uint32_t)slot << (8 * (q % 4));
+            }
+            ops.push_back(op);
         }
-        strad.push_back(op);
-    }
-    d->nlow = (int)low.size();
+        return ops;
+    };
+    const std::vector<WgOp<T>> front = pieces(below), strad = pieces(across);
+    d->nfront = (int)front.size();
     d->nstrad = (int)strad.size();
-    d->mh = (nH + kWgPiece - 1) / kWgPiece * kWgPiece;
+    auto padded = [](int n) { return (n + kWgPiece - 1) / kWgPiece * kWgPiece; };
+    d->mh1 = padded(nH - nH2);
+    d->mh = d->mh1 + padded(nH2);
     d->hw = (4 + 2 * d->nslot + 3 + 8) / 4 * 4;       // slot reads go in fours
     std::vector<int> cls(2 * (K + 1));
     for (int a = 0; a <= K; ++a) {
@@ -511,7 +597,7 @@ static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t
         return at;
     };
     const size_t nblk = (size_t)t->n_blocks;
-    const size_t o_low = add(low.size() * sizeof(WgOp<T>)),
+    const size_t o_front = add(front.size() * sizeof(WgOp<T>)),
                  o_str = add(strad.size() * sizeof(WgOp<T>)), o_vb = add(vbit.size() * 4),
                  o_cls = add(cls.size() * 4), hostlen = total;
     const size_t o_hdr = add(nblk * d->hw * 4), o_hoff = add(nblk * d->mh * 4),
@@ -520,7 +606,7 @@ static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t
     auto put = [&](size_t at, const void *p, size_t bytes) {
         if (bytes) std::memcpy(host.data() + at, p, bytes);
     };
-    put(o_low, low.data(), low.size() * sizeof(WgOp<T>));
+    put(o_front, front.data(), front.size() * sizeof(WgOp<T>));
     put(o_str, strad.data(), strad.size() * sizeof(WgOp<T>));
     put(o_vb, vbit.data(), vbit.size() * 4);
     put(o_cls, cls.data(), cls.size() * 4);
@@ -528,7 +614,7 @@ static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t
     if (e == hipSuccess) e = hipMemcpy(d->mem, host.data(), hostlen, hipMemcpyHostToDevice);
     if (e != hipSuccess) return e;
     unsigned char *m = (unsigned char *)d->mem;
-    d->low = m + o_low;
+    d->front = m + o_front;
     d->strad = m + o_str;
     d->vbit = (uint32_t *)(m + o_vb);
     d->hdr = (uint32_t *)(m + o_hdr);
@@ -536,8 +622,8 @@ static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t
     d->hcf = m + o_hcf;
     const int grid = (int)std::min<int64_t>((t->n_blocks + kBlock - 1) / kBlock, kMaxGrid);
     hipLaunchKernelGGL(wg_rows<T>, dim3(grid), dim3(kBlock), 0, nullptr, t->d_blocks, t->n_blocks,
-                       t->d_off, K, b->A, (const int *)(m + o_cls), c->dev, c->nb, d->vbit,
-                       d->nslot, d->mh, d->hw, d->hdr, d->hoff, (T *)d->hcf);
+                       t->d_off, K, K0, b->A, (const int *)(m + o_cls), c->dev, c->nb, d->vbit,
+                       d->nslot, d->mh1, d->mh, d->hw, d->hdr, d->hoff, (T *)d->hcf);
     e = hipGetLastError();
     // other streams may use the tables from now on
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
@@ -593,7 +679,7 @@ static void launch_wg_t(const Basis *b, const Couplings *c, const WgTables *t, c
     WgArgs<T> g{};
     g.rankL = t->d_rankL;
     g.unrankL = t->d_unrankL;
-    g.low = (const WgOp<T> *)d->low;
+    g.front = (const WgOp<T> *)d->front;
     g.strad = (const WgOp<T> *)d->strad;
     g.hdr = d->hdr;
     g.hoff = d->hoff;
@@ -601,9 +687,10 @@ static void launch_wg_t(const Basis *b, const Couplings *c, const WgTables *t, c
     g.n_blocks = (uint32_t)t->n_blocks;
     g.run = 1;
     g.K = t->K;
-    g.nlow = d->nlow;
+    g.nfront = d->nfront;
     g.nstrad = d->nstrad;
     g.nslot = d->nslot;
+    g.mh1 = d->mh1;
     g.mh = d->mh;
     g.hw = d->hw;
     g.stride = t->smax;
@@ -623,20 +710,28 @@ static void launch_wg_t(const Basis *b, const Couplings *c, const WgTables *t, c
 #undef HM_LAUNCH
 }
 
-int launch_hx_wg(const Basis *cb, const Couplings *c, int dtype, const HxPass &p, hipStream_t st) {
+// items: the dots of hx_half_kernel (a launch of their own; FP64).
+int launch_hx_wg(const Basis *cb, const Couplings *c, int dtype, bool items, const HxPass &p,
+                 hipStream_t st) {
     Basis *b = const_cast<Basis *>(cb);
     WgTables *t = nullptr;
     const WgBonds *d = nullptr;
     const int rc = wg_get(b, c, dtype, st, &t, &d);
-    if (rc == HM_ENOMEM && !p.partial) {
+    if (rc == HM_ENOMEM && !p.step.sigma) {
         // no memory for the tables, or a product captured before its first use
         clear_error();
         (void)hipGetLastError();
         return launch_hx_generic(b, c, dtype, p, st);
     }
     HM_TRY(rc);
-    if (dtype == HM_F64) launch_wg_t<double>(b, c, t, d, p, st);
-    else launch_wg_t<float>(b, c, t, d, p, st);
+    HxPass rows = p;
+    if (items) rows.partial = nullptr;
+    if (dtype == HM_F64) launch_wg_t<double>(b, c, t, d, rows, st);
+    else launch_wg_t<float>(b, c, t, d, rows, st);
+    if (items && p.partial)
+        hipLaunchKernelGGL(wg_dots_kernel, dim3(hx_half_grid(b)), dim3(kBlock), 0, st, t->d_items,
+                           (uint32_t)t->n_items, (const double *)p.y, (const double *)p.x,
+                           p.step.sigma + p.step.k, p.partial);
     HM_HIP(hipGetLastError());
     return HM_OK;
 }

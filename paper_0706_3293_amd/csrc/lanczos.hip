@@ -35,6 +35,7 @@ int hx_generic_grid(const Basis *b);
 int launch_hx_half(const Basis *b, const Couplings *c, int dtype, bool staged, const HxPass &p,
                    hipStream_t st);
 int hx_half_grid(const Basis *b);
+int hx_half_chain(const Basis *b);
 int hx_staged_grid(const Basis *b);
 bool half_supported(const Basis *b);
 int half_prepare_tables(Basis *b, const Couplings *c, bool staged);
@@ -46,7 +47,8 @@ int launch_hx_digit(const Basis *b, const Couplings *c, int dtype, const HxPass 
 int hx_digit_grid(const Basis *b);
 int digit_prepare_tables(Basis *b, const Couplings *c, int dtype);
 bool digit_fits(const Basis *b, const Couplings *c);
-int launch_hx_wg(const Basis *b, const Couplings *c, int dtype, const HxPass &p, hipStream_t st);
+int launch_hx_wg(const Basis *b, const Couplings *c, int dtype, bool items, const HxPass &p,
+                 hipStream_t st);
 int hx_wg_grid(const Basis *b);
 int wg_prepare_tables(Basis *b, const Couplings *c, int dtype);
 bool wg_fits(const Basis *b, const Couplings *c, int dtype);
@@ -55,14 +57,30 @@ bool wg_fits(const Basis *b, const Couplings *c, int dtype);
 // and its tables fit the budget, else the generic digit kernel), 1 = generic,
 // 2 = spin-1/2 block kernel (-1 if it does not apply).  Chosen by 0 only:
 // kKernelDigit, the block kernel for s >= 1, kKernelWg, the spin-1/2 kernel with
-// one workgroup per block, and kKernelStaged, the spin-1/2 block kernel in its
-// automatic FP64 split.
-constexpr int kKernelDigit = 5, kKernelWg = 6, kKernelStaged = 7;
+// one workgroup per block, kKernelStaged, the spin-1/2 block kernel in its
+// automatic FP64 split, and for a run without reorthogonalization (plain_run)
+// kKernelWgItems, kKernelWg with the dots of kernel 2 in a launch of their own.
+constexpr int kKernelDigit = 5, kKernelWg = 6, kKernelStaged = 7, kKernelWgItems = 8;
 
-int choose_kernel(const Basis *b, const Couplings *c, int requested, int dtype) {
+// Past convergence such a run amplifies its roundings (all-to-all model, 20 sites,
+// 300 steps: 1e-16 to 4e-9 of dE0/dJ), so its sums keep kernel 2's order.  The
+// launch of the dots pays where kernel 2's waves take three items or more in turn,
+// or have many bonds to gather (us a FP64 step, kernel 2 / kKernelWgItems): N = 14
+// (14 in turn) 51 / 21, N = 15 (6) 29 / 20, N = 16 (3) 22.3 / 19.8, N = 17 (2, 34
+// bonds) 19.6 / 19.8; with all bonds N = 17 (136) 36 / 33, N = 20 (190) 48 / 39; N = 12
+// and 13 (1, 66 and 78) 17 / 25 and 19 / 27.
+constexpr int kItemsChain = 3, kItemsBonds = 128;
+static bool wg_items_pay(const Basis *b, const Couplings *c) {
+    return hx_half_chain(b) >= kItemsChain || c->nb >= kItemsBonds;
+}
+
+int choose_kernel(const Basis *b, const Couplings *c, int requested, int dtype, bool plain_run) {
     if (requested == 1) return 1;
     if (requested == 0 && b->two_s >= 2) return digit_fits(b, c) ? kKernelDigit : 1;
-    if (requested == 0 && wg_fits(b, c, dtype)) return kKernelWg;
+    if (requested == 0 && wg_fits(b, c, dtype)) {
+        if (!plain_run) return kKernelWg;
+        if (c && wg_items_pay(b, c)) return kKernelWgItems;
+    }
     if (requested == 0 && c && staged_fits(b, c, dtype)) return kKernelStaged;
     const bool ok = c ? half_fits(b, c) : half_supported(b);
     if (requested == 2) return ok ? 2 : -1;
@@ -74,6 +92,7 @@ int hx_partial_count(const Basis *b, int kernel) {
         case 2: return hx_half_grid(b);
         case kKernelDigit: return hx_digit_grid(b);
         case kKernelWg: return hx_wg_grid(b);
+        case kKernelWgItems: return hx_half_grid(b);
         case kKernelStaged: return hx_staged_grid(b);
         default: return hx_generic_grid(b);
     }
@@ -83,7 +102,7 @@ int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel) {
     if (kernel == 2 || kernel == kKernelStaged)
         return half_prepare_tables(b, c, kernel == kKernelStaged);
     if (kernel == kKernelDigit) return digit_prepare_tables(b, c, dtype);
-    if (kernel == kKernelWg) return wg_prepare_tables(b, c, dtype);
+    if (kernel == kKernelWg || kernel == kKernelWgItems) return wg_prepare_tables(b, c, dtype);
     return HM_OK;
 }
 
@@ -92,7 +111,8 @@ int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel, const H
     if (kernel == 2 || kernel == kKernelStaged)
         return launch_hx_half(b, c, dtype, kernel == kKernelStaged, p, st);
     if (kernel == kKernelDigit) return launch_hx_digit(b, c, dtype, p, st);
-    if (kernel == kKernelWg) return launch_hx_wg(b, c, dtype, p, st);
+    if (kernel == kKernelWg || kernel == kKernelWgItems)
+        return launch_hx_wg(b, c, dtype, kernel == kKernelWgItems, p, st);
     return launch_hx_generic(b, c, dtype, p, st);
 }
 
@@ -133,20 +153,20 @@ static int vec_grid(int64_t n) {
     return (int)g;
 }
 
-// Workgroups of pass B: about 8 16-byte vectors per thread, so that long
+// Slices (partials) of pass B: about 8 16-byte vectors per thread of 256, so that long
 // vectors run on many more workgroups than fit at once and the dispatcher
 // keeps every CU busy to the end (601 M FP32 rows: 1.51 ms on 2048
-// workgroups, 1.36 ms on 65536).  Shorter vectors (up to 1024 such
-// workgroups) take two 16-byte vectors per thread on at most 1024 workgroups,
-// few enough partials for the next kernel to sum.
+// workgroups, 1.36 ms on 65536); a row or two per thread on shorter ones.
 constexpr int64_t kMaxGridB = 65536;
 static int pass_b_grid(int64_t n, size_t es) {
-    const int64_t vec = (int64_t)(16 / es) * kBlock, per = 8 * vec;
+    const int64_t per = (int64_t)(16 / es) * kBlock * 8;
     int64_t g = std::min<int64_t>((n + per - 1) / per, kMaxGridB);
-    if (g <= 1024) g = std::min<int64_t>((n + 2 * vec - 1) / (2 * vec), 1024);
+    g = std::max<int64_t>(g, vec_grid(n));
     if (g >= kXcds) g -= g % kXcds;
-    return (int)std::max<int64_t>(g, 1);
+    return (int)g;
 }
+// Grids (pass B's and the H x pass's) up to which pass B goes by single rows.
+constexpr int kRowsMaxGrid = 64;
 
 // Workspace layout; the partial-sum area holds one entry per workgroup of
 // whichever H x kernel may run (kMaxGrid, or a block kernel's grid when that is
@@ -230,10 +250,6 @@ __device__ double fixed_sum(const double *__restrict__ partial, int n, double *r
     return block_sum(s, red);
 }
 
-// Threads of the finish that sums the H x pass's partials (one per workgroup
-// of that pass, up to 2^20): 16 waves, the most block_sum combines.
-constexpr int kFinishBlock = 1024;
-
 // r_0 = v0 / |v0| from the partials of |v0|^2, and the run's first scalars.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void init_write(const double *__restrict__ v0,
@@ -242,7 +258,7 @@ __global__ __launch_bounds__(kBlock) void init_write(const double *__restrict__ 
                                                      double *sigma, double *cprev, double *scale,
                                                      double tol) {
     __shared__ double red[17];
-    const double s = fold_sum(partial, np, red);
+    const double s = fold_sum<kEndsBlock>(partial, np, red);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         lz->bad_start = !(s > 0.0);
         lz->stopped = 0;
@@ -280,69 +296,141 @@ template <> struct VecOf<double> { using type = double2; };
 // PSI: the ground-state pass, psi += c_k v_k = c_k sigma_k r_k in FP64 (the
 // first step writes psi); r_k is read anyway, so this saves a launch and a
 // read of r_k per step.
-template <typename T, bool PSI>
+//
+// The rows are cut into `slices`, each summed like a workgroup of 256 threads
+// would: thread t takes vectors t, t + 256, ..., then the lanes of every wave and
+// the four waves in turn are added.  Here a wave takes a whole slice, its lanes the
+// four threads of that number, so a slice's sum needs no barrier and a workgroup
+// folds alpha_k once for several of them.  GROUPED: a workgroup takes the eight
+// slices of a group of fold_groups, two per wave, and writes their sum (kGroups
+// workgroups); else four slices, each with a partial of its own.
+template <typename T, bool PSI, bool GROUPED>
 __global__ __launch_bounds__(kBlock) void pass_b(T *__restrict__ w, const T *__restrict__ r,
-                                                 int64_t n, const double *__restrict__ apart,
-                                                 int n_hx,
+                                                 int64_t n, int slices,
+                                                 const double *__restrict__ apart, int n_hx,
                                                  double *__restrict__ alpha,
                                                  const double *__restrict__ sigma, int k,
-                                                 double *__restrict__ partial,
+                                                 bool vectors, double *__restrict__ partial,
                                                  const double *__restrict__ coef,
                                                  double *__restrict__ psi) {
     if (sigma[k] == 0.0) return;
     __shared__ double red[17];
-    int64_t first, last;
-    block_rows<int64_t>(xcd_logical_block(blockIdx.x, gridDim.x), gridDim.x, n, first, last);
+    constexpr int S = GROUPED ? 2 : 1;            // slices of a wave
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    // slice b lies where workgroup b of as many would have its rows: those of one
+    // XCD are consecutive (workgroup b runs on XCD b % 8, here too)
+    int b[S];
+    if constexpr (GROUPED) {
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+            b[i] = blockIdx.x / 16 * 64 + blockIdx.x % 16 + 16 * wid + 1024 * i;
+    } else {
+        b[0] = slices % kXcds == 0
+                   ? (blockIdx.x / kXcds * 4 + wid) * kXcds + blockIdx.x % kXcds
+                   : blockIdx.x * 4 + wid;
+    }
     // 16-byte vector loads and stores over the aligned middle of the range
     // (the buffers start on 256-byte boundaries), single elements at its ends
     constexpr int V = 16 / sizeof(T);
     using Vec = typename VecOf<T>::type;
-    const int64_t m0 = std::min(last, (first + V - 1) / V * V);
-    const int64_t m1 = std::max(m0, last / V * V);
     Vec *wv = reinterpret_cast<Vec *>(w);
     const Vec *rv = reinterpret_cast<const Vec *>(r);
+    int64_t i0[S], j0[S], m0[S], m1[S], j1[S], last[S];
     // the first loads are on their way while alpha_k is summed
-    int64_t j = m0 / V + threadIdx.x;
-    const bool have = j < m1 / V;
-    Vec w0, r0;
-    if (have) {
-        w0 = wv[j];
-        r0 = rv[j];
+    Vec wj[S][4], rj[S][4];
+    T wi[S][4], ri[S][4];
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+        int64_t first = 0;
+        last[i] = 0;
+        if (b[i] < slices)
+            block_rows<int64_t>(xcd_logical_block(b[i], slices), slices, n, first, last[i]);
+        m0[i] = vectors ? std::min(last[i], (first + V - 1) / V * V) : last[i];
+        m1[i] = std::max(m0[i], last[i] / V * V);
+        i0[i] = first + lane;
+        j0[i] = m0[i] / V + lane;
+        j1[i] = m1[i] / V;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (j0[i] + 64 * q < j1[i]) {
+                wj[i][q] = wv[j0[i] + 64 * q];
+                rj[i][q] = rv[j0[i] + 64 * q];
+            }
+            if (i0[i] + 64 * q < m0[i]) {
+                wi[i][q] = w[i0[i] + 64 * q];
+                ri[i][q] = r[i0[i] + 64 * q];
+            }
+        }
     }
-    const double al = apart ? fold_sum(apart, n_hx, red) : alpha[k];
+    const double al = apart ? fold_sum<kFinishBlock>(apart, n_hx, red) : alpha[k];
     if (apart && blockIdx.x == 0 && threadIdx.x == 0) alpha[k] = al;
     const double sg = sigma[k], a = al * sg;
     const double cp = PSI ? coef[k] * sg : 0.0;
-    double s = 0.0;
-    auto one = [&](int64_t i) {
-        const T ri = r[i], wi = (T)((double)w[i] - a * (double)ri);
-        w[i] = wi;
-        s += (double)wi * (double)wi;
-        if constexpr (PSI) psi[i] = (k > 0 ? psi[i] : 0.0) + cp * (double)ri;
-    };
-    auto vec = [&](int64_t jj, Vec wj, const Vec rj) {
-        T *we = reinterpret_cast<T *>(&wj);
-        const T *re = reinterpret_cast<const T *>(&rj);
+    double sum = 0.0;
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-            we[e] = (T)((double)we[e] - a * (double)re[e]);
-            s += (double)we[e] * (double)we[e];
-        }
-        wv[jj] = wj;
-        if constexpr (PSI)
+    for (int i = 0; i < S; ++i) {
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        auto one = [&](int q, int64_t at, T wo, T ro) {
+            const T wn = (T)((double)wo - a * (double)ro);
+            w[at] = wn;
+            s[q] += (double)wn * (double)wn;
+            if constexpr (PSI) psi[at] = (k > 0 ? psi[at] : 0.0) + cp * (double)ro;
+        };
+        auto vec = [&](int q, int64_t jj, Vec wo, const Vec ro) {
+            T *we = reinterpret_cast<T *>(&wo);
+            const T *re = reinterpret_cast<const T *>(&ro);
 #pragma unroll
             for (int e = 0; e < V; ++e) {
-                const int64_t i = jj * V + e;
-                psi[i] = (k > 0 ? psi[i] : 0.0) + cp * (double)re[e];
+                we[e] = (T)((double)we[e] - a * (double)re[e]);
+                s[q] += (double)we[e] * (double)we[e];
             }
-    };
-    for (int64_t i = first + threadIdx.x; i < m0; i += blockDim.x) one(i);
-    if (have) vec(j, w0, r0);
-#pragma unroll 2
-    for (j += blockDim.x; j < m1 / V; j += blockDim.x) vec(j, wv[j], rv[j]);
-    for (int64_t i = m1 + threadIdx.x; i < last; i += blockDim.x) one(i);
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+            wv[jj] = wo;
+            if constexpr (PSI)
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const int64_t at = jj * V + e;
+                    psi[at] = (k > 0 ? psi[at] : 0.0) + cp * (double)re[e];
+                }
+        };
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (i0[i] + 64 * q < m0[i]) one(q, i0[i] + 64 * q, wi[i][q], ri[i][q]);
+            for (int64_t at = i0[i] + 64 * q + 256; at < m0[i]; at += 256)
+                one(q, at, w[at], r[at]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (j0[i] + 64 * q < j1[i]) vec(q, j0[i] + 64 * q, wj[i][q], rj[i][q]);
+        for (int64_t j = j0[i] + 256; j < j1[i]; j += 256) {
+            Vec wn[4], rn[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (j + 64 * q < j1[i]) {
+                    wn[q] = wv[j + 64 * q];
+                    rn[q] = rv[j + 64 * q];
+                }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (j + 64 * q < j1[i]) vec(q, j + 64 * q, wn[q], rn[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            for (int64_t at = m1[i] + lane + 64 * q; at < last[i]; at += 256)
+                one(q, at, w[at], r[at]);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s[q] += __shfl_xor(s[q], off, 64);
+        const double slice = ((s[0] + s[1]) + s[2]) + s[3];
+        sum = i == 0 ? slice : sum + slice;
+    }
+    if constexpr (GROUPED) {
+        if (lane == 0) red[wid] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) partial[blockIdx.x] = (red[0] + red[2]) + (red[1] + red[3]);
+    } else {
+        if (lane == 0 && b[0] < slices) partial[b[0]] = sum;
+    }
 }
 
 // beta_k and the scalars of step k + 1 from the |w|^2 partials.
@@ -356,7 +444,7 @@ __global__ __launch_bounds__(kFinishBlock) void finish_beta(const LzDev *lz,
         return;
     }
     __shared__ double red[16];
-    const double s = fixed_sum(partial, n, red);
+    const double s = n ? fixed_sum(partial, n, red) : fold_groups(partial, red);
     if (threadIdx.x == 0) {
         const LzScalars c = lz_advance(lz, k + 1, s, alpha, sigma, scale);
         beta[k] = c.beta;
@@ -448,7 +536,7 @@ __global__ __launch_bounds__(kBlock) void psi_axpy(double *__restrict__ psi,
 __global__ __launch_bounds__(kBlock) void scale_psi(double *__restrict__ psi, int64_t n, LzDev *lz,
                                                     const double *__restrict__ partial, int np) {
     __shared__ double red[17];
-    const double nrm = sqrt(fold_sum(partial, np, red));
+    const double nrm = sqrt(fold_sum<kEndsBlock>(partial, np, red));
     if (blockIdx.x == 0 && threadIdx.x == 0) lz->psi_norm = nrm;
     if (!(nrm > 0.0)) return;
     const double inv = 1.0 / nrm;
@@ -641,16 +729,16 @@ struct TableArgs {
     double *psi;
 };
 
-// Sum over the workgroup in every thread, one barrier; the caller alternates
-// between two `red`, so that a fast wave cannot overwrite what a slow one reads.
+// Sum over the workgroup in every thread in block_sum's order, one barrier; the
+// caller alternates between two `red`, so that a fast wave cannot overwrite what a
+// slow one reads.
 __device__ __forceinline__ double all_sum(double v, double *red /* 16 */) {
     v = wave_sum(v);
-    const int lane = threadIdx.x & 63;
-    if (lane == 0) red[threadIdx.x >> 6] = v;
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    v = red[lane & 15];
+    v = 0.0;
 #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    for (int w = 0; w < kSmallBlock / 64; ++w) v += red[w];
     return v;
 }
 
@@ -919,6 +1007,11 @@ static int enqueue_steps(Run &R, int k0, int k1, std::vector<hipEvent_t> *ev) {
     const int dtype = R.prec == HM_PREC_F64 ? HM_F64 : HM_F32;
     // sums of few enough partials are left to the kernel that needs them
     const bool fold_a = Ghx <= kFoldMax, fold_b = Gb <= kFoldMax;
+    const bool vectors = G > kRowsMaxGrid || Ghx > kRowsMaxGrid;
+    // (few slices: a group would leave most workgroups without one)
+    const bool grouped = fold_b && !R.reorth && Gb > kGroups;
+    const int Wb = grouped ? kGroups
+                           : Gb % kXcds == 0 ? (Gb / kXcds + 3) / 4 * kXcds : (Gb + 3) / 4;
     for (int k = k0; k < k1; ++k) {
         T *rk = buf[k % 3], *rprev = buf[(k + 2) % 3], *wn = buf[(k + 1) % 3];
         HxPass p;
@@ -927,7 +1020,7 @@ static int enqueue_steps(Run &R, int k0, int k1, std::vector<hipEvent_t> *ev) {
         p.p = k > 0 ? rprev : nullptr;
         p.step.lz = lz;
         p.step.bpart = fold_b && k > R.table ? bpart : nullptr;
-        p.step.nb = Gb;
+        p.step.nb = grouped ? 0 : Gb;
         p.step.k = k;
         p.step.alpha = alpha;
         p.step.beta = beta;
@@ -944,12 +1037,11 @@ static int enqueue_steps(Run &R, int k0, int k1, std::vector<hipEvent_t> *ev) {
                                Ghx, alpha, k);
         const double *apart = fold_a ? partial : nullptr;
         if (!R.reorth) {
-            if (R.psi)
-                hipLaunchKernelGGL((pass_b<T, true>), dim3(Gb), dim3(kBlock), 0, R.st, wn, rk, n,
-                                   apart, Ghx, alpha, sigma, k, bpart, coef, R.psi);
-            else
-                hipLaunchKernelGGL((pass_b<T, false>), dim3(Gb), dim3(kBlock), 0, R.st, wn, rk, n,
-                                   apart, Ghx, alpha, sigma, k, bpart, coef, R.psi);
+            const auto pass_b_kernel = R.psi ? (grouped ? pass_b<T, true, true> : pass_b<T, true, false>)
+                                             : (grouped ? pass_b<T, false, true>
+                                                        : pass_b<T, false, false>);
+            hipLaunchKernelGGL(pass_b_kernel, dim3(Wb), dim3(kBlock), 0, R.st, wn, rk, n, Gb, apart,
+                               Ghx, alpha, sigma, k, vectors, bpart, coef, R.psi);
         } else {
             // beta is the norm after the second pass
             const int nv = k + 1, splits = tall_splits<1>(n, nv);
@@ -986,8 +1078,8 @@ static int enqueue_steps(Run &R, int k0, int k1, std::vector<hipEvent_t> *ev) {
             }
         }
         if (!fold_b || k + 1 == R.steps)
-            hipLaunchKernelGGL(finish_beta, dim3(1), dim3(kFinishBlock), 0, R.st, lz, bpart, Gb,
-                               alpha, beta, sigma, cprev, scale, k);
+            hipLaunchKernelGGL(finish_beta, dim3(1), dim3(kFinishBlock), 0, R.st, lz, bpart,
+                               grouped ? 0 : Gb, alpha, beta, sigma, cprev, scale, k);
     }
     HM_HIP(hipGetLastError());
     return HM_OK;
@@ -1278,19 +1370,24 @@ static int check_opts(const Basis *b, const hm_lanczos_opts *o) {
     if (o->kernel == 3 && b->dim > kSmallMaxDim)
         return fail(HM_ERANGE, "the one-workgroup run takes at most %lld rows",
                     (long long)kSmallMaxDim);
-    if (o->kernel != 3 && choose_kernel(b, nullptr, o->kernel, HM_F64) < 0)
+    if (o->kernel != 3 && choose_kernel(b, nullptr, o->kernel, HM_F64, false) < 0)
         return fail(HM_EINVAL, "spin-1/2 block kernel not applicable to this basis");
     return HM_OK;
 }
 
 // Steps that the automatic choice gives to lanczos_table_kernel: a number that
 // does not depend on the length of the run, so that the recompute pass of a run
-// that stopped early takes the same kernels.
+// that stopped early takes the same kernels.  Without reorthogonalization only
+// the smallest runs: beyond convergence such a run amplifies its roundings (1e-16
+// to 1e-8 of the ground state in 200 steps), so from kSmallWork row-bonds on its
+// sums keep the order of the multi-kernel step (924 rows, FP64: 13 us a step
+// instead of 5.6).
 constexpr int64_t kSmallWork = 16384;
 static int table_steps(const Basis *b, int64_t work, const hm_lanczos_opts *o) {
     const int64_t es = o->precision == HM_PREC_F64 ? 8 : 4;
-    if (!table_fits(b) || work * es > kTableBytes) return 0;
-    if (!o->full_reorth) return INT32_MAX;
+    if (!table_fits(b)) return 0;
+    if (!o->full_reorth) return work <= kSmallWork ? INT32_MAX : 0;
+    if (work * es > kTableBytes) return 0;
     return (int)std::min<int64_t>(kTableCoefs, kTableBytes / (b->dim * es));
 }
 
@@ -1309,7 +1406,7 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     const int table = o->kernel == 0 && !g_timing ? table_steps(b, work, o) : 0;
     const bool small = o->kernel == 3 || table >= steps;
     const int dtype = o->precision == HM_PREC_F64 ? HM_F64 : HM_F32;
-    int kernel = small ? 1 : choose_kernel(b, c, o->kernel, dtype);
+    int kernel = small ? 1 : choose_kernel(b, c, o->kernel, dtype, !o->full_reorth);
     if (kernel < 0) return fail(HM_ERANGE, "block kernel tables too large for these couplings");
     int prc = prepare_kernel(b, c, dtype, kernel);
     if (prc == HM_ENOMEM && kernel == kKernelStaged) {
@@ -1328,10 +1425,10 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     Run R{};
     R.small = small ? 1 : 0;
     R.table = small ? 0 : table;
-    // FP32 roundings of the shortest runs, and of those asked for
-    R.normed = o->kernel == 3 || (!o->full_reorth && work <= kSmallWork);
-    if (table > 0 && (o->full_reorth || work > kSmallWork) && half_supported(b))
-        R.halfK = half_low_bits(b);
+    // the roundings of the run asked for by number; with reorthogonalization those
+    // of the step that the run goes on with
+    R.normed = o->kernel == 3 || !o->full_reorth;
+    if (table > 0 && o->full_reorth && half_supported(b)) R.halfK = half_low_bits(b);
     R.b = b;
     R.c = c;
     R.steps = steps;

@@ -7,8 +7,7 @@
 // kernel of one workgroup costs a launch each (4.6 us back to back, more than
 // the pass B of a million rows), so on grids of up to kFoldMax workgroups
 // every workgroup sums them itself, in the same fixed order, while its first
-// loads would be waiting anyway: at 2048 partials 8 loads per thread.  Larger
-// grids keep the one-workgroup finishes, whose share is small there.
+// loads would be waiting anyway: 8 loads per thread.  Larger grids keep the one-workgroup finishes, whose share is small there.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -37,35 +36,82 @@ constexpr int kFoldMax = 2048;
 struct LzStep {
     const LzDev *lz = nullptr;
     const double *bpart = nullptr;   // |w|^2 partials of step k - 1 (null: finished already)
-    int nb = 0, k = 0;
+    int nb = 0, k = 0;               // their number, 0: in groups (fold_groups)
     const double *alpha = nullptr;
     double *beta = nullptr, *sigma = nullptr, *cprev = nullptr, *scale = nullptr;
 };
 
-// Sum of n partials in a fixed order, returned to every thread: thread t adds
-// partials t, t + blockDim, ... (8 loads in flight), then the wave and
-// workgroup sums.
+// Sum of n <= kFoldMax partials, returned to every thread, in the order of a workgroup of VT
+// threads that adds partials t, t + VT, ... in thread t, then the lanes of every
+// wave and the waves in turn: bit for bit the finish kernel of that size
+// (fixed_sum in lanczos.hip), so a run's coefficients do not depend on whether
+// its sums are folded.  (Runs past convergence amplify one rounding to 1e-8 of
+// the ground state.)  The waves that a smaller workgroup does not have are taken
+// by its own ones in turn; all 8 loads of a thread are in flight together.
+template <int VT>
 __device__ __forceinline__ double fold_sum(const double *__restrict__ partial, int n,
-                                           double *red /* >= 17 */) {
-    constexpr int U = 8;
-    const int stride = blockDim.x;
-    double s = 0.0;
-    int t = threadIdx.x;
-    for (; t + (U - 1) * stride < n; t += U * stride) {
-        double v[U];
+                                           double *red /* >= VT / 64 */) {
+    constexpr int kWaves = VT / 64, U = kFoldMax / VT, Q = VT / 256;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    for (int w0 = wid; w0 < kWaves; w0 += Q * nw) {
+        // loads without branches: one past the end reads partial 0 and adds 0
+        double v[Q][U], s[Q];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = partial[t + u * stride];
+        for (int q = 0; q < Q; ++q)
 #pragma unroll
-        for (int u = 0; u < U; ++u) s += v[u];
+            for (int u = 0; u < U; ++u) {
+                const int t = (w0 + q * nw) * 64 + lane + u * VT;
+                v[q][u] = partial[t < n ? t : 0];
+            }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            s[q] = 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) s[q] += (w0 + q * nw) * 64 + lane + u * VT < n ? v[q][u] : 0.0;
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) s[q] += __shfl_xor(s[q], off, 64);
+        if (lane == 0)
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (w0 + q * nw < kWaves) red[w0 + q * nw] = s[q];
     }
-    for (; t < n; t += stride) s += partial[t];
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) red[16] = s;
     __syncthreads();
-    s = red[16];
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) s += red[w];
     __syncthreads();
     return s;
 }
+
+// Pass B's sums come in groups already: partial 16 w + a of kGroups is the sum of
+// the slices 64 w + a + 16 j + 1024 i (j < 4, i < 2) that fold_sum<1024> would add
+// first, the two of a thread and then the lanes 32 and 16 apart.  What is left of
+// that order is four exchanges and the waves in turn: one load per thread instead
+// of eight (705,432 rows, FP32, H x with 2048 workgroups: 3 us less).
+constexpr int kGroups = 256;
+
+__device__ __forceinline__ double fold_groups(const double *__restrict__ partial,
+                                              double *red /* >= 16 */) {
+    for (int t = threadIdx.x; t < kGroups; t += blockDim.x) {
+        double s = partial[t];
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (t % 16 == 0) red[t / 16] = s;
+    }
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kGroups / 16; ++w) s += red[w];
+    __syncthreads();
+    return s;
+}
+
+// Threads of the finishes of the steps' sums, and of the sums before and after
+// the steps.
+constexpr int kFinishBlock = 1024, kEndsBlock = 256;
 
 // A value that is the same in every lane, in scalar registers.
 __device__ __forceinline__ double uniform(double v) {
@@ -112,8 +158,9 @@ __device__ __forceinline__ bool lz_begin(const LzStep &s, double *red /* >= kLzL
             if (first) s.sigma[s.k] = 0.0;
             return false;
         }
-        const LzScalars c =
-            lz_advance(s.lz, s.k, fold_sum(s.bpart, s.nb, red), s.alpha, s.sigma, s.scale);
+        const double w2 =
+            s.nb ? fold_sum<kFinishBlock>(s.bpart, s.nb, red) : fold_groups(s.bpart, red);
+        const LzScalars c = lz_advance(s.lz, s.k, w2, s.alpha, s.sigma, s.scale);
         if (first) {
             red[17] = c.beta;
             red[18] = c.scale;

@@ -53,7 +53,7 @@ struct TallSub {
 // alpha_k sigma_k of a TallSub; `write`: this workgroup stores alpha_k.
 template <typename T>
 __device__ __forceinline__ double tall_factor(const TallSub<T> &sub, double *red, bool write) {
-    const double al = sub.apart ? fold_sum(sub.apart, sub.n_hx, red) : sub.alpha[sub.k];
+    const double al = sub.apart ? fold_sum<kFinishBlock>(sub.apart, sub.n_hx, red) : sub.alpha[sub.k];
     if (write && sub.apart && threadIdx.x == 0) sub.alpha[sub.k] = al;
     return uniform(al * sub.sigma[sub.k]);
 }
