@@ -858,6 +858,12 @@ int hm_lanczos_batched(int32_t ninst, const hm_basis *bases, const double *const
                 beta[o + s] = s < done ? be[p * steps + s] : 0.0;
             }
             steps_done[k * nvec + q] = done;
+            // an infinite start entry, couplings beyond FP32: no energy (the search
+            // of batch_ground_kernel passes over NaN)
+            for (int s = 0; s < done; ++s)
+                if (!std::isfinite(alpha[o + s]) || (s + 1 < done && !std::isfinite(beta[o + s])))
+                    return fail(HM_EINVAL, "vector %d of instance %d: non-finite tridiagonal entry",
+                                q, k);
             E0[k * nvec + q] = e0[p];
         }
     return HM_OK;
