@@ -192,6 +192,12 @@ int choose_kernel(const Basis *b, const Couplings *c, int requested, int dtype, 
 // of a graph capture, where nothing may be allocated).
 int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel);
 DigitSplit choose_digit_split(const Basis *b);
+// Whether work enqueued on `st` is being captured: nothing may be allocated then.
+inline bool is_capturing(hipStream_t st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return st && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+           cap != hipStreamCaptureStatusNone;
+}
 // Ablation kernels of hm_apply_kernel: 3 = successor sweep, 4 = column scatter.
 int launch_hx_ablation(const Basis *b, const Couplings *c, int dtype, int kernel,
                        const void *x, void *y, hipStream_t st);

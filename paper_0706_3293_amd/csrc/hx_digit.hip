@@ -1138,13 +1138,7 @@ static int digit_get(Basis *b, const Couplings *c, int dtype, hipStream_t st, Di
     }
     auto *set = (DigitBondSet *)cc->half;
     const int k = dtype == HM_F64 ? 0 : 1;
-    if (!set->have[k]) {
-        // nothing may be allocated while the stream is capturing
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (st && hipStreamIsCapturing(st, &cap) == hipSuccess &&
-            cap != hipStreamCaptureStatusNone)
-            return HM_ENOMEM;
-    }
+    if (!set->have[k] && is_capturing(st)) return HM_ENOMEM;
     DigitTables *t = nullptr;
     HM_TRY(digit_prepare(b, &t));
     if (!set->have[k]) {

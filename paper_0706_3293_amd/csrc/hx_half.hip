@@ -37,6 +37,9 @@
 
 namespace hm {
 
+int launch_hx_generic(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
+                      hipStream_t st);
+
 constexpr int kHalfMaxK = 14;
 constexpr int kHalfMaxHighBits = 24;
 constexpr int kGroup = 8;
@@ -1183,14 +1186,39 @@ bool staged_fits(const Basis *b, const Couplings *c, int dtype) {
                std::min(kMaxNeighbourBytes, (size_t)b->dim * 2 * sizeof(double));
 }
 
+// Whether the tables of a split exist for these couplings.
+static bool half_built(Basis *b, const Couplings *c, bool staged) {
+    std::lock_guard<std::mutex> lock(b->mu);
+    const auto *t = (const HalfTables *)(staged ? b->staged_tables : b->half_tables);
+    const auto *hb = (const HalfBonds *)(staged ? c->staged : c->half);
+    return t && hb && hb->K == t->K;
+}
+
+int launch_hx_half(const Basis *b, const Couplings *c, int dtype, bool staged, const HxPass &p,
+                   hipStream_t st);
+
+// A plain product whose own kernel has no tables, for want of memory or because the
+// stream is capturing (nothing may be allocated then): the handle's split if it is
+// built (a product in FP32 or of the kernel by number builds it), else the generic
+// kernel.
+int launch_hx_built(const Basis *cb, const Couplings *c, int dtype, const HxPass &p,
+                    hipStream_t st) {
+    Basis *b = const_cast<Basis *>(cb);
+    return half_built(b, c, false) ? launch_hx_half(b, c, dtype, false, p, st)
+                                   : launch_hx_generic(b, c, dtype, p, st);
+}
+
 int launch_hx_half(const Basis *cb, const Couplings *c, int dtype, bool staged, const HxPass &p,
                    hipStream_t st) {
     Basis *b = const_cast<Basis *>(cb);
+    const bool product = !p.step.sigma;
+    if (staged && product && is_capturing(st) && !half_built(b, c, true))
+        return launch_hx_built(b, c, dtype, p, st);
     HalfTables *t = nullptr;
     const HalfBonds *hb = nullptr;
     int rc = half_prepare(b, staged, &t);
     if (rc == HM_OK) rc = half_bonds(b, c, t, staged, &hb);
-    if (rc == HM_ENOMEM && staged && !p.step.sigma) {   // a plain product: the handle's split
+    if (rc == HM_ENOMEM && staged && product) {         // the handle's split
         clear_error();
         (void)hipGetLastError();
         return launch_hx_half(b, c, dtype, false, p, st);

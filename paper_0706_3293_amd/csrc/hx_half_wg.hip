@@ -32,8 +32,8 @@
 
 namespace hm {
 
-int launch_hx_generic(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
-                      hipStream_t st);
+int launch_hx_built(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
+                    hipStream_t st);
 
 int half_low_bits(const Basis *b);
 int hx_half_grid(const Basis *b);
@@ -641,13 +641,7 @@ static int wg_get(Basis *b, const Couplings *c, int dtype, hipStream_t st, WgTab
     }
     auto *set = (WgBondSet *)cc->wg;
     const int k = dtype == HM_F64 ? 0 : 1;
-    if (!set->have[k]) {
-        // nothing may be allocated while the stream is capturing
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (st && hipStreamIsCapturing(st, &cap) == hipSuccess &&
-            cap != hipStreamCaptureStatusNone)
-            return HM_ENOMEM;
-    }
+    if (!set->have[k] && is_capturing(st)) return HM_ENOMEM;
     WgTables *t = nullptr;
     HM_TRY(wg_prepare(b, &t));
     if (!set->have[k]) {
@@ -721,7 +715,7 @@ int launch_hx_wg(const Basis *cb, const Couplings *c, int dtype, bool items, con
         // no memory for the tables, or a product captured before its first use
         clear_error();
         (void)hipGetLastError();
-        return launch_hx_generic(b, c, dtype, p, st);
+        return launch_hx_built(b, c, dtype, p, st);
     }
     HM_TRY(rc);
     HxPass rows = p;
