@@ -19,13 +19,16 @@
 // A wave takes R blocks of one digit-sum class (the low-word work is done once
 // for R rows), copies them to its LDS slice, interleaved, so that one LDS read
 // serves the R rows, and goes over them 64 rows at a time.  Every row adds its
-// bonds in list order, as row_hx (hx_row.h) does.  In FP64 the diagonal element
-// is the sum of a low-word part, a high-word part (both tabulated) and the
-// straddling bonds.  In FP32 it is summed bond by bond with the roundings of
-// row_hx, so that the result is the generic kernel's bit for bit: with equal
-// couplings those roundings are the same for many rows and do not average out
-// (coefficients of FP32-mixed runs 1e-8 apart).  Where FP32 holds all of these
-// sums exactly, the tabulated parts give the same.
+// bonds in list order, as row_hx (hx_row.h) does.  In FP32 the diagonal element is
+// summed bond by bond with the roundings of row_hx, so that the rows are the
+// generic kernel's bit for bit: with equal couplings those roundings are the same
+// for many rows and do not average out (coefficients of FP32-mixed runs 1e-8
+// apart).  So it is in FP64 where a run's dots are the generic kernel's too (one lane
+// per row, up to 2^19 rows): coefficients past convergence then do not depend on
+// the kernel.  In larger FP64 subspaces it is the sum of a low-word part, a high-word
+// part (both tabulated) and the straddling bonds (16 sites, s = 1, couplings of
+// 1.03: 95 us, bond by bond 140).  Where the type holds all of these sums exactly,
+// the tabulated parts give the same.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -114,7 +117,8 @@ struct DigitBonds {
     uint32_t *mcnt = nullptr;        // [block] moves the block's high word allows
     void *dhigh = nullptr;           // [block] diagonal part of the high-word bonds
     void *kdiag = nullptr;           // [block][nH] (2 m_u)(2 m_v) of the high-word bonds and
-    void *hJ4 = nullptr;             // [nH] their -J/4 (FP32; nH padded to fours with zeros)
+    void *hJ4 = nullptr;             // [nH] their -J/4, where the diagonal goes bond by bond
+                                     // (nH padded to fours with zeros)
     void *strad = nullptr;           // [block][nS][2] target blocks of the straddling moves
     int n_ops = 0, nF = 0, nS = 0, nH = 0, mw = 0;   // mw: moves of a row, padded to fours
     void *mem = nullptr;                             // the allocation that holds them
@@ -215,7 +219,7 @@ __device__ __forceinline__ void low_bonds(const uint32_t *__restrict__ low, int 
             off[m] += c[q][0] * x1[q][m];
             off[m] += c[q][1] * x2[q][m];
         }
-    if (chain)
+    if (sizeof(T) == 4 && chain)
 #pragma unroll
         for (int q = 0; q < W; ++q) {
             const T k = kt[e[q] >> (2 * kRankBits)];
@@ -240,10 +244,10 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
     T *xs = reinterpret_cast<T *>(smem + ((size_t)(ncf + WW * WW) * sizeof(T) + 31) / 32 * 32) +
             (size_t)(threadIdx.x >> 6) * R * (g.smax + 1);
     for (int t = threadIdx.x; t < ncf; t += blockDim.x) cf[t] = g.cf[t];
-    stage_products(kt, g.two_s);
+    if constexpr (sizeof(T) == 4) stage_products(kt, g.two_s);
     __syncthreads();
     const Const<T> *kdiag = as_const(g.kdiag), *hJ4 = as_const(g.hJ4);
-    const bool chain = g.kdiag != nullptr;
+    const bool chain = sizeof(T) == 4 && g.kdiag;
     const int nHc = chain ? g.nH : 0;
 
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
@@ -348,6 +352,7 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
                 const uint32_t e = lo[0], rk1 = e & ((1u << kRankBits) - 1u);
                 const uint32_t rk2 = (e >> kRankBits) & ((1u << kRankBits) - 1u);
                 const int au = (int)(e >> (2 * kRankBits));
+                const T sJ = op.mJ4[0] * (T)(two_s - 2 * au);
                 T g1[R], g2[R], c[R][2];
 #pragma unroll
                 for (int m = 0; m < R; ++m) {
@@ -358,7 +363,8 @@ __global__ __launch_bounds__(kBlock) void hx_digit_kernel(
                     const T v1 = load_at(x, a1 ? so[0] + (I)rk1 : off0[m] + (I)r);
                     const T v2 = load_at(x, a2 ? so[1] + (I)rk2 : off0[m] + (I)r);
                     lds_row<T, 2>(cfb + (au * WW + av) * 2, c[m]);
-                    diag[m] += op.mJ4[0] * (T)((two_s - 2 * au) * (two_s - 2 * av));
+                    if constexpr (sizeof(T) == 8) diag[m] += sJ * (T)(two_s - 2 * av);
+                    else diag[m] += op.mJ4[0] * (T)((two_s - 2 * au) * (two_s - 2 * av));
                     g1[m] = a1 ? v1 : (T)0;
                     g2[m] = a2 ? v2 : (T)0;
                 }
@@ -971,6 +977,12 @@ static int digit_prepare(Basis *b, DigitTables **out) {
     return HM_OK;
 }
 
+// Whether a run has the generic kernel's partial sums, so that equal rows make its
+// coefficients equal: one lane per row and a workgroup for every 256 rows.
+static bool generic_bits(const Basis *b) {
+    return b->digit.flat && b->dim <= (int64_t)kMaxGrid * kBlock;
+}
+
 // Whether T holds every sum of diagonal terms of these couplings exactly
 // (multiples of one power of two, the largest below 2^24 or 2^53 of it; couplings
 // of 1 or 0.25, say): then no order of summation rounds.
@@ -1085,7 +1097,7 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
     const size_t o_moves = arena.reserve(nblk * (d->mw / 4) * sizeof(DigitMoves<T, I>));
     const size_t o_mcnt = arena.reserve(nblk * sizeof(uint32_t));
     const size_t o_dhigh = arena.reserve(nblk * sizeof(T));
-    const bool chain = !exact_diagonal<T>(b, c);
+    const bool chain = (sizeof(T) == 4 || generic_bits(b)) && !exact_diagonal<T>(b, c);
     d->nH = chain ? (nH + 3) / 4 * 4 : 0;
     const size_t o_kdiag = arena.reserve(nblk * d->nH * sizeof(T));
     const size_t o_hJ4 = arena.reserve(d->nH * sizeof(T));
@@ -1243,7 +1255,8 @@ int launch_hx_digit(const Basis *cb, const Couplings *c, int dtype, const HxPass
     const int rc = digit_get(b, c, dtype, st, &t, &d);
     if (rc == HM_ENOMEM && !p.step.sigma) {
         // no memory for the tables, or a product captured before its first
-        // use: the generic kernel's sums are the same bit for bit
+        // use: the generic kernel's rows are the same bit for bit, in larger FP64
+        // subspaces within rounding
         clear_error();
         (void)hipGetLastError();
         return launch_hx_generic(b, c, dtype, p, st);

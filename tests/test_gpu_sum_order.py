@@ -78,18 +78,6 @@ def test_general_spin_run_has_the_bits_of_the_generic_kernel(N, two_s, A, kind, 
     assert torch.equal(b.apply(J, x), b.apply(J, x, kernel=1))
 
 
-@pytest.mark.parametrize("N,two_s,A", [(15, 2, 15), (12, 3, 18)])
-def test_long_blocks_have_the_rows_of_the_generic_kernel(N, two_s, A):
-    """A wave per group of blocks (over 2^20 rows): FP64 products bit for bit."""
-    from paper_0706_3293_amd import Basis
-    b = Basis(N, two_s=two_s, two_M=N * two_s - 2 * A)
-    x = torch.rand(b.dim, dtype=torch.float64, device="cuda",
-                   generator=torch.Generator(device="cuda").manual_seed(1)) - 0.5
-    for kind in ("ring", "all"):
-        J = _couplings(N, kind)
-        assert torch.equal(b.apply(J, x), b.apply(J, x, kernel=1))
-
-
 @pytest.mark.parametrize("case", range(6))
 def test_gradient_past_convergence(case):
     """The stored gradients come from the same coefficients bit for bit, so what is
