@@ -309,7 +309,7 @@ int hm_basis_set_schedule(hm_basis h, int32_t low_bits, int32_t block_threads,
     if (!h) return fail(HM_EINVAL, "null handle");
     hm::Basis &b = h->impl;
     std::lock_guard<std::mutex> lock(b.mu);
-    if (b.half_tables || b.staged_tables || b.wg_tables) return fail(HM_EINVAL, "schedule must be set before the first device use");
+    if (b.schedule_used()) return fail(HM_EINVAL, "schedule must be set before the first device use");
     if (low_bits != 0 && (low_bits < 1 || low_bits > 14 || low_bits > b.N || b.N - low_bits > 24))
         return fail(HM_EINVAL, "low_bits %d outside 1..min(14, N) with N - low_bits <= 24",
                     low_bits);
@@ -329,7 +329,7 @@ int hm_basis_set_items_per_wave(hm_basis h, int32_t items_per_wave) {
     if (!h) return fail(HM_EINVAL, "null handle");
     hm::Basis &b = h->impl;
     std::lock_guard<std::mutex> lock(b.mu);
-    if (b.half_tables || b.staged_tables || b.wg_tables)
+    if (b.schedule_used())
         return fail(HM_EINVAL, "items per wave must be set before the first device use");
     if (items_per_wave < 0 || items_per_wave > (1 << 16))
         return fail(HM_EINVAL, "items per wave %d outside 0..65536", items_per_wave);
@@ -342,7 +342,7 @@ int hm_basis_set_staging(hm_basis h, int32_t mode) {
     if (!h) return fail(HM_EINVAL, "null handle");
     hm::Basis &b = h->impl;
     std::lock_guard<std::mutex> lock(b.mu);
-    if (b.half_tables || b.staged_tables || b.wg_tables) return fail(HM_EINVAL, "staging must be set before the first device use");
+    if (b.schedule_used()) return fail(HM_EINVAL, "staging must be set before the first device use");
     if (mode < 0 || mode > 2) return fail(HM_EINVAL, "staging mode %d outside 0..2", mode);
     b.half_staging = mode;
     return HM_OK;

@@ -132,6 +132,10 @@ struct Basis {
     // spin-1/2 kernel with one workgroup per block: tables (first use)
     void *wg_tables = nullptr;
     void (*wg_tables_free)(void *) = nullptr;
+    // a one-workgroup run took the arithmetic of the block kernel's low sites
+    bool table_used = false;
+    // whether the block kernel's schedule is in use and may not change any more
+    bool schedule_used() const { return half_tables || staged_tables || wg_tables || table_used; }
     // block kernel for s >= 1: the split (fixed at creation) and its tables
     // (first use)
     DigitSplit digit;

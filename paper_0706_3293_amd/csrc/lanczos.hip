@@ -1428,7 +1428,11 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     // the roundings of the run asked for by number; with reorthogonalization those
     // of the step that the run goes on with
     R.normed = o->kernel == 3 || !o->full_reorth;
-    if (table > 0 && o->full_reorth && half_supported(b)) R.halfK = half_low_bits(b);
+    if (table > 0 && o->full_reorth && half_supported(b)) {
+        std::lock_guard<std::mutex> lock(b->mu);
+        b->table_used = true;
+        R.halfK = half_low_bits(b);
+    }
     R.b = b;
     R.c = c;
     R.steps = steps;
