@@ -87,8 +87,10 @@ __global__ __launch_bounds__(kCorrBlock) void bond_corr_kernel(
             }
 #pragma unroll
             for (int q = 0; q < kCorrBatch; ++q) {
-                c[q] += B > 1 ? w1[q] * x1[q] : (w1[q] + w2[q]) * x1[q];
-                if (B > 1) c[q] += w2[q] * x2[q];
+                // (a move that is not allowed read some entry, which may be infinite)
+                const double w = B > 1 ? w1[q] : w1[q] + w2[q];
+                c[q] += w * (w != 0.0 ? x1[q] : 0.0);
+                if (B > 1) c[q] += w2[q] * (w2[q] != 0.0 ? x2[q] : 0.0);
                 c[q] *= pi;
             }
             // sums of 8 values over the wave: each exchange halves the values a
