@@ -995,6 +995,7 @@ static bool exact_diagonal(const Basis *b, const Couplings *c) {
     for (const BondDev &bd : c->host) {
         const T f = (T)bd.mJ4;
         if (f == (T)0) continue;
+        if (!std::isfinite(f)) return false;
         int e;
         const double m = std::frexp((double)f, &e);
         const int bit = e - kBits + __builtin_ctzll((uint64_t)std::fabs(std::ldexp(m, kBits)));
@@ -1084,9 +1085,10 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
         const T mJ2 = (T)bd->mJ2;
         for (int au = 0; au < W; ++au)
             for (int av = 0; av < W; ++av) {
+                // (0 where the digits do not allow the move, also for an infinite mJ2)
                 const T one = mJ2 * (T)b->ladder[au], two = mJ2 * (T)b->ladder[av];
-                cf.push_back(one * (T)b->ladder[av + 1]);
-                cf.push_back(two * (T)b->ladder[au + 1]);
+                cf.push_back(au >= 1 && av < two_s ? one * (T)b->ladder[av + 1] : (T)0);
+                cf.push_back(av >= 1 && au < two_s ? two * (T)b->ladder[au + 1] : (T)0);
             }
     }
     Arena arena;
