@@ -45,7 +45,7 @@ int launch_hx_generic(const Basis *b, const Couplings *c, int dtype, const HxPas
                       hipStream_t st);
 
 constexpr int kDigitMaxWords = 16384;        // low words
-constexpr size_t kDigitMaxLds = 64 * 1024;
+constexpr size_t kDigitMaxLds = 64 * 1024;   // dynamic; kLzLds scalars more, of the CU's 160 KiB
 constexpr size_t kDigitMaxTables = (size_t)8 << 30;
 constexpr int64_t kDigitMaxGrid = 16384;     // workgroups of one launch
 constexpr uint32_t kNoBlock = 0xFFFFFFFFu;   // padding slot of a group of blocks
@@ -77,13 +77,13 @@ struct DigitMoves {
     T cf[4];             // matrix elements
 };
 
-// One block: its packed high digits, its first row, and the start and size of
-// its digit-sum class among the low words.
+// One block: its packed high digits, its first row, the start and size of its
+// digit-sum class among the low words, and its number among the blocks of that class.
 template <typename I>
 struct DigitBlock {
     uint64_t hword;
     I off;
-    int32_t cs, size, pad;
+    int32_t cs, size, rank;
 };
 
 // Tables of the split that depend on the basis only.
@@ -581,6 +581,83 @@ __device__ __forceinline__ I block_offset(const PI *__restrict__ P, uint64_t hw,
     return o;
 }
 
+// The blocks in memory order, one thread per block.  count[n][u]: strings of n digits
+// that bring a digit sum u of the sites above into hmin..hmax, so a block's number
+// decodes to its high word as a row's does to its state.  With groups of R > 1 blocks
+// of one class (digit sum of the low word): the number of blocks of a class before
+// this one is a sum over the prefix table, which counts the words of fewer sites;
+// a group takes its place by its first block, after those of every class that start
+// earlier, so the sweep follows memory order.
+// Enumerated on the host, these tables were 0.2 ms of the first product at 484,500
+// rows and 3 ms at 5.6 M rows in blocks of 8.5.
+template <typename I, typename PI>
+__global__ __launch_bounds__(kBlock) void digit_blocks(
+    const PI *__restrict__ P, const uint32_t *__restrict__ count, const int *__restrict__ cls,
+    const uint32_t *__restrict__ base, int64_t n, int N, int K, int A, int two_s, int bits,
+    int hmin, int hmax, int R, DigitBlock<I> *__restrict__ blocks, uint32_t *__restrict__ groups,
+    uint32_t *__restrict__ place) {
+    const uint32_t mask = (1u << bits) - 1u;
+    const int nh = N - K, W = two_s + 1;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        uint32_t r = (uint32_t)i;
+        int sum = 0;
+        uint64_t hw = 0;
+        for (int k = nh - 1; k >= 0; --k) {
+            const uint32_t *__restrict__ row = count + (size_t)k * (hmax + 1);
+            int a = 0;
+            for (; sum + a <= hmax && r >= row[sum + a]; ++a) r -= row[sum + a];
+            hw |= (uint64_t)a << (k * bits);
+            sum += a;
+        }
+        DigitBlock<I> blk;
+        blk.hword = hw;
+        blk.off = block_offset<I, PI>(P, hw, N, K, A, two_s, bits, mask);
+        blk.cs = cls[2 * (A - sum)];
+        blk.size = cls[2 * (A - sum) + 1];
+        blk.rank = 0;
+        if (groups && R == 1) groups[i] = (uint32_t)i;
+        if (groups && R > 1) {
+            auto before = [&](int s) {       // high words of digit sum s below hw
+                uint32_t c = 0;
+                for (int k = nh - 1; k >= 0 && s >= 0; --k) {
+                    const int a = (int)((hw >> (k * bits)) & mask);
+                    c += (uint32_t)P[((size_t)k * (A + 1) + s) * W + a];
+                    s -= a;
+                }
+                return c;
+            };
+            const uint32_t q = before(sum);
+            blk.rank = (int32_t)q;
+            if (q % R == 0) {
+                uint32_t g = 0;
+                for (int s = hmin; s <= hmax; ++s) g += (before(s) + R - 1) / R;
+                groups[(size_t)g * R] = (uint32_t)i;
+                for (int m = 1; m < R; ++m) groups[(size_t)g * R + m] = kNoBlock;
+                place[base[sum - hmin] + q / R] = g;
+            }
+        }
+        blocks[i] = blk;
+    }
+}
+
+// The other blocks of every group.
+template <typename I>
+__global__ __launch_bounds__(kBlock) void digit_group_rest(
+    const DigitBlock<I> *__restrict__ blocks, int64_t n, int nh, int bits, int hmin, int R,
+    const uint32_t *__restrict__ base, const uint32_t *__restrict__ place,
+    uint32_t *__restrict__ groups) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t q = (uint32_t)blocks[i].rank;
+        if (q % R == 0) continue;
+        int sum = 0;
+        for (int k = 0; k < nh; ++k)
+            sum += (int)((blocks[i].hword >> (k * bits)) & ((1u << bits) - 1u));
+        groups[(size_t)place[base[sum - hmin] + q / R] * R + q % R] = (uint32_t)i;
+    }
+}
+
 // Block of every row: one wave per block.
 template <typename I>
 __global__ __launch_bounds__(kBlock) void digit_row_blocks(const DigitBlock<I> *__restrict__ blocks,
@@ -704,23 +781,14 @@ struct Arena {
         total = (total + bytes + 255) / 256 * 256;
         return at;
     }
-    // Small parts in one copy; large ones as they are (gathering them first took
-    // longer than the copies: 0.1 ms for 0.25 MB).
     hipError_t upload(void **mem) const {
         hipError_t e = hipMalloc(mem, total + 256);
-        if (filled <= kSmallArena) {
-            std::vector<unsigned char> host(filled);
-            for (const Part &p : parts) std::memcpy(host.data() + p.at, p.src, p.bytes);
-            if (e == hipSuccess && filled)
-                e = hipMemcpy(*mem, host.data(), filled, hipMemcpyHostToDevice);
-            return e;
-        }
-        for (const Part &p : parts)
-            if (e == hipSuccess)
-                e = hipMemcpy((unsigned char *)*mem + p.at, p.src, p.bytes, hipMemcpyHostToDevice);
+        std::vector<unsigned char> host(filled);
+        for (const Part &p : parts) std::memcpy(host.data() + p.at, p.src, p.bytes);
+        if (e == hipSuccess && filled)
+            e = hipMemcpy(*mem, host.data(), filled, hipMemcpyHostToDevice);
         return e;
     }
-    static constexpr size_t kSmallArena = 64 * 1024;
 };
 
 void count_bonds(const Couplings *c, int K, int *nF, int *nH, int *nS) {
@@ -834,88 +902,35 @@ int hx_digit_grid(const Basis *b) {
     return b->digit.flat ? grid_of((b->dim + 63) / 64) : grid_of(b->digit.n_groups);
 }
 
-// The high words in memory order, an odometer over their digits (site N - 1
-// most significant) that keeps those whose low word has a digit sum in range,
-// and the groups of R blocks of one class.
-template <typename I>
+// The blocks and groups, on the device.
+template <typename I, typename PI>
 static int put_blocks(const Basis *b, DigitTables *t) {
     const int nh = b->N - t->K, two_s = b->two_s, A = b->A, R = t->R;
     const int hmin = std::max(0, A - t->K * two_s), hmax = std::min(A, nh * two_s);
-    std::vector<DigitBlock<I>> blocks;
-    std::vector<uint8_t> cls_of;
-    blocks.reserve(t->n_blocks);
-    cls_of.reserve(t->n_blocks);
-    std::vector<int> dig(nh, 0);
-    uint64_t packed = 0, off = 0;
-    auto set = [&](int i, int a) {
-        packed += (uint64_t)(int64_t)(a - dig[i]) << (i * b->bits);
-        dig[i] = a;
-    };
-    auto lowest = [&](int upto, int sum) {   // smallest digits of sites 0..upto-1 with that sum
-        for (int i = 0; i < upto; ++i) {
-            const int a = std::min(sum, two_s);
-            set(i, a);
-            sum -= a;
-        }
-    };
-    lowest(nh, hmin);
-    int hsum = hmin;
-    for (;;) {
-        const int a = A - hsum;
-        DigitBlock<I> blk{};
-        blk.hword = packed;
-        blk.off = (I)off;
-        blk.cs = t->cls[2 * a];
-        blk.size = t->cls[2 * a + 1];
-        blocks.push_back(blk);
-        cls_of.push_back((uint8_t)a);
-        off += (uint64_t)blk.size;
-        // successor: raise the lowest site whose raise leaves a sum that the
-        // sites below it can bring into range
-        int i = 0, below = 0;
-        for (; i < nh; ++i) {
-            const int rest = hsum - below - dig[i];          // sites above i
-            if (dig[i] < two_s && rest + dig[i] + 1 <= hmax) {
-                const int need = std::max(0, hmin - rest - dig[i] - 1);
-                if (need <= i * two_s) {
-                    set(i, dig[i] + 1);
-                    hsum = rest + dig[i] + need;
-                    lowest(i, need);
-                    break;
-                }
-            }
-            below += dig[i];
-        }
-        if (i == nh) break;
+    std::vector<uint32_t> count((size_t)(nh + 1) * (hmax + 1), 0);
+    for (int u = hmin; u <= hmax; ++u) count[u] = 1;
+    for (int n = 1; n <= nh; ++n)
+        for (int u = 0; u <= hmax; ++u)
+            for (int a = 0; a <= two_s && u + a <= hmax; ++a)
+                count[(size_t)n * (hmax + 1) + u] += count[(size_t)(n - 1) * (hmax + 1) + u + a];
+    const uint32_t blocks = count[(size_t)nh * (hmax + 1)];
+    std::vector<uint32_t> base;                 // first group of every digit sum
+    uint32_t groups = 0;
+    for (int s = hmin; s <= hmax; ++s) {
+        base.push_back(groups);
+        groups += (uint32_t)((b->count(nh, s) + R - 1) / R);
     }
-    if ((int64_t)blocks.size() != t->n_blocks || (int64_t)off != b->dim)
-        return fail(HM_EINVAL, "internal: %zu blocks with %llu rows, expected %lld with %lld",
-                    blocks.size(), (unsigned long long)off, (long long)t->n_blocks,
-                    (long long)b->dim);
-    std::vector<uint32_t> groups;
-    if (!b->digit.flat) {
-        // a class's blocks go in groups of R in order; a group takes its place
-        // by its first block, so the sweep follows memory order
-        std::vector<uint32_t> open(t->nclass, 0);
-        std::vector<int> used(t->nclass, R);       // entries of a class's last group
-        groups.reserve(t->n_groups * R);
-        for (size_t i = 0; i < blocks.size(); ++i) {
-            const int a = cls_of[i];
-            if (used[a] == R) {
-                used[a] = 0;
-                open[a] = (uint32_t)groups.size();
-                for (int m = 0; m < R; ++m) groups.push_back(kNoBlock);
-            }
-            groups[open[a] + used[a]++] = (uint32_t)i;
-        }
-        if ((int64_t)groups.size() != t->n_groups * R)
-            return fail(HM_EINVAL, "internal: %zu group entries, expected %lld", groups.size(),
-                        (long long)t->n_groups * R);
-    }
+    if ((int64_t)blocks != t->n_blocks || (int64_t)groups != t->n_groups)
+        return fail(HM_EINVAL, "internal: %u blocks in %u groups, expected %lld in %lld", blocks,
+                    groups, (long long)t->n_blocks, (long long)t->n_groups);
+    const bool flat = b->digit.flat;
     Arena arena;
-    const size_t o_blocks = arena.add(blocks), o_groups = arena.add(groups);
+    const size_t o_count = arena.add(count), o_base = arena.add(base), o_cls = arena.add(t->cls);
     const size_t o_rank = arena.add(t->rank), o_word = arena.add(t->word);
-    const size_t o_rows = arena.reserve(b->digit.flat ? (size_t)b->dim * sizeof(uint32_t) : 0);
+    const size_t o_blocks = arena.reserve((size_t)t->n_blocks * sizeof(DigitBlock<I>));
+    const size_t o_groups = arena.reserve(flat ? 0 : (size_t)groups * R * sizeof(uint32_t));
+    const size_t o_place = arena.reserve(flat || R == 1 ? 0 : (size_t)groups * sizeof(uint32_t));
+    const size_t o_rows = arena.reserve(flat ? (size_t)b->dim * sizeof(uint32_t) : 0);
     const hipError_t e = arena.upload(&t->mem);
     if (e != hipSuccess)
         return fail(e == hipErrorOutOfMemory ? HM_ENOMEM : HM_EDEVICE, "block kernel tables: %s",
@@ -926,11 +941,21 @@ static int put_blocks(const Basis *b, DigitTables *t) {
     t->rowblk = (uint32_t *)(m + o_rows);
     t->d_rank = (uint16_t *)(m + o_rank);
     t->d_word = (uint16_t *)(m + o_word);
-    if (b->digit.flat) {
-        hipLaunchKernelGGL(digit_row_blocks<I>, dim3(kMaxGrid), dim3(kBlock), 0, nullptr,
-                           (const DigitBlock<I> *)t->blocks, t->n_blocks, t->rowblk);
-        HM_HIP(hipGetLastError());
-    }
+    auto *blk = (DigitBlock<I> *)t->blocks;
+    const uint32_t *d_base = (const uint32_t *)(m + o_base);
+    uint32_t *place = (uint32_t *)(m + o_place);
+    const dim3 grid((unsigned)std::min<int64_t>((t->n_blocks + kBlock - 1) / kBlock, kMaxGrid));
+    hipLaunchKernelGGL((digit_blocks<I, PI>), grid, dim3(kBlock), 0, nullptr,
+                       (const PI *)b->d_prefix, (const uint32_t *)(m + o_count),
+                       (const int *)(m + o_cls), d_base, t->n_blocks, b->N, t->K, A, two_s, b->bits,
+                       hmin, hmax, R, blk, flat ? nullptr : t->groups, place);
+    if (!flat && R > 1)
+        hipLaunchKernelGGL(digit_group_rest<I>, grid, dim3(kBlock), 0, nullptr, blk, t->n_blocks,
+                           nh, b->bits, hmin, R, d_base, place, t->groups);
+    if (flat)
+        hipLaunchKernelGGL(digit_row_blocks<I>, dim3(kMaxGrid), dim3(kBlock), 0, nullptr, blk,
+                           t->n_blocks, t->rowblk);
+    HM_HIP(hipGetLastError());
     return HM_OK;
 }
 
@@ -959,14 +984,16 @@ static int digit_prepare(Basis *b, DigitTables **out) {
     t->rank.resize(words);
     t->word.resize(words);
     std::vector<int> fill(t->nclass, 0);
+    std::vector<uint8_t> digits(words, 0);             // digit sums
     for (int n = 0; n < words; ++n) {
-        int a = 0;
-        for (int q = n; q > 0; q /= W) a += q % W;
+        const int a = digits[n] = (uint8_t)(digits[n / W] + n % W);
         t->rank[n] = (uint16_t)fill[a];
         t->word[t->cls[2 * a] + fill[a]] = (uint16_t)n;
         ++fill[a];
     }
-    const int rc = small_index(b) ? put_blocks<uint32_t>(b, t) : put_blocks<uint64_t>(b, t);
+    const int rc = small_index(b) ? put_blocks<uint32_t, uint32_t>(b, t)
+                   : b->idx32     ? put_blocks<uint64_t, uint32_t>(b, t)
+                                  : put_blocks<uint64_t, uint64_t>(b, t);
     if (rc != HM_OK) {
         free_digit(t);
         return rc;
