@@ -571,12 +571,13 @@ __global__ __launch_bounds__(kBlock) void hx_digit_flat_kernel(
 template <typename I, typename PI>
 __device__ __forceinline__ I block_offset(const PI *__restrict__ P, uint64_t hw, int N, int K,
                                           int A, int two_s, int bits, uint32_t mask) {
+    const int W = two_s + 1, site = (A + 1) * W;
     I o = 0;
-    int Ak = A;
-    for (int k = N; k > K; --k) {
-        const int a = (int)((hw >> ((k - 1 - K) * bits)) & mask);
-        o += (I)P[((size_t)(k - 1) * (A + 1) + Ak) * (two_s + 1) + a];
-        Ak -= a;
+    int at = (N - 1) * site + A * W;              // entry of digit 0 at the next site
+    for (int sh = (N - 1 - K) * bits; sh >= 0; sh -= bits) {
+        const int a = (int)((hw >> sh) & mask);
+        o += (I)P[at + a];
+        at -= site + a * W;
     }
     return o;
 }
@@ -597,7 +598,7 @@ __global__ __launch_bounds__(kBlock) void digit_blocks(
     int hmin, int hmax, int R, DigitBlock<I> *__restrict__ blocks, uint32_t *__restrict__ groups,
     uint32_t *__restrict__ place) {
     const uint32_t mask = (1u << bits) - 1u;
-    const int nh = N - K, W = two_s + 1;
+    const int nh = N - K, W = two_s + 1, site = (A + 1) * W;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         uint32_t r = (uint32_t)i;
@@ -620,9 +621,11 @@ __global__ __launch_bounds__(kBlock) void digit_blocks(
         if (groups && R > 1) {
             auto before = [&](int s) {       // high words of digit sum s below hw
                 uint32_t c = 0;
-                for (int k = nh - 1; k >= 0 && s >= 0; --k) {
-                    const int a = (int)((hw >> (k * bits)) & mask);
-                    c += (uint32_t)P[((size_t)k * (A + 1) + s) * W + a];
+                int at = (nh - 1) * site + s * W;
+                for (int sh = (nh - 1) * bits; sh >= 0 && s >= 0; sh -= bits) {
+                    const int a = (int)((hw >> sh) & mask);
+                    c += (uint32_t)P[at + a];
+                    at -= site + a * W;
                     s -= a;
                 }
                 return c;
@@ -672,61 +675,82 @@ __global__ __launch_bounds__(kBlock) void digit_row_blocks(const DigitBlock<I> *
 // a_u - 1, a_v + 1, then the other; padded with the own block and 0), the
 // diagonal part, and the target blocks of the straddling bonds' two moves (the
 // own block where the high digit does not allow one).  The matrix elements
-// have the roundings of row_hx.
+// have the roundings of row_hx.  2^log_parts threads share a block, each with a range of
+// its bonds, since a thread waits for the walks of its targets one after the other
+// (484,500 rows, 47,672 blocks, J1-J2 ring: 108 us with a thread per block, 20 with
+// 8); the places of a range's moves are counted from the digits alone.
 template <typename T, typename I, typename PI>
 __global__ __launch_bounds__(kBlock) void digit_rows(
-    const PI *__restrict__ P, const DigitBlock<I> *__restrict__ blocks, int64_t n, int N, int K,
-    int A, int two_s, int bits, uint32_t mask, const BondDev *__restrict__ bonds, int nb,
-    const double *__restrict__ ladder, int nS, int mw, DigitMoves<T, I> *__restrict__ moves,
+    const PI *__restrict__ P, const DigitBlock<I> *__restrict__ blocks, int64_t n, int log_parts,
+    bool lane_per_row, int N, int K, int A, int two_s, int bits, uint32_t mask, const BondDev *__restrict__ bonds, int nb,
+    int nF, const double *__restrict__ ladder, int nS, int mw, DigitMoves<T, I> *__restrict__ moves,
     uint32_t *__restrict__ mcnt, T *__restrict__ dhigh, int nH, T *__restrict__ kdiag,
     T *__restrict__ hJ4, I *__restrict__ strad) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
+    const int parts = 1 << log_parts;
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n << log_parts;
+         t += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t i = t >> log_parts;
+        const int part = (int)t & (parts - 1);
+        const int b0 = (nb * part) >> log_parts, b1 = (nb * (part + 1)) >> log_parts;
         const uint64_t hw = blocks[i].hword;
         const I own = blocks[i].off;
+        auto digit = [&](int site) { return (int)((hw >> ((site - K) * bits)) & mask); };
+        auto target = [&](uint64_t to) {
+            return block_offset<I, PI>(P, to, N, K, A, two_s, bits, mask);
+        };
         DigitMoves<T, I> *row = moves + (size_t)i * (mw / 4);
         auto put = [&](int c, I o, T f) {
             row[c / 4].off[c % 4] = o;
             row[c / 4].cf[c % 4] = f;
         };
-        int c = 0, s = 0, h = 0;
-        double d = 0.0;
-        for (int b = 0; b < nb; ++b) {
+        int c = 0, s = 0;                 // moves and straddling bonds before b0
+        for (int b = 0; b < b0; ++b) {
             const int u = bonds[b].u, v = bonds[b].v;
             if (v < K) continue;
-            const int sv = (v - K) * bits, av = (int)((hw >> sv) & mask);
-            const uint64_t ev = 1ull << sv;
             if (u < K) {
-                I *o = strad + ((size_t)i * nS + s) * 2;
-                o[0] = av < two_s ? block_offset<I, PI>(P, hw + ev, N, K, A, two_s, bits, mask) : own;
-                o[1] = av >= 1 ? block_offset<I, PI>(P, hw - ev, N, K, A, two_s, bits, mask) : own;
                 ++s;
                 continue;
             }
-            const int su = (u - K) * bits, au = (int)((hw >> su) & mask);
-            const uint64_t eu = 1ull << su;
+            const int au = digit(u), av = digit(v);
+            c += (au >= 1 && av < two_s) + (av >= 1 && au < two_s);
+        }
+        for (int b = b0; b < b1; ++b) {
+            const int u = bonds[b].u, v = bonds[b].v;
+            if (v < K) continue;
+            const int av = digit(v);
+            const uint64_t ev = 1ull << ((v - K) * bits);
+            if (u < K) {
+                I *o = strad + ((size_t)i * nS + s++) * 2;
+                o[0] = av < two_s ? target(hw + ev) : own;
+                o[1] = av >= 1 ? target(hw - ev) : own;
+                continue;
+            }
+            const int au = digit(u);
+            const uint64_t eu = 1ull << ((u - K) * bits);
             const T mJ2 = (T)bonds[b].mJ2;
             if (au >= 1 && av < two_s)
-                put(c++, block_offset<I, PI>(P, hw - eu + ev, N, K, A, two_s, bits, mask),
-                    mJ2 * (T)ladder[au] * (T)ladder[av + 1]);
+                put(c++, target(hw - eu + ev), mJ2 * (T)ladder[au] * (T)ladder[av + 1]);
             if (av >= 1 && au < two_s)
-                put(c++, block_offset<I, PI>(P, hw + eu - ev, N, K, A, two_s, bits, mask),
-                    mJ2 * (T)ladder[av] * (T)ladder[au + 1]);
-            const int k = (two_s - 2 * au) * (two_s - 2 * av);
-            d += (double)(T)bonds[b].mJ4 * (double)k;
+                put(c++, target(hw + eu - ev), mJ2 * (T)ladder[av] * (T)ladder[au + 1]);
             if (kdiag) {
-                kdiag[(size_t)i * nH + h] = (T)k;
-                if (i == 0) hJ4[h] = (T)bonds[b].mJ4;
-                ++h;
+                kdiag[(size_t)i * nH + b - nF] = (T)((two_s - 2 * au) * (two_s - 2 * av));
+                if (i == 0) hJ4[b - nF] = (T)bonds[b].mJ4;
             }
         }
-        for (; kdiag && h < nH; ++h) {
+        if (part + 1 < parts) continue;
+        double d = 0.0;
+        for (int b = nF; b < nb; ++b)
+            d += (double)(T)bonds[b].mJ4 *
+                 (double)((two_s - 2 * digit(bonds[b].u)) * (two_s - 2 * digit(bonds[b].v)));
+        for (int h = nb - nF; kdiag && h < nH; ++h) {
             kdiag[(size_t)i * nH + h] = 0;
             if (i == 0) hJ4[h] = 0;
         }
         mcnt[i] = (uint32_t)c;
         dhigh[i] = (T)d;
-        for (; c < mw; ++c) put(c, own, (T)0);
+        // (one lane per row reads its own list only, a wave of R blocks the longest)
+        const int end = lane_per_row ? (c + 3) / 4 * 4 : mw;
+        for (; c < end; ++c) put(c, own, (T)0);
     }
 }
 
@@ -1034,11 +1058,10 @@ static bool exact_diagonal(const Basis *b, const Couplings *c) {
 }
 
 // The low-word table: per bond of a low site (the first nF of the list, which is
-// sorted by u) and low word, the ranks that its two moves lead to (smax where a move
-// is not allowed; with the other site in the high word, the rank with u alone
-// changed) and the entry of its matrix elements; and per low word the diagonal part
-// of the bonds inside it.  Built on the host it made the first product with new
-// couplings 135 us at 1,107 rows and 155 at 73,789; now 80 and 95 (25 afterwards).
+// sorted by u; blockIdx.y) and low word, the ranks that its two moves lead to (smax
+// where a move is not allowed; with the other site in the high word, the rank with u
+// alone changed) and the entry of its matrix elements.  The last blockIdx.y: per low
+// word the diagonal part of the bonds inside it.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void digit_low(const BondDev *__restrict__ bonds, int nF, int K,
                                                     int two_s, int words, int smax,
@@ -1046,33 +1069,39 @@ __global__ __launch_bounds__(kBlock) void digit_low(const BondDev *__restrict__ 
                                                     const uint16_t *__restrict__ word,
                                                     uint32_t *__restrict__ low,
                                                     T *__restrict__ dlow) {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
+    const int i = blockIdx.x * kBlock + threadIdx.x, f = blockIdx.y;
     if (i >= words) return;
     const int W = two_s + 1, n = word[i];
     constexpr uint32_t kMask = (1u << kRankBits) - 1u;
-    double dsum = 0.0;
-    for (int f = 0; f < nF; ++f) {
-        const int u = bonds[f].u, v = bonds[f].v;
-        int wu = 1, wv = 1;
-        for (int q = 0; q < u; ++q) wu *= W;
-        const int au = n / wu % W;
-        uint32_t r1, r2, e;
-        if (v < K) {
-            for (int q = 0; q < v; ++q) wv *= W;
-            const int av = n / wv % W;
-            r1 = au >= 1 && av < two_s ? rank[n - wu + wv] : smax;
-            r2 = av >= 1 && au < two_s ? rank[n + wu - wv] : smax;
-            e = (uint32_t)(au * W + av);
-            dsum += (double)(T)bonds[f].mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
-        } else {
-            r1 = au >= 1 ? rank[n - wu] : rank[n];
-            r2 = au < two_s ? rank[n + wu] : rank[n];
-            e = (uint32_t)au;
+    auto power = [&](int q) {
+        int w = 1;
+        while (q-- > 0) w *= W;
+        return w;
+    };
+    if (f == nF) {
+        double sum = 0.0;
+        for (int b = 0; b < nF; ++b) {
+            if (bonds[b].v >= K) continue;
+            const int au = n / power(bonds[b].u) % W, av = n / power(bonds[b].v) % W;
+            sum += (double)(T)bonds[b].mJ4 * (double)((two_s - 2 * au) * (two_s - 2 * av));
         }
-        // (a class without blocks may be larger than the field, and is not used)
-        low[(size_t)f * words + i] = (r1 & kMask) | (r2 & kMask) << kRankBits | e << (2 * kRankBits);
+        dlow[i] = (T)sum;
+        return;
     }
-    dlow[i] = (T)dsum;
+    const int v = bonds[f].v, wu = power(bonds[f].u), au = n / wu % W;
+    uint32_t r1, r2, e;
+    if (v < K) {
+        const int wv = power(v), av = n / wv % W;
+        r1 = au >= 1 && av < two_s ? rank[n - wu + wv] : smax;
+        r2 = av >= 1 && au < two_s ? rank[n + wu - wv] : smax;
+        e = (uint32_t)(au * W + av);
+    } else {
+        r1 = au >= 1 ? rank[n - wu] : rank[n];
+        r2 = au < two_s ? rank[n + wu] : rank[n];
+        e = (uint32_t)au;
+    }
+    // (a class without blocks may be larger than the field, and is not used)
+    low[(size_t)f * words + i] = (r1 & kMask) | (r2 & kMask) << kRankBits | e << (2 * kRankBits);
 }
 
 template <typename T, typename I, typename PI>
@@ -1144,14 +1173,20 @@ static hipError_t build_bonds(const Basis *b, const Couplings *c, const DigitTab
     d->kdiag = chain ? m + o_kdiag : nullptr;
     d->hJ4 = m + o_hJ4;
     d->strad = m + o_strad;
-    hipLaunchKernelGGL(digit_low<T>, dim3((words + kBlock - 1) / kBlock), dim3(kBlock), 0, nullptr,
-                       c->dev, d->nF, K, two_s, words, t->smax, t->d_rank, t->d_word, d->low,
+    hipLaunchKernelGGL(digit_low<T>, dim3((words + kBlock - 1) / kBlock, d->nF + 1), dim3(kBlock), 0,
+                       nullptr, c->dev, d->nF, K, two_s, words, t->smax, t->d_rank, t->d_word, d->low,
                        (T *)d->dlow);
-    const int grid = (int)std::min<int64_t>((t->n_blocks + kBlock - 1) / kBlock, kMaxGrid);
+    // threads for the whole chip, at most one for two bonds
+    int log_parts = 0;
+    while (log_parts < 5 && (t->n_blocks << log_parts) < kMaxGrid * kBlock &&
+           4 << log_parts <= c->nb)
+        ++log_parts;
+    const int grid = (int)std::min<int64_t>(((t->n_blocks << log_parts) + kBlock - 1) / kBlock,
+                                            4 * kMaxGrid);
     hipLaunchKernelGGL((digit_rows<T, I, PI>), dim3(grid), dim3(kBlock), 0, nullptr,
-                       (const PI *)b->d_prefix, (const DigitBlock<I> *)t->blocks, t->n_blocks, b->N,
-                       K, b->A, two_s, b->bits, (1u << b->bits) - 1u, c->dev, c->nb, b->d_ladder,
-                       d->nS, d->mw, (DigitMoves<T, I> *)d->moves, d->mcnt, (T *)d->dhigh,
+                       (const PI *)b->d_prefix, (const DigitBlock<I> *)t->blocks, t->n_blocks, log_parts,
+                       b->digit.flat, b->N, K, b->A, two_s, b->bits, (1u << b->bits) - 1u, c->dev, c->nb, d->nF,
+                       b->d_ladder, d->nS, d->mw, (DigitMoves<T, I> *)d->moves, d->mcnt, (T *)d->dhigh,
                        d->nH, (T *)d->kdiag, (T *)d->hJ4, (I *)d->strad);
     e = hipGetLastError();
     // other streams may use the tables from now on
