@@ -46,7 +46,12 @@ int launch_hx_generic(const Basis *b, const Couplings *c, int dtype, const HxPas
 
 constexpr int kDigitMaxWords = 16384;        // low words
 constexpr size_t kDigitMaxLds = 64 * 1024;   // dynamic; kLzLds scalars more, of the CU's 160 KiB
-constexpr size_t kDigitMaxTables = (size_t)8 << 30;
+// Most bytes of tables of one coupling list: a GiB, or what four FP64 vectors take, up
+// to 8 GiB.  Sectors far from M = 0 have blocks of a few rows and would hold up to 600
+// times the vector (31 sites, s = 1, A = 5, all bonds: 1.1 GB for 2.5 MB) for a product
+// that is at most twice as fast (ring of 24 sites, A = 8, 0.44 GB for 45 MB: 224 and 387
+// us); four lists of two types may be cached.
+constexpr size_t kDigitMaxTables = (size_t)8 << 30, kDigitFreeTables = (size_t)1 << 30;
 constexpr int64_t kDigitMaxGrid = 16384;     // workgroups of one launch
 constexpr uint32_t kNoBlock = 0xFFFFFFFFu;   // padding slot of a group of blocks
 
@@ -907,7 +912,9 @@ bool digit_fits(const Basis *b, const Couplings *c) {
     int nF, nH, nS;
     count_bonds(c, s.K, &nF, &nH, &nS);
     return digit_lds(b, s.flat ? 0 : s.R, s.smax, nF, 8) <= kDigitMaxLds &&
-           digit_table_bytes(b, s, c, 8) <= kDigitMaxTables;
+           digit_table_bytes(b, s, c, 8) <=
+               std::min(kDigitMaxTables,
+                        std::max(kDigitFreeTables, 4 * sizeof(double) * (size_t)b->dim));
 }
 
 // Workgroups for n_groups waves of work: one group per wave up to a grid far
