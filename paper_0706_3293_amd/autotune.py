@@ -6,7 +6,9 @@ For a given problem (N, M, couplings, element type) every candidate schedule
 and timed with HIP events over the H x pass of a few Lanczos steps (the kernel
 variant the steps run: with the previous vector and the FP64 dot, whose
 register needs differ from the bare H x); then the grid of the fastest is
-tuned (work items per wave, 0 for the default grid).  The result, a 5-tuple, is remembered in a JSON cache keyed by the
+tuned (work items per wave, 0 for the default grid).  A handle without a schedule is
+timed too, since the automatic choice has FP64 kernels that no schedule asks for; all
+zeros stand for it.  The result, a 5-tuple, is remembered in a JSON cache keyed by the
 problem.
 A chosen schedule is fixed for the lifetime of its basis handle, so the two
 Lanczos passes of the gradient (which must agree bit for bit) always run the
@@ -30,6 +32,7 @@ TIE = 0.01      # relative timing difference treated as a tie
 # work items per wave tried for the grid of the fastest schedule (0: the
 # default grid, listed first so that near-ties keep it)
 IPW_CANDIDATES = (0, 4, 8, 16, 32, 64)
+NO_SCHEDULE = (0, 0, 0, 0, 0)   # the automatic choice of kernel and split
 
 
 def candidates(N):
@@ -60,9 +63,9 @@ def _indices_fit_32(N):
 
 def _key(N, two_M, J, dtype):
     h = hashlib.sha1(np.ascontiguousarray(np.asarray(J, dtype=np.float64)).tobytes()).hexdigest()
-    # "passA": timed on the Lanczos H x pass (entries timed on the bare H x
-    # have keys without it and are tuned again)
-    return f"passA:N={N},2M={two_M},dtype={dtype},J={h[:16]}"
+    # "passA2": timed on the Lanczos H x pass of the present kernels (entries of
+    # older ones have other keys and are tuned again)
+    return f"passA2:N={N},2M={two_M},dtype={dtype},J={h[:16]}"
 
 
 def time_apply(b, J, x, y, reps):
@@ -78,13 +81,13 @@ def time_apply(b, J, x, y, reps):
     return start.elapsed_time(stop) / reps
 
 
-def time_pass_a(b, J, v0, precision, reps):
+def time_pass_a(b, J, v0, precision, reps, kernel=2):
     """Average ms of the H x pass of Lanczos steps (the library's HIP events
     around every pass), over reps + 1 steps after a two-step warm-up."""
-    b.lanczos(J, v0, 2, precision=precision, kernel=2)
+    b.lanczos(J, v0, 2, precision=precision, kernel=kernel)
     api.set_timing(True)
     try:
-        b.lanczos(J, v0, reps + 1, precision=precision, kernel=2)
+        b.lanczos(J, v0, reps + 1, precision=precision, kernel=kernel)
     finally:
         api.set_timing(False)
     t = api.last_timing()
@@ -140,6 +143,15 @@ def tune(N, J, two_M=0, dtype=torch.float32, reps=5, cache=DEFAULT_CACHE, verbos
     staged2 = [(s, ms) for s, ms in trials if len(s) == 5]
     fastest = min(ms for _, ms in staged2)
     best, best_ms = next((s, ms) for s, ms in staged2 if ms <= (1.0 + TIE) * fastest)
+    # no schedule, where that is faster by more than a tie
+    b = Basis(N, two_s=1, two_M=two_M)
+    ms = time_pass_a(b, J, v0, precision, reps, kernel=0)
+    trials.append((NO_SCHEDULE, ms))
+    if verbose:
+        print(f"[autotune] no schedule: {ms:.3f} ms", flush=True)
+    del b
+    if ms < (1.0 - TIE) * best_ms:
+        best, best_ms = NO_SCHEDULE, ms
     if cache:
         table[key] = {"schedule": list(best), "ms": best_ms,
                       "trials": [[list(s), m] for s, m in trials]}
@@ -168,7 +180,9 @@ BATCH_CANDIDATES = [(0, 0)] + [(c, w) for w in (4, 2, 8, 1) for c in (1, 2, 4, 8
 def _batch_key(bases, nvec, steps):
     shapes = ";".join(f"{b.N}/{b.two_s}/{b.two_M}" for b in bases)
     h = hashlib.sha1(shapes.encode()).hexdigest()[:16]
-    return f"batched:n={len(bases)},nvec={nvec},steps={steps},shapes={h}"
+    # "batched2": a launch per pass (schedules of the one persistent launch have
+    # other keys and are tuned again)
+    return f"batched2:n={len(bases)},nvec={nvec},steps={steps},shapes={h}"
 
 
 def tune_batched(bases, Js, V0s, steps, reps=2, cache=DEFAULT_CACHE, verbose=False):
