@@ -1409,8 +1409,9 @@ static int run_common(hm_basis h, const double *J, const double *d_v0, int32_t s
     int kernel = small ? 1 : choose_kernel(b, c, o->kernel, dtype, !o->full_reorth);
     if (kernel < 0) return fail(HM_ERANGE, "block kernel tables too large for these couplings");
     int prc = prepare_kernel(b, c, dtype, kernel);
-    if (prc == HM_ENOMEM && kernel == kKernelStaged) {
-        kernel = 2;                   // the handle's split
+    if (prc == HM_ENOMEM &&
+        (kernel == kKernelStaged || kernel == kKernelWg || kernel == kKernelWgItems)) {
+        kernel = 2;                   // the handle's split, the same tables asked for by number
         clear_error();
         (void)hipGetLastError();
         prc = prepare_kernel(b, c, dtype, kernel);
