@@ -71,15 +71,6 @@ struct BatchArgs {
     int chunk;                 // items a workgroup takes at a time
 };
 
-// Read-only tables through the constant address space: the kernels store through
-// pointers that may alias them, which would turn their uniform reads into
-// vector loads per lane.
-template <typename T> using Const = const __attribute__((address_space(4))) T;
-template <typename T>
-__device__ __forceinline__ const Const<T> *as_const(const T *p) {
-    return (const Const<T> *)p;
-}
-
 template <int NV>
 __device__ __forceinline__ void load_row(const float *__restrict__ p, float (&v)[NV]) {
     if constexpr (NV % 4 == 0) {

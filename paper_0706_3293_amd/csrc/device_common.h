@@ -34,6 +34,33 @@ __device__ __forceinline__ uint32_t sweep_item(uint32_t l, uint32_t x8) {
     return (l / kSweepRun) * (kXcds * kSweepRun) + x8 * kSweepRun + l % kSweepRun;
 }
 
+// Read-only tables seen through the constant address space: wave-uniform reads
+// are scalar loads whatever the kernel stores in between.  (Through plain
+// pointers, a store that might alias them makes every such read a vector load
+// per lane: twice the time of the spin-1/2 N = 28 pass in FP64.)
+template <typename T>
+using Const = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ const Const<T> *as_const(const T *p) {
+    return (const Const<T> *)p;
+}
+
+// Element at a byte offset from a wave-uniform base pointer.
+template <typename T>
+__device__ __forceinline__ T load_bytes(const T *__restrict__ base, uint32_t byte_off) {
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + byte_off);
+}
+
+// Element i of a wave-uniform base.  With 32-bit indices the vectors are
+// smaller than 4 GiB, so the address is the scalar base and a 32-bit byte
+// offset: one vector instruction per gather, where a scalar 64-bit base per
+// target block took three or four and spilled scalar registers.
+template <typename T, typename I>
+__device__ __forceinline__ T load_at(const T *__restrict__ base, I i) {
+    if constexpr (sizeof(I) == 4) return load_bytes(base, (uint32_t)i * (uint32_t)sizeof(T));
+    else return base[i];
+}
+
 // Rows [first, last) of logical workgroup lb when `dim` rows are split into
 // `grid` contiguous ranges.
 template <typename I>

@@ -159,25 +159,6 @@ struct DigitArgs {
     int n_ops, nF, nS, nH, mq, words, smax, two_s, mask;   // mq: move pieces of a row
 };
 
-template <typename T> using Const = const __attribute__((address_space(4))) T;
-template <typename T>
-__device__ __forceinline__ const Const<T> *as_const(const T *p) {
-    return (const Const<T> *)p;
-}
-
-// Element i of a wave-uniform base.  With 32-bit indices the vectors are
-// smaller than 4 GiB, so the address is the scalar base and a 32-bit byte
-// offset: one vector instruction per gather, where a scalar 64-bit base per
-// target block took three or four and spilled scalar registers.
-template <typename T, typename I>
-__device__ __forceinline__ T load_at(const T *__restrict__ base, I i) {
-    if constexpr (sizeof(I) == 4)
-        return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
-                                            i * (uint32_t)sizeof(T));
-    else
-        return base[i];
-}
-
 // R consecutive elements of LDS (16-byte reads where they fit).
 template <typename T, int R>
 __device__ __forceinline__ void lds_row(const T *p, T (&v)[R]) {

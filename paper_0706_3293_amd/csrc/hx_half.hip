@@ -121,12 +121,6 @@ struct HalfArgs {
     int class_size[kHalfMaxK + 2];
 };
 
-// Element at a byte offset from a wave-uniform base pointer.
-template <typename T>
-__device__ __forceinline__ T load_at(const T *__restrict__ base, uint32_t byte_off) {
-    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + byte_off);
-}
-
 // Copies a table of n = 2^K 16-bit entries to LDS, 16 bytes per load: two bytes
 // at a time, the two tables of K = 12 were 32 dependent rounds that cost a
 // workgroup several microseconds, most of the launch for 13,000 rows.
@@ -161,16 +155,6 @@ __device__ __forceinline__ void for_pieces(int n, F &&f) {
     for (; k < n; k += 2) f(std::integral_constant<int, 2>{}, k);
 }
 
-// Read-only tables seen through the constant address space: wave-uniform reads
-// are scalar loads whatever the kernel stores in between.  (Through plain
-// pointers, a store that might alias them makes every such read a vector load
-// per lane: twice the time of the N = 28 pass in FP64.)
-template <typename T>
-using Const = const __attribute__((address_space(4))) T;
-template <typename T>
-__device__ __forceinline__ const Const<T> *as_const(const T *p) {
-    return (const Const<T> *)p;
-}
 template <typename T> __device__ __forceinline__ T coefc(const Const<BondGroup> &g, int q);
 template <> __device__ __forceinline__ float coefc<float>(const Const<BondGroup> &g, int q) {
     return g.c32[q];
@@ -250,7 +234,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
         for (int m = 0; m < R; ++m) {
             off[m] = offs[hs[m]];
             nb[m] = nbr + (size_t)hs[m] * g.width;
-            xi[m] = load_at(x + off[m], r_bytes);
+            xi[m] = load_bytes(x + off[m], r_bytes);
             acc[m] = 0;
         }
         // bonds inside the low word: the test and rankL(L ^ m) once per lane
@@ -271,7 +255,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
                 const T *__restrict__ xb = x + off[m];
                 T xj[W];
 #pragma unroll
-                for (int q = 0; q < W; ++q) xj[q] = load_at(xb, idx[q]);
+                for (int q = 0; q < W; ++q) xj[q] = load_bytes(xb, idx[q]);
 #pragma unroll
                 for (int q = 0; q < W; ++q) acc[m] += coefc<T>(G, q0 + q) * (xj[q] - xi[m]);
             }
@@ -297,7 +281,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
 #pragma unroll
                 for (int m = 0; m < R; ++m)
 #pragma unroll
-                    for (int q = 0; q < W; ++q) xj[m][q] = load_at(x + nb[m][k + q], r_bytes);
+                    for (int q = 0; q < W; ++q) xj[m][q] = load_bytes(x + nb[m][k + q], r_bytes);
 #pragma unroll
                 for (int m = 0; m < R; ++m)
 #pragma unroll
@@ -315,7 +299,7 @@ __global__ __launch_bounds__(256) void hx_half_kernel(
                     constexpr int W = decltype(Wc)::value;
                     T xj[W];
 #pragma unroll
-                    for (int q = 0; q < W; ++q) xj[q] = load_at(x + nb[m][k + q], r_bytes);
+                    for (int q = 0; q < W; ++q) xj[q] = load_bytes(x + nb[m][k + q], r_bytes);
 #pragma unroll
                     for (int q = 0; q < W; ++q) {
                         const uint32_t b = bi[k + q];
@@ -427,7 +411,7 @@ __device__ __forceinline__ void staged_item(const HalfArgs<I> &g, const StagedWa
         nb[m] = w.nbr + (size_t)hs[m] * g.width;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            xi[m][j] = load_at(w.x + off[m], rb[j] * (uint32_t)sizeof(T));
+            xi[m][j] = load_bytes(w.x + off[m], rb[j] * (uint32_t)sizeof(T));
             acc[m][j] = 0;
         }
     }
@@ -496,7 +480,7 @@ __device__ __forceinline__ void staged_item(const HalfArgs<I> &g, const StagedWa
                 T xj[W];
 #pragma unroll
                 for (int q = 0; q < W; ++q)
-                    xj[q] = load_at(w.x + o[q], rb[j] * (uint32_t)sizeof(T));
+                    xj[q] = load_bytes(w.x + o[q], rb[j] * (uint32_t)sizeof(T));
 #pragma unroll
                 for (int q = 0; q < W; ++q) acc[m][j] += c[q] * (xj[q] - xi[m][j]);
             }

@@ -48,13 +48,12 @@ constexpr int kWgPiece = 8;          // high-word targets of a piece
 // three wide scalar loads.  Low: m holds the two bits of every bond.
 // Straddling: the bonds share their low site (m[0] its bit), slot holds the
 // slot of every high site.
-template <typename T>
 struct WgOp {
     int32_t n;           // bonds in use: 8, 4, 2 or 1
     uint32_t slot[2];    // a byte each
     int32_t straddle;    // 0: both sites in the low word
     uint32_t m[8];
-    T c[8];              // -J/2
+    double c[8];         // -J/2
 };
 
 struct WgTables {
@@ -80,57 +79,38 @@ static void free_wg(void *p) {
 
 struct WgBonds {
     void *mem = nullptr;
-    void *front = nullptr, *strad = nullptr; // WgOp<T>: below K0, straddling K0
+    WgOp *front = nullptr, *strad = nullptr; // below K0, straddling K0
     uint32_t *vbit = nullptr;                // bit of every straddling high site
     uint32_t *hdr = nullptr;                 // [block][hw]: off, size | start << 16, flips, bits of
                                              // the straddling high sites by slot, then per slot:
                                              // off, size (flips: of the two lists, 16 bits each)
     uint32_t *hoff = nullptr;                // [block][mh] target blocks of the high-word bonds,
-    void *hcf = nullptr;                     // [block][mh] their -J/2: mh1 of the first list
+    double *hcf = nullptr;                   // [block][mh] their -J/2: mh1 of the first list
     int nfront = 0, nstrad = 0, nslot = 0, mh1 = 0, mh = 0, hw = 0;
 };
-struct WgBondSet {
-    WgBonds by_type[2];
-    bool have[2] = {false, false};
-};
 static void free_wg_bonds(void *p) {
-    auto *s = (WgBondSet *)p;
-    if (!s) return;
-    for (auto &b : s->by_type)
-        if (b.mem) (void)hipFree(b.mem);
-    delete s;
+    auto *d = (WgBonds *)p;
+    if (!d) return;
+    if (d->mem) (void)hipFree(d->mem);
+    delete d;
 }
 
-template <typename T>
 struct WgArgs {
     const uint16_t *rankL, *unrankL;
-    const WgOp<T> *front, *strad;
+    const WgOp *front, *strad;
     const uint32_t *hdr, *hoff;
-    const T *hcf;
-    uint32_t n_blocks, run;
+    const double *hcf;
+    uint32_t n_blocks;
     int K, nfront, nstrad, nslot, mh1, mh, hw, stride;
     double shift;
 };
 
-template <typename T> using Const = const __attribute__((address_space(4))) T;
-template <typename T>
-__device__ __forceinline__ const Const<T> *as_const(const T *p) {
-    return (const Const<T> *)p;
-}
-
-// Element i of a vector below 4 GiB: scalar base and 32-bit byte offset.
-template <typename T>
-__device__ __forceinline__ T load_at(const T *__restrict__ base, uint32_t i) {
-    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
-                                        i * (uint32_t)sizeof(T));
-}
-
 // W low-word bonds from LDS.
-template <int W, typename T>
-__device__ __forceinline__ void wg_low(const Const<WgOp<T>> &op, uint32_t L, uint32_t r,
-                                       const uint16_t *rankL, const T *xs, T xi, T &acc) {
+template <int W>
+__device__ __forceinline__ void wg_low(const Const<WgOp> &op, uint32_t L, uint32_t r,
+                                       const uint16_t *rankL, const double *xs, double xi, double &acc) {
     uint32_t idx[W];
-    T xj[W];
+    double xj[W];
 #pragma unroll
     for (int q = 0; q < W; ++q) {
         const uint32_t m = op.m[q], t = rankL[L ^ m];
@@ -144,11 +124,11 @@ __device__ __forceinline__ void wg_low(const Const<WgOp<T>> &op, uint32_t L, uin
 
 // W straddling bonds of one low site: they flip where the low bit differs from
 // the bond's high bit, which is the same for the whole block.
-template <int W, typename T>
-__device__ __forceinline__ void wg_straddle(const Const<WgOp<T>> &op, uint32_t hmask, bool set,
-                                            uint32_t rk, uint32_t r, int stride, const T *xs, T xi,
-                                            T &acc) {
-    T xj[W];
+template <int W>
+__device__ __forceinline__ void wg_straddle(const Const<WgOp> &op, uint32_t hmask, bool set,
+                                            uint32_t rk, uint32_t r, int stride, const double *xs, double xi,
+                                            double &acc) {
+    double xj[W];
 #pragma unroll
     for (int q = 0; q < W; ++q) {
         const uint32_t slot = (op.slot[q / 4] >> (8 * (q % 4))) & 0xffu;
@@ -159,35 +139,30 @@ __device__ __forceinline__ void wg_straddle(const Const<WgOp<T>> &op, uint32_t h
     for (int q = 0; q < W; ++q) acc += op.c[q] * (xj[q] - xi);
 }
 
-template <typename T, bool DOT, bool STORE>
+template <bool DOT, bool STORE>
 __global__ __launch_bounds__(256) void hx_half_wg_kernel(
-    const WgArgs<T> g, const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ prev,
-    const LzStep step, double *__restrict__ partial, T *__restrict__ store) {
+    const WgArgs g, const double *__restrict__ x, double *__restrict__ y,
+    const double *__restrict__ prev, const LzStep step, double *__restrict__ partial,
+    double *__restrict__ store) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[kLzLds];
-    T *xs = reinterpret_cast<T *>(smem);
+    double *xs = reinterpret_cast<double *>(smem);
     uint16_t *rankL = reinterpret_cast<uint16_t *>(
-        smem + ((size_t)(1 + g.nslot) * g.stride * sizeof(T) + 15) / 16 * 16);
+        smem + ((size_t)(1 + g.nslot) * g.stride * sizeof(double) + 15) / 16 * 16);
     {
         const uint4 *s4 = reinterpret_cast<const uint4 *>(g.rankL);
         uint4 *d4 = reinterpret_cast<uint4 *>(rankL);
         for (int t = threadIdx.x; t < (1 << g.K) / 8; t += blockDim.x) d4[t] = s4[t];
     }
     double sigma = 1.0, cprev = 0.0;
-    const T shift = (T)g.shift;
+    const double shift = g.shift;
     const Const<uint32_t> *hdrs = as_const(g.hdr), *hoffs = as_const(g.hoff);
-    const Const<T> *hcfs = as_const(g.hcf);
-    const Const<WgOp<T>> *front = as_const(g.front), *strad = as_const(g.strad);
-    // XCDs (workgroup b runs on XCD b % 8) take turns on runs of g.run blocks
-    const bool by_xcd = gridDim.x % kXcds == 0;
-    const uint32_t x8 = by_xcd ? blockIdx.x % kXcds : 0;
-    const uint32_t l0 = by_xcd ? blockIdx.x / kXcds : blockIdx.x;
-    const uint32_t lstep = by_xcd ? gridDim.x / kXcds : gridDim.x;
+    const Const<double> *hcfs = as_const(g.hcf);
+    const Const<WgOp> *front = as_const(g.front), *strad = as_const(g.strad);
     double dot = 0.0;
-    for (uint32_t l = l0;; l += lstep) {
-        const uint32_t it = by_xcd ? (l / g.run) * (kXcds * g.run) + x8 * g.run + l % g.run : l;
+    for (uint32_t it = blockIdx.x;; it += gridDim.x) {
         const bool any = it < g.n_blocks;
-        if (!any && l != l0) break;
+        if (!any && it != blockIdx.x) break;
         const Const<uint32_t> *hdr = hdrs + (size_t)(any ? it : 0) * g.hw;
         const uint32_t off = hdr[0], hmask = hdr[3];
         const int S = any ? (int)(hdr[1] & 0xffffu) : 0, cs = (int)(hdr[1] >> 16);
@@ -195,10 +170,10 @@ __global__ __launch_bounds__(256) void hx_half_wg_kernel(
         // one round of coalesced loads: this block and those its straddling
         // bonds reach
         for (int r = threadIdx.x; any && r < g.stride; r += blockDim.x) {
-            T v = 0;
+            double v = 0;
             if (r < S) v = load_at(x, off + (uint32_t)r);
             for (int s0 = 0; s0 < g.nslot; s0 += 4) {
-                T t[4];
+                double t[4];
                 bool in[4];
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
@@ -212,7 +187,7 @@ __global__ __launch_bounds__(256) void hx_half_wg_kernel(
             if (r < S) xs[r] = v;
         }
         // the step's scalars while the first round is on its way
-        if (l == l0) {
+        if (it == blockIdx.x) {
             double sg, cp;
             if (!lz_begin(step, red, sg, cp)) return;
             sigma = uniform(sg);
@@ -221,34 +196,34 @@ __global__ __launch_bounds__(256) void hx_half_wg_kernel(
         }
         __syncthreads();
         const Const<uint32_t> *hoff = hoffs + (size_t)it * g.mh;
-        const Const<T> *hcf = hcfs + (size_t)it * g.mh;
+        const Const<double> *hcf = hcfs + (size_t)it * g.mh;
         for (int r0 = 0; r0 < S; r0 += blockDim.x) {
             const uint32_t r = (uint32_t)r0 + threadIdx.x;
             if ((int)r >= S) break;
             const uint32_t L = g.unrankL[cs + r];
             // the first pieces of high-word targets are on their way meanwhile
-            T xh[kWgPiece], xc[kWgPiece];
+            double xh[kWgPiece], xc[kWgPiece];
 #pragma unroll
-            for (int q = 0; q < kWgPiece; ++q) xh[q] = q < g.mh1 ? load_at(x, hoff[q] + r) : (T)0;
+            for (int q = 0; q < kWgPiece; ++q) xh[q] = q < g.mh1 ? load_at(x, hoff[q] + r) : 0.0;
 #pragma unroll
             for (int q = 0; q < kWgPiece; ++q)
-                xc[q] = g.mh1 + q < g.mh ? load_at(x, hoff[g.mh1 + q] + r) : (T)0;
-            T pv = 0;
+                xc[q] = g.mh1 + q < g.mh ? load_at(x, hoff[g.mh1 + q] + r) : 0.0;
+            double pv = 0;
             if (prev) pv = load_at(prev, off + r);
-            const T xi = xs[r];
-            T acc = 0;
-            auto straddle = [&](const Const<WgOp<T>> &op) {
+            const double xi = xs[r];
+            double acc = 0;
+            auto straddle = [&](const Const<WgOp> &op) {
                 const uint32_t m1 = op.m[0], rk = rankL[L ^ m1];
                 const bool set = (L & m1) != 0;
-                if (op.n == 8) wg_straddle<8, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
-                else if (op.n == 4) wg_straddle<4, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
-                else if (op.n == 2) wg_straddle<2, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
-                else wg_straddle<1, T>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
+                if (op.n == 8) wg_straddle<8>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
+                else if (op.n == 4) wg_straddle<4>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
+                else if (op.n == 2) wg_straddle<2>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
+                else wg_straddle<1>(op, hmask, set, rk, r, g.stride, xs, xi, acc);
             };
             // high-word bonds that flip for h, n of them from place `at` of the
             // block's list (padded with the own block and coefficient 0); the first
             // piece is loaded
-            auto high = [&](int at, int n, T (&xj)[kWgPiece]) {
+            auto high = [&](int at, int n, double (&xj)[kWgPiece]) {
                 for (int q0 = 0; q0 < n; q0 += kWgPiece) {
                     if (q0 > 0)
 #pragma unroll
@@ -258,23 +233,22 @@ __global__ __launch_bounds__(256) void hx_half_wg_kernel(
                 }
             };
             for (int o = 0; o < g.nfront; ++o) {
-                const Const<WgOp<T>> &op = front[o];
+                const Const<WgOp> &op = front[o];
                 if (op.straddle) straddle(op);
-                else if (op.n == 8) wg_low<8, T>(op, L, r, rankL, xs, xi, acc);
-                else if (op.n == 4) wg_low<4, T>(op, L, r, rankL, xs, xi, acc);
-                else if (op.n == 2) wg_low<2, T>(op, L, r, rankL, xs, xi, acc);
-                else wg_low<1, T>(op, L, r, rankL, xs, xi, acc);
+                else if (op.n == 8) wg_low<8>(op, L, r, rankL, xs, xi, acc);
+                else if (op.n == 4) wg_low<4>(op, L, r, rankL, xs, xi, acc);
+                else if (op.n == 2) wg_low<2>(op, L, r, rankL, xs, xi, acc);
+                else wg_low<1>(op, L, r, rankL, xs, xi, acc);
             }
             high(0, nf, xh);
             for (int o = 0; o < g.nstrad; ++o) straddle(strad[o]);
             high(g.mh1, nc, xc);
-            const T hv = shift * xi + acc;
-            double w = sigma * (double)hv;
-            if (prev) w -= cprev * (double)pv;
-            const T wt = (T)w;
-            y[off + r] = wt;
-            if constexpr (DOT) dot += (double)wt * (sigma * (double)xi);
-            if constexpr (STORE) store[off + r] = (T)(sigma * (double)xi);
+            const double hv = shift * xi + acc;
+            double w = sigma * hv;
+            if (prev) w -= cprev * pv;
+            y[off + r] = w;
+            if constexpr (DOT) dot += w * (sigma * xi);
+            if constexpr (STORE) store[off + r] = sigma * xi;
         }
         __syncthreads();       // the next block overwrites the slices
     }
@@ -327,7 +301,6 @@ __global__ __launch_bounds__(kBlock) void wg_dots_kernel(const uint2 *__restrict
 }
 
 // Rows of the block tables, one thread per block.
-template <typename T>
 __global__ __launch_bounds__(kBlock) void wg_rows(const uint32_t *__restrict__ blocks, int64_t n,
                                                   const uint32_t *__restrict__ off, int K, int K0,
                                                   int A,
@@ -337,7 +310,7 @@ __global__ __launch_bounds__(kBlock) void wg_rows(const uint32_t *__restrict__ b
                                                   int mh1, int mh, int hw,
                                                   uint32_t *__restrict__ hdr,
                                                   uint32_t *__restrict__ hoff,
-                                                  T *__restrict__ hcf) {
+                                                  double *__restrict__ hcf) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t h = blocks[i], own = off[h];
@@ -364,7 +337,7 @@ __global__ __launch_bounds__(kBlock) void wg_rows(const uint32_t *__restrict__ b
             const int list = bonds[b].u < K0 && bonds[b].v >= K0;
             const size_t at = (size_t)i * mh + (list ? mh1 + c[1]++ : c[0]++);
             hoff[at] = off[h ^ m];
-            hcf[at] = (T)bonds[b].mJ2;
+            hcf[at] = bonds[b].mJ2;
         }
         row[2] = (uint32_t)c[0] | (uint32_t)c[1] << 16;
         for (int list = 0; list < 2; ++list)
@@ -426,8 +399,8 @@ static void wg_counts(const Couplings *c, int K, int *nL, int *nH, int *nS, int 
     *nslot = __builtin_popcount(*vmask);
 }
 
-static size_t wg_lds(int K, int nslot, size_t es) {
-    return ((size_t)(1 + nslot) * choose2(K, K / 2) * es + 15) / 16 * 16 + ((size_t)2 << K);
+static size_t wg_lds(int K, int nslot) {
+    return ((size_t)(1 + nslot) * choose2(K, K / 2) * sizeof(double) + 15) / 16 * 16 + ((size_t)2 << K);
 }
 
 // Where it is the automatic choice: FP64, up to kWgRows rows, blocks of
@@ -453,7 +426,7 @@ bool wg_fits(const Basis *b, const Couplings *c, int dtype) {
     int nL, nH, nS, nslot;
     uint32_t vm;
     wg_counts(c, K, &nL, &nH, &nS, &nslot, &vm);
-    return wg_lds(K, nslot, 8) <= kWgMaxLds &&
+    return wg_lds(K, nslot) <= kWgMaxLds &&
            (size_t)n * ((nH + 16) * 12 + 64 + 8 * nslot) <= kWgMaxTables;
 }
 
@@ -533,7 +506,6 @@ static int wg_prepare(Basis *b, WgTables **out) {
     return HM_OK;
 }
 
-template <typename T>
 static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t, WgBonds *d) {
     const int K = t->K;
     int nH;
@@ -553,19 +525,19 @@ static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t
         else if (bd.u < K0 && bd.v >= K0) ++nH2;
     }
     auto pieces = [&](const std::vector<const BondDev *> &v) {
-        std::vector<WgOp<T>> ops;
+        std::vector<WgOp> ops;
         for (size_t i = 0; i < v.size();) {
             const bool straddle = v[i]->v >= K;
             size_t n = 1;
             while (i + n < v.size() && (v[i + n]->v >= K) == straddle &&
                    (!straddle || v[i + n]->u == v[i]->u))
                 ++n;
-            WgOp<T> op{};
+            WgOp op{};
             op.n = n >= 8 ? 8 : n >= 4 ? 4 : n >= 2 ? 2 : 1;
             op.straddle = straddle;
             if (straddle) op.m[0] = 1u << v[i]->u;
             for (int q = 0; q < op.n; ++q, ++i) {
-                op.c[q] = (T)v[i]->mJ2;
+                op.c[q] = v[i]->mJ2;
                 if (!straddle) {
                     op.m[q] = 1u << v[i]->u | 1u << v[i]->v;
                     continue;
@@ -577,7 +549,7 @@ static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t
         }
         return ops;
     };
-    const std::vector<WgOp<T>> front = pieces(below), strad = pieces(across);
+    const std::vector<WgOp> front = pieces(below), strad = pieces(across);
     d->nfront = (int)front.size();
     d->nstrad = (int)strad.size();
     auto padded = [](int n) { return (n + kWgPiece - 1) / kWgPiece * kWgPiece; };
@@ -597,89 +569,78 @@ static hipError_t wg_build(const Basis *b, const Couplings *c, const WgTables *t
         return at;
     };
     const size_t nblk = (size_t)t->n_blocks;
-    const size_t o_front = add(front.size() * sizeof(WgOp<T>)),
-                 o_str = add(strad.size() * sizeof(WgOp<T>)), o_vb = add(vbit.size() * 4),
+    const size_t o_front = add(front.size() * sizeof(WgOp)),
+                 o_str = add(strad.size() * sizeof(WgOp)), o_vb = add(vbit.size() * 4),
                  o_cls = add(cls.size() * 4), hostlen = total;
     const size_t o_hdr = add(nblk * d->hw * 4), o_hoff = add(nblk * d->mh * 4),
-                 o_hcf = add(nblk * d->mh * sizeof(T));
+                 o_hcf = add(nblk * d->mh * sizeof(double));
     std::vector<unsigned char> host(hostlen);
     auto put = [&](size_t at, const void *p, size_t bytes) {
         if (bytes) std::memcpy(host.data() + at, p, bytes);
     };
-    put(o_front, front.data(), front.size() * sizeof(WgOp<T>));
-    put(o_str, strad.data(), strad.size() * sizeof(WgOp<T>));
+    put(o_front, front.data(), front.size() * sizeof(WgOp));
+    put(o_str, strad.data(), strad.size() * sizeof(WgOp));
     put(o_vb, vbit.data(), vbit.size() * 4);
     put(o_cls, cls.data(), cls.size() * 4);
     hipError_t e = hipMalloc(&d->mem, total);
     if (e == hipSuccess) e = hipMemcpy(d->mem, host.data(), hostlen, hipMemcpyHostToDevice);
     if (e != hipSuccess) return e;
     unsigned char *m = (unsigned char *)d->mem;
-    d->front = m + o_front;
-    d->strad = m + o_str;
+    d->front = (WgOp *)(m + o_front);
+    d->strad = (WgOp *)(m + o_str);
     d->vbit = (uint32_t *)(m + o_vb);
     d->hdr = (uint32_t *)(m + o_hdr);
     d->hoff = (uint32_t *)(m + o_hoff);
-    d->hcf = m + o_hcf;
+    d->hcf = (double *)(m + o_hcf);
     const int grid = (int)std::min<int64_t>((t->n_blocks + kBlock - 1) / kBlock, kMaxGrid);
-    hipLaunchKernelGGL(wg_rows<T>, dim3(grid), dim3(kBlock), 0, nullptr, t->d_blocks, t->n_blocks,
+    hipLaunchKernelGGL(wg_rows, dim3(grid), dim3(kBlock), 0, nullptr, t->d_blocks, t->n_blocks,
                        t->d_off, K, K0, b->A, (const int *)(m + o_cls), c->dev, c->nb, d->vbit,
-                       d->nslot, d->mh1, d->mh, d->hw, d->hdr, d->hoff, (T *)d->hcf);
+                       d->nslot, d->mh1, d->mh, d->hw, d->hdr, d->hoff, d->hcf);
     e = hipGetLastError();
     // other streams may use the tables from now on
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     return e;
 }
 
-static int wg_get(Basis *b, const Couplings *c, int dtype, hipStream_t st, WgTables **tout,
+static int wg_get(Basis *b, const Couplings *c, hipStream_t st, WgTables **tout,
                   const WgBonds **bout) {
     std::lock_guard<std::mutex> lock(b->mu);
     HM_TRY(device_prepare(b));
     auto *cc = const_cast<Couplings *>(c);
+    if (!cc->wg && is_capturing(st)) return HM_ENOMEM;
+    HM_TRY(wg_prepare(b, tout));
     if (!cc->wg) {
-        cc->wg = new WgBondSet;
-        cc->wg_free = free_wg_bonds;
-    }
-    auto *set = (WgBondSet *)cc->wg;
-    const int k = dtype == HM_F64 ? 0 : 1;
-    if (!set->have[k] && is_capturing(st)) return HM_ENOMEM;
-    WgTables *t = nullptr;
-    HM_TRY(wg_prepare(b, &t));
-    if (!set->have[k]) {
-        WgBonds d;
-        const hipError_t e = dtype == HM_F64 ? wg_build<double>(b, c, t, &d)
-                                             : wg_build<float>(b, c, t, &d);
+        auto *d = new WgBonds;
+        const hipError_t e = wg_build(b, c, *tout, d);
         if (e != hipSuccess) {
-            if (d.mem) (void)hipFree(d.mem);
+            free_wg_bonds(d);
             return fail(e == hipErrorOutOfMemory ? HM_ENOMEM : HM_EDEVICE, "block kernel bonds: %s",
                         hipGetErrorString(e));
         }
-        set->by_type[k] = d;
-        set->have[k] = true;
+        cc->wg = d;
+        cc->wg_free = free_wg_bonds;
     }
-    *tout = t;
-    *bout = &set->by_type[k];
+    *bout = (const WgBonds *)cc->wg;
     return HM_OK;
 }
 
-int wg_prepare_tables(Basis *b, const Couplings *c, int dtype) {
+int wg_prepare_tables(Basis *b, const Couplings *c) {
     WgTables *t = nullptr;
     const WgBonds *d = nullptr;
-    return wg_get(b, c, dtype, nullptr, &t, &d);
+    return wg_get(b, c, nullptr, &t, &d);
 }
 
-template <typename T>
-static void launch_wg_t(const Basis *b, const Couplings *c, const WgTables *t, const WgBonds *d,
+static void launch_rows(const Basis *b, const Couplings *c, const WgTables *t, const WgBonds *d,
                         const HxPass &p, hipStream_t st) {
-    WgArgs<T> g{};
+    WgArgs g{};
     g.rankL = t->d_rankL;
     g.unrankL = t->d_unrankL;
-    g.front = (const WgOp<T> *)d->front;
-    g.strad = (const WgOp<T> *)d->strad;
+    g.front = d->front;
+    g.strad = d->strad;
     g.hdr = d->hdr;
     g.hoff = d->hoff;
-    g.hcf = (const T *)d->hcf;
+    g.hcf = d->hcf;
     g.n_blocks = (uint32_t)t->n_blocks;
-    g.run = 1;
     g.K = t->K;
     g.nfront = d->nfront;
     g.nstrad = d->nstrad;
@@ -690,11 +651,11 @@ static void launch_wg_t(const Basis *b, const Couplings *c, const WgTables *t, c
     g.stride = t->smax;
     g.shift = c->diag_shift;
     const int grid = hx_wg_grid(b);
-    const size_t lds = wg_lds(t->K, d->nslot, sizeof(T));
-    const T *x = (const T *)p.x, *pr = (const T *)p.p;
-    T *y = (T *)p.y, *store = (T *)p.store;
+    const size_t lds = wg_lds(t->K, d->nslot);
+    const double *x = (const double *)p.x, *pr = (const double *)p.p;
+    double *y = (double *)p.y, *store = (double *)p.store;
 #define HM_LAUNCH(D, S)                                                                      \
-    hipLaunchKernelGGL((hx_half_wg_kernel<T, D, S>), dim3(grid), dim3(t->threads), lds, st, g, \
+    hipLaunchKernelGGL((hx_half_wg_kernel<D, S>), dim3(grid), dim3(t->threads), lds, st, g,  \
                        x, y, pr, p.step, p.partial, store)
     const bool dot = p.partial != nullptr, sto = store != nullptr;
     if (!dot && !sto) HM_LAUNCH(false, false);
@@ -704,24 +665,23 @@ static void launch_wg_t(const Basis *b, const Couplings *c, const WgTables *t, c
 #undef HM_LAUNCH
 }
 
-// items: the dots of hx_half_kernel (a launch of their own; FP64).
-int launch_hx_wg(const Basis *cb, const Couplings *c, int dtype, bool items, const HxPass &p,
+// items: the dots of hx_half_kernel, in a launch of their own.
+int launch_hx_wg(const Basis *cb, const Couplings *c, bool items, const HxPass &p,
                  hipStream_t st) {
     Basis *b = const_cast<Basis *>(cb);
     WgTables *t = nullptr;
     const WgBonds *d = nullptr;
-    const int rc = wg_get(b, c, dtype, st, &t, &d);
+    const int rc = wg_get(b, c, st, &t, &d);
     if (rc == HM_ENOMEM && !p.step.sigma) {
         // no memory for the tables, or a product captured before its first use
         clear_error();
         (void)hipGetLastError();
-        return launch_hx_built(b, c, dtype, p, st);
+        return launch_hx_built(b, c, HM_F64, p, st);
     }
     HM_TRY(rc);
     HxPass rows = p;
     if (items) rows.partial = nullptr;
-    if (dtype == HM_F64) launch_wg_t<double>(b, c, t, d, rows, st);
-    else launch_wg_t<float>(b, c, t, d, rows, st);
+    launch_rows(b, c, t, d, rows, st);
     if (items && p.partial)
         hipLaunchKernelGGL(wg_dots_kernel, dim3(hx_half_grid(b)), dim3(kBlock), 0, st, t->d_items,
                            (uint32_t)t->n_items, (const double *)p.y, (const double *)p.x,

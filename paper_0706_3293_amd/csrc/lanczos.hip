@@ -47,10 +47,10 @@ int launch_hx_digit(const Basis *b, const Couplings *c, int dtype, const HxPass 
 int hx_digit_grid(const Basis *b);
 int digit_prepare_tables(Basis *b, const Couplings *c, int dtype);
 bool digit_fits(const Basis *b, const Couplings *c);
-int launch_hx_wg(const Basis *b, const Couplings *c, int dtype, bool items, const HxPass &p,
+int launch_hx_wg(const Basis *b, const Couplings *c, bool items, const HxPass &p,
                  hipStream_t st);
 int hx_wg_grid(const Basis *b);
-int wg_prepare_tables(Basis *b, const Couplings *c, int dtype);
+int wg_prepare_tables(Basis *b, const Couplings *c);
 bool wg_fits(const Basis *b, const Couplings *c, int dtype);
 
 // 0 = automatic (the block kernel of the spin, where it applies to the basis
@@ -102,7 +102,7 @@ int prepare_kernel(Basis *b, const Couplings *c, int dtype, int kernel) {
     if (kernel == 2 || kernel == kKernelStaged)
         return half_prepare_tables(b, c, kernel == kKernelStaged);
     if (kernel == kKernelDigit) return digit_prepare_tables(b, c, dtype);
-    if (kernel == kKernelWg || kernel == kKernelWgItems) return wg_prepare_tables(b, c, dtype);
+    if (kernel == kKernelWg || kernel == kKernelWgItems) return wg_prepare_tables(b, c);
     return HM_OK;
 }
 
@@ -112,7 +112,7 @@ int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel, const H
         return launch_hx_half(b, c, dtype, kernel == kKernelStaged, p, st);
     if (kernel == kKernelDigit) return launch_hx_digit(b, c, dtype, p, st);
     if (kernel == kKernelWg || kernel == kKernelWgItems)
-        return launch_hx_wg(b, c, dtype, kernel == kKernelWgItems, p, st);
+        return launch_hx_wg(b, c, kernel == kKernelWgItems, p, st);
     return launch_hx_generic(b, c, dtype, p, st);
 }
 
