@@ -668,8 +668,8 @@ __global__ __launch_bounds__(kBlock) void digit_row_blocks(const DigitBlock<I> *
 template <typename T, typename I, typename PI>
 __global__ __launch_bounds__(kBlock) void digit_rows(
     const PI *__restrict__ P, const DigitBlock<I> *__restrict__ blocks, int64_t n, int log_parts,
-    bool lane_per_row, int N, int K, int A, int two_s, int bits, uint32_t mask, const BondDev *__restrict__ bonds, int nb,
-    int nF, const double *__restrict__ ladder, int nS, int mw, DigitMoves<T, I> *__restrict__ moves,
+    bool lane_per_row, int N, int K, int A, int two_s, int bits, uint32_t mask,
+    const BondDev *__restrict__ bonds, int nb, int nF, const double *__restrict__ ladder, int nS, int mw, DigitMoves<T, I> *__restrict__ moves,
     uint32_t *__restrict__ mcnt, T *__restrict__ dhigh, int nH, T *__restrict__ kdiag,
     T *__restrict__ hJ4, I *__restrict__ strad) {
     const int parts = 1 << log_parts;

@@ -108,7 +108,8 @@ struct WgArgs {
 // W low-word bonds from LDS.
 template <int W>
 __device__ __forceinline__ void wg_low(const Const<WgOp> &op, uint32_t L, uint32_t r,
-                                       const uint16_t *rankL, const double *xs, double xi, double &acc) {
+                                       const uint16_t *rankL, const double *xs, double xi,
+                                       double &acc) {
     uint32_t idx[W];
     double xj[W];
 #pragma unroll
@@ -126,8 +127,8 @@ __device__ __forceinline__ void wg_low(const Const<WgOp> &op, uint32_t L, uint32
 // the bond's high bit, which is the same for the whole block.
 template <int W>
 __device__ __forceinline__ void wg_straddle(const Const<WgOp> &op, uint32_t hmask, bool set,
-                                            uint32_t rk, uint32_t r, int stride, const double *xs, double xi,
-                                            double &acc) {
+                                            uint32_t rk, uint32_t r, int stride,
+                                            const double *xs, double xi, double &acc) {
     double xj[W];
 #pragma unroll
     for (int q = 0; q < W; ++q) {
@@ -359,8 +360,8 @@ static int64_t choose2(int n, int k) {
 }
 
 // Low sites: blocks of at most 252 rows, a row per thread, and about as many
-// blocks as rows of one for small N.  Measured (us per FP64 Lanczos step, J1-J2
-// rings unless said, K = 8 / 9 / 10 / 11): N = 16 15.9 / 15.7 / 16.1 / 18.4;
+// blocks as rows of one for small N.  Measured (us per FP64 Lanczos step with the
+// dots taken in this kernel, J1-J2 rings unless said, K = 8 / 9 / 10 / 11): N = 16 15.9 / 15.7 / 16.1 / 18.4;
 // N = 18 20.1 / 16.8 / 16.4 / 19.7; N = 20 27.0 / 23.7 / 22.9 / 24.5; N = 20 with
 // all bonds 47.8 / 41.0 / 36.3 / 43.5.
 static int wg_low_bits(const Basis *b) { return std::min(10, (b->N + 2) / 2); }
@@ -400,17 +401,18 @@ static void wg_counts(const Couplings *c, int K, int *nL, int *nH, int *nS, int 
 }
 
 static size_t wg_lds(int K, int nslot) {
-    return ((size_t)(1 + nslot) * choose2(K, K / 2) * sizeof(double) + 15) / 16 * 16 + ((size_t)2 << K);
+    return ((size_t)(1 + nslot) * choose2(K, K / 2) * sizeof(double) + 15) / 16 * 16 +
+           ((size_t)2 << K);
 }
 
 // Where it is the automatic choice: FP64, up to kWgRows rows, blocks of
 // kWgRowsPerBlock rows on average, and no schedule asked for (that is one of
 // hx_half.hip's kernels).  Measured against hx_half_kernel (us per FP64 Lanczos
-// step): N = 12 13.0 / 14.3, N = 16 15.7 / 20.7, N = 18 16.4 / 19.8, N = 20 22.9 /
+// step, the dots taken in either kernel): N = 12 13.0 / 14.3, N = 16 15.7 / 20.7, N = 18 16.4 / 19.8, N = 20 22.9 /
 // 24.7, N = 20 with all 190 bonds 36.3 / 51.7; N = 21 28 / 28, N = 22 42 / 37, N = 24
 // 118 / 108, where the wave's own rows keep enough gathers in flight; N = 28,
-// M = 10 (5 rows per block) 33 / 23.  In FP32 another K changes the order of a
-// row's sums, which FP32-mixed runs in subspaces this small show.
+// M = 10 (5 rows per block) 33 / 23.  A run whose dots have a launch of their own
+// chooses again among these (wg_items_pay in lanczos.hip).
 constexpr int64_t kWgRows = (int64_t)1 << 18;
 constexpr int64_t kWgRowsPerBlock = 48;
 

@@ -121,8 +121,8 @@ int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel, const H
 constexpr int64_t kTableRows = 3072;
 constexpr int64_t kSmallMaxDim = 1 << 20;
 constexpr int kTableCoefs = 1024;    // most reorthogonalization coefficients (LDS)
-// Most bytes of matrix elements, and of stored vectors in a step, that one
-// compute unit reads faster than a step's launches take.  One workgroup against
+// With reorthogonalization: most bytes of matrix elements, and of stored vectors in
+// a step, that one compute unit reads faster than a step's launches take.  One workgroup against
 // several kernels, us a step: 2,024 rows, 97,152 row-bonds FP64 10.1 / 18.7;
 // 1,716 rows, 133,848 row-bonds FP64 19.4 / 19.1, FP32 12.6 / 20.3; 60
 // reorthogonalized steps at 924 rows FP64 20 / 31, at 1,716 rows FP64 33 / 34,
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(kBlock) void scale_psi(double *__restrict__ psi, in
 // lanczos_table_kernel (up to kTableRows rows) finds every row's moves and
 // matrix elements once at the start of the run and keeps them in the
 // workspace, v_k and w in LDS and the thread's rows in registers: at 924 rows
-// and 12 bonds a step is 5.6 us in FP64 (two launches: 13.3) and over 20
+// and 12 bonds a step is 4.6 us in FP64 (two launches: 13.3) and over 20
 // reorthogonalized steps 13 us (five launches: 28).  What bounds it is one
 // compute unit's reads of the move tables and of the stored vectors from L2.
 // lanczos_small_kernel (v_k stored normalized) runs larger subspaces when asked
@@ -1380,8 +1380,8 @@ static int check_opts(const Basis *b, const hm_lanczos_opts *o) {
 // that stopped early takes the same kernels.  Without reorthogonalization only
 // the smallest runs: beyond convergence such a run amplifies its roundings (1e-16
 // to 1e-8 of the ground state in 200 steps), so from kSmallWork row-bonds on its
-// sums keep the order of the multi-kernel step (924 rows, FP64: 13 us a step
-// instead of 5.6).
+// sums keep the order of the multi-kernel step (924 rows, FP64: 14 us a step with
+// 24 bonds; with 12 bonds, in one workgroup, 4.6).
 constexpr int64_t kSmallWork = 16384;
 static int table_steps(const Basis *b, int64_t work, const hm_lanczos_opts *o) {
     const int64_t es = o->precision == HM_PREC_F64 ? 8 : 4;

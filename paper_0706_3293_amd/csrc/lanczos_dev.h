@@ -7,7 +7,8 @@
 // kernel of one workgroup costs a launch each (4.6 us back to back, more than
 // the pass B of a million rows), so on grids of up to kFoldMax workgroups
 // every workgroup sums them itself, in the same fixed order, while its first
-// loads would be waiting anyway: 8 loads per thread.  Larger grids keep the one-workgroup finishes, whose share is small there.
+// loads would be waiting anyway: 8 loads per thread.  Larger grids keep the
+// one-workgroup finishes, whose share is small there.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,10 +42,10 @@ struct LzStep {
     double *beta = nullptr, *sigma = nullptr, *cprev = nullptr, *scale = nullptr;
 };
 
-// Sum of n <= kFoldMax partials, returned to every thread, in the order of a workgroup of VT
-// threads that adds partials t, t + VT, ... in thread t, then the lanes of every
-// wave and the waves in turn: bit for bit the finish kernel of that size
-// (fixed_sum in lanczos.hip), so a run's coefficients do not depend on whether
+// Sum of n <= kFoldMax partials, returned to every thread, in the order of a
+// workgroup of VT threads that adds partials t, t + VT, ... in thread t, then the
+// lanes of every wave and the waves in turn: bit for bit the finish kernel of that
+// size (fixed_sum in lanczos.hip), so a run's coefficients do not depend on whether
 // its sums are folded.  (Runs past convergence amplify one rounding to 1e-8 of
 // the ground state.)  The waves that a smaller workgroup does not have are taken
 // by its own ones in turn; all 8 loads of a thread are in flight together.
