@@ -172,7 +172,9 @@ int hm_rank_dev(hm_basis h, const uint64_t *d_state, int64_t n,
  * kernel of the spin (s = 1/2, or s >= 1 up to 15/2) where its tables fit,
  * else the generic digit kernel.  The block kernels build device tables for a
  * coupling list on its first use (and element type, for s >= 1: at most 1 GiB or
- * four FP64 vectors, whichever is more, and 8 GiB).  A product captured before its
+ * four FP64 vectors, whichever is more, and 8 GiB; on its second product where the
+ * generic kernel computes the first, the same bits, in less time than the tables
+ * take).  A product captured before its
  * tables exist takes the kernel whose tables do, at last the generic one.
  * Asynchronous on `stream`.
  * HM_EINVAL: bad J (see above), null pointers, unknown dtype, d_x == d_y.

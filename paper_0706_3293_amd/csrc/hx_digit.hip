@@ -23,9 +23,9 @@
 // summed bond by bond with the roundings of row_hx, so that the rows are the
 // generic kernel's bit for bit: with equal couplings those roundings are the same
 // for many rows and do not average out (coefficients of FP32-mixed runs 1e-8
-// apart).  So it is in FP64 where a run's dots are the generic kernel's too (one lane
-// per row, up to 2^19 rows): coefficients past convergence then do not depend on
-// the kernel.  In larger FP64 subspaces it is the sum of a low-word part, a high-word
+// apart).  So it is in FP64 with one lane per row up to 2^20 rows; up to 2^19 a run's
+// dots are the generic kernel's too, and coefficients past convergence then do not
+// depend on the kernel.  In larger FP64 subspaces it is the sum of a low-word part, a high-word
 // part (both tabulated) and the straddling bonds (16 sites, s = 1, couplings of
 // 1.03: 95 us, bond by bond 140).  Where the type holds all of these sums exactly,
 // the tabulated parts give the same.
@@ -131,6 +131,7 @@ struct DigitBonds {
 struct DigitBondSet {
     DigitBonds by_type[2];
     bool have[2] = {false, false};
+    bool seen[2] = {false, false};    // the generic kernel has had the first product
 };
 static void free_digit_bonds(void *p) {
     auto *s = (DigitBondSet *)p;
@@ -1016,11 +1017,13 @@ static int digit_prepare(Basis *b, DigitTables **out) {
     return HM_OK;
 }
 
-// Whether a run has the generic kernel's partial sums, so that equal rows make its
-// coefficients equal: one lane per row and a workgroup for every 256 rows.
-static bool generic_bits(const Basis *b) {
-    return b->digit.flat && b->dim <= (int64_t)kMaxGrid * kBlock;
-}
+// Whether the rows are the generic kernel's in FP64 too.  Up to 2^19 rows a run has
+// that kernel's partial sums as well (one lane per row, a workgroup for every 256
+// rows), so that equal rows make its coefficients equal; up to kFlatRows the first
+// product may come from either kernel (digit_put_off).  The sums bond by bond cost 0
+// to 4 % there, in short blocks of larger subspaces 15 to 36 % (24 sites, s = 1,
+// A = 8, 5.6 M rows: 241 and 278 us).
+static bool generic_bits(const Basis *b) { return b->digit.flat && b->dim <= kFlatRows; }
 
 // Whether T holds every sum of diagonal terms of these couplings exactly
 // (multiples of one power of two, the largest below 2^24 or 2^53 of it; couplings
@@ -1191,16 +1194,20 @@ static hipError_t build_bonds_t(const Basis *b, const Couplings *c, const DigitT
 }
 
 // The tables of these couplings in this element type, built on first use.
-static int digit_get(Basis *b, const Couplings *c, int dtype, hipStream_t st, DigitTables **tout,
-                     const DigitBonds **bout) {
-    std::lock_guard<std::mutex> lock(b->mu);
-    HM_TRY(device_prepare(b));
+static DigitBondSet *bond_set(const Couplings *c) {
     auto *cc = const_cast<Couplings *>(c);
     if (!cc->half) {
         cc->half = new DigitBondSet;
         cc->half_free = free_digit_bonds;
     }
-    auto *set = (DigitBondSet *)cc->half;
+    return (DigitBondSet *)cc->half;
+}
+
+static int digit_get(Basis *b, const Couplings *c, int dtype, hipStream_t st, DigitTables **tout,
+                     const DigitBonds **bout) {
+    std::lock_guard<std::mutex> lock(b->mu);
+    HM_TRY(device_prepare(b));
+    DigitBondSet *set = bond_set(c);
     const int k = dtype == HM_F64 ? 0 : 1;
     if (!set->have[k] && is_capturing(st)) return HM_ENOMEM;
     DigitTables *t = nullptr;
@@ -1299,9 +1306,40 @@ static void launch_digit_t(const Basis *b, const DigitTables *t, const DigitBond
     else launch_digit_r<T, I, 4>(t, g, lds, p, st);
 }
 
+// Whether a coupling list's first plain product goes to the generic kernel, whose
+// rows are the same bit for bit: where that product costs less than this kernel's
+// tables, which a list used once never pays back.  That is below some kFirstWork
+// row-bonds, and in blocks of a few rows, whose tables take as long as the rows.
+// Measured (us of a first product with new couplings on a used basis, generic kernel
+// / tables and product; FP32, J1-J2 rings unless said):
+//   s = 1,   12 sites, M = 0,     73,789 rows,   24 bonds:   61 / 90,  later  50 / 30
+//   s = 1,   14 sites, M = 0,    616,227 rows,   28 bonds:   97 / 104, later  85 / 38
+//   s = 3/2, 12 sites, M = 0,  1,703,636 rows,   12 bonds:  103 / 116, later  91 / 48
+//   s = 1,   15 sites, M = 0,  1,787,607 rows,   15 bonds:  120 / 121, later 109 / 48
+//   s = 1,   14 sites, M = 0,    616,227 rows,   91 bonds:  308 / 200, later 290 / 86
+//   s = 1,   20 sites, M = 13,   484,500 rows,   40 bonds:  112 / 188, later 101 / 54
+//   s = 1,   24 sites, M = 16, 5,612,805 rows,   48 bonds:  762 / 1048, later 748 / 406
+constexpr int64_t kFirstWork = (int64_t)1 << 25, kFirstRows = 16;
+
+static bool digit_put_off(Basis *b, const Couplings *c, int dtype) {
+    if (dtype == HM_F64 && !generic_bits(b)) return false;
+    if (b->dim * c->nb >= kFirstWork && b->dim >= kFirstRows * b->digit.n_blocks) return false;
+    std::lock_guard<std::mutex> lock(b->mu);
+    DigitBondSet *set = bond_set(c);
+    const int k = dtype == HM_F64 ? 0 : 1;
+    if (set->have[k] || set->seen[k]) return false;
+    set->seen[k] = true;
+    return true;
+}
+
 int launch_hx_digit(const Basis *cb, const Couplings *c, int dtype, const HxPass &p,
                     hipStream_t st) {
     Basis *b = const_cast<Basis *>(cb);
+    if (!p.step.sigma && digit_put_off(b, c, dtype)) {
+        const int rc = launch_hx_generic(b, c, dtype, p, st);
+        if (rc != HM_ERANGE) return rc;
+        clear_error();                 // a prefix table beyond that kernel's LDS
+    }
     DigitTables *t = nullptr;
     const DigitBonds *d = nullptr;
     const int rc = digit_get(b, c, dtype, st, &t, &d);
