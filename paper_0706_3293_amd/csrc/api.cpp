@@ -55,7 +55,10 @@ int hm_apply(hm_basis h, const double *J, const void *d_x, void *d_y, int32_t dt
     hm::HxPass p;
     p.x = d_x;
     p.y = d_y;
-    return hm::launch_hx(b, c, dtype, hm::choose_kernel(b, c, 0, dtype, false), p, (hipStream_t)stream);
+    const hipStream_t st = (hipStream_t)stream;
+    const int k = hm::choose_kernel(b, c, 0, dtype, false);
+    if (k == 2 && hm::is_capturing(st)) return hm::launch_hx_built(b, c, dtype, p, st);
+    return hm::launch_hx(b, c, dtype, k, p, st);
 }
 
 // Variant of hm_apply that forces one H x kernel (1: generic digits, 2: the

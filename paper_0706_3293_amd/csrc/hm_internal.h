@@ -191,6 +191,10 @@ struct HxPass {
 int hx_partial_count(const Basis *b, int kernel);      // partial slots needed
 int launch_hx(const Basis *b, const Couplings *c, int dtype, int kernel,
               const HxPass &pass, hipStream_t st);
+// A plain product by the handle's spin-1/2 split if its tables are built, else by the
+// generic kernel: what a capturing stream can take.
+int launch_hx_built(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
+                    hipStream_t st);
 int choose_kernel(const Basis *b, const Couplings *c, int requested, int dtype, bool plain_run);
 // Builds what kernel `kernel` needs on the device for these couplings (ahead
 // of a graph capture, where nothing may be allocated).

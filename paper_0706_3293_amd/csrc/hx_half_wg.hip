@@ -32,11 +32,9 @@
 
 namespace hm {
 
-int launch_hx_built(const Basis *b, const Couplings *c, int dtype, const HxPass &p,
-                    hipStream_t st);
-
 int half_low_bits(const Basis *b);
 int hx_half_grid(const Basis *b);
+int hx_half_chain(const Basis *b);
 
 constexpr int kWgMaxK = 12;
 constexpr int kWgMaxHighBits = 20;
@@ -406,15 +404,20 @@ static size_t wg_lds(int K, int nslot) {
 }
 
 // Where it is the automatic choice: FP64, up to kWgRows rows, blocks of
-// kWgRowsPerBlock rows on average, and no schedule asked for (that is one of
-// hx_half.hip's kernels).  Measured against hx_half_kernel (us per FP64 Lanczos
-// step, the dots taken in either kernel): N = 12 13.0 / 14.3, N = 16 15.7 / 20.7, N = 18 16.4 / 19.8, N = 20 22.9 /
-// 24.7, N = 20 with all 190 bonds 36.3 / 51.7; N = 21 28 / 28, N = 22 42 / 37, N = 24
-// 118 / 108, where the wave's own rows keep enough gathers in flight; N = 28,
-// M = 10 (5 rows per block) 33 / 23.  A run whose dots have a launch of their own
-// chooses again among these (wg_items_pay in lanczos.hip).
+// kWgRowsPerBlock rows on average, no schedule asked for (that is one of
+// hx_half.hip's kernels), and two items or more in turn for a wave of hx_half_kernel.
+// Measured against hx_half_kernel (us per FP64 Lanczos step, the dots taken in either
+// kernel): N = 16 15.7 / 20.7, N = 18 16.4 / 19.8, N = 20 22.9 / 24.7, N = 20 with all
+// 190 bonds 36.3 / 51.7; N = 21 28 / 28, N = 22 42 / 37, N = 24 118 / 108, where the
+// wave's own rows keep enough gathers in flight; N = 28, M = 10 (5 rows per block)
+// 33 / 23.  One H x with its call, where a wave has one item: N = 8 with all bonds
+// 25 / 20, N = 12 24 / 20 (all bonds 29 / 23), N = 13 24 / 22 (31 / 25), 16 sites and
+// A = 3 24 / 22 (34 / 29); where it has more: N = 14 24 / 53, 16 sites and A = 4
+// 27 / 47.  A run whose dots have a launch of their own chooses again among these
+// (wg_items_pay in lanczos.hip).
 constexpr int64_t kWgRows = (int64_t)1 << 18;
 constexpr int64_t kWgRowsPerBlock = 48;
+constexpr int kWgChain = 2;
 
 bool wg_fits(const Basis *b, const Couplings *c, int dtype) {
     if (b->two_s != 1 || dtype != HM_F64 || b->N < 4 || b->dim > kWgRows) return false;
@@ -424,6 +427,7 @@ bool wg_fits(const Basis *b, const Couplings *c, int dtype) {
     const int64_t n = wg_blocks(b);
     // (small N: a block holds what there is)
     if (b->N > 16 && b->dim < kWgRowsPerBlock * n) return false;
+    if (hx_half_chain(b) < kWgChain) return false;
     if (!c) return true;
     int nL, nH, nS, nslot;
     uint32_t vm;
